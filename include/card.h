@@ -226,6 +226,20 @@ int card_verify_static(const card_model_cfg* cfg, const void* packed_weights_dev
 size_t card_static_scratch_bytes(void);
 int card_static_scratch_reset(void);
 
+/* A prompt: forwards n tokens at positions ctx_len .. ctx_len + n - 1 (ctx_len a multiple of 16), leaves
+ * their K and V in the cache and writes the arg-max behind the last one to next_token_dev (dev, one
+ * int32; NULL = not wanted).  Same values as card_verify calls over the same tokens, up to the order
+ * of the fp32 sums; ordinary kernels that wait for nobody, in passes of up to 1024 rows, as many as
+ * workspace_rows has room for:
+ *   workspace_dev : dev, card_prompt_workspace_bytes(cfg, workspace_rows) bytes, 1024-byte aligned, no
+ *                   initialisation; calls sharing it must not overlap
+ * Token ids outside [0, vocab) are clamped, as in the forward of card_verify.
+ * Errors: CARD_EINVAL, CARD_ECAPACITY (ctx_len + n > max_ctx), CARD_EDEVICE. */
+size_t card_prompt_workspace_bytes(const card_model_cfg* cfg, int32_t workspace_rows);
+int card_prompt(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv, int32_t ctx_len,
+                const int32_t* tokens_dev, int32_t n, void* workspace_dev, int32_t workspace_rows, void* stream,
+                int32_t* next_token_dev);
+
 /* Test entry point, not on the timed path: the same forward, additionally storing the fp32
  * logits [r][vocab] (dev) so that tests can bound the error of the final-layer logits. */
 int card_verify_debug_logits(const card_model_cfg* cfg, const void* packed_weights_dev,

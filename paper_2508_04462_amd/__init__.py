@@ -34,6 +34,8 @@ from .binding import (  # noqa: F401
     card_verify,
     card_verify_debug_logits,
     card_verify_static,
+    card_prompt,
+    card_prompt_workspace_bytes,
     card_draft_level,
     card_cache_select,
     card_tree_mask_level,

@@ -114,6 +114,10 @@ def _declare(lib: C.CDLL) -> C.CDLL:
     lib.card_static_scratch_bytes.argtypes = []
     lib.card_static_scratch_reset.restype = C.c_int
     lib.card_static_scratch_reset.argtypes = []
+    lib.card_prompt_workspace_bytes.restype = C.c_size_t
+    lib.card_prompt_workspace_bytes.argtypes = [_cfgp, C.c_int32]
+    lib.card_prompt.restype = C.c_int
+    lib.card_prompt.argtypes = [_cfgp, _P, _kvp, C.c_int32, _P, C.c_int32, _P, C.c_int32, _P, _P]
     lib.card_verify_debug_logits.restype = C.c_int
     lib.card_verify_debug_logits.argtypes = [_cfgp, _P, _kvp, C.c_int32, _P, C.c_int32, _P, _P, _P, _P, _P]
     lib.card_kv_gather.restype = C.c_int
@@ -267,6 +271,16 @@ def card_static_scratch_bytes() -> int:
 
 def card_static_scratch_reset() -> int:
     return lib.card_static_scratch_reset()
+
+
+def card_prompt_workspace_bytes(cfg, workspace_rows: int) -> int:
+    return lib.card_prompt_workspace_bytes(C.byref(cfg), workspace_rows)
+
+
+def card_prompt(cfg, packed_dev, kv: CardKV, ctx_len: int, tokens_dev, n: int, workspace_dev, workspace_rows: int,
+                stream=None, next_token_dev=None) -> int:
+    return lib.card_prompt(C.byref(cfg), _ptr(packed_dev), C.byref(kv), ctx_len, _ptr(tokens_dev), n,
+                           _ptr(workspace_dev), workspace_rows, _ptr(stream), _ptr(next_token_dev))
 
 
 def card_verify_debug_logits(cfg, packed_dev, kv: CardKV, ctx_len: int, cand_dev, r: int, workspace_dev,

@@ -15,6 +15,7 @@
 #endif
 #include "card_pack.hip"
 #include "card_verify.hip"
+#include "card_prompt.hip"
 
 using namespace card;
 
@@ -269,6 +270,189 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     if (r <= 8) return h == 128 ? launch_mega<1, 128, true, false>(a, st) : launch_mega<1, 64, true, false>(a, st);
     if (r <= 16) return h == 128 ? launch_mega<1, 128, false, false>(a, st) : launch_mega<1, 64, false, false>(a, st);
     return h == 128 ? launch_mega<2, 128, false, false>(a, st) : launch_mega<2, 64, false, false>(a, st);
+}
+
+// ---- prompt pass (card_prompt.hip) -----------------------------------------------------------------
+constexpr int kPromptMaxRows = 1024;  // rows per pass: the chip is full (more rows per pass measured no gain)
+
+// Into how many K ranges a product is cut: the count with the least estimated time.  A workgroup's
+// time goes with its k-steps, plus about six for filling and draining: 0.52 us per step alone on a compute
+// unit, 0.88 with a second one beside it; every K range writes and reads the product once more in fp32
+// (6 TB/s), and a cut gate/up product needs a kernel of its own behind it.  Measured on the 1B, 7B and 8B
+// shapes with 100-1000 rows: the choice is the fastest of S = 1, 2, 3, 4, 6, 8, 12, 16 or within 5 % of it (8B,
+// 1000 rows: QKV 2, O 2, gate/up 1, down 2; 100 rows: 4, 8, 1, 8).
+int prompt_splits(int Nt, int Ks, int mts, bool swiglu) {
+    const int64_t blocks = int64_t(ceil_div(Nt, kPgWaves * kPgN)) * ceil_div(mts, kPgTiles);
+    const int turns = ceil_div(Ks, kPgUnroll);
+    int best = 1;
+    double best_us = 1e30;
+    for (int s = 1; s <= 16 && (s == 1 || turns / s >= 2); ++s) {
+        const int64_t wgs = blocks * s;
+        double us = (ceil_div(turns, s) * kPgUnroll + 6) * (wgs <= 256 ? 0.52 : 0.88 * std::max(1.0, double(wgs) / 512));
+        if (!swiglu || s > 1) us += double(s) * Nt * mts * 2048.0 / 6e6 + (swiglu ? 4.0 : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
+}
+
+struct PromptLayout {
+    size_t x, xf, ss, att, act, q, rope, best, part, bytes;
+    int mcap, groups;
+};
+PromptLayout prompt_layout(const card_model_cfg* cfg, const Layout& L, int rows) {
+    PromptLayout p = {};
+    p.mcap = ceil_div(rows, 16 * kPgTiles) * kPgTiles;
+    p.groups = ceil_div(cfg->d_model, kPgGroup);
+    const size_t cap = size_t(p.mcap) * 16, h = cfg->head_dim;
+    size_t w = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = w;
+        w = align_up(w + bytes, 1024);
+        return at;
+    };
+    p.x = take(cap * cfg->d_model * 4);
+    p.xf = take(size_t(L.qkv.Ks) * p.mcap * 2048);
+    p.ss = take(cap * p.groups * 4);
+    p.att = take(size_t(L.wo.Ks) * p.mcap * 2048);
+    p.act = take(size_t(L.wd.Ks) * p.mcap * 2048);
+    p.q = take(cap * cfg->n_q_heads * h * 4);
+    p.rope = take(cap * h * 4);
+    p.best = take(8);
+    size_t part = 0;
+    for (int m = 1; m <= p.mcap; ++m)
+        for (const MatDesc* d : {&L.qkv, &L.wo, &L.gu, &L.wd}) {
+            const int s = prompt_splits(d->Nt, d->Ks, m, d == &L.gu);
+            if (d != &L.gu || s > 1) part = std::max(part, size_t(s) * d->Nt * align_up(m, kPgTiles) * 1024);
+        }
+    p.part = take(part);
+    p.bytes = w;
+    return p;
+}
+
+// The product of the row tiles [mt0, g.mts).
+void prompt_gemm(PgemmArgs g, PgemmEpi epi, int mt0, hipStream_t st) {
+    g.nblk = ceil_div(g.Nt, kPgWaves * kPgN);
+    g.mb0 = mt0 / kPgTiles;
+    g.mblk = ceil_div(g.mts, kPgTiles) - g.mb0;
+    const dim3 grid(uint32_t(ceil_div(int64_t(g.nblk) * g.mblk * g.splits, 8) * 8)), block(kPgWaves * 64);
+    if (epi == PG_ARGMAX) hipLaunchKernelGGL(k_prompt_gemm<PG_ARGMAX>, grid, block, 0, st, g);
+    else if (epi == PG_SWIGLU) hipLaunchKernelGGL(k_prompt_gemm<PG_SWIGLU>, grid, block, 0, st, g);
+    else hipLaunchKernelGGL(k_prompt_gemm<PG_PART>, grid, block, 0, st, g);
+}
+
+// One pass: `rows` tokens at positions ctx_len .. (a multiple of 16).  next_token: where the arg-max behind the
+// last row goes, or null.
+int prompt_pass(const card_model_cfg* cfg, const Layout& L, const PromptLayout& P, const char* packed, const card_kv* kv,
+                int ctx_len, const int32_t* tokens, int rows, char* ws, int nwg, hipStream_t st, int32_t* next_token) {
+    const int mts = ceil_div(rows, 16), h = cfg->head_dim, d = cfg->d_model, G = cfg->n_q_heads / cfg->n_kv_heads;
+    const int mpad = ceil_div(mts, kPgTiles) * kPgTiles;
+    __bf16* xf = reinterpret_cast<__bf16*>(ws + P.xf);
+    __bf16* att = reinterpret_cast<__bf16*>(ws + P.att);
+    __bf16* act = reinterpret_cast<__bf16*>(ws + P.act);
+    PepiArgs e = {};
+    e.part = reinterpret_cast<float*>(ws + P.part);
+    e.d = d;
+    e.rows = rows;
+    e.x = reinterpret_cast<float*>(ws + P.x);
+    e.xf = xf;
+    e.ss = reinterpret_cast<float*>(ws + P.ss);
+    e.ss_groups = P.groups;
+    e.embed = reinterpret_cast<const __bf16*>(packed + L.embed_off);
+    e.tokens = tokens;
+    e.V = cfg->vocab;
+    e.best = reinterpret_cast<unsigned long long*>(ws + P.best);
+    e.qd = cfg->n_q_heads * h;
+    e.kvd = cfg->n_kv_heads * h;
+    e.h = h;
+    e.Hkv = cfg->n_kv_heads;
+    e.G = G;
+    e.ctx_len = ctx_len;
+    e.qcap = mpad * 16 * G;
+    e.inv_d = 1.0f / float(d);
+    e.eps = cfg->rms_eps;
+    e.inv_sqrt_h = 1.4426950408889634f / sqrtf(float(h));
+    e.rope = reinterpret_cast<float*>(ws + P.rope);
+    e.rope_rows = mpad * 16;
+    e.q = reinterpret_cast<__bf16*>(ws + P.q);
+    e.block_table = kv->block_table;
+    const auto gain = [&](int l, bool ffn) {
+        if (l == cfg->n_layers) return reinterpret_cast<const float*>(packed + L.g_final_off);
+        const char* lb = packed + L.layer0_off + size_t(l) * L.layer_stride;
+        return reinterpret_cast<const float*>(lb + (ffn ? L.g_ffn_off : L.g_attn_off));
+    };
+    const auto gemm = [&](const MatDesc& m, const char* base, const __bf16* in, PgemmEpi epi, int mt0) {
+        PgemmArgs g = {};
+        g.w = base + m.off;
+        g.bytes = uint32_t(m.bytes());
+        g.Nt = m.Nt;
+        g.Ks = m.Ks;
+        g.NB = m.NB;
+        g.nwg = nwg;
+        g.x = in;
+        g.mts = mts;
+        g.mp0 = e.mp0 = mt0 / kPgTiles * kPgTiles;  // (a tile that goes on alone may be cut many ways: its partials get few rows)
+        g.mcap = e.mcap = mpad - g.mp0;
+        g.part = const_cast<float*>(e.part);
+        g.ss = e.ss;
+        g.ss_groups = P.groups;
+        g.inv_d = e.inv_d;
+        g.eps = e.eps;
+        g.act = act;
+        g.Ks_out = L.wd.Ks;
+        g.row = rows - 1;
+        g.V = cfg->vocab;
+        g.best = e.best;
+        g.splits = epi == PG_ARGMAX ? 1 : prompt_splits(m.Nt, m.Ks, mts - mt0, epi == PG_SWIGLU);
+        e.splits = g.splits;
+        e.Nt = m.Nt;
+        if (epi == PG_SWIGLU && g.splits > 1) {
+            prompt_gemm(g, PG_PART, mt0, st);
+            e.mt0 = mt0;
+            hipLaunchKernelGGL(k_prompt_swiglu, dim3(uint32_t(ceil_div(m.Nt, 2 * kPgWaves)), uint32_t(mts - mt0)), dim3(256), 0, st, e, act,
+                               L.wd.Ks);
+        } else {
+            prompt_gemm(g, epi, mt0, st);
+        }
+    };
+    const auto resid = [&](const float* next_gain, int mt0) {
+        e.gain = next_gain;
+        e.mt0 = mt0;
+        hipLaunchKernelGGL(k_prompt_resid<false>, dim3(uint32_t(P.groups), uint32_t(mts - mt0)), dim3(256), 0, st, e);
+    };
+    const size_t pool_layer = size_t(kv->n_pages) * cfg->n_kv_heads * 16 * h;
+    e.gain = gain(0, false);
+    hipLaunchKernelGGL(k_prompt_resid<true>, dim3(uint32_t(P.groups), uint32_t(mts)), dim3(256), 0, st, e);
+    hipLaunchKernelGGL(k_prompt_rope, dim3(uint32_t(ceil_div(int64_t(rows) * (h / 2), 256))), dim3(256), 0, st,
+                       reinterpret_cast<float*>(ws + P.rope), rows, mpad * 16, h / 2, ctx_len, cfg->rope_theta, h);
+    for (int l = 0; l < cfg->n_layers; ++l) {
+        const char* lb = packed + L.layer0_off + size_t(l) * L.layer_stride;
+        const bool last = l + 1 == cfg->n_layers;
+        gemm(L.qkv, lb, xf, PG_PART, 0);
+        e.kpool = static_cast<__bf16*>(kv->k_pages) + size_t(l) * pool_layer;
+        e.vpool = static_cast<__bf16*>(kv->v_pages) + size_t(l) * pool_layer;
+        hipLaunchKernelGGL(k_prompt_qkv, dim3(uint32_t(ceil_div(L.qkv.Nt, 16)), uint32_t(mts)), dim3(256), 0, st, e);
+        // behind the last layer's K and V only the row that predicts is still of use: its row tile goes on alone
+        if (last && !next_token) break;
+        const int mt0 = last ? mts - 1 : 0;
+        const PattnArgs t = {e.q, e.kpool, e.vpool, kv->block_table, e.qcap, rows, G, e.Hkv, ctx_len, ceil_div(int64_t(rows) * G, 16),
+                             L.wo.Ks, att};
+        const dim3 ag(uint32_t(ceil_div(last ? std::min(G, t.row_tiles) : t.row_tiles, kPgWaves) * e.Hkv));
+        if (h == 128) hipLaunchKernelGGL(k_prompt_attn<128>, ag, dim3(256), 0, st, t);
+        else hipLaunchKernelGGL(k_prompt_attn<64>, ag, dim3(256), 0, st, t);
+        gemm(L.wo, lb, att, PG_PART, mt0);
+        resid(gain(l, true), mt0);
+        gemm(L.gu, lb, xf, PG_SWIGLU, mt0);
+        gemm(L.wd, lb, act, PG_PART, mt0);
+        resid(gain(l + 1, false), mt0);
+    }
+    if (next_token) {
+        gemm(L.lm, packed, xf, PG_ARGMAX, mts - 1);
+        hipLaunchKernelGGL(k_prompt_token, dim3(1), dim3(1), 0, st, e.best, next_token);
+    }
+    return launch_status();
 }
 
 }  // namespace
@@ -542,6 +726,35 @@ int card_verify_debug_logits(const card_model_cfg* cfg, const void* packed_weigh
     if (!logits_dev) return CARD_EINVAL;
     return verify_impl(cfg, packed_weights_dev, kv, ctx_len, cand_tokens_dev, r, workspace_dev, stream, out_dev,
                        row_argmax_dev, logits_dev);
+}
+
+size_t card_prompt_workspace_bytes(const card_model_cfg* cfg, int32_t rows) {
+    const Layout L = make_layout(cfg);
+    if (!L.ok || rows < 1) return 0;
+    return prompt_layout(cfg, L, std::min(rows, kPromptMaxRows)).bytes;
+}
+
+int card_prompt(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv, int32_t ctx_len,
+                const int32_t* tokens_dev, int32_t n, void* workspace_dev, int32_t workspace_rows, void* stream,
+                int32_t* next_token_dev) {
+    if (!cfg || !packed_weights_dev || !kv || !tokens_dev || !workspace_dev) return CARD_EINVAL;
+    const Layout L = make_layout(cfg);
+    if (!L.ok) return CARD_EINVAL;
+    if (!kv->k_pages || !kv->v_pages || !kv->block_table || kv->n_pages <= 0) return CARD_EINVAL;
+    if (ctx_len < 0 || ctx_len % kKvBlock || n < 1 || workspace_rows < 1) return CARD_EINVAL;
+    if (int64_t(ctx_len) + n > cfg->max_ctx) return CARD_ECAPACITY;
+    const int nwg = grid_size(cfg);
+    if (nwg <= 0) return CARD_EDEVICE;
+    const PromptLayout P = prompt_layout(cfg, L, std::min(workspace_rows, kPromptMaxRows));
+    // passes of about equal size, whole blocks of row tiles
+    const int passes = ceil_div(n, P.mcap * 16), per = ceil_div(ceil_div(n, passes), 16 * kPgTiles) * 16 * kPgTiles;
+    for (int at = 0; at < n; at += per) {
+        const int st = prompt_pass(cfg, L, P, static_cast<const char*>(packed_weights_dev), kv, ctx_len + at, tokens_dev + at,
+                                   std::min(per, n - at), static_cast<char*>(workspace_dev), nwg, as_stream(stream),
+                                   at + per >= n ? next_token_dev : nullptr);
+        if (st != CARD_OK) return st;
+    }
+    return CARD_OK;
 }
 
 int card_profile_timeline(void* buf_dev, int32_t layer) {

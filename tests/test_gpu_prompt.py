@@ -1,0 +1,102 @@
+"""The prompt pass (card_prompt) against the CPU oracle: K and V of every position, the token behind
+the last one, and a verification step on top of the cache it leaves.
+
+Bars as for the verify step: K and V within one bf16 step (2^-8 of the largest value; layers above
+the first also carry the rounding of the caches below: 2^-7), logits within 2e-2 of the row maximum,
+tokens equal where the oracle's two best are more than 0.05 apart."""
+import numpy as np
+import pytest
+import torch
+
+import card_inputs as ci
+from gpu_common import GAP, logits_rel_err, make_pair
+from oracle import card_oracle as co
+
+pytestmark = pytest.mark.gpu
+TINY = ci.SHAPES["tiny"]
+# head_dim 128, G = 4; the FFN ends inside a k-step, the vocabulary inside a tile, three layers
+MID = ci.ModelShape("mid", 3, 512, 8, 2, 128, 1048, 3001, ctx=200, r=8)
+# G = 3: row tiles that do not divide the heads; one layer; a QKV product with more tiles than workgroups
+WIDE = ci.ModelShape("wide", 1, 192, 24, 8, 128, 264, 515, ctx=64, r=4)
+
+
+def _check_kv(tgt, kv, shape, n):
+    for layer in range(shape.n_layers):
+        k, v = tgt.kv_gather(layer, 0, n)
+        for got, ref in ((k, kv.k[layer][:n]), (v, kv.v[layer][:n])):
+            assert np.abs(got.numpy() - ref).max() <= (2.0 ** -8 if layer == 0 else 2.0 ** -7) * np.abs(ref).max(), layer
+
+
+def _top(row):
+    order = np.argsort(row)[::-1]
+    return int(order[0]), float(row[order[0]] - row[order[1]])
+
+
+# around the row tiles (16) and row blocks (64) of the product kernel, one row more than a verify call
+# takes, more than one pass (1024 rows), and a last pass that is a remainder
+@pytest.mark.parametrize("shape,n", [(TINY, 33), (TINY, 64), (TINY, 65), (MID, 47), (MID, 48), (MID, 49), (MID, 63), (MID, 129),
+                                     (MID, 1040), (TINY, 2100), (WIDE, 50), (WIDE, 81)],
+                         ids=lambda p: getattr(p, "name", p))
+def test_prompt_against_the_oracle(shape, n):
+    r = 4
+    tgt, w = make_pair(shape, 7, max_ctx=n + r, gain_jitter=0.2, pool_fill=0xFF)
+    toks = ci.uniform_tokens(7, "ctx_tokens", n, n + r, shape.vocab).tolist()
+    kv = co.OracleKV.empty(shape, n + r + 15)
+    co.prefill(shape, w, kv, toks[: n - 1], chunk=256)
+    row = co.forward_rows(shape, w, kv, toks[n - 1: n], n - 1)[0]
+    g0 = tgt.prefill(toks[:n])
+    best, gap = _top(row)
+    assert g0 == best or (gap <= GAP and g0 in np.argsort(row)[-2:])
+    _check_kv(tgt, kv, shape, n)
+    # slots behind the last token are cleared with the page they are in: a step on top is finite and right
+    ref = co.verify(shape, w, kv, n, -1, toks[n:], keep_logits=True)
+    res = tgt.verify(n, -1, toks[n:], want_logits=True)
+    assert torch.isfinite(res["logits"]).all()
+    assert logits_rel_err(res["logits"], ref.logits) <= 2e-2
+
+
+def _prompt(tgt, toks, ctx_len, rows, next_token=True):
+    import paper_2508_04462_amd as card
+
+    ws = torch.full((card.card_prompt_workspace_bytes(tgt.cfg, rows),), 0xFF, dtype=torch.uint8, device=tgt.device)
+    dev = torch.tensor(toks, dtype=torch.int32, device=tgt.device)
+    out = torch.full((1,), -9, dtype=torch.int32, device=tgt.device)
+    st = card.card_prompt(tgt.cfg, tgt.packed, tgt.kv(-1), ctx_len, dev, len(toks), ws, rows, tgt._stream(), out if next_token else None)
+    torch.cuda.synchronize()
+    return st, int(out.item())
+
+
+@pytest.mark.parametrize("shape,parts,rows", [(MID, (160, 37), 64), (TINY, (16, 100), 1), (MID, (32, 1), 128), (TINY, (112, 300), 192)],
+                         ids=["mid-passes", "tiny-one-row-of-workspace", "mid-one-token", "tiny-passes"])
+def test_prompt_in_parts_and_passes(shape, parts, rows):
+    """A second prompt on top of the first (ctx_len > 0), and a workspace with room for fewer rows
+    than the prompt has (several passes); the workspace starts as bf16 NaN patterns."""
+    n = sum(parts)
+    tgt, w = make_pair(shape, 8, max_ctx=n + 16, gain_jitter=0.2, pool_fill=0xFF)
+    toks = ci.uniform_tokens(8, "ctx_tokens", 0, n, shape.vocab).tolist()
+    kv = co.OracleKV.empty(shape, n + 16)
+    co.prefill(shape, w, kv, toks[: n - 1], chunk=256)
+    row = co.forward_rows(shape, w, kv, toks[n - 1:], n - 1)[0]
+    assert _prompt(tgt, toks[: parts[0]], 0, rows, next_token=False) == (0, -9)
+    st, token = _prompt(tgt, toks[parts[0]:], parts[0], rows)
+    assert st == 0
+    best, gap = _top(row)
+    assert token == best or (gap <= GAP and token in np.argsort(row)[-2:])
+    _check_kv(tgt, kv, shape, n)
+
+
+def test_prompt_refuses_what_it_cannot_do():
+    import paper_2508_04462_amd as card
+
+    tgt, _ = make_pair(TINY, 1, max_ctx=96)
+    toks = list(range(40))
+    assert _prompt(tgt, toks, 8, 64)[0] == card.CARD_EINVAL  # not at a page
+    assert _prompt(tgt, toks, 64, 64)[0] == card.CARD_ECAPACITY
+    assert _prompt(tgt, toks, -16, 64)[0] == card.CARD_EINVAL
+    assert card.card_prompt_workspace_bytes(tgt.cfg, 0) == 0
+    assert card.card_prompt(tgt.cfg, tgt.packed, tgt.kv(-1), 0, tgt.cand, 0, tgt.workspace, 64, None) == card.CARD_EINVAL
+    with pytest.raises(card.CardError) as e:  # through the wrapper: as before
+        tgt.prefill(list(range(100)))
+    assert e.value.status == card.CARD_ECAPACITY
+    # tokens outside the vocabulary are clamped, as the verify step's forward does
+    assert tgt.prefill([5000, -3] + toks[2:]) == tgt.prefill([TINY.vocab - 1, 0] + toks[2:])
