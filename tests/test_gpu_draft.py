@@ -141,6 +141,33 @@ def test_select_exact_on_dyadic_scores_with_ties():
     assert card.card_cache_select(bad, bad, bad, 200, 16, 10, bad, bad, bad) == card.CARD_ERANGE
 
 
+@pytest.mark.parametrize("M,k,K", [(1, 1, 1), (16, 4, 64), (13, 5, 65), (21, 3, 40), (128, 16, 2048), (127, 16, 100)])
+def test_select_at_the_edges_of_its_workgroups(M, k, K):
+    """A workgroup ranks 64 tuples against all of them (padded to a multiple of four): counts around
+    64, the largest (2048), odd ones, a third of the tuples empty, many equal scores."""
+    import paper_2508_04462_amd as card
+
+    rng = np.random.default_rng(M * 100 + k)
+    toks = rng.integers(0, 1000, size=(M, k)).astype(np.int32)
+    toks[rng.random((M, k)) < 0.33] = -1
+    prob = (rng.integers(0, 8, size=(M, k)) / 8.0).astype(np.float32)  # (a score of zero is a score)
+    sigma = (rng.integers(1, 5, size=M) / 4.0).astype(np.float32)
+    score = (prob * sigma[:, None]).reshape(-1)
+    order = [i for i in sorted(range(M * k), key=lambda i: (-score[i], i)) if toks.reshape(-1)[i] >= 0]
+    n = min(K, M * k)
+    want = order[:n]
+    dev = "cuda:0"
+    ot = torch.full((n,), -7, dtype=torch.int32, device=dev)
+    os_, op = torch.full((n,), -7.0, dtype=torch.float32, device=dev), torch.full((n,), -7, dtype=torch.int32, device=dev)
+    assert card.card_cache_select(torch.from_numpy(sigma).to(dev), torch.from_numpy(toks).to(dev), torch.from_numpy(prob).to(dev), M, k,
+                                  K, ot, os_, op) == n
+    torch.cuda.synchronize()
+    pad = n - len(want)
+    assert ot.tolist() == toks.reshape(-1)[want].tolist() + [-1] * pad
+    assert os_.tolist() == score[want].tolist() + [0.0] * pad
+    assert op.tolist() == [i // k for i in want] + [-1] * pad
+
+
 def test_three_levels_built_on_the_device_and_written_to_the_cache():
     """Cache construction end to end: level after level, the device expands the current nodes
     (card_draft_level), scores and selects the next level (card_cache_select), the host stores it
