@@ -31,6 +31,24 @@ __device__ __forceinline__ void split_bf16(float v, __bf16& hi, __bf16& lo) {
     hi = static_cast<__bf16>(v);
     lo = static_cast<__bf16>(v - static_cast<float>(hi));
 }
+// Largest of a group of LPR neighbouring lanes' values (8 or 16, all of them active): register moves
+// inside a row of sixteen lanes, no trip through LDS.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_max_step(unsigned long long v) {
+    const int lo = int(uint32_t(v)), hi = int(uint32_t(v >> 32));
+    const unsigned long long o = uint64_t(uint32_t(__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false))) |
+                                 (uint64_t(uint32_t(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false))) << 32);
+    return o > v ? o : v;
+}
+template <int LPR>
+__device__ __forceinline__ unsigned long long group_max(unsigned long long v) {
+    static_assert(LPR == 8 || LPR == 16, "part of a row of lanes");
+    v = dpp_max_step<0xB1>(v);   // lane ^ 1
+    v = dpp_max_step<0x4E>(v);   // lane ^ 2
+    v = dpp_max_step<0x141>(v);  // mirrored in eight: the other four
+    if constexpr (LPR == 16) v = dpp_max_step<0x140>(v);  // mirrored in sixteen: the other eight
+    return v;
+}
 // element (head element j, token t) inside the V block of one page and head: pairs of 16-row
 // tiles are interleaved so that one 16-byte load per lane feeds two P*V matrix instructions
 __device__ __forceinline__ int v_page_index(int j, int t) {

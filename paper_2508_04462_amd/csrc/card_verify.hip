@@ -918,10 +918,13 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                 // Draft side (Cache Construction, eqs. (1)-(2)): per row the k most probable tokens and
                 // the log-sum-exp that turns their logits into probabilities, without storing the
                 // row.  The lanes of a row are consecutive (16 of them with one row tile, 8 with
-                // two), each owns eight columns of the batch and a share of the row's running best
-                // sixteen; sixteen rounds of "largest key among the row's lanes" rebuild that list
-                // from the old list and the new columns.  Keys are (ordered logit, ~token): unique,
-                // so the lane that holds a round's winner knows it and drops it.
+                // two), each owns eight columns of the batch and a share of the row's running best;
+                // k rounds of "largest key among the row's lanes" rebuild that list from the old list
+                // and the new columns.  Keys are (ordered logit, ~token): unique, so the lane that holds
+                // a round's winner knows it and drops it.  The weight stream stands still meanwhile, so
+                // the rounds' maxima go by register moves and there are k of them: with sixteen rounds of
+                // shuffles through LDS a 32-row call of the 1B shape (k = 8, eight times 64 columns per
+                // workgroup) took 71 us longer (1402 -> 1331).
                 constexpr int LPR = kMegaThreads / COLS, CPL = NBS * 16 / LPR, RUN = 16 / LPR;
                 static_assert(CPL == 8 && RUN * LPR == 16, "eight columns per lane, sixteen entries per row");
                 LmState& lm = *ea.lm;
@@ -948,18 +951,13 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
 #pragma unroll
                 for (int u = 0; u < RUN; ++u) nr[u] = 0ull;
 #pragma unroll 1
-                for (int j = 0; j < 16; ++j) {
+                for (int j = 0; j < a.topk; ++j) {
                     unsigned long long loc = 0ull;
 #pragma unroll
                     for (int q = 0; q < CPL; ++q) loc = cand[q] > loc ? cand[q] : loc;
 #pragma unroll
                     for (int u = 0; u < RUN; ++u) loc = lm.run[u] > loc ? lm.run[u] : loc;
-                    unsigned long long best = loc;
-#pragma unroll
-                    for (int o = 1; o < LPR; o <<= 1) {
-                        const unsigned long long other = __shfl_xor(best, o);
-                        best = other > best ? other : best;
-                    }
+                    const unsigned long long best = group_max<LPR>(loc);
                     if (best != 0ull) {
 #pragma unroll
                         for (int q = 0; q < CPL; ++q) cand[q] = cand[q] == best ? 0ull : cand[q];
@@ -974,40 +972,42 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
 #pragma unroll
                 for (int u = 0; u < RUN; ++u) lm.run[u] = nr[u];
             }
-            constexpr int PARTS = kMegaThreads / COLS;
-            constexpr int ROWS_PER = NBS * 16 / PARTS;
-            static_assert(ROWS_PER >= 1, "rows per thread");
-            {
-                const int m = tid % COLS, part = tid / COLS;
-                unsigned long long best = 0ull;
-                if (m < r) {
-                    const float sc = sm.row_scale[m];
-                    // row m predicts the token at position ctx_len + m + 1
-                    const uint32_t rkey = gumbel_row_key(a.seed_lo, a.seed_hi, uint32_t(a.ctx_len + m + 1));
-#pragma unroll
-                    for (int q = 0; q < ROWS_PER; ++q) {
-                        const int nl = part * ROWS_PER + q, i = nl >> 4;
-                        const int n = (tile0 + i * a.nwg) * 16 + (nl & 15);
-                        if (i < nvalid_s && n < a.V) {
-                            float val = sm.tile[nl * COLS + m] * sc;
-                            if (a.inv_temp > 0.f) val = val * a.inv_temp + gumbel_noise(rkey, uint32_t(n));
-                            const unsigned long long key =
-                                (static_cast<unsigned long long>(float_key(val)) << 32) |
-                                (0xffffffffu - uint32_t(n));
-                            best = key > best ? key : best;
+            if constexpr (EPI == ME_LM) {
+                constexpr int PARTS = kMegaThreads / COLS;
+                constexpr int ROWS_PER = NBS * 16 / PARTS;
+                static_assert(ROWS_PER >= 1, "rows per thread");
+                {
+                    const int m = tid % COLS, part = tid / COLS;
+                    unsigned long long best = 0ull;
+                    if (m < r) {
+                        const float sc = sm.row_scale[m];
+                        // row m predicts the token at position ctx_len + m + 1
+                        const uint32_t rkey = gumbel_row_key(a.seed_lo, a.seed_hi, uint32_t(a.ctx_len + m + 1));
+    #pragma unroll
+                        for (int q = 0; q < ROWS_PER; ++q) {
+                            const int nl = part * ROWS_PER + q, i = nl >> 4;
+                            const int n = (tile0 + i * a.nwg) * 16 + (nl & 15);
+                            if (i < nvalid_s && n < a.V) {
+                                float val = sm.tile[nl * COLS + m] * sc;
+                                if (a.inv_temp > 0.f) val = val * a.inv_temp + gumbel_noise(rkey, uint32_t(n));
+                                const unsigned long long key =
+                                    (static_cast<unsigned long long>(float_key(val)) << 32) |
+                                    (0xffffffffu - uint32_t(n));
+                                best = key > best ? key : best;
+                            }
                         }
                     }
+                    sm.part_best[part * COLS + m] = best;
                 }
-                sm.part_best[part * COLS + m] = best;
-            }
-            cbar(sm, cgen);
-            if (tid < r) {
-                unsigned long long best = sm.wg_best[tid];
-                for (int part = 0; part < PARTS; ++part) {
-                    const unsigned long long k = sm.part_best[part * COLS + tid];
-                    best = k > best ? k : best;
+                cbar(sm, cgen);
+                if (tid < r) {
+                    unsigned long long best = sm.wg_best[tid];
+                    for (int part = 0; part < PARTS; ++part) {
+                        const unsigned long long k = sm.part_best[part * COLS + tid];
+                        best = k > best ? k : best;
+                    }
+                    sm.wg_best[tid] = best;
                 }
-                sm.wg_best[tid] = best;
             }
         } else {  // ME_QKV
             // packed rows: [q heads | k heads | v heads]; in q and k heads row 2p is element p of the
@@ -1702,7 +1702,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.lm = &lm;
         gemm_phase<kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK>(a, p_lm, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
                                           uint32_t(a.xfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
-        if (tid < a.r && sm.wg_best[tid] != 0ull)
+        if (!DR && tid < a.r && sm.wg_best[tid] != 0ull)
             __hip_atomic_fetch_max(&a.best[tid], sm.wg_best[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if constexpr (DR) {
             // this workgroup's share of every row: its sixteen best keys and its (max, sum of exp)
