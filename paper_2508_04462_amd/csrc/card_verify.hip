@@ -121,6 +121,7 @@ struct __align__(16) MegaSmem {
     int ws_ok;
     uint32_t epoch;
     int pred[kMaxR + 1];
+    int row_page[kMaxR];  // page that row m's key and value go to
 };
 
 // ---- device-scope (write-through) stores -------------------------------------------------
@@ -197,7 +198,8 @@ __device__ __forceinline__ void cbar(MegaSmem& sm, uint32_t& cgen) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(kWaitLds);
     if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(&sm.cbar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    while (int32_t(lds_peek(&sm.cbar) - cgen) < 0) __builtin_amdgcn_s_sleep(1);
+    while (int32_t(lds_peek(&sm.cbar) - cgen) < 0) {  // (a sleep between the polls cost 0.3-1.2 % of a step)
+    }
     asm volatile("" ::: "memory");
 }
 
@@ -593,15 +595,15 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
     constexpr int GRP = PK ? kGroup : (MT == 2 ? (NB < 2 ? 2 : NB) : (NB < kGroup ? kGroup / 2 : kGroup));
     static_assert(NB <= GRP && GRP % NB == 0, "batch width");
     constexpr int SG = GRP / NB;  // k-steps per group
-    // k-steps in the activation ring (a multiple of SG): eight single-operand steps, four
-    // two-operand steps, two four-operand steps
+    // k-steps in the activation ring (a multiple of SG): eight single-operand steps, four two-operand
+    // steps, four-operand steps four in the narrow batches (1B shape, 32 rows: 1306 -> 1294 us) and else two
     static_assert(!PK || MT == 1, "packed halves: one row tile");
     static_assert(!GRP4 || (!PK && NB == 4 && EPI == ME_RESID), "grouped phases: four tiles, residual epilogue");
     const int t_inner = GRP4 ? 1 : a.nwg, t_batch = GRP4 ? a.nwg : NB * a.nwg;  // tile id steps inside a batch, between batches
     // grouped phases: the fragment with stream index n carries tile n & 3, so accumulator i of this
     // wavefront holds tile (i + rho) & 3, rho = stream index of the phase's first fragment & 3
     const uint32_t rho = GRP4 ? (fc.head & 3u) : 0u;
-    constexpr int XD = PK ? 8 : (MT == 2 ? 2 : 4);
+    constexpr int XD = PK ? 8 : (MT == 2 ? (NB <= 2 ? 4 : 2) : 4);
     static_assert(XD % SG == 0, "ring of whole groups");
     constexpr int COLS = 16 * MT;
     constexpr int NSUB = NB * MT > 8 ? 2 : 1, NBS = NB / NSUB;  // reduction rounds per batch, tiles per round
@@ -1017,8 +1019,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                 const int h = a.h, half = h >> 1;
                 const int prow = (tile0 + i * a.nwg) * 16;
                 const float sc = sm.row_scale[m];
-                const int slot = a.slot0 + m;
-                const int page = a.block_table[slot >> 4], tk = slot & 15;
+                const int page = sm.row_page[m], tk = (a.slot0 + m) & 15;
                 if (prow < a.qd + a.kvd) {
                     const bool is_q = prow < a.qd;
                     const int rel = is_q ? prow : prow - a.qd;
@@ -1048,68 +1049,40 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     }
                 }
             }
-            // V rows: work item (tile, head element j of the tile); the r tokens of one element are
-            // consecutive 2-byte slots inside a page row, written as the widest aligned stores
-            const int jj = (tid & 1) * 8 + ((tid >> 1) & 7);
-            const bool v_lane = ((tid >> 1) % kMaxR) < 8;
-            if (i < nvalid_s && v_lane && (tile0 + i * a.nwg) * 16 >= a.qd + a.kvd) {
+            // V rows: work item (tile, head element j of the tile, group of four slots): four consecutive
+            // aligned tokens of an element are 8 contiguous bytes.  A page is opened by the call that writes its
+            // first slot: that call clears the slots behind its last row, so that a later step never multiplies
+            // a zero probability with bits nobody stored (0 x NaN).
+            const int first = a.slot0, end = first + r;
+            const int jj = tid & 15, vi = (tid >> 4) % NB;
+            if (vi < nvalid_s && (tile0 + vi * a.nwg) * 16 >= a.qd + a.kvd) {
                 const int h = a.h;
-                const int rel = (tile0 + i * a.nwg) * 16 - a.qd - a.kvd + jj;
+                const int rel = (tile0 + vi * a.nwg) * 16 - a.qd - a.kvd + jj;
                 const int head = rel / h, jg = rel % h;
-                int m2 = 0;
-                while (m2 < r) {
-                    const int slot = a.slot0 + m2;
-                    const int page = a.block_table[slot >> 4], tk = slot & 15;
-                    const int run = min(r - m2, 16 - tk);
-                    const size_t vb = (size_t(page) * a.Hkv + head) * (16 * h);
-                    auto val = [&](int t) {
-                        return static_cast<__bf16>(sm.tile[(i * 16 + jj) * COLS + m2 + t] * sm.row_scale[m2 + t]);
-                    };
-                    int q = 0;
-                    while (q < run) {  // four consecutive aligned tokens are 8 contiguous bytes
-                        const int t = tk + q;
-                        __bf16* dst = ea.vpool + vb + v_page_index(jg, t);
-                        if ((t & 3) == 0 && q + 4 <= run) {
-                            const unsigned long long w = uint64_t(pack_bf16(val(q), val(q + 1))) |
-                                                         (uint64_t(pack_bf16(val(q + 2), val(q + 3))) << 32);
-                            __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), w, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                            q += 4;
-                        } else if ((t & 1) == 0 && q + 2 <= run) {
-                            __hip_atomic_store(reinterpret_cast<uint32_t*>(dst), pack_bf16(val(q), val(q + 1)),
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            q += 2;
-                        } else {
-                            st_dev_bf16(dst, val(q));
-                            q += 1;
-                        }
+                const int stop = ((end - 1) & ~15) >= first ? (end + 15) & ~15 : end;  // first slot behind the ones to write
+                for (int g = (first & ~3) + 4 * (tid / (16 * NB)); g < stop; g += 4 * (kMegaThreads / (16 * NB))) {
+                    __bf16 v4[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int m = min(max(g + q - first, 0), r - 1);
+                        const float z = sm.tile[(vi * 16 + jj) * COLS + m] * sm.row_scale[m];
+                        v4[q] = static_cast<__bf16>(g + q < end ? z : 0.f);
                     }
-                    // a page is opened by the call that writes its first slot: clear the slots behind
-                    // the ones written, so that a later step never multiplies a zero probability with
-                    // bits nobody stored (0 x NaN)
-                    if (tk == 0) {
-                        int t = run;
-                        while (t < 16) {
-                            __bf16* dst = ea.vpool + vb + v_page_index(jg, t);
-                            if ((t & 3) == 0) {
-                                __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), 0ull, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                                t += 4;
-                            } else if ((t & 1) == 0) {
-                                __hip_atomic_store(reinterpret_cast<uint32_t*>(dst), 0u, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                                t += 2;
-                            } else {
-                                st_dev_bf16(dst, static_cast<__bf16>(0.f));
-                                t += 1;
-                            }
-                        }
+                    const int page = sm.row_page[min(max(g - first, 0), r - 1)];  // (a group of four lies in one page)
+                    __bf16* dst = ea.vpool + (size_t(page) * a.Hkv + head) * (16 * h) + v_page_index(jg, g & 15);
+                    if (g >= first && g + 4 <= stop) {
+                        const unsigned long long w = uint64_t(pack_bf16(v4[0], v4[1])) | (uint64_t(pack_bf16(v4[2], v4[3])) << 32);
+                        __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (g + q >= first && g + q < stop) st_dev_bf16(dst + q, v4[q]);
                     }
-                    m2 += run;
                 }
             }
         }
-        cbar(sm, cgen);  // red / tile are reused by the next batch
+        // red / tile are reused by the next round (behind the last one stands the grid barrier)
+        if (b + 1 < n_batches || sb + 1 < NSUB) cbar(sm, cgen);
         }
     }
     if (!hook_done) after_k();
@@ -1525,7 +1498,10 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         sm.ws_ok = __hip_atomic_load(&a.bar[kBarMagic], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kWsMagic;
     }
     if (tid < kMegaWaves) sm.tail[tid] = sm.head[tid] = 0;
-    if (tid < kMaxR) sm.wg_best[tid] = 0ull;
+    if (tid < kMaxR) {
+        sm.wg_best[tid] = 0ull;
+        sm.row_page[tid] = tid < a.r ? a.block_table[(a.slot0 + tid) >> 4] : 0;
+    }
     __syncthreads();  // the only hardware barrier: producers and consumers part ways here
     // A workspace whose control words were never prepared could hold flags that let barriers fall
     // through: every workgroup reads the same word, so all of them leave, and the step fails.
