@@ -433,7 +433,7 @@ int prompt_pass(const card_model_cfg* cfg, const Layout& L, const PromptLayout& 
         gemm(L.qkv, lb, xf, PG_PART, 0);
         e.kpool = static_cast<__bf16*>(kv->k_pages) + size_t(l) * pool_layer;
         e.vpool = static_cast<__bf16*>(kv->v_pages) + size_t(l) * pool_layer;
-        hipLaunchKernelGGL(k_prompt_qkv, dim3(uint32_t(ceil_div(L.qkv.Nt, 16)), uint32_t(mts)), dim3(256), 0, st, e);
+        hipLaunchKernelGGL(k_prompt_qkv, dim3(uint32_t(ceil_div(L.qkv.Nt, kPgWaves)), uint32_t(mts)), dim3(256), 0, st, e);
         // behind the last layer's K and V only the row that predicts is still of use: its row tile goes on alone
         if (last && !next_token) break;
         const int mt0 = last ? mts - 1 : 0;

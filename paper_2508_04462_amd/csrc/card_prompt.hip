@@ -111,13 +111,15 @@ struct PgTile {
 // zeros, no memory access), so that the compiler's waits leave the others in flight.
 // What bounds it: 24 KiB per workgroup and k-step from L2 (55 GB/s per compute unit) at 1.27 PFLOP/s
 // issued, halves counted (gate/up above); eight row tiles per workgroup move a third less, but leave
-// registers for one step ahead only: 403 us.
+// registers for one step ahead only: 403 us.  The 32x32x16 instruction on the same tiles: no gain.
 template <int EPI>
 __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
-    constexpr int MT = kPgTiles, XF = 2 * MT, XW = XF / kPgWaves;  // activation fragments per k-step, per wavefront
-    constexpr int DA = 4, DB = 4;                                  // register stages of weights, of activations
+    constexpr int MT = kPgTiles;
+    constexpr int KB = 2;                                // k-steps between two barriers
+    constexpr int XF = KB * 2 * MT, XW = XF / kPgWaves;  // their activation fragments, per wavefront
+    constexpr int DA = 4, DB = 2;  // register stages: weights of a k-step, activations of KB k-steps
     constexpr int U = kPgUnroll;
-    static_assert(U % DA == 0 && U % DB == 0 && U % 2 == 0, "static ring indices");
+    static_assert(U % DA == 0 && U == KB * DB && DB == 2, "static ring indices");
     __shared__ uint4v xs[2][XF][64];
     __shared__ __align__(8) float scale[MT * 16];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -156,13 +158,15 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
         ++sa;
     };
     const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x + px_frag(a.Ks, 0, mt0), uint32_t(a.Ks) * (kPgTiles * 2048));
-    const int xoff = (wave * XW * 64 + lane) * 16;
+    const int xoff = (wave * XW * 64 + lane) * 16;  // (the fragments of consecutive k-steps are contiguous)
     int sb = k0;
     auto load_b = [&](uint4v (&r)[XW]) {
-        const int voff = sb < min(k1, a.Ks) ? xoff : kOutOfRange;
 #pragma unroll
-        for (int q = 0; q < XW; ++q) r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff + q * 1024, sb * (kPgTiles * 2048), 0);
-        ++sb;
+        for (int q = 0; q < XW; ++q) {
+            const int voff = sb + (wave * XW + q) / (2 * MT) < min(k1, a.Ks) ? xoff + q * 1024 : kOutOfRange;
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff, sb * (kPgTiles * 2048), 0);
+        }
+        sb += KB;
     };
     auto store_b = [&](int buf, const uint4v (&r)[XW]) {
 #pragma unroll
@@ -189,26 +193,30 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
         asm volatile("" ::: "memory");
     };
     sync();
-    // k-step u of a turn: multiply LDS buffer u % 2; the weights DA - 1 steps on are requested, the
-    // activations of the next step go to the other buffer (everybody has left it at the last barrier) and
-    // their registers take those DB steps behind it
+    // Half turn h: multiply LDS buffer h; the weights DA - 1 k-steps on are requested, the activations of
+    // the next half turn go to the other buffer (everybody has left it at the last barrier) and their
+    // registers take those DB half turns behind it
     for (int s = k0; s < k1; s += U) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            load_a(wa[(u + DA - 1) % DA]);
+        for (int h = 0; h < DB; ++h) {
 #pragma unroll
-            for (int j = 0; j < MT; ++j) {
-                const bf16x8 bh = __builtin_bit_cast(bf16x8, xs[u & 1][2 * j][lane]);
-                const bf16x8 bl = __builtin_bit_cast(bf16x8, xs[u & 1][2 * j + 1][lane]);
+            for (int k = 0; k < KB; ++k) {
+                const int u = h * KB + k;
+                load_a(wa[(u + DA - 1) % DA]);
 #pragma unroll
-                for (int i = 0; i < kPgN; ++i)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bh, acc[i][j], 0, 0, 0);
+                for (int j = 0; j < MT; ++j) {
+                    const bf16x8 bh = __builtin_bit_cast(bf16x8, xs[h][(k * MT + j) * 2][lane]);
+                    const bf16x8 bl = __builtin_bit_cast(bf16x8, xs[h][(k * MT + j) * 2 + 1][lane]);
 #pragma unroll
-                for (int i = 0; i < kPgN; ++i)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bl, acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < kPgN; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bh, acc[i][j], 0, 0, 0);
+#pragma unroll
+                    for (int i = 0; i < kPgN; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bl, acc[i][j], 0, 0, 0);
+                }
             }
-            store_b((u + 1) & 1, xb[(u + 1) % DB]);
-            load_b(xb[(u + 1) % DB]);
+            store_b(h ^ 1, xb[h ^ 1]);
+            load_b(xb[h ^ 1]);
             sync();
         }
     }
@@ -418,7 +426,7 @@ __global__ __launch_bounds__(256) void k_prompt_rope(float* rope, int rows, int 
 
 // QKV: sum of the K ranges, RMSNorm scale, rotation; q (scaled by log2(e)/sqrt(h), split) for the
 // attention kernel, K and V into their pages.  A row tile is one page (a pass starts on one).
-// One workgroup: 16 rows x 4 tiles per wavefront.
+// One workgroup: 16 rows, a tile per wavefront (four: 9.1 instead of 5.4 us on 203 rows of the 1B shape).
 __global__ __launch_bounds__(256) void k_prompt_qkv(PepiArgs a) {
     __shared__ float scale[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -430,55 +438,52 @@ __global__ __launch_bounds__(256) void k_prompt_qkv(PepiArgs a) {
     const int h = a.h, half = h >> 1, slot = a.ctx_len + row, tk = slot & 15;
     const bool on = row < a.rows;
     const int page = a.block_table[slot >> 4];  // (a tile has at least one row, and is one page)
+    const int t = blockIdx.x * kPgWaves + wave;
+    if (t >= a.Nt) return;
+    floatx4 v = part_sum(a, t, mt, lane);
+    v *= sc;
+    const int prow = t * 16;
+    if (prow < a.qd + a.kvd) {
+        const bool is_q = prow < a.qd;
+        const int rel = is_q ? prow : prow - a.qd;
+        const int head = rel / h, p0 = ((rel % h) >> 1) + kq * 2;  // pairs p0, p0 + 1
+        if (!on) return;
+        const float* cp = a.rope + size_t(row) * half + p0;
+        const float* sp = cp + size_t(a.rope_rows) * half;
+        float lo2[2], hi2[2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = (blockIdx.x * kPgWaves + wave) * 4 + i;
-        if (t >= a.Nt) break;
-        floatx4 v = part_sum(a, t, mt, lane);
-        v *= sc;
-        const int prow = t * 16;
-        if (prow < a.qd + a.kvd) {
-            const bool is_q = prow < a.qd;
-            const int rel = is_q ? prow : prow - a.qd;
-            const int head = rel / h, p0 = ((rel % h) >> 1) + kq * 2;  // pairs p0, p0 + 1
-            if (!on) continue;
-            const float* cp = a.rope + size_t(row) * half + p0;
-            const float* sp = cp + size_t(a.rope_rows) * half;
-            float lo2[2], hi2[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                lo2[q] = v[2 * q] * cp[q] - v[2 * q + 1] * sp[q];
-                hi2[q] = v[2 * q + 1] * cp[q] + v[2 * q] * sp[q];
-            }
-            if (is_q) {
-                const int kvh = head / a.G, gl = head % a.G;
-                __bf16* qp = a.q + (size_t(kvh) * a.qcap + size_t(row) * a.G + gl) * (2 * h);
-#pragma unroll
-                for (int w = 0; w < 2; ++w) {
-                    const int j = p0 + w * half;
-                    __bf16 h0, l0, h1, l1;
-                    split_bf16((w ? hi2[0] : lo2[0]) * a.inv_sqrt_h, h0, l0);
-                    split_bf16((w ? hi2[1] : lo2[1]) * a.inv_sqrt_h, h1, l1);
-                    *reinterpret_cast<uint32_t*>(qp + (j >> 3) * 16 + (j & 7)) = pack_bf16(h0, h1);
-                    *reinterpret_cast<uint32_t*>(qp + (j >> 3) * 16 + (j & 7) + 8) = pack_bf16(l0, l1);
-                }
-            } else {
-                __bf16* kp = a.kpool + (size_t(page) * a.Hkv + head) * (16 * h) + tk * 8;
-#pragma unroll
-                for (int w = 0; w < 2; ++w) {
-                    const int j = p0 + w * half;
-                    *reinterpret_cast<uint32_t*>(kp + (j >> 3) * 128 + (j & 7)) =
-                        w ? pack_bf16(static_cast<__bf16>(hi2[0]), static_cast<__bf16>(hi2[1]))
-                          : pack_bf16(static_cast<__bf16>(lo2[0]), static_cast<__bf16>(lo2[1]));
-                }
-            }
-        } else {  // (the slots behind the prompt's last token are cleared: the page is opened here)
-            if (!on) v = floatx4{0.f, 0.f, 0.f, 0.f};
-            const int rel = prow - a.qd - a.kvd, head = rel / h, jg = rel % h + kq * 4;
-            __bf16* vp = a.vpool + (size_t(page) * a.Hkv + head) * (16 * h);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) vp[v_page_index(jg + e, tk)] = static_cast<__bf16>(v[e]);
+        for (int q = 0; q < 2; ++q) {
+            lo2[q] = v[2 * q] * cp[q] - v[2 * q + 1] * sp[q];
+            hi2[q] = v[2 * q + 1] * cp[q] + v[2 * q] * sp[q];
         }
+        if (is_q) {
+            const int kvh = head / a.G, gl = head % a.G;
+            __bf16* qp = a.q + (size_t(kvh) * a.qcap + size_t(row) * a.G + gl) * (2 * h);
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const int j = p0 + w * half;
+                __bf16 h0, l0, h1, l1;
+                split_bf16((w ? hi2[0] : lo2[0]) * a.inv_sqrt_h, h0, l0);
+                split_bf16((w ? hi2[1] : lo2[1]) * a.inv_sqrt_h, h1, l1);
+                *reinterpret_cast<uint32_t*>(qp + (j >> 3) * 16 + (j & 7)) = pack_bf16(h0, h1);
+                *reinterpret_cast<uint32_t*>(qp + (j >> 3) * 16 + (j & 7) + 8) = pack_bf16(l0, l1);
+            }
+        } else {
+            __bf16* kp = a.kpool + (size_t(page) * a.Hkv + head) * (16 * h) + tk * 8;
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const int j = p0 + w * half;
+                *reinterpret_cast<uint32_t*>(kp + (j >> 3) * 128 + (j & 7)) =
+                    w ? pack_bf16(static_cast<__bf16>(hi2[0]), static_cast<__bf16>(hi2[1]))
+                      : pack_bf16(static_cast<__bf16>(lo2[0]), static_cast<__bf16>(lo2[1]));
+            }
+        }
+    } else {  // (the slots behind the prompt's last token are cleared: the page is opened here)
+        if (!on) v = floatx4{0.f, 0.f, 0.f, 0.f};
+        const int rel = prow - a.qd - a.kvd, head = rel / h, jg = rel % h + kq * 4;
+        __bf16* vp = a.vpool + (size_t(page) * a.Hkv + head) * (16 * h);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vp[v_page_index(jg + e, tk)] = static_cast<__bf16>(v[e]);
     }
 }
 
