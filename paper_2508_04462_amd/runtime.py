@@ -205,25 +205,30 @@ class Target:
         (below), and for a model that shares the GPU with another persistent kernel (grid_wgs:
         card_prompt takes every compute unit)."""
         n = len(tokens)
-        if chunk >= 32 and self.cfg.grid_wgs == 0 and PROMPT_MIN_TOKENS <= n <= self.cfg.max_ctx:
-            return self._prompt(tokens)
+        if (chunk >= 32 and self.cfg.grid_wgs == 0 and PROMPT_MIN_TOKENS <= n <= self.cfg.max_ctx
+                and self._prompt_workspace(min(n, 1024))):
+            toks = torch.tensor([int(t) for t in tokens], dtype=torch.int32, device=self.device)
+            _check(B.card_prompt(self.cfg, self.packed, self.kv(-1), 0, toks, n, self._prompt_ws, self._prompt_rows, self._stream(),
+                                 self._prompt_token), "card_prompt")
+            return int(self._prompt_token.item())
         chunk = min(chunk, self.cfg.max_r)
         last = None
         for s in range(0, n, chunk):
             last = self.verify(s, -1, tokens[s:s + chunk])
         return last["row_argmax"][-1]
 
-    def _prompt(self, tokens: Sequence[int]) -> int:
-        rows = min(len(tokens), 1024)
-        if rows > self._prompt_rows:
-            self._prompt_ws, self._prompt_rows = None, 0
-            nbytes = B.card_prompt_workspace_bytes(self.cfg, rows)
-            self._prompt_ws = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-            self._prompt_rows = rows
-        toks = torch.tensor([int(t) for t in tokens], dtype=torch.int32, device=self.device)
-        _check(B.card_prompt(self.cfg, self.packed, self.kv(-1), 0, toks, len(tokens), self._prompt_ws, self._prompt_rows,
-                             self._stream(), self._prompt_token), "card_prompt")
-        return int(self._prompt_token.item())
+    def _prompt_workspace(self, rows: int) -> bool:
+        """Room for passes of `rows` rows, kept for the next prompt; fewer rows where the device is nearly
+        full, none (False) where it is full."""
+        while rows > self._prompt_rows:
+            self._prompt_ws, held = None, self._prompt_rows
+            self._prompt_rows = 0
+            try:
+                self._prompt_ws = torch.empty(B.card_prompt_workspace_bytes(self.cfg, rows), dtype=torch.uint8, device=self.device)
+                self._prompt_rows = rows
+            except torch.cuda.OutOfMemoryError:
+                rows = max(held, rows // 2) if rows > 64 else 0
+        return self._prompt_rows > 0
 
     def kv_gather(self, layer: int, first: int, count: int):
         shp = (count, self.cfg.n_kv_heads, self.cfg.head_dim)

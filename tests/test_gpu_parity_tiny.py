@@ -383,3 +383,28 @@ def test_the_grid_size_changes_no_bit_at_r_up_to_eight():
     for other in out[1:]:
         assert torch.equal(other[0], out[0][0]) and torch.equal(other[1], out[0][1]) and torch.equal(other[2], out[0][2])
         assert other[3] == out[0][3]
+
+
+@pytest.mark.parametrize("ctx_len,r", [(0, 1), (0, 32), (3, 2), (13, 3), (13, 5), (14, 2), (15, 1), (15, 18), (16, 4), (30, 31), (31, 17)])
+def test_keys_and_values_land_in_their_slots_whatever_the_alignment(ctx_len, r):
+    """A step's V rows are written in groups of four slots: first and last groups that are only partly
+    the step's own, rows over one, two and three pages, pages opened by the step or before it.  The
+    pools start as 0xFF bytes: older slots keep their bits, the step's slots hold the oracle's values,
+    and the slots behind them in a page that the step opens are cleared."""
+    shape, n = TINY, 64
+    tgt, w = make_pair(shape, 19, max_ctx=n, gain_jitter=0.2, pool_fill=0xFF)
+    toks = ci.uniform_tokens(19, "ctx_tokens", 0, n, shape.vocab).tolist()
+    kv = co.OracleKV.empty(shape, n)
+    co.prefill(shape, w, kv, toks[: ctx_len + r])
+    for s in range(0, ctx_len, 7):
+        tgt.verify(s, -1, toks[s: min(ctx_len, s + 7)])
+    old = [tgt.kv_gather(layer, 0, ctx_len) for layer in range(2)] if ctx_len else []
+    tgt.verify(ctx_len, -1, toks[ctx_len: ctx_len + r])
+    end, page_end = ctx_len + r, (ctx_len + r + 15) // 16 * 16
+    for layer in range(2):
+        k, v = tgt.kv_gather(layer, 0, page_end)
+        if ctx_len:
+            assert torch.equal(k[:ctx_len], old[layer][0]) and torch.equal(v[:ctx_len], old[layer][1])
+        for got, ref in ((k, kv.k[layer]), (v, kv.v[layer])):
+            assert np.abs(got[ctx_len:end].numpy() - ref[ctx_len:end]).max() <= 2.0 ** -7 * np.abs(ref[:end]).max()
+        assert (v[end:] == 0).all()  # (every page here was opened by one of these calls)

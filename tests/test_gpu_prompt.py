@@ -100,3 +100,27 @@ def test_prompt_refuses_what_it_cannot_do():
     assert e.value.status == card.CARD_ECAPACITY
     # tokens outside the vocabulary are clamped, as the verify step's forward does
     assert tgt.prefill([5000, -3] + toks[2:]) == tgt.prefill([TINY.vocab - 1, 0] + toks[2:])
+
+
+def test_prompt_on_a_full_device_goes_through_verify_calls(monkeypatch):
+    """Where the device has no room for the prompt's workspace a prompt is what it was without it:
+    verify calls of 32 rows (the same bits), with room for fewer rows only, more passes."""
+    from paper_2508_04462_amd import runtime
+
+    tgt, w = make_pair(TINY, 4, max_ctx=320)
+    toks = ci.uniform_tokens(4, "ctx_tokens", 0, 300, TINY.vocab).tolist()
+    real = runtime.B.card_prompt_workspace_bytes
+    monkeypatch.setattr(runtime, "PROMPT_MIN_TOKENS", 10 ** 9)
+    g0 = tgt.prefill(toks)
+    by_calls = tgt.kv_gather(1, 0, 300)
+    monkeypatch.setattr(runtime, "PROMPT_MIN_TOKENS", 33)
+    for most, rows in ((0, 0), (80, 75)):  # (asked for 300, then 150, then 75 rows)
+        monkeypatch.setattr(runtime.B, "card_prompt_workspace_bytes", lambda cfg, n: real(cfg, n) if n <= most else 1 << 45)
+        tgt._prompt_ws, tgt._prompt_rows = None, 0
+        got = tgt.prefill(toks)
+        assert tgt._prompt_rows == rows
+        k, v = tgt.kv_gather(1, 0, 300)
+        if rows == 0:
+            assert got == g0 and torch.equal(k, by_calls[0]) and torch.equal(v, by_calls[1])
+        else:
+            assert (k - by_calls[0]).abs().max() <= 2.0 ** -7 * by_calls[0].abs().max()
