@@ -338,10 +338,18 @@ int card_cache_read_level(const card_cache* c, int32_t level, int32_t* tokens, i
  * is set.  mask_base is a multiple of 16, at most ctx_len (bits of context slots at or above
  * mask_base must be set by the caller); first_slot + n_rows <= mask_base + 32 * mask_words;
  * mask_words <= 32 (1024 tree slots).  A level wider than max_r rows is forwarded in several
- * calls (peers do not see each other, so the calls are independent).  Results, without the
- * logits ever being stored: per row the k <= 16 most probable tokens (most probable first, equal
+ * calls (peers do not see each other, so the calls are independent).  Calls that may run at the
+ * same time (on streams and workspaces of their own, grid_wgs chosen so that all of them fit the
+ * compute units) go through card_draft_level_piece: card_draft_level clears the slots behind its
+ * rows in a page that it opens, and reads the pages of earlier slots through caches that another
+ * call's stores do not reach.  Results, without the logits ever being stored: per row the k <= 16 most probable tokens (most probable first, equal
  * logits by ascending token id) and their probabilities under softmax over the whole vocabulary.
  * logits_dev (optional, test use): fp32 [n_rows][vocab].  Errors as card_verify.
+ *
+ * card_draft_level_piece: one of several calls that forward a level, in any order or at the same
+ * time.  The level owns the slots [level_first, level_end) (ctx_len <= level_first <= first_slot,
+ * first_slot + n_rows <= level_end <= max_ctx); those that are not this call's rows belong to the
+ * level's other calls and are neither cleared nor used, whatever they hold.
  *
  * card_cache_select, eqs. (3)-(7): scores every (parent i, its j-th token) pair
  * w = prob[i][j] * sigma[i] (sigma: cumulative probability of parent i's sequence, eq. (4)),
@@ -373,6 +381,10 @@ int card_draft_level(const card_model_cfg* cfg, const void* packed_weights_dev, 
                      int32_t ctx_len, const card_tree_rows* rows, int32_t n_rows, int32_t k,
                      void* workspace_dev, void* stream, int32_t* topk_tokens_dev,
                      float* topk_probs_dev, float* logits_dev);
+int card_draft_level_piece(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv,
+                           int32_t ctx_len, const card_tree_rows* rows, int32_t n_rows, int32_t level_first,
+                           int32_t level_end, int32_t k, void* workspace_dev, void* stream, int32_t* topk_tokens_dev,
+                           float* topk_probs_dev, float* logits_dev);
 int card_cache_select(const float* sigma_dev, const int32_t* topk_tokens_dev,
                       const float* topk_probs_dev, int32_t n_parents, int32_t k, int32_t K,
                       int32_t* out_tokens_dev, float* out_scores_dev, int32_t* out_parents_dev,

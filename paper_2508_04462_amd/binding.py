@@ -97,6 +97,9 @@ def _declare(lib: C.CDLL) -> C.CDLL:
     lib.card_verify_sampled.argtypes = [_cfgp, _P, _kvp, C.c_int32, _P, C.c_int32, C.POINTER(CardSampling), _P, _P, _P, _P, _P]
     lib.card_draft_level.restype = C.c_int
     lib.card_draft_level.argtypes = [_cfgp, _P, _kvp, C.c_int32, C.POINTER(CardTreeRows), C.c_int32, C.c_int32, _P, _P, _P, _P, _P]
+    lib.card_draft_level_piece.restype = C.c_int
+    lib.card_draft_level_piece.argtypes = [_cfgp, _P, _kvp, C.c_int32, C.POINTER(CardTreeRows), C.c_int32, C.c_int32, C.c_int32, C.c_int32,
+                                           _P, _P, _P, _P, _P]
     lib.card_tree_mask_level.restype = C.c_int
     lib.card_tree_mask_level.argtypes = [_P, _i32p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _P]
     lib.card_cache_select.restype = C.c_int
@@ -210,6 +213,13 @@ def card_verify_sampled(cfg, packed_dev, kv: CardKV, ctx_len: int, cand_dev, r: 
     return lib.card_verify_sampled(C.byref(cfg), _ptr(packed_dev), C.byref(kv), ctx_len, _ptr(cand_dev), r,
                                    C.byref(sampling), _ptr(workspace_dev), _ptr(stream), _ptr(out_dev),
                                    _ptr(row_token_dev), _ptr(logits_dev))
+
+
+def card_draft_level_piece(cfg, packed_dev, kv: CardKV, ctx_len: int, rows: CardTreeRows, n_rows: int, level_first: int,
+                           level_end: int, k: int, workspace_dev, stream, topk_tokens_dev, topk_probs_dev, logits_dev=None) -> int:
+    return lib.card_draft_level_piece(C.byref(cfg), _ptr(packed_dev), C.byref(kv), ctx_len, C.byref(rows), n_rows, level_first,
+                                      level_end, k, _ptr(workspace_dev), _ptr(stream), _ptr(topk_tokens_dev),
+                                      _ptr(topk_probs_dev), _ptr(logits_dev))
 
 
 def card_draft_level(cfg, packed_dev, kv: CardKV, ctx_len: int, rows: CardTreeRows, n_rows: int, k: int,

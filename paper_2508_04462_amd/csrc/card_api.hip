@@ -96,7 +96,7 @@ int grid_size(const card_model_cfg* cfg) {
 // workgroup per compute unit, so on an otherwise idle device the dispatcher places all of them.
 // Should other work hold compute units for longer than the kernel's bounded waits, the step ends
 // with accepted_len = -1 instead of hanging.
-template <int MT, int H, bool PK, bool DR>
+template <int MT, int H, bool PK, bool DR, bool PC = false>
 int launch_mega(MegaArgs& a, hipStream_t st) {
     static std::atomic<int> fits[kMaxDevices];  // 0 unknown, 1 yes, -1 no
     int dev = 0;
@@ -104,13 +104,13 @@ int launch_mega(MegaArgs& a, hipStream_t st) {
     int f = fits[dev].load(std::memory_order_relaxed);
     if (f == 0) {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify<MT, H, PK, DR>, kBlockThreads, 0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify<MT, H, PK, DR, PC>, kBlockThreads, 0) != hipSuccess)
             return CARD_EDEVICE;
         f = per_cu >= 1 ? 1 : -1;
         fits[dev].store(f, std::memory_order_relaxed);
     }
     if (f < 0 || a.nwg > cu_count()) return CARD_EDEVICE;
-    hipLaunchKernelGGL((k_verify<MT, H, PK, DR>), dim3(a.nwg), dim3(kBlockThreads), 0, st, a);
+    hipLaunchKernelGGL((k_verify<MT, H, PK, DR, PC>), dim3(a.nwg), dim3(kBlockThreads), 0, st, a);
     return launch_status();
 }
 
@@ -137,6 +137,8 @@ struct TreeOpt {
     int32_t topk;
     int32_t* topk_tok;
     float* topk_prob;
+    bool piece;  // one of several calls, perhaps at the same time, that forward the level in these slots
+    int32_t level_first, level_end;
 };
 
 // One persistent kernel runs the whole step (card_verify.hip).
@@ -159,6 +161,10 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
         if (tree->mask_words < 1 || tree->mask_words > 32 || tree->topk < 1 || tree->topk > 16) return CARD_ERANGE;
         if (tree->mask_base < 0 || tree->mask_base % kKvBlock || tree->mask_base > ctx_len) return CARD_EINVAL;
         if (slot0 < ctx_len || int64_t(slot0) + r > int64_t(tree->mask_base) + 32 * tree->mask_words) return CARD_ERANGE;
+        if (tree->piece) {
+            if (tree->level_first < ctx_len || tree->level_first > slot0 || tree->level_end < slot0 + r) return CARD_ERANGE;
+            if (tree->level_end > cfg->max_ctx) return CARD_ECAPACITY;
+        }
     }
     const int cus = grid_size(cfg);
     if (cus <= 0) return CARD_EDEVICE;
@@ -203,6 +209,8 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.pages_used = ceil_div(slot0 + r, kKvBlock);
     a.slot0 = slot0;
     a.old_end = tree ? tree->mask_base : ctx_len;
+    a.clear_from = tree && tree->piece ? tree->level_end : slot0 + r;
+    a.level_first = tree && tree->piece ? tree->level_first : 0;
     a.row_tiles = ceil_div(a.G * r, 16);
     // Cut the context so that a workgroup's share fits the page buffers of its wavefronts (all of
     // its old-context pages are then in flight before the barrier in front of attention), as long
@@ -262,6 +270,11 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.ts_layer = g_ts_layer;
     hipStream_t st = as_stream(stream);
     ProfScope ps(st);
+    if (tree && tree->piece) {
+        if (r <= 8) return h == 128 ? launch_mega<1, 128, true, true, true>(a, st) : launch_mega<1, 64, true, true, true>(a, st);
+        if (r <= 16) return h == 128 ? launch_mega<1, 128, false, true, true>(a, st) : launch_mega<1, 64, false, true, true>(a, st);
+        return h == 128 ? launch_mega<2, 128, false, true, true>(a, st) : launch_mega<2, 64, false, true, true>(a, st);
+    }
     if (tree) {
         if (r <= 8) return h == 128 ? launch_mega<1, 128, true, true>(a, st) : launch_mega<1, 64, true, true>(a, st);
         if (r <= 16) return h == 128 ? launch_mega<1, 128, false, true>(a, st) : launch_mega<1, 64, false, true>(a, st);
@@ -270,6 +283,17 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     if (r <= 8) return h == 128 ? launch_mega<1, 128, true, false>(a, st) : launch_mega<1, 64, true, false>(a, st);
     if (r <= 16) return h == 128 ? launch_mega<1, 128, false, false>(a, st) : launch_mega<1, 64, false, false>(a, st);
     return h == 128 ? launch_mega<2, 128, false, false>(a, st) : launch_mega<2, 64, false, false>(a, st);
+}
+
+int draft_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv, int32_t ctx_len, const card_tree_rows* rows,
+               int32_t n_rows, int32_t k, void* workspace, void* stream, int32_t* topk_tokens, float* topk_probs, float* logits,
+               bool piece, int32_t level_first, int32_t level_end) {
+    if (!rows || !kv) return CARD_EINVAL;
+    const TreeOpt t = {rows->positions_dev, rows->first_slot, rows->mask_dev, rows->mask_words, rows->mask_base, k,
+                       topk_tokens, topk_probs, piece, level_first, level_end};
+    card_kv kv2 = *kv;
+    kv2.pending_token = -1;
+    return verify_impl(cfg, packed, &kv2, ctx_len, rows->tokens_dev, n_rows, workspace, stream, nullptr, nullptr, logits, nullptr, &t);
 }
 
 // ---- prompt pass (card_prompt.hip) -----------------------------------------------------------------
@@ -571,15 +595,15 @@ int card_verify_sampled(const card_model_cfg* cfg, const void* packed_weights_de
 int card_draft_level(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv, int32_t ctx_len,
                      const card_tree_rows* rows, int32_t n_rows, int32_t k, void* workspace_dev, void* stream,
                      int32_t* topk_tokens_dev, float* topk_probs_dev, float* logits_dev) {
-    if (!rows) return CARD_EINVAL;
-    TreeOpt t = {rows->positions_dev, rows->first_slot, rows->mask_dev, rows->mask_words, rows->mask_base, k,
-                 topk_tokens_dev, topk_probs_dev};
-    card_kv kv2;
-    if (!kv) return CARD_EINVAL;
-    kv2 = *kv;
-    kv2.pending_token = -1;
-    return verify_impl(cfg, packed_weights_dev, &kv2, ctx_len, rows->tokens_dev, n_rows, workspace_dev, stream, nullptr,
-                       nullptr, logits_dev, nullptr, &t);
+    return draft_impl(cfg, packed_weights_dev, kv, ctx_len, rows, n_rows, k, workspace_dev, stream, topk_tokens_dev, topk_probs_dev,
+                      logits_dev, false, 0, 0);
+}
+
+int card_draft_level_piece(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv, int32_t ctx_len,
+                           const card_tree_rows* rows, int32_t n_rows, int32_t level_first, int32_t level_end, int32_t k,
+                           void* workspace_dev, void* stream, int32_t* topk_tokens_dev, float* topk_probs_dev, float* logits_dev) {
+    return draft_impl(cfg, packed_weights_dev, kv, ctx_len, rows, n_rows, k, workspace_dev, stream, topk_tokens_dev, topk_probs_dev,
+                      logits_dev, true, level_first, level_end);
 }
 
 int card_tree_mask_level(const uint32_t* parent_mask_host, const int32_t* parent_idx_host, int32_t n_rows,

@@ -83,6 +83,9 @@ struct MegaArgs {
     // row_pos[m] and in cache slot slot0 + m; it sees every slot below tmask_base and, from there on,
     // the slots whose bit is set in its mask row tmask[m * tmask_words ..]
     int32_t slot0, old_end;       // slot of row 0; slots below old_end hold context written by earlier calls
+    int32_t clear_from;           // a page opened by this call is cleared from this slot on: behind its rows and, in a piece
+                                  // of a level, behind those of its peers in calls that may run at the same time
+    int32_t level_first;          // piece of a level: the slots from this one on are written by such calls too
     const int32_t* row_pos;
     const uint32_t* tmask;
     int32_t tmask_words, tmask_base;
@@ -1052,8 +1055,9 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
             // V rows: work item (tile, head element j of the tile, group of four slots): four consecutive
             // aligned tokens of an element are 8 contiguous bytes.  A page is opened by the call that writes its
             // first slot: that call clears the slots behind its last row, so that a later step never multiplies
-            // a zero probability with bits nobody stored (0 x NaN).
-            const int first = a.slot0, end = first + r;
+            // a zero probability with bits nobody stored (0 x NaN).  Slots between its last row and clear_from
+            // are peers' of the same draft-side level: their own calls write them, before or after this.
+            const int first = a.slot0, end = first + r, clear = a.clear_from;
             const int jj = tid & 15, vi = (tid >> 4) % NB;
             if (vi < nvalid_s && (tile0 + vi * a.nwg) * 16 >= a.qd + a.kvd) {
                 const int h = a.h;
@@ -1070,13 +1074,13 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     }
                     const int page = sm.row_page[min(max(g - first, 0), r - 1)];  // (a group of four lies in one page)
                     __bf16* dst = ea.vpool + (size_t(page) * a.Hkv + head) * (16 * h) + v_page_index(jg, g & 15);
-                    if (g >= first && g + 4 <= stop) {
+                    if (g >= first && g + 4 <= stop && (g + 4 <= end || clear == end || g >= clear)) {
                         const unsigned long long w = uint64_t(pack_bf16(v4[0], v4[1])) | (uint64_t(pack_bf16(v4[2], v4[3])) << 32);
                         __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     } else {
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            if (g + q >= first && g + q < stop) st_dev_bf16(dst + q, v4[q]);
+                            if (g + q >= first && g + q < stop && (g + q < end || g + q >= clear)) st_dev_bf16(dst + q, v4[q]);
                     }
                 }
             }
@@ -1137,6 +1141,22 @@ __device__ __forceinline__ void attn_load_page(const MegaArgs& a, const __bf16* 
                                                int pid, int lane, bf16x8 (&kf)[H / 32], short4v (&vf)[H / 16]) {
     attn_load_k<H>(a, kpool, kvh, pid, lane, kf);
     attn_load_v<H>(a, vpool, kvh, pid, lane, vf);
+}
+
+// A page that calls running beside this one write to.  Device-scope loads: a plain one could find a line that such a
+// call's workgroup on the same compute die fetched before this call's rows were stored, or leave one behind for it.
+template <int H>
+__device__ __forceinline__ void attn_load_shared_page(const MegaArgs& a, const __bf16* kpool, const __bf16* vpool, int kvh,
+                                                      int pid, int lane, bf16x8 (&kf)[H / 32], short4v (&vf)[H / 16]) {
+    const int off = __builtin_amdgcn_readfirstlane(int((uint32_t(pid) * uint32_t(a.Hkv) + uint32_t(kvh)) * uint32_t(32 * H)));
+    const __amdgpu_buffer_rsrc_t kr = make_rsrc(kpool, 0xffffffffu), vr = make_rsrc(vpool, 0xffffffffu);
+#pragma unroll
+    for (int st = 0; st < H / 32; ++st) {
+        kf[st] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(kr, lane * 16 + st * 1024, off, kAuxDev));
+        const uint4v w = __builtin_amdgcn_raw_buffer_load_b128(vr, lane * 16 + st * 1024, off, kAuxDev);
+        vf[2 * st] = __builtin_bit_cast(short4v, uint2v{w[0], w[1]});
+        vf[2 * st + 1] = __builtin_bit_cast(short4v, uint2v{w[2], w[3]});
+    }
 }
 
 // Second half of an attention task: merge the four consumer wavefronts' partials in LDS, then
@@ -1304,7 +1324,9 @@ __device__ __forceinline__ void attn_page_ids(const MegaArgs& a, int wave, int w
     }
 }
 
-template <int H, bool TREE>
+// TREE: draft-side rows with mask rows.  PIECE: of a level whose other rows are forwarded by calls that may run at the
+// same time: the last pages of the walk are shared with them.
+template <int H, bool TREE, bool PIECE>
 __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSmem& sm, int wave, int lane, int wg,
                                            AttnBufs<H>& bf, const int (&pid0)[8], bool (&loaded)[8], uint32_t& cgen) {
     constexpr int ST = H / 32, HT = H / 16, PART = 16 * (H + 2), NBUF = AttnBufs<H>::N;
@@ -1324,13 +1346,18 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
         // tree rows: the lane's mask row (rows beyond R read row 0 and are dropped by mrow < 0)
         const uint32_t* mrow_mask = TREE ? a.tmask + size_t(mrow < 0 ? 0 : mrow) * a.tmask_words : nullptr;
         int pg = t.pg0 + wave;
+        // pages below `own` are loaded ahead; pairs of pages from `pair_end` on (the same for a call that is no piece) hold
+        // a shared one and are taken one by one behind them
+        const int shared = PIECE ? a.level_first >> 4 : 0;
+        const int own = PIECE ? min(t.pg1, shared) : t.pg1;
+        const int pair_end = PIECE && t.pg1 > shared ? shared - kMegaWaves : t.pg1;
         {
             int pid[NBUF];
             bool need[NBUF];
 #pragma unroll
             for (int i = 0; i < NBUF; ++i) {
                 const int pgi = pg + i * kMegaWaves;
-                need[i] = pgi < t.pg1 && !(task == wg && loaded[i]);
+                need[i] = pgi < own && !(task == wg && loaded[i]);
                 pid[i] = task == wg ? pid0[i] : (need[i] ? a.block_table[pgi] : 0);
             }
 #pragma unroll
@@ -1357,7 +1384,7 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
         // `scores_done` runs once the K operands have been consumed: the refill of those registers
         // starts there, a softmax and an output update ahead of the refill of V
         auto use_two = [&](int pga, const bf16x8 (&ka)[ST], const short4v (&va)[HT], int pgb, const bf16x8 (&kb)[ST],
-                           const short4v (&vb)[HT], auto&& scores_done) {
+                           const short4v (&vb)[HT], auto&& scores_done, auto&& weights_done) {
             floatx4 sa = floatx4{0.f, 0.f, 0.f, 0.f}, sb = floatx4{0.f, 0.f, 0.f, 0.f};
             // Tree rows (draft side: a node sees the context, its ancestors and itself, never its
             // peers): the 16 visibility bits of each page come from the row's mask word, fetched
@@ -1416,6 +1443,7 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
                 pbh[v] = __builtin_bit_cast(short, hi);
                 pbl[v] = __builtin_bit_cast(short, lo);
             }
+            weights_done(oka, okb);
 #pragma unroll
             for (int i = 0; i < HT; ++i) {
                 floatx4 acc = o[i];
@@ -1434,33 +1462,66 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int nx = pg + (NBUF + q) * kMegaWaves;
-            pid_nx[q] = nx < t.pg1 ? a.block_table[nx] : 0;
+            pid_nx[q] = nx < own ? a.block_table[nx] : 0;
         }
-        while (pg < t.pg1) {
+        while (pg < pair_end) {
 #pragma unroll
             for (int i = 0; i < NBUF; i += 2) {
-                if (pg < t.pg1) {
+                const bool go = pg < pair_end;
+                if (go) {
                     use_two(pg, bf.k[i], bf.v[i], pg + kMegaWaves, bf.k[i + 1], bf.v[i + 1], [&]() {
 #pragma unroll
                         for (int q = 0; q < 2; ++q) {
                             const int nx = pg + (NBUF + q) * kMegaWaves;
-                            if (nx < t.pg1) attn_load_k<H>(a, kpool, kvh, pid_nx[q], lane, bf.k[i + q]);
+                            if (nx < own) attn_load_k<H>(a, kpool, kvh, pid_nx[q], lane, bf.k[i + q]);
                         }
-                    });
+                    }, [](const bool (&)[4], const bool (&)[4]) {});
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         const int nx = pg + (NBUF + q) * kMegaWaves;
-                        if (nx < t.pg1) attn_load_v<H>(a, vpool, kvh, pid_nx[q], lane, bf.v[i + q]);
+                        if (nx < own) attn_load_v<H>(a, vpool, kvh, pid_nx[q], lane, bf.v[i + q]);
                     }
                     // ids for the refills after these: behind the page loads in the queue, they will
                     // have arrived a round later
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         const int nx2 = pg + (NBUF + 2 + q) * kMegaWaves;
-                        pid_nx[q] = nx2 < t.pg1 ? a.block_table[nx2] : 0;
+                        pid_nx[q] = nx2 < own ? a.block_table[nx2] : 0;
                     }
                 }
-                pg += 2 * kMegaWaves;
+                if (!PIECE || go) pg += 2 * kMegaWaves;
+            }
+        }
+        if constexpr (PIECE) {
+            // shared pages that this call's rows see: those of its own slots, and the first if it begins with older ones
+            auto seen = [&](int p) {
+                return p < shared || (p == shared && (a.level_first & 15) != 0) || (p * 16 < a.slot0 + a.r && p * 16 + 16 > a.slot0);
+            };
+            for (; pg < t.pg1; pg += 2 * kMegaWaves) {
+                const int pgb = pg + kMegaWaves;
+                const bool on_a = seen(pg), on_b = pgb < t.pg1 && seen(pgb);
+                if (!on_a && !on_b) continue;  // (would add zeros)
+                // a page that is not seen gets the other's bits and no weight
+                const int ia = a.block_table[on_a ? pg : pgb], ib = a.block_table[on_b ? pgb : pg];
+                const int ln = opaque_v(lane);
+                attn_load_shared_page<H>(a, kpool, vpool, kvh, ia, ln, bf.k[0], bf.v[0]);
+                attn_load_shared_page<H>(a, kpool, vpool, kvh, ib, ln, bf.k[1], bf.v[1]);
+                // V of the slots that none of the tile's rows sees becomes zero: a slot of a peer whose call has not
+                // stored it yet holds whatever the pool held (0 x NaN)
+                use_two(pg, bf.k[0], bf.v[0], pgb, bf.k[1], bf.v[1], []() {}, [&](const bool (&oka)[4], const bool (&okb)[4]) {
+                    const int sh = opaque_v(lane) >> 4 << 4;
+                    short4v ma, mb;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        ma[v] = ((__builtin_amdgcn_ballot_w64(oka[v]) >> sh) & 0xffffull) != 0ull ? short(-1) : short(0);
+                        mb[v] = ((__builtin_amdgcn_ballot_w64(okb[v]) >> sh) & 0xffffull) != 0ull ? short(-1) : short(0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < HT; ++i) {
+                        bf.v[0][i] &= ma;
+                        bf.v[1][i] &= mb;
+                    }
+                });
             }
         }
 
@@ -1484,8 +1545,10 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
     }
 }
 // ---- the kernel ----------------------------------------------------------------------------------
-// DR: draft-side call (tree rows with a visibility mask, per-row top-k in the vocabulary phase)
-template <int MT, int H, bool PK, bool DR>
+// DR: draft-side call (tree rows with a visibility mask, per-row top-k in the vocabulary phase).  PC: one of several
+// such calls for a level, perhaps at the same time (a kernel of its own: with the walk over shared pages in the other
+// draft-side kernels a 32-row call of the 1B shape takes 1302 us instead of 1274).
+template <int MT, int H, bool PK, bool DR, bool PC = false>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_verify(MegaArgs a) {
     __shared__ MegaSmem sm;
     const int tid = threadIdx.x;
@@ -1610,7 +1673,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         CARD_TS(12)
         grid_wait(a, gen, sm, cgen);
         CARD_TS(2)
-        attn_phase<H, DR>(a, l, sm, wave, lane, wg, bf, pid0, loaded, cgen);
+        attn_phase<H, DR, PC>(a, l, sm, wave, lane, wg, bf, pid0, loaded, cgen);
         CARD_TS(3)
         store_wait();
         grid_wait(a, gen, sm, cgen);

@@ -33,6 +33,14 @@ def _lane_streams(device, lanes: int) -> list:
     return have[:lanes]
 
 
+def level_pieces(n: int, lanes: int) -> List[tuple]:
+    """The rows [c0, c1) of the calls that forward a level of n nodes on `lanes` lanes."""
+    calls = (n + 31) // 32
+    calls = (calls + lanes - 1) // lanes * lanes  # full rounds of side-by-side calls, rows spread evenly
+    per = min(32, ((n + calls - 1) // calls + 7) // 8 * 8)  # whole 8-row groups per call where the level allows
+    return [(c0, min(n, c0 + per)) for c0 in range(0, n, per)]
+
+
 def _check(st: int, where: str) -> None:
     if st != B.CARD_OK:
         raise B.CardError(st, where)
@@ -163,8 +171,9 @@ class Target:
         """card_draft_level for a level of any width: the rows are cut into calls of at most 32, `lanes`
         of them at a time enqueued side by side, each on its own stream with its own workspace
         (peers of a level never see each other, so the calls are independent; they share the weights
-        and the KV cache and write different slots; a lane's calls follow each other on its stream).
-        Same results as the calls one after the other."""
+        and the KV cache and write different slots, of the same page too where a call ends inside one:
+        card_draft_level_piece; a lane's calls follow each other on its stream).  Same results as the
+        calls one after the other."""
         n, words, dev = len(tokens), len(mask_rows[0]), self.device
         lanes = len(self._lane_ws)
         tok = torch.tensor([int(t) for t in tokens], dtype=torch.int32, device=dev)
@@ -176,20 +185,17 @@ class Target:
         cur = torch.cuda.current_stream(dev)
         ready = torch.cuda.Event()
         ready.record(cur)
-        calls = (n + 31) // 32
-        calls = (calls + lanes - 1) // lanes * lanes  # full rounds of side-by-side calls, rows spread evenly
-        per = min(32, ((n + calls - 1) // calls + 7) // 8 * 8)  # whole 8-row groups per call where the level allows
         done = []
-        for i, c0 in enumerate(range(0, n, per)):
-            c1 = min(n, c0 + per)
+        for i, (c0, c1) in enumerate(level_pieces(n, lanes)):
             lane = i % lanes
             st = self._lane_streams[lane]
             if i < lanes:
                 st.wait_event(ready)
             rows = B.CardTreeRows(tok[c0:c1].data_ptr(), pos[c0:c1].data_ptr(), int(first_slot) + c0, mask[c0:c1].data_ptr(),
                                   words, int(mask_base))
-            _check(B.card_draft_level(self.cfg, self.packed, self.kv(-1), ctx_len, rows, c1 - c0, k, self._lane_ws[lane],
-                                      st.cuda_stream, tk[c0:c1], tp[c0:c1], None), "card_draft_level")
+            _check(B.card_draft_level_piece(self.cfg, self.packed, self.kv(-1), ctx_len, rows, c1 - c0, int(first_slot),
+                                            int(first_slot) + n, k, self._lane_ws[lane], st.cuda_stream, tk[c0:c1], tp[c0:c1], None),
+                   "card_draft_level_piece")
             ev = torch.cuda.Event()
             ev.record(st)
             done.append(ev)

@@ -69,6 +69,11 @@ def test_argument_errors_are_caught_on_the_host():
     assert card.card_verify(cfg, 0x1000, kv, -1, 0x1000, 8, 0x1000, None, 0x1000) == card.CARD_EINVAL
     assert card.card_weights_pack_tensor(cfg, 99, 0, 0x1000, 0x1000) == card.CARD_EINVAL
     assert card.card_weights_pack_tensor(cfg, card.TENSOR_IDS["wq"], 7, 0x1000, 0x1000) == card.CARD_ERANGE
+    rows = card.CardTreeRows(0x1000, 0x1000, 100, 0x1000, 8, 96)
+    piece = lambda n, a, b: card.card_draft_level_piece(cfg, 0x1000, kv, 100, rows, n, a, b, 4, 0x1000, None, 0x1000, 0x1000)  # noqa: E731
+    assert piece(8, 100, 107) == card.CARD_ERANGE  # the level ends before the piece does
+    assert piece(8, 101, 120) == card.CARD_ERANGE and piece(8, 99, 120) == card.CARD_ERANGE  # begins behind it, or in the context
+    assert piece(8, 100, 257) == card.CARD_ECAPACITY
     assert card.card_strerror(card.CARD_ECAPACITY) == "KV cache capacity exceeded"
 
 

@@ -267,6 +267,84 @@ def test_a_wide_level_in_calls_side_by_side_equals_the_calls_one_after_the_other
     assert (out["wide"][0] >= 0).all()
 
 
+def _level_twice(shape, seed, ctx_len, first, n, k, lanes):
+    """Roots from the last page in use on, and a level of n nodes behind them from slot `first`, on two models with the same weights whose pools
+    start as 0xFF bytes (NaN patterns): forwarded in a row on the first; -> both models, the row call's results, and the
+    level's arguments."""
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd.runtime import level_pieces
+    from paper_2508_04462_amd.synthetic import load_synthetic_weights
+
+    ctx = ci.uniform_tokens(seed, "ctx_tokens", 0, ctx_len, shape.vocab).tolist()
+    mask_base, base = ctx_len // 16 * 16, first - ((first - 1) % 16 + 1)
+    words = (first + n - mask_base + 31) // 32
+    base, roots = max(base, ctx_len), first - max(base, ctx_len)
+    st, root_rows = card.card_tree_mask_level(None, [-1] * roots, base, ctx_len, mask_base, words)
+    assert st == card.CARD_OK
+    st, rows = card.card_tree_mask_level(root_rows, [i % roots for i in range(n)], first, ctx_len, mask_base, words)
+    assert st == card.CARD_OK
+    tgts = []
+    for _ in range(2):
+        tgt = card.Target(shape, 320, max_r=32, grid_wgs=64, pool_fill=0xFF)
+        load_synthetic_weights(tgt, shape, seed, 0.2)
+        tgt.enable_lanes(lanes)
+        tgt.prefill(ctx)
+        tgt.draft_level(ctx_len, list(range(5, 5 + roots)), [ctx_len] * roots, base, root_rows, mask_base, k)
+        tgts.append(tgt)
+    toks = ci.uniform_tokens(seed, "ctx_tokens", 1, n, shape.vocab).tolist()
+    pieces = level_pieces(n, lanes)
+    parts = [tgts[0].draft_level(ctx_len, toks[a:b], [ctx_len + 1] * (b - a), first + a, rows[a:b], mask_base, k) for a, b in pieces]
+    want = tuple(torch.cat([p[key].cpu() for p in parts]) for key in ("topk_tokens", "topk_probs"))
+    return tgts, want, toks, rows, mask_base, pieces
+
+
+def _same_level(tgts, want, got, shape, first, n):
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+    end = (first + n + 15) // 16 * 16
+    for layer in range(shape.n_layers):
+        for one, two in zip(tgts[0].kv_gather(layer, 0, first + n), tgts[1].kv_gather(layer, 0, first + n)):
+            assert torch.equal(one.view(torch.int32), two.view(torch.int32))  # (slots that nobody wrote hold NaN)
+        assert torch.isfinite(tgts[1].kv_gather(layer, first, n)[1]).all()
+        if end > first + n and end - 16 >= first:  # a page that the level opened: cleared behind the level
+            assert (tgts[1].kv_gather(layer, first + n, end - first - n)[1] == 0).all()
+
+
+# levels that start and end anywhere in a page; cuts inside pages
+LEVELS = [(80, 33), (81, 40), (87, 48), (95, 17), (79, 12), (81, 100), (80, 100), (93, 66), (88, 9)]
+
+
+@pytest.mark.parametrize("first,n", LEVELS)
+@pytest.mark.parametrize("shape", [TINY, MID], ids=["tiny", "mid"])
+def test_pieces_of_a_level_in_any_order(shape, first, n):
+    """The last piece first: a piece that opens a page leaves the slots of the level's other pieces alone, and a
+    piece that runs before its neighbours does not mind what their slots hold."""
+    import paper_2508_04462_amd as card
+
+    k = 6
+    tgts, want, toks, rows, mask_base, pieces = _level_twice(shape, 23, 70, first, n, k, 2)
+    tgt, dev = tgts[1], tgts[1].device
+    tok = torch.tensor(toks, dtype=torch.int32, device=dev)
+    pos = torch.full((n,), 71, dtype=torch.int32, device=dev)
+    mask = torch.tensor([[w - (1 << 32) if w >= 1 << 31 else w for w in row] for row in rows], dtype=torch.int32, device=dev)
+    tk = torch.full((n, k), -7, dtype=torch.int32, device=dev)
+    tp = torch.zeros((n, k), dtype=torch.float32, device=dev)
+    for a, b in reversed(pieces):
+        r = card.CardTreeRows(tok[a:b].data_ptr(), pos[a:b].data_ptr(), first + a, mask[a:b].data_ptr(), len(rows[0]), mask_base)
+        assert card.card_draft_level_piece(tgt.cfg, tgt.packed, tgt.kv(-1), 70, r, b - a, first, first + n, k, tgt.workspace,
+                                           tgt._stream(), tk[a:b], tp[a:b]) == card.CARD_OK
+    torch.cuda.synchronize()
+    _same_level(tgts, want, (tk.cpu(), tp.cpu()), shape, first, n)
+
+
+@pytest.mark.parametrize("lanes", [2, 4])
+@pytest.mark.parametrize("first,n", LEVELS)
+def test_a_wide_level_from_any_slot_leaves_what_calls_in_a_row_leave(first, n, lanes):
+    """Pieces side by side that share a page, on pools that nobody has written these slots of before."""
+    tgts, want, toks, rows, mask_base, _ = _level_twice(MID, 24, 70, first, n, 5, lanes)
+    res = tgts[1].draft_level_wide(70, toks, [71] * n, first, rows, mask_base, 5)
+    _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), MID, first, n)
+
+
 @pytest.mark.parametrize("n", [8, 13, 29])
 def test_a_chain_forwarded_as_tree_rows_equals_the_verify_step_bit_for_bit(n):
     """Tree rows whose mask is the plain causal chain (row i sees the context and rows 0..i, slots
