@@ -357,7 +357,8 @@ int card_cache_read_level(const card_cache* c, int32_t level, int32_t* tokens, i
  * (eq. (7)): out_tokens / out_scores / out_parents [K], best first, equal scores by (parent, rank).
  * n_parents * k <= 2048.  Entries of topk_tokens_dev that are negative are skipped; if fewer than
  * the returned count remain, the outputs behind them are marked empty (token -1, score 0, parent
- * -1).  Returns the number of entries written, min(K, n_parents * k), or a negative status.  Appending token m to
+ * -1).  An output array may lie over an input array (path scores updated in place), not over another
+ * output.  Returns the number of entries written, min(K, n_parents * k), or a negative status.  Appending token m to
  * parent m's sequence (eqs. (8)-(9)) is what card_cache_write stores from these arrays.
  * ---------------------------------------------------------------------------------------- */
 /* Host helper, Mask Construction for Draft Model: the mask rows of one level from the rows of

@@ -638,7 +638,9 @@ int card_cache_select(const float* sigma_dev, const int32_t* topk_tokens_dev, co
     if (n_parents < 1 || k < 1 || k > 16 || K < 1 || int64_t(n_parents) * k > kSelMax) return CARD_ERANGE;
     SelectArgs a = {sigma_dev, topk_tokens_dev, topk_probs_dev, n_parents, k, K, out_tokens_dev, out_scores_dev,
                     out_parents_dev};
-    hipLaunchKernelGGL(k_cache_select, dim3(uint32_t(ceil_div(n_parents * k, kSelRank))), dim3(256), 0, as_stream(stream), a);
+    int threads = 64;  // two keys each
+    while (2 * threads < n_parents * k) threads *= 2;
+    hipLaunchKernelGGL(k_cache_select, dim3(1), dim3(uint32_t(threads)), 0, as_stream(stream), a);
     const int st = launch_status();
     return st != CARD_OK ? st : (K < n_parents * k ? K : n_parents * k);
 }

@@ -58,11 +58,12 @@ __global__ __launch_bounds__(256) void k_ws_init(uint4v* ws, size_t n16, uint32_
 
 // Cache construction, eqs. (3)-(7): score every (parent, top-k token) pair w = p * sigma(parent),
 // pool the M * k tuples and keep the K best, best first; equal scores in (parent, rank) order.  Keys are
-// unique, so a tuple's place in the order is the number of larger keys: every workgroup holds all
-// keys in LDS and ranks 64 of them, four lanes to a key, each lane against a quarter of the others.
-// Latency-bound: a few thousand compares per workgroup; K rounds of "largest key left" by one workgroup,
-// two barriers each, took 68 us at M = 100, k = 8, K = 100; this takes 6.3 at K = 50, launch included.
-constexpr int kSelMax = 2048, kSelRank = 64;
+// unique and sorted in LDS (bitonic network) by one workgroup, which has read every input before it writes an
+// output: the outputs may lie over the inputs.  Bound by the latency of the network's steps, 55 for 1024 keys;
+// a wavefront compares pairs of its own 128 keys, so only steps of larger distance need a barrier.
+// M = 100, k = 8, K = 100, a call among others: 10 us; keys ranked by many workgroups that each count the larger ones 14
+// (and no output over an input); K rounds of "largest key left", two barriers each, 68.  M = 32, K = 50: 6.2; ranked 5.6.
+constexpr int kSelMax = 2048;
 struct SelectArgs {
     const float* sigma;     // [M] cumulative probability of each parent sequence, eq. (4)
     const int32_t* tok;     // [M][k] eq. (2)
@@ -73,44 +74,42 @@ struct SelectArgs {
     int32_t* out_parent;    // [K]
 };
 
-__global__ __launch_bounds__(256) void k_cache_select(SelectArgs a) {
+__global__ __launch_bounds__(kSelMax / 2) void k_cache_select(SelectArgs a) {
     __shared__ unsigned long long keys[kSelMax];
-    const int tid = threadIdx.x, total = a.M * a.k;
-    const int padded = (total + 3) & ~3;
-    for (int flat = tid; flat < padded; flat += 256) {
+    __shared__ int toks[kSelMax];
+    const int tid = threadIdx.x, total = a.M * a.k, n = 2 * blockDim.x;  // n: a power of two
+    for (int flat = tid; flat < n; flat += blockDim.x) {
         unsigned long long key = 0ull;  // an empty tuple
-        if (flat < total && a.tok[flat] >= 0) {
+        const int tok = flat < total ? a.tok[flat] : -1;
+        if (tok >= 0) {
             const float w = a.prob[flat] * a.sigma[flat / a.k];
             // non-negative floats order like their bit patterns; +1 keeps a zero score above "empty"
             key = ((static_cast<unsigned long long>(__float_as_uint(w)) + 1ull) << 32) | (0xffffffffu - uint32_t(flat));
         }
         keys[flat] = key;
+        toks[flat] = tok;
     }
+    for (int size = 2; size <= n; size <<= 1)
+        for (int dist = size >> 1; dist > 0; dist >>= 1) {
+            // this step touches other wavefronts' keys, or the step before did (or it was the load)
+            if (dist >= 128 || (dist == 64 && size > 128) || size == 2) __syncthreads();
+            const int lo = 2 * tid - (tid & (dist - 1)), hi = lo + dist;
+            const unsigned long long x = keys[lo], y = keys[hi];
+            if ((x < y) == ((lo & size) == 0)) {
+                keys[lo] = y;
+                keys[hi] = x;
+            }
+            asm volatile("" ::: "memory");
+        }
     __syncthreads();
-    const int mine = blockIdx.x * kSelRank + (tid >> 2), part = tid & 3;
-    const unsigned long long key = mine < total ? keys[mine] : 0ull;
-    int larger = 0, filled = 0;
-    for (int i = part; i < padded; i += 4) {
-        const unsigned long long o = keys[i];
-        larger += o > key ? 1 : 0;
-        filled += o != 0ull ? 1 : 0;
-    }
-#pragma unroll
-    for (int o = 1; o < 4; o <<= 1) {
-        larger += __shfl_xor(larger, o);
-        filled += __shfl_xor(filled, o);
-    }
     const int n_out = a.K < total ? a.K : total;
-    if (part == 0 && key != 0ull && larger < n_out) {
-        a.out_tok[larger] = a.tok[mine];
-        a.out_score[larger] = __uint_as_float(uint32_t((key >> 32) - 1ull));
-        a.out_parent[larger] = mine / a.k;
-    }
-    // fewer tuples than places: the rest is marked empty
-    if (part == 0 && mine < n_out && mine >= filled) {
-        a.out_tok[mine] = -1;
-        a.out_score[mine] = 0.f;
-        a.out_parent[mine] = -1;
+    for (int j = tid; j < n_out; j += blockDim.x) {
+        const unsigned long long key = keys[j];
+        const int flat = int(0xffffffffu - uint32_t(key & 0xffffffffull));
+        // fewer tuples than places: the rest is marked empty
+        a.out_tok[j] = key != 0ull ? toks[flat] : -1;
+        a.out_score[j] = key != 0ull ? __uint_as_float(uint32_t((key >> 32) - 1ull)) : 0.f;
+        a.out_parent[j] = key != 0ull ? flat / a.k : -1;
     }
 }
 

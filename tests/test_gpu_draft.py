@@ -141,10 +141,10 @@ def test_select_exact_on_dyadic_scores_with_ties():
     assert card.card_cache_select(bad, bad, bad, 200, 16, 10, bad, bad, bad) == card.CARD_ERANGE
 
 
-@pytest.mark.parametrize("M,k,K", [(1, 1, 1), (16, 4, 64), (13, 5, 65), (21, 3, 40), (128, 16, 2048), (127, 16, 100)])
+@pytest.mark.parametrize("M,k,K", [(1, 1, 1), (16, 4, 64), (13, 5, 65), (21, 3, 40), (16, 8, 128), (43, 3, 129), (128, 16, 2048), (127, 16, 100)])
 def test_select_at_the_edges_of_its_workgroups(M, k, K):
-    """A workgroup ranks 64 tuples against all of them (padded to a multiple of four): counts around
-    64, the largest (2048), odd ones, a third of the tuples empty, many equal scores."""
+    """Keys are sorted as a power of two of them, 128 per wavefront: counts around 64 and 128, the largest
+    (2048), odd ones, a third of the tuples empty, many equal scores."""
     import paper_2508_04462_amd as card
 
     rng = np.random.default_rng(M * 100 + k)
@@ -166,6 +166,30 @@ def test_select_at_the_edges_of_its_workgroups(M, k, K):
     assert ot.tolist() == toks.reshape(-1)[want].tolist() + [-1] * pad
     assert os_.tolist() == score[want].tolist() + [0.0] * pad
     assert op.tolist() == [i // k for i in want] + [-1] * pad
+
+
+@pytest.mark.parametrize("M,k,K", [(100, 8, 100), (128, 16, 2048), (70, 5, 33)])
+@pytest.mark.parametrize("over", ["sigma", "probs", "tokens", "inside"])
+def test_select_in_place(M, k, K, over):
+    """An output over an input, or over a part of one: the same as with arrays of its own."""
+    import paper_2508_04462_amd as card
+
+    g = torch.Generator().manual_seed(M)
+    n = min(K, M * k)
+    toks = torch.randint(-1, 1000, (M, k), generator=g, dtype=torch.int32).cuda()
+    prob, sigma = torch.rand((M, k), generator=g).cuda(), torch.rand(max(M, n), generator=g).cuda()
+    own = [torch.full((n,), -7, dtype=t, device="cuda") for t in (torch.int32, torch.float32, torch.int32)]
+    assert card.card_cache_select(sigma, toks, prob, M, k, K, *own) == n
+    want = [t.clone() for t in own]
+    outs = list(own)
+    if over == "tokens":
+        outs[0] = toks.view(-1)[:n]
+    else:
+        outs[1] = {"sigma": sigma[:n], "probs": prob.view(-1)[:n], "inside": prob.view(-1)[M * k - n:]}[over]
+    assert card.card_cache_select(sigma, toks, prob, M, k, K, *outs) == n
+    torch.cuda.synchronize()
+    for a, b in zip(outs, want):
+        assert torch.equal(a, b)
 
 
 def test_three_levels_built_on_the_device_and_written_to_the_cache():
