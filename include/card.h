@@ -233,6 +233,8 @@ int card_static_scratch_reset(void);
  * workspace_rows has room for:
  *   workspace_dev : dev, card_prompt_workspace_bytes(cfg, workspace_rows) bytes, 1024-byte aligned, no
  *                   initialisation; calls sharing it must not overlap
+ * next_token_dev receives -1, and what the cache holds for these positions is void, if the weights were
+ * packed for another grid size (as card_verify reports it; without next_token_dev there is no sign).
  * Token ids outside [0, vocab) are clamped, as in the forward of card_verify.
  * Errors: CARD_EINVAL, CARD_ECAPACITY (ctx_len + n > max_ctx), CARD_EDEVICE. */
 size_t card_prompt_workspace_bytes(const card_model_cfg* cfg, int32_t workspace_rows);

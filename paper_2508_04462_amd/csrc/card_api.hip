@@ -474,7 +474,8 @@ int prompt_pass(const card_model_cfg* cfg, const Layout& L, const PromptLayout& 
     }
     if (next_token) {
         gemm(L.lm, packed, xf, PG_ARGMAX, mts - 1);
-        hipLaunchKernelGGL(k_prompt_token, dim3(1), dim3(1), 0, st, e.best, next_token);
+        hipLaunchKernelGGL(k_prompt_token, dim3(1), dim3(1), 0, st, e.best, reinterpret_cast<const uint32_t*>(packed + L.stamp_off),
+                           nwg, next_token);
     }
     return launch_status();
 }

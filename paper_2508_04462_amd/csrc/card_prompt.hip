@@ -298,8 +298,10 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
     }
 }
 
-__global__ void k_prompt_token(const unsigned long long* best, int32_t* out) {
-    *out = int32_t(0xffffffffu - uint32_t(*best & 0xffffffffull));
+// stamp: as in the verify kernel, weights laid out for another grid size are in the wrong order: no token
+__global__ void k_prompt_token(const unsigned long long* best, const uint32_t* stamp, int nwg, int32_t* out) {
+    const bool bad_layout = stamp[0] != kStampMagic || stamp[1] != uint32_t(nwg);
+    *out = bad_layout ? -1 : int32_t(0xffffffffu - uint32_t(*best & 0xffffffffull));
 }
 
 // ---- what stands between the products ----------------------------------------------------------------

@@ -216,7 +216,10 @@ class Target:
             toks = torch.tensor([int(t) for t in tokens], dtype=torch.int32, device=self.device)
             _check(B.card_prompt(self.cfg, self.packed, self.kv(-1), 0, toks, n, self._prompt_ws, self._prompt_rows, self._stream(),
                                  self._prompt_token), "card_prompt")
-            return int(self._prompt_token.item())
+            token = int(self._prompt_token.item())
+            if token < 0:  # weights not packed, or for another grid size
+                raise B.CardError(B.CARD_EDEVICE, "card_prompt")
+            return token
         chunk = min(chunk, self.cfg.max_r)
         last = None
         for s in range(0, n, chunk):

@@ -85,6 +85,26 @@ def test_prompt_in_parts_and_passes(shape, parts, rows):
     _check_kv(tgt, kv, shape, n)
 
 
+def test_prompt_on_weights_not_packed_for_this_grid():
+    """As a verification step reports them: a blob that was never packed, and one packed for another grid size."""
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd.synthetic import load_synthetic_weights
+
+    toks = ci.uniform_tokens(3, "ctx_tokens", 0, 40, TINY.vocab).tolist()
+    tgt, other = card.Target(TINY, 96), card.Target(TINY, 96, grid_wgs=64)
+    load_synthetic_weights(other, TINY, 3)
+    want = _prompt(other, toks, 0, 64)
+    assert want[0] == 0 and 0 <= want[1] < TINY.vocab
+    for blob in (torch.zeros_like(tgt.packed), other.packed):
+        tgt.packed.copy_(blob)
+        assert _prompt(tgt, toks, 0, 64) == (0, -1)
+        assert tgt.verify(0, -1, toks[:4])["accepted_len"] == -1
+        with pytest.raises(card.CardError):
+            tgt.prefill(toks)
+    load_synthetic_weights(tgt, TINY, 3)
+    assert _prompt(tgt, toks, 0, 64) == want and tgt.prefill(toks) == want[1]
+
+
 def test_prompt_refuses_what_it_cannot_do():
     import paper_2508_04462_amd as card
 
