@@ -141,6 +141,11 @@ struct TreeOpt {
     int32_t level_first, level_end;
 };
 
+// one layer of a page pool is addressed with 32-bit byte offsets
+bool pool_fits(const card_model_cfg* cfg, const card_kv* kv) {
+    return size_t(kv->n_pages) * cfg->n_kv_heads * 16 * cfg->head_dim * 2 < (size_t(1) << 32);
+}
+
 // One persistent kernel runs the whole step (card_verify.hip).
 int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv, int32_t ctx_len,
                 const int32_t* cand, int32_t r, void* workspace, void* stream, card_verify_result* out,
@@ -150,8 +155,7 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     const Layout L = make_layout(cfg);
     if (!L.ok) return CARD_EINVAL;
     if (!kv->k_pages || !kv->v_pages || !kv->block_table || kv->n_pages <= 0) return CARD_EINVAL;
-    // one layer of a page pool is addressed with 32-bit byte offsets
-    if (size_t(kv->n_pages) * cfg->n_kv_heads * 16 * cfg->head_dim * 2 >= (size_t(1) << 32)) return CARD_EINVAL;
+    if (!pool_fits(cfg, kv)) return CARD_EINVAL;
     if (r < 1 || r > cfg->max_r) return CARD_ERANGE;
     if (ctx_len < 0) return CARD_EINVAL;
     const int32_t slot0 = tree ? tree->first_slot : ctx_len;
@@ -768,6 +772,7 @@ int card_prompt(const card_model_cfg* cfg, const void* packed_weights_dev, const
     const Layout L = make_layout(cfg);
     if (!L.ok) return CARD_EINVAL;
     if (!kv->k_pages || !kv->v_pages || !kv->block_table || kv->n_pages <= 0) return CARD_EINVAL;
+    if (!pool_fits(cfg, kv)) return CARD_EINVAL;  // (no step could follow)
     if (ctx_len < 0 || ctx_len % kKvBlock || n < 1 || workspace_rows < 1) return CARD_EINVAL;
     if (int64_t(ctx_len) + n > cfg->max_ctx) return CARD_ECAPACITY;
     const int nwg = grid_size(cfg);

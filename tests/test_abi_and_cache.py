@@ -74,6 +74,12 @@ def test_argument_errors_are_caught_on_the_host():
     assert piece(8, 100, 107) == card.CARD_ERANGE  # the level ends before the piece does
     assert piece(8, 101, 120) == card.CARD_ERANGE and piece(8, 99, 120) == card.CARD_ERANGE  # begins behind it, or in the context
     assert piece(8, 100, 257) == card.CARD_ECAPACITY
+    # a page pool of 4 GiB per layer: no step can use it, so no prompt fills it
+    big = card.CardKV(0x1000, 0x1000, 0x1000, 2 ** 32 // (cfg.n_kv_heads * 16 * cfg.head_dim * 2), -1)
+    assert card.card_verify(cfg, 0x1000, big, 0, 0x1000, 8, 0x1000, None, 0x1000) == card.CARD_EINVAL
+    assert card.card_prompt(cfg, 0x1000, big, 0, 0x1000, 40, 0x1000, 64) == card.CARD_EINVAL
+    big.n_pages -= 1
+    assert card.card_prompt(cfg, 0x1000, big, 0, 0x1000, 257, 0x1000, 64) == card.CARD_ECAPACITY  # (past that check)
     assert card.card_strerror(card.CARD_ECAPACITY) == "KV cache capacity exceeded"
 
 
