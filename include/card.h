@@ -231,7 +231,7 @@ int card_static_scratch_reset(void);
  * int32; NULL = not wanted).  Same values as card_verify calls over the same tokens, up to the order
  * of the fp32 sums; ordinary kernels that wait for nobody, in passes of up to 1024 rows, as many as
  * workspace_rows has room for:
- *   workspace_dev : dev, card_prompt_workspace_bytes(cfg, workspace_rows) bytes, 1024-byte aligned, no
+ *   workspace_dev : dev, card_prompt_workspace_bytes(cfg, workspace_rows) bytes, 16-byte aligned, no
  *                   initialisation; calls sharing it must not overlap
  * next_token_dev receives -1, and what the cache holds for these positions is void, if the weights were
  * packed for another grid size (as card_verify reports it; without next_token_dev there is no sign).

@@ -774,6 +774,7 @@ int card_prompt(const card_model_cfg* cfg, const void* packed_weights_dev, const
     if (!kv->k_pages || !kv->v_pages || !kv->block_table || kv->n_pages <= 0) return CARD_EINVAL;
     if (!pool_fits(cfg, kv)) return CARD_EINVAL;  // (no step could follow)
     if (ctx_len < 0 || ctx_len % kKvBlock || n < 1 || workspace_rows < 1) return CARD_EINVAL;
+    if (reinterpret_cast<uintptr_t>(workspace_dev) % 16) return CARD_EINVAL;  // 16-byte loads and stores
     if (int64_t(ctx_len) + n > cfg->max_ctx) return CARD_ECAPACITY;
     const int nwg = grid_size(cfg);
     if (nwg <= 0) return CARD_EDEVICE;

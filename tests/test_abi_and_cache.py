@@ -80,6 +80,9 @@ def test_argument_errors_are_caught_on_the_host():
     assert card.card_prompt(cfg, 0x1000, big, 0, 0x1000, 40, 0x1000, 64) == card.CARD_EINVAL
     big.n_pages -= 1
     assert card.card_prompt(cfg, 0x1000, big, 0, 0x1000, 257, 0x1000, 64) == card.CARD_ECAPACITY  # (past that check)
+    # the prompt's workspace: 16-byte aligned, no more
+    assert card.card_prompt(cfg, 0x1000, kv, 0, 0x1000, 40, 0x1008, 64) == card.CARD_EINVAL
+    assert card.card_prompt(cfg, 0x1000, kv, 0, 0x1000, 257, 0x1010, 64) == card.CARD_ECAPACITY
     assert card.card_strerror(card.CARD_ECAPACITY) == "KV cache capacity exceeded"
 
 

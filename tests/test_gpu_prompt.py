@@ -85,6 +85,28 @@ def test_prompt_in_parts_and_passes(shape, parts, rows):
     _check_kv(tgt, kv, shape, n)
 
 
+def test_prompt_workspace_at_the_alignment_it_asks_for():
+    import paper_2508_04462_amd as card
+
+    tgt, _ = make_pair(MID, 6, max_ctx=112)
+    toks = ci.uniform_tokens(6, "ctx_tokens", 0, 100, MID.vocab).tolist()
+    want = tgt.prefill(toks)
+    kv = [tgt.kv_gather(layer, 0, 100) for layer in range(MID.n_layers)]
+    size = card.card_prompt_workspace_bytes(tgt.cfg, 100)
+    ws = torch.full((size + 1024,), 0xFF, dtype=torch.uint8, device=tgt.device)
+    at = (16 - ws.data_ptr()) % 1024  # 16 bytes behind a multiple of 1024
+    dev = torch.tensor(toks, dtype=torch.int32, device=tgt.device)
+    out = torch.full((1,), -9, dtype=torch.int32, device=tgt.device)
+    tgt.k_pages.fill_(0xFF)
+    tgt.v_pages.fill_(0xFF)
+    assert card.card_prompt(tgt.cfg, tgt.packed, tgt.kv(-1), 0, dev, 100, ws[at:], 100, tgt._stream(), out) == card.CARD_OK
+    assert int(out.item()) == want
+    assert (ws[size + at:] == 0xFF).all()
+    for layer in range(MID.n_layers):
+        for a, b in zip(kv[layer], tgt.kv_gather(layer, 0, 100)):
+            assert torch.equal(a, b)
+
+
 def test_prompt_on_weights_not_packed_for_this_grid():
     """As a verification step reports them: a blob that was never packed, and one packed for another grid size."""
     import paper_2508_04462_amd as card
