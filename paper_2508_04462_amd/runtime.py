@@ -74,7 +74,6 @@ class Target:
         assert sorted(order) == list(range(self.n_pages))
         self.block_table = torch.tensor(order, dtype=torch.int32, device=self.device)
         self._prompt_ws, self._prompt_rows = None, 0
-        self._prompt_token = torch.zeros(1, dtype=torch.int32, device=self.device)
         self.out = torch.zeros(4, dtype=torch.int32, device=self.device)
         self.row_argmax = torch.zeros(32, dtype=torch.int32, device=self.device)
         self.cand = torch.zeros(32, dtype=torch.int32, device=self.device)
@@ -206,18 +205,25 @@ class Target:
 
     def prefill(self, tokens: Sequence[int], chunk: int = 32) -> int:
         """Build KV[0:n); returns the arg-max after the last context token (the pending prediction
-        g0).  Through card_prompt, or, in pieces of at most `chunk` tokens, through verify calls that
+        g0).  `out` then holds what a step reports, accepted_len = -1 where a token lies outside the
+        vocabulary.  Through card_prompt, or, in pieces of at most `chunk` tokens, through verify calls that
         carry no pending token: where the caller asks for smaller pieces than 32, for short prompts
         (below), and for a model that shares the GPU with another persistent kernel (grid_wgs:
         card_prompt takes every compute unit)."""
         n = len(tokens)
         if (chunk >= 32 and self.cfg.grid_wgs == 0 and PROMPT_MIN_TOKENS <= n <= self.cfg.max_ctx
                 and self._prompt_workspace(min(n, 1024))):
-            toks = torch.tensor([int(t) for t in tokens], dtype=torch.int32, device=self.device)
-            _check(B.card_prompt(self.cfg, self.packed, self.kv(-1), 0, toks, n, self._prompt_ws, self._prompt_rows, self._stream(),
-                                 self._prompt_token), "card_prompt")
-            token = int(self._prompt_token.item())
+            # `out` as a step leaves it: all n tokens taken, the next one, their slots; or, where a token id lies outside
+            # the vocabulary (it is forwarded as the nearest one inside), as a failed step leaves it
+            ids = [int(t) for t in tokens]
+            up = torch.tensor(ids + [n, -1, 0, n, -1, -1, 0, 0], dtype=torch.int32, device=self.device)
+            _check(B.card_prompt(self.cfg, self.packed, self.kv(-1), 0, up, n, self._prompt_ws, self._prompt_rows, self._stream(),
+                                 up.data_ptr() + 4 * (n + 1)), "card_prompt")
+            valid = 0 <= min(ids) and max(ids) < self.cfg.vocab
+            self.out.copy_(up[n:n + 4] if valid else up[n + 4:])
+            token = int(up[n + 1].item())
             if token < 0:  # weights not packed, or for another grid size
+                self.out.copy_(up[n + 4:])
                 raise B.CardError(B.CARD_EDEVICE, "card_prompt")
             return token
         chunk = min(chunk, self.cfg.max_r)

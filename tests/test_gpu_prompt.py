@@ -107,6 +107,25 @@ def test_prompt_workspace_at_the_alignment_it_asks_for():
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("n", [20, 33, 300])
+def test_prefill_reports_like_a_step(n):
+    """`out` behind a prompt, whichever way it went (20 tokens: verify calls): the next token and the slots of this
+    prompt, not of what ran before it; failed where a token lies outside the vocabulary."""
+    tgt, _ = make_pair(TINY, 4, max_ctx=320)
+    toks = ci.uniform_tokens(4, "ctx_tokens", 0, n, TINY.vocab).tolist()
+    tgt.verify(0, -1, toks[:3])
+    g0 = tgt.prefill(toks)
+    taken, token, first, count = tgt.out.tolist()
+    if n > 32:
+        assert (taken, token, first, count) == (n, g0, 0, n)
+    assert taken >= 1 and first + count <= n
+    assert tgt.prefill([TINY.vocab] + toks[1:]) == tgt.prefill([TINY.vocab - 1] + toks[1:])
+    for bad in (-1, TINY.vocab):
+        tgt.prefill(toks[:-1] + [bad])
+        assert tgt.out.tolist()[:2] == [-1, -1] and tgt.out.tolist()[3] == 0
+        assert 0 <= tgt.prefill(toks) == g0
+
+
 def test_prompt_on_weights_not_packed_for_this_grid():
     """As a verification step reports them: a blob that was never packed, and one packed for another grid size."""
     import paper_2508_04462_amd as card
