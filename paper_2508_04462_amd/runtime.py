@@ -232,9 +232,13 @@ class Target:
             last = self.verify(s, -1, tokens[s:s + chunk])
         return last["row_argmax"][-1]
 
+    def release_prompt_workspace(self) -> None:
+        """Give the memory back that prompts work in (8B shape: 0.25 GB; the next prompt takes it again)."""
+        self._prompt_ws, self._prompt_rows = None, 0
+
     def _prompt_workspace(self, rows: int) -> bool:
-        """Room for passes of `rows` rows, kept for the next prompt; fewer rows where the device is nearly
-        full, none (False) where it is full."""
+        """Room for passes of `rows` rows, kept for the next prompt (release_prompt_workspace gives it
+        back); fewer rows where the device is nearly full, none (False) where it is full."""
         while rows > self._prompt_rows:
             self._prompt_ws, held = None, self._prompt_rows
             self._prompt_rows = 0

@@ -163,6 +163,17 @@ def test_prompt_refuses_what_it_cannot_do():
     assert tgt.prefill([5000, -3] + toks[2:]) == tgt.prefill([TINY.vocab - 1, 0] + toks[2:])
 
 
+def test_prompt_workspace_can_be_given_back():
+    tgt, _ = make_pair(MID, 5, max_ctx=200)
+    toks = ci.uniform_tokens(5, "ctx_tokens", 0, 150, MID.vocab).tolist()
+    before = torch.cuda.memory_allocated()
+    g0 = tgt.prefill(toks)
+    assert torch.cuda.memory_allocated() > before
+    tgt.release_prompt_workspace()
+    assert torch.cuda.memory_allocated() == before
+    assert tgt.prefill(toks) == g0
+
+
 def test_prompt_on_a_full_device_goes_through_verify_calls(monkeypatch):
     """Where the device has no room for the prompt's workspace a prompt is what it was without it:
     verify calls of 32 rows (the same bits), with room for fewer rows only, more passes."""
