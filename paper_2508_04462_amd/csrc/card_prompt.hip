@@ -42,6 +42,30 @@ __device__ __forceinline__ void px_store4(__bf16* x, int Ks, int mt, int m, int 
     *reinterpret_cast<uint2v*>(p + 512) = uint2v{pack_bf16(l[0], l[1]), pack_bf16(l[2], l[3])};
 }
 
+// SwiGLU of two gate/up tiles ta and tb (of Nt) and 16 rows: a tile holds eight gate rows (lanes 0-31 of the accumulator)
+// and the eight up rows that belong to them (lanes 32-63).  The tiles trade halves: lanes 0-31 finish ta, lanes 32-63 tb.
+// sc: the RMSNorm scale of row m = lane & 15; `on`: whether this lane's tile exists.
+__device__ __forceinline__ void px_swiglu(__bf16* act, int Ks_out, int Nt, int mt, int lane, float sc, const floatx4& a,
+                                          const floatx4& b, int ta, int tb, bool on) {
+    const bool low = lane < 32;
+    const int t = low ? ta : tb, m = lane & 15;
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float give = low ? b[e] : a[e];
+        const float got = __shfl_xor(give, 32);
+        const float g = (low ? a[e] : got) * sc, u = (low ? got : b[e]) * sc;
+        v[e] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
+    }
+    if (!on) return;
+    const int k = t * 8 + ((lane >> 4) & 1) * 4;
+    px_store4(act, Ks_out, mt, m, k, v);
+    // whoever writes the last tile fills the rest of the next product's last k-step with zeros
+    const float z[4] = {0.f, 0.f, 0.f, 0.f};
+    if (t == Nt - 1)
+        for (int kz = k + 8; kz < Ks_out * 32; kz += 8) px_store4(act, Ks_out, mt, m, kz, z);
+}
+
 // ---- product ------------------------------------------------------------------------------------
 struct PgemmArgs {
     const char* w;       // packed matrix
@@ -231,40 +255,17 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
                 if (mt0 + j < a.mts) *reinterpret_cast<floatx4*>(p + j * 256) = acc[i][j];
         }
     } else if constexpr (EPI == PG_SWIGLU) {
-        // SwiGLU: a tile holds eight gate rows (lanes 0-31 of the accumulator) and the eight up rows that
-        // belong to them (lanes 32-63).  Two tiles trade halves: lanes 0-31 finish tile i, lanes 32-63 tile i + 1.
         for (int e = tid; e < MT * 64; e += kPgWaves * 64) {
             const float sc = px_row_scale<4>(a.ss + size_t(mt0 * 16 + (e >> 2)) * a.ss_groups, a.ss_groups, e & 3, a.inv_d, a.eps);
             if ((e & 3) == 0) scale[e >> 2] = sc;
         }
         sync();
-        const bool low = lane < 32;
-        const int m = lane & 15;
 #pragma unroll
-        for (int i = 0; i < kPgN; i += 2) {
-            const int t = low ? tl[i].t : tl[i + 1].t;
-            const bool on = v0 + i + (low ? 0 : 1) < a.Nt;
+        for (int i = 0; i < kPgN; i += 2)
 #pragma unroll
-            for (int j = 0; j < MT; ++j) {
-                const float sc = scale[j * 16 + m];
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float give = low ? acc[i + 1][j][e] : acc[i][j][e];
-                    const float got = __shfl_xor(give, 32);
-                    const float g = (low ? acc[i][j][e] : got) * sc, u = (low ? got : acc[i + 1][j][e]) * sc;
-                    v[e] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
-                }
-                const int k = t * 8 + ((lane >> 4) & 1) * 4;
-                if (on && mt0 + j < a.mts) {
-                    px_store4(a.act, a.Ks_out, mt0 + j, m, k, v);
-                    // whoever writes the last tile fills the rest of the next product's last k-step with zeros
-                    const float z[4] = {0.f, 0.f, 0.f, 0.f};
-                    if (t == a.Nt - 1)
-                        for (int kz = k + 8; kz < a.Ks_out * 32; kz += 8) px_store4(a.act, a.Ks_out, mt0 + j, m, kz, z);
-                }
-            }
-        }
+            for (int j = 0; j < MT; ++j)
+                px_swiglu(a.act, a.Ks_out, a.Nt, mt0 + j, lane, scale[j * 16 + (lane & 15)], acc[i][j], acc[i + 1][j], tl[i].t,
+                          tl[i + 1].t, v0 + i + (lane < 32 ? 0 : 1) < a.Nt && mt0 + j < a.mts);
     } else {
         // arg-max of one row: (ordered logit, ~token) keys, the lowest token among equals
         const float sc = px_row_scale<64>(a.ss + size_t(a.row) * a.ss_groups, a.ss_groups, lane, a.inv_d, a.eps);
@@ -387,33 +388,17 @@ __global__ __launch_bounds__(256) void k_prompt_resid(PepiArgs a) {
     if (tid < 16) a.ss[size_t(mt * 16 + tid) * a.ss_groups + grp] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
-// SwiGLU of a gate/up product that was cut along K.  One workgroup: 16 rows, a tile pair per wavefront:
-// lanes 0-31 of the first tile and lanes 32-63 of the second (see the fused form above).
+// SwiGLU of a gate/up product that was cut along K.  One workgroup: 16 rows, a tile pair per wavefront.
 __global__ __launch_bounds__(256) void k_prompt_swiglu(PepiArgs a, __bf16* act, int Ks_out) {
     __shared__ float scale[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, mt = a.mt0 + blockIdx.y, m = lane & 15;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, mt = a.mt0 + blockIdx.y;
     const float rsc = px_row_scale<16>(a.ss + size_t(mt * 16 + (tid >> 4)) * a.ss_groups, a.ss_groups, tid & 15, a.inv_d, a.eps);
     if ((tid & 15) == 0) scale[tid >> 4] = rsc;
     __syncthreads();
-    const float sc = scale[m];
-    const bool low = lane < 32;
     const int ta = (blockIdx.x * kPgWaves + wave) * 2, tb = min(ta + 1, a.Nt - 1);
     if (ta >= a.Nt) return;
     const floatx4 pa = part_sum(a, ta, mt, lane), pb = part_sum(a, tb, mt, lane);
-    const int t = low ? ta : ta + 1;
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float give = low ? pb[e] : pa[e];
-        const float got = __shfl_xor(give, 32);
-        const float g = (low ? pa[e] : got) * sc, u = (low ? got : pb[e]) * sc;
-        v[e] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
-    }
-    const int k = t * 8 + ((lane >> 4) & 1) * 4;
-    if (t < a.Nt) px_store4(act, Ks_out, mt, m, k, v);
-    const float z[4] = {0.f, 0.f, 0.f, 0.f};
-    if (t == a.Nt - 1)
-        for (int kz = k + 8; kz < Ks_out * 32; kz += 8) px_store4(act, Ks_out, mt, m, kz, z);
+    px_swiglu(act, Ks_out, a.Nt, mt, lane, scale[lane & 15], pa, pb, ta, ta + 1, (lane < 32 ? ta : ta + 1) < a.Nt);
 }
 
 // Rotation table of the pass's positions, angles in fp64 as in the verify kernel.
