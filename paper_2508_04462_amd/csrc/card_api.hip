@@ -91,7 +91,7 @@ int grid_size(const card_model_cfg* cfg) {
 
 // The kernel synchronises its workgroups through flags in memory, so all of them have to be
 // resident at once.  It is launched as an ordinary kernel: one workgroup fills a compute unit
-// (158.5 KiB of its LDS, 512 threads with 256 registers each), the grid is no larger than the
+// (158.6 of its 160 KiB of LDS, 512 threads with 256 registers each), the grid is no larger than the
 // number of compute units, and the occupancy query below confirms that the device can hold a
 // workgroup per compute unit, so on an otherwise idle device the dispatcher places all of them.
 // Should other work hold compute units for longer than the kernel's bounded waits, the step ends

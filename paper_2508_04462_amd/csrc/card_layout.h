@@ -176,7 +176,7 @@ inline Layout make_layout(const card_model_cfg* c) {
     L.m_acount_off = take(size_t(c->n_kv_heads) * (2 * G) * 4);
     L.m_best_off = take(size_t(kMaxR) * 8);
     L.m_rope_off = take(size_t(kMaxR) * h * 4);
-    L.m_topk_off = take(size_t(256) * kMaxR * 16 * 8);  // per workgroup and row: sixteen best keys
+    L.m_topk_off = take(size_t(256) * kMaxR * 16 * 8);  // per workgroup and row: up to sixteen best keys
     L.m_lse_off = take(size_t(256) * kMaxR * 2 * 4);    // per workgroup and row: (max, sum of exp)
     L.m_out_off = take(64);                             // where a draft-side call parks the verify result
     // down-projection at r > 8: the four workgroups of a group each hold a quarter of K of the

@@ -91,7 +91,7 @@ struct MegaArgs {
     int32_t tmask_words, tmask_base;
     // per-row top-k of the vocabulary phase instead of the arg-max (topk = 0: arg-max)
     int32_t topk;
-    unsigned long long* topk_part;  // [nwg][kMaxR][16] best keys of each workgroup's columns
+    unsigned long long* topk_part;  // [nwg][kMaxR][16] topk best keys of each workgroup's columns, then zeros
     float* lse_part;                // [nwg][kMaxR][2]  (max, sum of exp) of each workgroup's columns
     int32_t* topk_tok;              // out [r][topk]
     float* topk_prob;               // out [r][topk]
@@ -540,7 +540,7 @@ enum MegaEpi { ME_QKV = 0, ME_RESID = 1, ME_SWIGLU = 2, ME_LM = 3, ME_LM_TOPK = 
 // Running state of one thread across the batches of the vocabulary phase when the phase keeps a
 // per-row top-k and a log-sum-exp (draft side) instead of the arg-max.
 struct LmState {
-    unsigned long long run[2];  // this lane's share of its row's sixteen best keys so far
+    unsigned long long run[2];  // this lane's share of its row's topk best keys so far (zeros behind them)
     float m, s;                 // running maximum and sum of exp(value - m) over this lane's columns
 };
 
@@ -981,37 +981,35 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                 constexpr int PARTS = kMegaThreads / COLS;
                 constexpr int ROWS_PER = NBS * 16 / PARTS;
                 static_assert(ROWS_PER >= 1, "rows per thread");
-                {
-                    const int m = tid % COLS, part = tid / COLS;
-                    unsigned long long best = 0ull;
-                    if (m < r) {
-                        const float sc = sm.row_scale[m];
-                        // row m predicts the token at position ctx_len + m + 1
-                        const uint32_t rkey = gumbel_row_key(a.seed_lo, a.seed_hi, uint32_t(a.ctx_len + m + 1));
-    #pragma unroll
-                        for (int q = 0; q < ROWS_PER; ++q) {
-                            const int nl = part * ROWS_PER + q, i = nl >> 4;
-                            const int n = (tile0 + i * a.nwg) * 16 + (nl & 15);
-                            if (i < nvalid_s && n < a.V) {
-                                float val = sm.tile[nl * COLS + m] * sc;
-                                if (a.inv_temp > 0.f) val = val * a.inv_temp + gumbel_noise(rkey, uint32_t(n));
-                                const unsigned long long key =
-                                    (static_cast<unsigned long long>(float_key(val)) << 32) |
-                                    (0xffffffffu - uint32_t(n));
-                                best = key > best ? key : best;
-                            }
+                const int m = tid % COLS, part = tid / COLS;
+                unsigned long long best = 0ull;
+                if (m < r) {
+                    const float sc = sm.row_scale[m];
+                    // row m predicts the token at position ctx_len + m + 1
+                    const uint32_t rkey = gumbel_row_key(a.seed_lo, a.seed_hi, uint32_t(a.ctx_len + m + 1));
+#pragma unroll
+                    for (int q = 0; q < ROWS_PER; ++q) {
+                        const int nl = part * ROWS_PER + q, i = nl >> 4;
+                        const int n = (tile0 + i * a.nwg) * 16 + (nl & 15);
+                        if (i < nvalid_s && n < a.V) {
+                            float val = sm.tile[nl * COLS + m] * sc;
+                            if (a.inv_temp > 0.f) val = val * a.inv_temp + gumbel_noise(rkey, uint32_t(n));
+                            const unsigned long long key =
+                                (static_cast<unsigned long long>(float_key(val)) << 32) |
+                                (0xffffffffu - uint32_t(n));
+                            best = key > best ? key : best;
                         }
                     }
-                    sm.part_best[part * COLS + m] = best;
                 }
+                sm.part_best[part * COLS + m] = best;
                 cbar(sm, cgen);
                 if (tid < r) {
-                    unsigned long long best = sm.wg_best[tid];
-                    for (int part = 0; part < PARTS; ++part) {
-                        const unsigned long long k = sm.part_best[part * COLS + tid];
-                        best = k > best ? k : best;
+                    unsigned long long of_row = sm.wg_best[tid];
+                    for (int p = 0; p < PARTS; ++p) {
+                        const unsigned long long k = sm.part_best[p * COLS + tid];
+                        of_row = k > of_row ? k : of_row;
                     }
-                    sm.wg_best[tid] = best;
+                    sm.wg_best[tid] = of_row;
                 }
             }
         } else {  // ME_QKV
@@ -1640,7 +1638,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         const bool last = l + 1 == a.L;
         EpiArgs ea = {};
         ea.layer = l;
-        
+
         // QKV (+norm scale, rotation, KV write).  Pages that hold only old context do not depend
         // on this phase: their loads are issued as soon as the k-loop is over, ahead of the
         // epilogue's stores, and land while the barrier in front of attention is crossed.
@@ -1734,7 +1732,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
 
     // vocabulary head + arg-max
     {
-                const PhasePlan p_lm = stream_phase<!PK>(a, 4 * a.L, wg, wave);
+        const PhasePlan p_lm = stream_phase<!PK>(a, 4 * a.L, wg, wave);
         EpiArgs ea = {};
         ea.ss_in = a.ss + size_t(2 * a.L) * ss_stride;
         LmState lm = {{0ull, 0ull}, -1e30f, 0.f};
@@ -1744,7 +1742,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         if (!DR && tid < a.r && sm.wg_best[tid] != 0ull)
             __hip_atomic_fetch_max(&a.best[tid], sm.wg_best[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if constexpr (DR) {
-            // this workgroup's share of every row: its sixteen best keys and its (max, sum of exp)
+            // this workgroup's share of every row: its topk best keys, zeros behind them, and its (max, sum of exp)
             constexpr int LPR = kMegaThreads / (16 * MT), RUN = 16 / LPR;
             const int m = tid / LPR, p = tid % LPR;
             float mx = lm.m;
@@ -1769,8 +1767,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
     grid_wait(a, gen, sm, cgen);
 
     if constexpr (DR) {
-        // Rows are merged by one workgroup each: thread t holds workgroup t's sorted list of sixteen
-        // keys for the row and its (max, sum) pair; the log-sum-exp folds the pairs, then k rounds of
+        // Rows are merged by one workgroup each: thread t holds workgroup t's sorted list of topk keys (in
+        // sixteen places) for the row and its (max, sum) pair; the log-sum-exp folds the pairs, then k rounds of
         // "largest list head in the workgroup" emit the row's k best tokens with their probabilities.
         for (int m = wg; m < a.r; m += nwg) {
             unsigned long long mine[16];
