@@ -213,7 +213,7 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.pages_used = ceil_div(slot0 + r, kKvBlock);
     a.slot0 = slot0;
     a.old_end = tree ? tree->mask_base : ctx_len;
-    a.clear_from = tree && tree->piece ? tree->level_end : slot0 + r;
+    a.clear_from = tree && tree->piece ? tree->level_end : 0;
     a.level_first = tree && tree->piece ? tree->level_first : 0;
     a.row_tiles = ceil_div(a.G * r, 16);
     // Cut the context so that a workgroup's share fits the page buffers of its wavefronts (all of

@@ -83,9 +83,9 @@ struct MegaArgs {
     // row_pos[m] and in cache slot slot0 + m; it sees every slot below tmask_base and, from there on,
     // the slots whose bit is set in its mask row tmask[m * tmask_words ..]
     int32_t slot0, old_end;       // slot of row 0; slots below old_end hold context written by earlier calls
-    int32_t clear_from;           // a page opened by this call is cleared from this slot on: behind its rows and, in a piece
-                                  // of a level, behind those of its peers in calls that may run at the same time
-    int32_t level_first;          // piece of a level: the slots from this one on are written by such calls too
+    // piece of a level, forwarded by several calls that may run at the same time: the slots from level_first on are
+    // written by the others too; a page opened by this call is cleared from clear_from on, behind the level's last slot
+    int32_t level_first, clear_from;
     const int32_t* row_pos;
     const uint32_t* tmask;
     int32_t tmask_words, tmask_base;
@@ -535,7 +535,8 @@ __device__ __forceinline__ float gumbel_noise(uint32_t row_key, uint32_t token) 
     return -logf(-logf(u));
 }
 
-enum MegaEpi { ME_QKV = 0, ME_RESID = 1, ME_SWIGLU = 2, ME_LM = 3, ME_LM_TOPK = 4 };
+// (ME_QKV_PIECE: ME_QKV of a piece of a draft-side level)
+enum MegaEpi { ME_QKV = 0, ME_RESID = 1, ME_SWIGLU = 2, ME_LM = 3, ME_LM_TOPK = 4, ME_QKV_PIECE = 5 };
 
 // Running state of one thread across the batches of the vocabulary phase when the phase keeps a
 // per-row top-k and a log-sum-exp (draft side) instead of the arg-max.
@@ -1012,7 +1013,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     sm.wg_best[tid] = of_row;
                 }
             }
-        } else {  // ME_QKV
+        } else {  // ME_QKV, ME_QKV_PIECE
             // packed rows: [q heads | k heads | v heads]; in q and k heads row 2p is element p of the
             // head and row 2p+1 its rotation partner p + h/2.  Work item: (tile, row m, which half).
             const int which = tid & 1, m = (tid >> 1) % kMaxR, i = tid / (2 * kMaxR);
@@ -1053,9 +1054,9 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
             // V rows: work item (tile, head element j of the tile, group of four slots): four consecutive
             // aligned tokens of an element are 8 contiguous bytes.  A page is opened by the call that writes its
             // first slot: that call clears the slots behind its last row, so that a later step never multiplies
-            // a zero probability with bits nobody stored (0 x NaN).  Slots between its last row and clear_from
-            // are peers' of the same draft-side level: their own calls write them, before or after this.
-            const int first = a.slot0, end = first + r, clear = a.clear_from;
+            // a zero probability with bits nobody stored (0 x NaN).  In a piece of a level the slots between its last
+            // row and clear_from are peers': their own calls write them, before or after this.
+            const int first = a.slot0, end = first + r, clear = EPI == ME_QKV_PIECE ? a.clear_from : end;
             const int jj = tid & 15, vi = (tid >> 4) % NB;
             if (vi < nvalid_s && (tile0 + vi * a.nwg) * 16 >= a.qd + a.kvd) {
                 const int h = a.h;
@@ -1072,13 +1073,15 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     }
                     const int page = sm.row_page[min(max(g - first, 0), r - 1)];  // (a group of four lies in one page)
                     __bf16* dst = ea.vpool + (size_t(page) * a.Hkv + head) * (16 * h) + v_page_index(jg, g & 15);
-                    if (g >= first && g + 4 <= stop && (g + 4 <= end || clear == end || g >= clear)) {
+                    if (g >= first && g + 4 <= stop && (EPI != ME_QKV_PIECE || g + 4 <= end || clear == end || g >= clear)) {
                         const unsigned long long w = uint64_t(pack_bf16(v4[0], v4[1])) | (uint64_t(pack_bf16(v4[2], v4[3])) << 32);
                         __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     } else {
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            if (g + q >= first && g + q < stop && (g + q < end || g + q >= clear)) st_dev_bf16(dst + q, v4[q]);
+                            if (g + q >= first && g + q < stop &&
+                                (EPI != ME_QKV_PIECE || g + q < end || g + q >= clear))
+                                st_dev_bf16(dst + q, v4[q]);
                     }
                 }
             }
@@ -1664,7 +1667,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         };
         CARD_TS(0)
         ea.ts0 = 21;
-        gemm_phase<kNbQkv, MT, ME_QKV, PK>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
+        gemm_phase<kNbQkv, MT, PC ? ME_QKV_PIECE : ME_QKV, PK>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
                                           sm, wave, lane, cgen, preload);
         CARD_TS(1)
         store_wait();
