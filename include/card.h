@@ -229,7 +229,9 @@ int card_static_scratch_reset(void);
 /* A prompt: forwards n tokens at positions ctx_len .. ctx_len + n - 1 (ctx_len a multiple of 16), leaves
  * their K and V in the cache and writes the arg-max behind the last one to next_token_dev (dev, one
  * int32; NULL = not wanted).  Same values as card_verify calls over the same tokens, up to the order
- * of the fp32 sums; ordinary kernels that wait for nobody, in passes of up to 1024 rows, as many as
+ * of the fp32 sums.  That order depends on the number of rows of a pass: the same first tokens get K
+ * and V of other last bits in a prompt of another length (the same prompt gives the same bits every
+ * time).  Ordinary kernels that wait for nobody, in passes of up to 1024 rows, as many as
  * workspace_rows has room for:
  *   workspace_dev : dev, card_prompt_workspace_bytes(cfg, workspace_rows) bytes, 16-byte aligned, no
  *                   initialisation; calls sharing it must not overlap

@@ -130,12 +130,13 @@ struct PgTile {
 // activation fragments; two workgroups per compute unit, so one's barriers and loads hide behind the
 // other's matrix instructions.
 // Loads in flight: a k-step's matrix instructions take 0.21 us, a load 0.5-1 us, so three steps of
-// weights and four of activations are ahead in registers (one and two steps ahead: gate/up of the 8B
-// shape, 1008 rows, 434 us instead of 371).  All loads are unconditional (out of range behind the end:
-// zeros, no memory access), so that the compiler's waits leave the others in flight.
-// What bounds it: 24 KiB per workgroup and k-step from L2 (55 GB/s per compute unit) at 1.27 PFLOP/s
-// issued, halves counted (gate/up above); eight row tiles per workgroup move a third less, but leave
-// registers for one step ahead only: 403 us.  The 32x32x16 instruction on the same tiles: no gain.
+// weights and four of activations are ahead in registers.  All loads are unconditional (out of range behind
+// the end: zeros, no memory access), so that the compiler's waits leave the others in flight.
+// Measured on gate/up of the 8B shape, 1000 rows (1792 workgroups, 128 k-steps, 474 GFLOP issued, halves
+// counted): 375-393 us from session to session, 1.2-1.26 PFLOP/s.  24 KiB per workgroup and k-step come from L2,
+// 14-15 TB/s, 56-59 GB/s per compute unit.  In one session, 393 us: one step of weights ahead 393 (the depth
+// no longer matters with two k-steps per barrier), eight row tiles per workgroup 588 (a third fewer bytes, but 58
+// registers spill).  The 32x32x16 instruction on the same tiles: no gain.
 template <int EPI>
 __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
     constexpr int MT = kPgTiles;

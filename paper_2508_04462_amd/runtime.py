@@ -15,8 +15,9 @@ def make_cfg(shape, max_ctx: int, max_r: int = 32, grid_wgs: int = 0) -> B.CardM
                           shape.d_ffn, shape.vocab, shape.rope_theta, shape.rms_eps, 16, max_ctx, max_r, grid_wgs)
 
 
-# Prompts of at least this many tokens go through card_prompt: whatever takes more than one verify call
-# (33 tokens, 8B shape: 4.2 ms against 6.6; 20 tokens: 4.3 against 3.4).
+# Prompts of at least this many tokens go through card_prompt: whatever takes more than one verify call.  us by
+# card_prompt / by verify calls, 20 tokens: 1B shape 1321 / 1152, 7B 4326 / 3621, 8B 4488 / 3629, 8 layers of 70B 3397 / 3009
+# (2 layers of 256 columns: 144 / 167); 33 tokens: 1367 / 2128, 4587 / 6879, 4442 / 6924, 3562 / 5872 (147 / 315).
 PROMPT_MIN_TOKENS = 33
 
 _LANE_STREAMS: Dict[str, list] = {}
@@ -208,8 +209,8 @@ class Target:
         g0).  `out` then holds what a step reports, accepted_len = -1 where a token lies outside the
         vocabulary.  Through card_prompt, or, in pieces of at most `chunk` tokens, through verify calls that
         carry no pending token: where the caller asks for smaller pieces than 32, for short prompts
-        (below), and for a model that shares the GPU with another persistent kernel (grid_wgs:
-        card_prompt takes every compute unit)."""
+        (PROMPT_MIN_TOKENS), and wherever grid_wgs is given, whether or not something runs beside the
+        model at that time (card_prompt's kernels spread over all compute units)."""
         n = len(tokens)
         if (chunk >= 32 and self.cfg.grid_wgs == 0 and PROMPT_MIN_TOKENS <= n <= self.cfg.max_ctx
                 and self._prompt_workspace(min(n, 1024))):
