@@ -1051,38 +1051,65 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     }
                 }
             }
-            // V rows: work item (tile, head element j of the tile, group of four slots): four consecutive
-            // aligned tokens of an element are 8 contiguous bytes.  A page is opened by the call that writes its
-            // first slot: that call clears the slots behind its last row, so that a later step never multiplies
-            // a zero probability with bits nobody stored (0 x NaN).  In a piece of a level the slots between its last
-            // row and clear_from are peers': their own calls write them, before or after this.
-            const int first = a.slot0, end = first + r, clear = EPI == ME_QKV_PIECE ? a.clear_from : end;
-            const int jj = tid & 15, vi = (tid >> 4) % NB;
-            if (vi < nvalid_s && (tile0 + vi * a.nwg) * 16 >= a.qd + a.kvd) {
+            // V rows: work item (tile, head element j of the tile); the r tokens of one element are
+            // consecutive 2-byte slots inside a page row, written as the widest aligned stores
+            const int jj = (tid & 1) * 8 + ((tid >> 1) & 7);
+            const bool v_lane = ((tid >> 1) % kMaxR) < 8;
+            if (i < nvalid_s && v_lane && (tile0 + i * a.nwg) * 16 >= a.qd + a.kvd) {
                 const int h = a.h;
-                const int rel = (tile0 + vi * a.nwg) * 16 - a.qd - a.kvd + jj;
+                const int rel = (tile0 + i * a.nwg) * 16 - a.qd - a.kvd + jj;
                 const int head = rel / h, jg = rel % h;
-                const int stop = ((end - 1) & ~15) >= first ? (end + 15) & ~15 : end;  // first slot behind the ones to write
-                for (int g = (first & ~3) + 4 * (tid / (16 * NB)); g < stop; g += 4 * (kMegaThreads / (16 * NB))) {
-                    __bf16 v4[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int m = min(max(g + q - first, 0), r - 1);
-                        const float z = sm.tile[(vi * 16 + jj) * COLS + m] * sm.row_scale[m];
-                        v4[q] = static_cast<__bf16>(g + q < end ? z : 0.f);
+                int m2 = 0;
+                while (m2 < r) {
+                    const int slot = a.slot0 + m2;
+                    const int page = sm.row_page[m2], tk = slot & 15;
+                    const int run = min(r - m2, 16 - tk);
+                    const size_t vb = (size_t(page) * a.Hkv + head) * (16 * h);
+                    auto val = [&](int t) {
+                        return static_cast<__bf16>(sm.tile[(i * 16 + jj) * COLS + m2 + t] * sm.row_scale[m2 + t]);
+                    };
+                    int q = 0;
+                    while (q < run) {  // four consecutive aligned tokens are 8 contiguous bytes
+                        const int t = tk + q;
+                        __bf16* dst = ea.vpool + vb + v_page_index(jg, t);
+                        if ((t & 3) == 0 && q + 4 <= run) {
+                            const unsigned long long w = uint64_t(pack_bf16(val(q), val(q + 1))) |
+                                                         (uint64_t(pack_bf16(val(q + 2), val(q + 3))) << 32);
+                            __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), w, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                            q += 4;
+                        } else if ((t & 1) == 0 && q + 2 <= run) {
+                            __hip_atomic_store(reinterpret_cast<uint32_t*>(dst), pack_bf16(val(q), val(q + 1)),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            q += 2;
+                        } else {
+                            st_dev_bf16(dst, val(q));
+                            q += 1;
+                        }
                     }
-                    const int page = sm.row_page[min(max(g - first, 0), r - 1)];  // (a group of four lies in one page)
-                    __bf16* dst = ea.vpool + (size_t(page) * a.Hkv + head) * (16 * h) + v_page_index(jg, g & 15);
-                    if (g >= first && g + 4 <= stop && (EPI != ME_QKV_PIECE || g + 4 <= end || clear == end || g >= clear)) {
-                        const unsigned long long w = uint64_t(pack_bf16(v4[0], v4[1])) | (uint64_t(pack_bf16(v4[2], v4[3])) << 32);
-                        __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (g + q >= first && g + q < stop &&
-                                (EPI != ME_QKV_PIECE || g + q < end || g + q >= clear))
-                                st_dev_bf16(dst + q, v4[q]);
+                    // a page is opened by the call that writes its first slot: clear the slots behind
+                    // the ones written, so that a later step never multiplies a zero probability with
+                    // bits nobody stored (0 x NaN); in a piece of a level those behind the level: the slots
+                    // between are peers', whose own calls write them, before or after this
+                    if (tk == 0) {
+                        int t = EPI == ME_QKV_PIECE ? max(run, a.clear_from - slot) : run;
+                        while (t < 16) {
+                            __bf16* dst = ea.vpool + vb + v_page_index(jg, t);
+                            if ((t & 3) == 0) {
+                                __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), 0ull, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                                t += 4;
+                            } else if ((t & 1) == 0) {
+                                __hip_atomic_store(reinterpret_cast<uint32_t*>(dst), 0u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+                                t += 2;
+                            } else {
+                                st_dev_bf16(dst, static_cast<__bf16>(0.f));
+                                t += 1;
+                            }
+                        }
                     }
+                    m2 += run;
                 }
             }
         }

@@ -387,8 +387,8 @@ def test_the_grid_size_changes_no_bit_at_r_up_to_eight():
 
 @pytest.mark.parametrize("ctx_len,r", [(0, 1), (0, 32), (3, 2), (13, 3), (13, 5), (14, 2), (15, 1), (15, 18), (16, 4), (30, 31), (31, 17)])
 def test_keys_and_values_land_in_their_slots_whatever_the_alignment(ctx_len, r):
-    """A step's V rows are written in groups of four slots: first and last groups that are only partly
-    the step's own, rows over one, two and three pages, pages opened by the step or before it.  The
+    """A step's V rows are written as the widest aligned stores: runs that begin and end off them, rows over
+    one, two and three pages, pages opened by the step or before it.  The
     pools start as 0xFF bytes: older slots keep their bits, the step's slots hold the oracle's values,
     and the slots behind them in a page that the step opens are cleared."""
     shape, n = TINY, 64
