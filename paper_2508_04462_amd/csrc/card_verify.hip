@@ -21,7 +21,8 @@
 //   * everything one workgroup writes for another is stored with device scope (write-through);
 //   * every such buffer is written exactly once per call, at an address nobody has read before
 //     in this call (one copy per layer and phase), so plain cached loads can never hit a stale
-//     line; the barrier flags themselves are only touched with device-scope accesses.
+//     line; the barrier flags themselves are only touched with device-scope accesses, and so are
+//     cache pages that other calls may be writing at the same time (pieces of a draft-side level).
 //
 // Activations travel between phases already split into bf16 high + low halves and laid out in
 // the operand order of the matrix instruction ("fragment order"): element (row m, column k) of
