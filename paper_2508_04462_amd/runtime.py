@@ -186,22 +186,24 @@ class Target:
         ready = torch.cuda.Event()
         ready.record(cur)
         done = []
-        for i, (c0, c1) in enumerate(level_pieces(n, lanes)):
-            lane = i % lanes
-            st = self._lane_streams[lane]
-            if i < lanes:
-                st.wait_event(ready)
-            rows = B.CardTreeRows(tok[c0:c1].data_ptr(), pos[c0:c1].data_ptr(), int(first_slot) + c0, mask[c0:c1].data_ptr(),
-                                  words, int(mask_base))
-            _check(B.card_draft_level_piece(self.cfg, self.packed, self.kv(-1), ctx_len, rows, c1 - c0, int(first_slot),
-                                            int(first_slot) + n, k, self._lane_ws[lane], st.cuda_stream, tk[c0:c1], tp[c0:c1], None),
-                   "card_draft_level_piece")
-            ev = torch.cuda.Event()
-            ev.record(st)
-            done.append(ev)
-        for ev in done:
-            cur.wait_event(ev)
-        cur.synchronize()
+        try:
+            for i, (c0, c1) in enumerate(level_pieces(n, lanes)):
+                lane = i % lanes
+                st = self._lane_streams[lane]
+                if i < lanes:
+                    st.wait_event(ready)
+                rows = B.CardTreeRows(tok[c0:c1].data_ptr(), pos[c0:c1].data_ptr(), int(first_slot) + c0, mask[c0:c1].data_ptr(),
+                                      words, int(mask_base))
+                _check(B.card_draft_level_piece(self.cfg, self.packed, self.kv(-1), ctx_len, rows, c1 - c0, int(first_slot),
+                                                int(first_slot) + n, k, self._lane_ws[lane], st.cuda_stream, tk[c0:c1], tp[c0:c1],
+                                                None), "card_draft_level_piece")
+                ev = torch.cuda.Event()
+                ev.record(st)
+                done.append(ev)
+        finally:  # (also where a later piece was refused: the enqueued ones use this call's tensors)
+            for ev in done:
+                cur.wait_event(ev)
+            cur.synchronize()
         return {"topk_tokens": tk, "topk_probs": tp}
 
     def prefill(self, tokens: Sequence[int], chunk: int = 32) -> int:

@@ -369,6 +369,21 @@ def test_a_wide_level_from_any_slot_leaves_what_calls_in_a_row_leave(first, n, l
     _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), MID, first, n)
 
 
+def test_a_wide_level_with_a_refused_piece_leaves_nothing_running():
+    """The pieces in front of a refused one work on tensors of the call: it ends behind them."""
+    import paper_2508_04462_amd as card
+
+    tgts, _, toks, rows, mask_base, pieces = _level_twice(MID, 25, 70, 80, 100, 5, 2)
+    assert len(pieces) == 4
+    short = [row[:3] for row in rows]  # 96 slots from mask_base = 64: the last pieces' lie behind them
+    with pytest.raises(card.CardError) as e:
+        tgts[1].draft_level_wide(70, toks, [71] * 100, 80, short, mask_base, 5)
+    assert e.value.status == card.CARD_ERANGE
+    assert all(st.query() for st in tgts[1]._lane_streams)
+    res = tgts[1].draft_level_wide(70, toks, [71] * 100, 80, rows, mask_base, 5)
+    assert (res["topk_tokens"] >= 0).all()
+
+
 @pytest.mark.parametrize("n", [8, 13, 29])
 def test_a_chain_forwarded_as_tree_rows_equals_the_verify_step_bit_for_bit(n):
     """Tree rows whose mask is the plain causal chain (row i sees the context and rows 0..i, slots
