@@ -300,7 +300,9 @@ def test_a_failure_on_the_draft_side_ends_the_loop_with_that_error():
             raise ValueError("planted failure")
         return list(tokens), list(parents)
 
-    loop = card.ConcurrentLoop(tgt, dr, shape.ctx, g0, K=8, k=4, depth=3, plant=failing_plant)
+    # the target waits for the draft's levels: on its own this small one may be through its 200 tokens (30 ms) before
+    # the draft has planted four
+    loop = card.ConcurrentLoop(tgt, dr, shape.ctx, g0, K=8, k=4, depth=3, plant=failing_plant, wait_levels=2, wait_ms=2000.0)
     with pytest.raises(ValueError, match="planted failure"):
         loop.run(n_new)
     assert len(loop.emitted) - 1 < n_new  # the target stopped early
