@@ -4,6 +4,8 @@ the last one, and a verification step on top of the cache it leaves.
 Bars as for the verify step: K and V within one bf16 step (2^-8 of the largest value; layers above
 the first also carry the rounding of the caches below: 2^-7), logits within 2e-2 of the row maximum,
 tokens equal where the oracle's two best are more than 0.05 apart."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -166,6 +168,7 @@ def test_prompt_refuses_what_it_cannot_do():
 def test_prompt_workspace_can_be_given_back():
     tgt, _ = make_pair(MID, 5, max_ctx=200)
     toks = ci.uniform_tokens(5, "ctx_tokens", 0, 150, MID.vocab).tolist()
+    gc.collect()  # (a model of an earlier test that is freed meanwhile would count)
     before = torch.cuda.memory_allocated()
     g0 = tgt.prefill(toks)
     assert torch.cuda.memory_allocated() > before
