@@ -355,6 +355,12 @@ int card_cache_read_level(const card_cache* c, int32_t level, int32_t* tokens, i
  * first_slot + n_rows <= level_end <= max_ctx); those that are not this call's rows belong to the
  * level's other calls and are neither cleared nor used, whatever they hold.
  *
+ * card_draft_level_wide: a level of any width in one call, the weights streamed once per 128 rows instead of
+ * once per call.  Same results, bit for bit, as card_draft_level_piece calls of rows_per_call rows each (the last
+ * may be shorter; 8 < rows_per_call <= max_r), whose errors it reports before anything is enqueued.  It spreads over all
+ * compute units that are free, whatever grid_wgs says.  workspace_dev: card_level_workspace_bytes, aligned to 16 bytes, no
+ * preparation; not shared with a call that may run at the same time.
+ *
  * card_cache_select, eqs. (3)-(7): scores every (parent i, its j-th token) pair
  * w = prob[i][j] * sigma[i] (sigma: cumulative probability of parent i's sequence, eq. (4)),
  * pools the n_parents * k tuples (eq. (5)), sorts them by score (eq. (6)) and keeps the K best
@@ -390,6 +396,11 @@ int card_draft_level_piece(const card_model_cfg* cfg, const void* packed_weights
                            int32_t ctx_len, const card_tree_rows* rows, int32_t n_rows, int32_t level_first,
                            int32_t level_end, int32_t k, void* workspace_dev, void* stream, int32_t* topk_tokens_dev,
                            float* topk_probs_dev, float* logits_dev);
+size_t card_level_workspace_bytes(const card_model_cfg* cfg);
+int card_draft_level_wide(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv,
+                          int32_t ctx_len, const card_tree_rows* rows, int32_t n_rows, int32_t rows_per_call,
+                          int32_t k, void* workspace_dev, void* stream, int32_t* topk_tokens_dev,
+                          float* topk_probs_dev);
 int card_cache_select(const float* sigma_dev, const int32_t* topk_tokens_dev,
                       const float* topk_probs_dev, int32_t n_parents, int32_t k, int32_t K,
                       int32_t* out_tokens_dev, float* out_scores_dev, int32_t* out_parents_dev,

@@ -100,6 +100,10 @@ def _declare(lib: C.CDLL) -> C.CDLL:
     lib.card_draft_level_piece.restype = C.c_int
     lib.card_draft_level_piece.argtypes = [_cfgp, _P, _kvp, C.c_int32, C.POINTER(CardTreeRows), C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                            _P, _P, _P, _P, _P]
+    lib.card_level_workspace_bytes.restype = C.c_size_t
+    lib.card_level_workspace_bytes.argtypes = [_cfgp]
+    lib.card_draft_level_wide.restype = C.c_int
+    lib.card_draft_level_wide.argtypes = [_cfgp, _P, _kvp, C.c_int32, C.POINTER(CardTreeRows), C.c_int32, C.c_int32, C.c_int32, _P, _P, _P, _P]
     lib.card_tree_mask_level.restype = C.c_int
     lib.card_tree_mask_level.argtypes = [_P, _i32p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _P]
     lib.card_cache_select.restype = C.c_int
@@ -227,6 +231,16 @@ def card_draft_level(cfg, packed_dev, kv: CardKV, ctx_len: int, rows: CardTreeRo
     return lib.card_draft_level(C.byref(cfg), _ptr(packed_dev), C.byref(kv), ctx_len, C.byref(rows), n_rows, k,
                                 _ptr(workspace_dev), _ptr(stream), _ptr(topk_tokens_dev), _ptr(topk_probs_dev),
                                 _ptr(logits_dev))
+
+
+def card_level_workspace_bytes(cfg) -> int:
+    return lib.card_level_workspace_bytes(C.byref(cfg))
+
+
+def card_draft_level_wide(cfg, packed_dev, kv: CardKV, ctx_len: int, rows: CardTreeRows, n_rows: int, rows_per_call: int, k: int,
+                          workspace_dev, stream, topk_tokens_dev, topk_probs_dev) -> int:
+    return lib.card_draft_level_wide(C.byref(cfg), _ptr(packed_dev), C.byref(kv), ctx_len, C.byref(rows), n_rows, rows_per_call, k,
+                                     _ptr(workspace_dev), _ptr(stream), _ptr(topk_tokens_dev), _ptr(topk_probs_dev))
 
 
 def card_tree_mask_level(parent_mask, parent_idx, first_slot: int, ctx_len: int, mask_base: int, mask_words: int):

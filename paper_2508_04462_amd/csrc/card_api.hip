@@ -16,6 +16,7 @@
 #include "card_pack.hip"
 #include "card_verify.hip"
 #include "card_prompt.hip"
+#include "card_level.hip"
 
 using namespace card;
 
@@ -146,6 +147,24 @@ bool pool_fits(const card_model_cfg* cfg, const card_kv* kv) {
     return size_t(kv->n_pages) * cfg->n_kv_heads * 16 * cfg->head_dim * 2 < (size_t(1) << 32);
 }
 
+// How attention cuts the list of pages of a step of r rows.  A workgroup's share fits the page buffers of its wavefronts (all of
+// its old-context pages are then in flight before the barrier in front of attention), as long
+// as every task still gets a workgroup of its own; beyond that the shares grow instead.
+// The cut length is a function of the context length in steps of 512 tokens, the grid and
+// the kernel (r <= 8, <= 16, <= 32), not of r itself: a row's keys are then cut, summed and
+// merged in the same order whether a step of eight rows or a plain decode step computes it,
+// and verification reproduces the plain decode's logits bit for bit (same kernel, same
+// 512-token stretch).
+void attn_cuts(const card_model_cfg* cfg, const Layout& L, int nwg, int r, int pages_used, int32_t& pages_per_cut, int32_t& cuts) {
+    const int G = cfg->n_q_heads / cfg->n_kv_heads;
+    const int share = kMegaWaves * (cfg->head_dim == 128 ? 2 : 4);
+    const int r_kernel = r <= 8 ? 8 : (r <= 16 ? 16 : 32);
+    const int max_cuts = std::min<int>(L.m_attn_max_splits, std::max(1, nwg / (cfg->n_kv_heads * ceil_div(G * r_kernel, 16))));
+    const int pages_stretch = ceil_div(pages_used, 32) * 32;
+    pages_per_cut = std::max(share, ceil_div(pages_stretch, max_cuts));
+    cuts = ceil_div(pages_used, pages_per_cut);
+}
+
 // One persistent kernel runs the whole step (card_verify.hip).
 int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv, int32_t ctx_len,
                 const int32_t* cand, int32_t r, void* workspace, void* stream, card_verify_result* out,
@@ -216,20 +235,7 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.clear_from = tree && tree->piece ? tree->level_end : 0;
     a.level_first = tree && tree->piece ? tree->level_first : 0;
     a.row_tiles = ceil_div(a.G * r, 16);
-    // Cut the context so that a workgroup's share fits the page buffers of its wavefronts (all of
-    // its old-context pages are then in flight before the barrier in front of attention), as long
-    // as every task still gets a workgroup of its own; beyond that the shares grow instead.
-    // The cut length is a function of the context length in steps of 512 tokens, the grid and
-    // the kernel (r <= 8, <= 16, <= 32), not of r itself: a row's keys are then cut, summed and
-    // merged in the same order whether a step of eight rows or a plain decode step computes it,
-    // and verification reproduces the plain decode's logits bit for bit (same kernel, same
-    // 512-token stretch).
-    const int share = kMegaWaves * (h == 128 ? 2 : 4);
-    const int r_kernel = r <= 8 ? 8 : (r <= 16 ? 16 : 32);
-    const int max_cuts = std::min<int>(L.m_attn_max_splits, std::max(1, cus / (a.Hkv * ceil_div(a.G * r_kernel, 16))));
-    const int pages_stretch = ceil_div(a.pages_used, 32) * 32;
-    a.pages_per_split = std::max(share, ceil_div(pages_stretch, max_cuts));
-    a.a_splits = ceil_div(a.pages_used, a.pages_per_split);
+    attn_cuts(cfg, L, cus, r, a.pages_used, a.pages_per_split, a.a_splits);
     a.xres = reinterpret_cast<float*>(ws + L.m_xres_off);
     a.xfrag = reinterpret_cast<__bf16*>(ws + L.m_xfrag_off);
     a.ss = reinterpret_cast<float*>(ws + L.m_ss_off);
@@ -481,6 +487,135 @@ int prompt_pass(const card_model_cfg* cfg, const Layout& L, const PromptLayout& 
         hipLaunchKernelGGL(k_prompt_token, dim3(1), dim3(1), 0, st, e.best, reinterpret_cast<const uint32_t*>(packed + L.stamp_off),
                            nwg, next_token);
     }
+    return launch_status();
+}
+
+// ---- wide levels (card_level.hip) -------------------------------------------------------------------
+struct LevelLayout {
+    size_t x, xf, ss, att, act, q, rope, part, apart, counts, logits, lse, best, bytes;
+    int n_counts;
+};
+LevelLayout level_layout(const card_model_cfg* cfg, const Layout& L) {
+    LevelLayout p = {};
+    constexpr size_t rows = kLvTiles * 16;
+    const size_t h = cfg->head_dim, G = cfg->n_q_heads / cfg->n_kv_heads;
+    size_t w = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = w;
+        w = align_up(w + bytes, 1024);
+        return at;
+    };
+    p.x = take(rows * cfg->d_model * 4);
+    p.xf = take(size_t(L.qkv.Ks) * kLvTiles * 2048);
+    p.ss = take(rows * (cfg->d_model / 16) * 4);
+    p.att = take(size_t(L.wo.Ks) * kLvTiles * 2048);
+    p.act = take(size_t(L.wd.Ks) * kLvTiles * 2048);
+    p.q = take(rows * cfg->n_q_heads * h * 4);
+    p.rope = take(rows * h * 4);
+    p.part = take(size_t(4) * std::max(L.qkv.Nt, std::max(L.wo.Nt, L.wd.Nt)) * kLvTiles * 1024);
+    // (a row tile's cuts never outnumber the grid, unless its heads do)
+    p.apart = take(kLvTiles * std::max<size_t>(256, cfg->n_kv_heads * G) * 16 * (h + 2) * 4);
+    p.n_counts = int(kLvTiles * cfg->n_kv_heads * G);
+    p.counts = take(size_t(p.n_counts) * 4);
+    p.logits = take(rows * L.lm.Nt * 16 * 4);
+    p.lse = take(rows * 256 * 8);
+    p.best = take(rows * 256 * 16 * 8);
+    p.bytes = w;
+    return p;
+}
+
+template <int EPI>
+void level_gemm(LvGemmArgs g, hipStream_t st) {
+    g.mblk = ceil_div(g.n_tiles, kPgTiles);
+    const int splits = EPI == LV_PART ? 4 : 1;
+    const auto grid = [&](int n) {
+        g.nblk = ceil_div(g.Nt, kPgWaves * n);
+        return dim3(uint32_t(ceil_div(int64_t(g.nblk) * splits * g.mblk, 8) * 8));
+    };
+    if constexpr (EPI == LV_PART) {
+        if (ceil_div(g.Nt, kPgWaves * 2) * splits * g.mblk < 256) {
+            const dim3 gr = grid(1);
+            hipLaunchKernelGGL((k_level_gemm<EPI, 1>), gr, dim3(kPgWaves * 64), 0, st, g);
+            return;
+        }
+    }
+    const dim3 gr = grid(2);
+    hipLaunchKernelGGL((k_level_gemm<EPI, 2>), gr, dim3(kPgWaves * 64), 0, st, g);
+}
+
+// The rows of `e.t` (of the n_rows of the level) through the model.
+int level_pass(const card_model_cfg* cfg, const Layout& L, const LevelLayout& P, const char* packed, const card_kv* kv, LvArgs e,
+               int tasks, const card_tree_rows* rows, int k, char* ws, int nwg, hipStream_t st, int32_t* tok, float* prob) {
+    const int h = cfg->head_dim;
+    uint32_t pk_tiles = 0;
+    for (int i = 0; i < e.n_tiles; ++i) pk_tiles |= uint32_t(e.t[i].pk) << i;
+    const auto gain = [&](int l, bool ffn) {
+        if (l == cfg->n_layers) return reinterpret_cast<const float*>(packed + L.g_final_off);
+        const char* lb = packed + L.layer0_off + size_t(l) * L.layer_stride;
+        return reinterpret_cast<const float*>(lb + (ffn ? L.g_ffn_off : L.g_attn_off));
+    };
+    const auto product = [&](const MatDesc& m, const char* base, const __bf16* in) {
+        LvGemmArgs g = {};
+        g.w = base + m.off;
+        g.bytes = uint32_t(m.bytes());
+        g.Nt = e.Nt = m.Nt;
+        g.Ks = m.Ks;
+        g.NB = m.NB;
+        g.nwg = nwg;
+        g.x = in;
+        g.n_tiles = e.n_tiles;
+        g.pk_tiles = pk_tiles;
+        g.part = const_cast<float*>(e.part);
+        g.ss = e.ss;
+        g.n_part = cfg->d_model / 16;
+        g.Ks_out = L.wd.Ks;
+        g.inv_d = e.inv_d;
+        g.eps = e.eps;
+        g.act = reinterpret_cast<__bf16*>(ws + P.act);
+        g.logits = reinterpret_cast<float*>(ws + P.logits);
+        g.ldl = L.lm.Nt * 16;
+        return g;
+    };
+    const dim3 cols(uint32_t(cfg->d_model / 64), uint32_t(e.n_tiles));
+    e.gain = gain(0, false);
+    hipLaunchKernelGGL(k_level_resid<true>, cols, dim3(256), 0, st, e);
+    hipLaunchKernelGGL(k_level_rope, dim3(uint32_t(ceil_div(e.n_tiles * 16 * (h / 2), 256))), dim3(256), 0, st, e,
+                       reinterpret_cast<float*>(ws + P.rope), rows->positions_dev, cfg->rope_theta);
+    const size_t pool_layer = size_t(kv->n_pages) * cfg->n_kv_heads * 16 * h;
+    for (int l = 0; l < cfg->n_layers; ++l) {
+        const char* lb = packed + L.layer0_off + size_t(l) * L.layer_stride;
+        level_gemm<LV_PART>(product(L.qkv, lb, e.xf), st);
+        e.kpool = static_cast<__bf16*>(kv->k_pages) + size_t(l) * pool_layer;
+        e.vpool = static_cast<__bf16*>(kv->v_pages) + size_t(l) * pool_layer;
+        hipLaunchKernelGGL(k_level_qkv, dim3(uint32_t(ceil_div(L.qkv.Nt, 4)), uint32_t(e.n_tiles)), dim3(256), 0, st, e);
+        if (h == 128) hipLaunchKernelGGL(k_level_attn<128>, dim3(uint32_t(tasks)), dim3(256), 0, st, e);
+        else hipLaunchKernelGGL(k_level_attn<64>, dim3(uint32_t(tasks)), dim3(256), 0, st, e);
+        level_gemm<LV_PART>(product(L.wo, lb, e.att), st);
+        e.gain = gain(l, true);
+        hipLaunchKernelGGL(k_level_resid<false>, cols, dim3(256), 0, st, e);
+        level_gemm<LV_SWIGLU>(product(L.gu, lb, e.xf), st);
+        LvGemmArgs g = product(L.wd, lb, reinterpret_cast<const __bf16*>(ws + P.act));
+        g.grouped = (nwg & 7) == 0 && (L.wd.Nt & 3) == 0;
+        level_gemm<LV_PART>(g, st);
+        e.gain = gain(l + 1, false);
+        hipLaunchKernelGGL(k_level_resid<false>, cols, dim3(256), 0, st, e);
+    }
+    level_gemm<LV_LOGITS>(product(L.lm, packed, e.xf), st);
+    LvTopkArgs t = {};
+    t.logits = reinterpret_cast<const float*>(ws + P.logits);
+    t.ldl = L.lm.Nt * 16;
+    t.V = cfg->vocab;
+    t.Nt = L.lm.Nt;
+    t.nwg = nwg;
+    t.n_tiles = e.n_tiles;
+    t.k = k;
+    std::copy(e.t, e.t + kLvTiles, t.t);
+    t.lse = reinterpret_cast<float*>(ws + P.lse);
+    t.best = reinterpret_cast<unsigned long long*>(ws + P.best);
+    t.tok = tok;
+    t.prob = prob;
+    hipLaunchKernelGGL(k_level_lse, dim3(uint32_t(ceil_div(nwg, 32)), uint32_t(e.n_tiles * 16)), dim3(256), 0, st, t);
+    hipLaunchKernelGGL(k_level_topk, dim3(uint32_t(e.n_tiles * 16)), dim3(256), 0, st, t);
     return launch_status();
 }
 
@@ -785,6 +920,92 @@ int card_prompt(const card_model_cfg* cfg, const void* packed_weights_dev, const
         const int st = prompt_pass(cfg, L, P, static_cast<const char*>(packed_weights_dev), kv, ctx_len + at, tokens_dev + at,
                                    std::min(per, n - at), static_cast<char*>(workspace_dev), nwg, as_stream(stream),
                                    at + per >= n ? next_token_dev : nullptr);
+        if (st != CARD_OK) return st;
+    }
+    return CARD_OK;
+}
+
+size_t card_level_workspace_bytes(const card_model_cfg* cfg) {
+    const Layout L = make_layout(cfg);
+    return L.ok ? level_layout(cfg, L).bytes : 0;
+}
+
+int card_draft_level_wide(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv, int32_t ctx_len,
+                          const card_tree_rows* rows, int32_t n_rows, int32_t rows_per_call, int32_t k, void* workspace_dev,
+                          void* stream, int32_t* topk_tokens_dev, float* topk_probs_dev) {
+    if (!cfg || !packed_weights_dev || !kv || !rows || !workspace_dev || !topk_tokens_dev || !topk_probs_dev) return CARD_EINVAL;
+    if (!rows->tokens_dev || !rows->positions_dev || !rows->mask_dev) return CARD_EINVAL;
+    const Layout L = make_layout(cfg);
+    if (!L.ok) return CARD_EINVAL;
+    if (!kv->k_pages || !kv->v_pages || !kv->block_table || kv->n_pages <= 0 || !pool_fits(cfg, kv)) return CARD_EINVAL;
+    if (reinterpret_cast<uintptr_t>(workspace_dev) % 16 || ctx_len < 0) return CARD_EINVAL;
+    if (n_rows < 1 || rows_per_call <= 8 || rows_per_call > cfg->max_r) return CARD_ERANGE;
+    const int first = rows->first_slot;
+    if (int64_t(first) + n_rows > cfg->max_ctx) return CARD_ECAPACITY;
+    if (rows->mask_words < 1 || rows->mask_words > 32 || k < 1 || k > 16) return CARD_ERANGE;
+    if (rows->mask_base < 0 || rows->mask_base % kKvBlock || rows->mask_base > ctx_len) return CARD_EINVAL;
+    if (first < ctx_len || int64_t(first) + n_rows > int64_t(rows->mask_base) + 32 * rows->mask_words) return CARD_ERANGE;
+    const int nwg = grid_size(cfg);
+    if (nwg <= 0) return CARD_EDEVICE;
+    const LevelLayout P = level_layout(cfg, L);
+    char* ws = static_cast<char*>(workspace_dev);
+    LvArgs e = {};
+    e.d = cfg->d_model;
+    e.Ks = L.qkv.Ks;
+    e.x = reinterpret_cast<float*>(ws + P.x);
+    e.xf = reinterpret_cast<__bf16*>(ws + P.xf);
+    e.ss = reinterpret_cast<float*>(ws + P.ss);
+    e.part = reinterpret_cast<float*>(ws + P.part);
+    e.embed = reinterpret_cast<const __bf16*>(static_cast<const char*>(packed_weights_dev) + L.embed_off);
+    e.tokens = rows->tokens_dev;
+    e.V = cfg->vocab;
+    e.n_counts = P.n_counts;
+    e.counts = reinterpret_cast<uint32_t*>(ws + P.counts);
+    e.h = cfg->head_dim;
+    e.qd = cfg->n_q_heads * e.h;
+    e.kvd = cfg->n_kv_heads * e.h;
+    e.Hkv = cfg->n_kv_heads;
+    e.G = cfg->n_q_heads / cfg->n_kv_heads;
+    e.first_slot = e.level_first = first;
+    e.level_end = first + n_rows;
+    e.last_row = n_rows - 1;
+    e.inv_d = 1.0f / float(cfg->d_model);
+    e.eps = cfg->rms_eps;
+    e.inv_sqrt_h = 1.4426950408889634f / sqrtf(float(e.h));
+    e.rope = reinterpret_cast<const float*>(ws + P.rope);
+    e.q = reinterpret_cast<__bf16*>(ws + P.q);
+    e.block_table = kv->block_table;
+    e.mask = rows->mask_dev;
+    e.mask_words = rows->mask_words;
+    e.mask_base = rows->mask_base;
+    e.apart = reinterpret_cast<float*>(ws + P.apart);
+    e.att = reinterpret_cast<__bf16*>(ws + P.att);
+    e.Ks_att = L.wo.Ks;
+    // passes of whole calls, eight row tiles at most
+    for (int c0 = 0; c0 < n_rows;) {
+        int tasks = 0, counts = 0;
+        e.n_tiles = 0;
+        while (c0 < n_rows) {
+            const int r = std::min(rows_per_call, n_rows - c0), tiles = ceil_div(r, 16);
+            if (e.n_tiles + tiles > kLvTiles) break;
+            for (int i = 0; i < tiles; ++i) {
+                LvTile& t = e.t[e.n_tiles++];
+                t.row0 = c0 + 16 * i;
+                t.n = std::min(16, r - 16 * i);
+                t.pk = r <= 8;
+                t.wide = r > 16;
+                t.pages = ceil_div(first + c0 + r, kKvBlock);
+                attn_cuts(cfg, L, nwg, r, t.pages, t.per_cut, t.cuts);
+                t.subs = ceil_div(t.n * e.G, 16);
+                t.task0 = tasks;
+                t.count0 = counts;
+                tasks += e.Hkv * t.subs * t.cuts;
+                counts += e.Hkv * t.subs;
+            }
+            c0 += r;
+        }
+        const int st = level_pass(cfg, L, P, static_cast<const char*>(packed_weights_dev), kv, e, tasks, rows, k, ws, nwg,
+                                  as_stream(stream), topk_tokens_dev, topk_probs_dev);
         if (st != CARD_OK) return st;
     }
     return CARD_OK;

@@ -42,14 +42,11 @@ __device__ __forceinline__ void px_store4(__bf16* x, int Ks, int mt, int m, int 
     *reinterpret_cast<uint2v*>(p + 512) = uint2v{pack_bf16(l[0], l[1]), pack_bf16(l[2], l[3])};
 }
 
-// SwiGLU of two gate/up tiles ta and tb (of Nt) and 16 rows: a tile holds eight gate rows (lanes 0-31 of the accumulator)
-// and the eight up rows that belong to them (lanes 32-63).  The tiles trade halves: lanes 0-31 finish ta, lanes 32-63 tb.
-// sc: the RMSNorm scale of row m = lane & 15; `on`: whether this lane's tile exists.
-__device__ __forceinline__ void px_swiglu(__bf16* act, int Ks_out, int Nt, int mt, int lane, float sc, const floatx4& a,
-                                          const floatx4& b, int ta, int tb, bool on) {
+// SwiGLU of two gate/up tiles a and b and 16 rows: a tile holds eight gate rows (lanes 0-31 of the accumulator)
+// and the eight up rows that belong to them (lanes 32-63).  The tiles trade halves: lanes 0-31 finish a, lanes 32-63 b.
+// sc: the RMSNorm scale of row lane & 15.
+__device__ __forceinline__ void px_swiglu_values(int lane, float sc, const floatx4& a, const floatx4& b, float (&v)[4]) {
     const bool low = lane < 32;
-    const int t = low ? ta : tb, m = lane & 15;
-    float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float give = low ? b[e] : a[e];
@@ -57,6 +54,13 @@ __device__ __forceinline__ void px_swiglu(__bf16* act, int Ks_out, int Nt, int m
         const float g = (low ? a[e] : got) * sc, u = (low ? got : b[e]) * sc;
         v[e] = g * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
     }
+}
+// ... of tiles ta and tb (of Nt); `on`: whether this lane's tile exists.
+__device__ __forceinline__ void px_swiglu(__bf16* act, int Ks_out, int Nt, int mt, int lane, float sc, const floatx4& a,
+                                          const floatx4& b, int ta, int tb, bool on) {
+    const int t = lane < 32 ? ta : tb, m = lane & 15;
+    float v[4];
+    px_swiglu_values(lane, sc, a, b, v);
     if (!on) return;
     const int k = t * 8 + ((lane >> 4) & 1) * 4;
     px_store4(act, Ks_out, mt, m, k, v);
@@ -485,6 +489,65 @@ struct PattnArgs {
     __bf16* att;
 };
 
+// One round of a wavefront's walk over the cache, two pages of 16 keys, for 16 query rows: scores, online softmax, output.
+// oka / okb: which keys of the lane's four its row sees.  scores_done runs once the K operands have been used,
+// weights_done before V is.
+template <int H, typename F1, typename F2>
+__device__ __forceinline__ void px_two_pages(const bf16x8 (&ka)[H / 32], const bf16x8 (&kb)[H / 32], const short4v (&va)[H / 16],
+                                             const short4v (&vb)[H / 16], const bf16x8 (&qh)[H / 32], const bf16x8 (&ql)[H / 32],
+                                             const bool (&oka)[4], const bool (&okb)[4], floatx4 (&o)[H / 16], float& mx,
+                                             float& sum, F1&& scores_done, F2&& weights_done) {
+    floatx4 sa = floatx4{0.f, 0.f, 0.f, 0.f}, sb = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < H / 32; ++st) {
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[st], qh[st], sa, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[st], qh[st], sb, 0, 0, 0);
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[st], ql[st], sa, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[st], ql[st], sb, 0, 0, 0);
+    }
+    scores_done();
+    float pmax = -1e30f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (oka[v]) pmax = fmaxf(pmax, sa[v]);
+        if (okb[v]) pmax = fmaxf(pmax, sb[v]);
+    }
+    pmax = fmaxf(pmax, __shfl_xor(pmax, 16));
+    pmax = fmaxf(pmax, __shfl_xor(pmax, 32));
+    const float mnew = fmaxf(mx, pmax);
+    const float alpha = __builtin_amdgcn_exp2f(mx - mnew);
+    float psum = 0.f;
+    short4v pah, pal, pbh, pbl;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float xa = oka[v] ? __builtin_amdgcn_exp2f(sa[v] - mnew) : 0.f;
+        const float xb = okb[v] ? __builtin_amdgcn_exp2f(sb[v] - mnew) : 0.f;
+        psum += xa + xb;
+        __bf16 hi, lo;
+        split_bf16(xa, hi, lo);
+        pah[v] = __builtin_bit_cast(short, hi);
+        pal[v] = __builtin_bit_cast(short, lo);
+        split_bf16(xb, hi, lo);
+        pbh[v] = __builtin_bit_cast(short, hi);
+        pbl[v] = __builtin_bit_cast(short, lo);
+    }
+    psum += __shfl_xor(psum, 16);
+    psum += __shfl_xor(psum, 32);
+    sum = sum * alpha + psum;
+    mx = mnew;
+    weights_done();
+#pragma unroll
+    for (int i = 0; i < H / 16; ++i) {
+        floatx4 acc = o[i];
+        acc[0] *= alpha; acc[1] *= alpha; acc[2] *= alpha; acc[3] *= alpha;
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va[i], pah, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[i], pbh, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va[i], pal, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[i], pbl, acc, 0, 0, 0);
+        o[i] = acc;
+    }
+}
+
 // Causal attention of the pass's rows over the paged cache.  A wavefront owns 16 rows (of the G query
 // heads that share a KV head, row (m, g) = m * G + g) and walks the pages up to its last row's position,
 // two per round, as the verify kernel does; the four wavefronts of a workgroup own neighbouring row tiles
@@ -528,62 +591,20 @@ __global__ __launch_bounds__(256, 2) void k_prompt_attn(PattnArgs a) {
     for (int pg = 0; pg < n_pages; pg += 2) {
         attn_load_v<H>(pa, a.vpool, kvh, ida, lane, va);
         attn_load_v<H>(pa, a.vpool, kvh, idb, lane, vb);
-        floatx4 sa = floatx4{0.f, 0.f, 0.f, 0.f}, sb = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int st = 0; st < ST; ++st) {
-            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[st], qh[st], sa, 0, 0, 0);
-            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[st], qh[st], sb, 0, 0, 0);
-            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[st], ql[st], sa, 0, 0, 0);
-            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[st], ql[st], sb, 0, 0, 0);
-        }
-        ida = id(pg + 2);
-        idb = id(pg + 3);
-        if (pg + 2 < n_pages) {
-            attn_load_k<H>(pa, a.kpool, kvh, ida, lane, ka);
-            attn_load_k<H>(pa, a.kpool, kvh, idb, lane, kb);
-        }
-        float pmax = -1e30f;
         bool oka[4], okb[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             oka[v] = pg * 16 + kq * 4 + v <= limit;
             okb[v] = pg * 16 + 16 + kq * 4 + v <= limit;
-            if (oka[v]) pmax = fmaxf(pmax, sa[v]);
-            if (okb[v]) pmax = fmaxf(pmax, sb[v]);
         }
-        pmax = fmaxf(pmax, __shfl_xor(pmax, 16));
-        pmax = fmaxf(pmax, __shfl_xor(pmax, 32));
-        const float mnew = fmaxf(mx, pmax);
-        const float alpha = __builtin_amdgcn_exp2f(mx - mnew);
-        float psum = 0.f;
-        short4v pah, pal, pbh, pbl;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float xa = oka[v] ? __builtin_amdgcn_exp2f(sa[v] - mnew) : 0.f;
-            const float xb = okb[v] ? __builtin_amdgcn_exp2f(sb[v] - mnew) : 0.f;
-            psum += xa + xb;
-            __bf16 hi, lo;
-            split_bf16(xa, hi, lo);
-            pah[v] = __builtin_bit_cast(short, hi);
-            pal[v] = __builtin_bit_cast(short, lo);
-            split_bf16(xb, hi, lo);
-            pbh[v] = __builtin_bit_cast(short, hi);
-            pbl[v] = __builtin_bit_cast(short, lo);
-        }
-        psum += __shfl_xor(psum, 16);
-        psum += __shfl_xor(psum, 32);
-        sum = sum * alpha + psum;
-        mx = mnew;
-#pragma unroll
-        for (int i = 0; i < HT; ++i) {
-            floatx4 acc = o[i];
-            acc[0] *= alpha; acc[1] *= alpha; acc[2] *= alpha; acc[3] *= alpha;
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va[i], pah, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[i], pbh, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(va[i], pal, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[i], pbl, acc, 0, 0, 0);
-            o[i] = acc;
-        }
+        px_two_pages<H>(ka, kb, va, vb, qh, ql, oka, okb, o, mx, sum, [&]() {
+            ida = id(pg + 2);
+            idb = id(pg + 3);
+            if (pg + 2 < n_pages) {
+                attn_load_k<H>(pa, a.kpool, kvh, ida, lane, ka);
+                attn_load_k<H>(pa, a.kpool, kvh, idb, lane, kb);
+            }
+        }, []() {});
     }
     if (!row_ok) return;
     const float inv = 1.0f / sum;

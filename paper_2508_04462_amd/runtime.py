@@ -20,6 +20,9 @@ def make_cfg(shape, max_ctx: int, max_r: int = 32, grid_wgs: int = 0) -> B.CardM
 # (2 layers of 256 columns: 144 / 167); 33 tokens: 1367 / 2128, 4587 / 6879, 4442 / 6924, 3562 / 5872 (147 / 315).
 PROMPT_MIN_TOKENS = 33
 
+# Levels of more rows than this go through card_draft_level_wide instead of calls side by side.
+LEVEL_ONE_PASS_ROWS = 32
+
 _LANE_STREAMS: Dict[str, list] = {}
 
 
@@ -164,11 +167,16 @@ class Target:
             _check(B.card_workspace_init(self.cfg, ws, self._stream()), "card_workspace_init")
             self._lane_ws.append(ws)
         self._lane_streams = _lane_streams(self.device, lanes)
+        try:
+            self._level_ws = torch.empty(B.card_level_workspace_bytes(self.cfg), dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:  # a full device: levels go through calls side by side
+            self._level_ws = None
         torch.cuda.current_stream(self.device).synchronize()
 
     def draft_level_wide(self, ctx_len: int, tokens: Sequence[int], positions: Sequence[int], first_slot: int,
                          mask_rows: Sequence[Sequence[int]], mask_base: int, k: int) -> Dict:
-        """card_draft_level for a level of any width: the rows are cut into calls of at most 32, `lanes`
+        """card_draft_level for a level of any width: in one pass over the weights (card_draft_level_wide), or, where one round of
+        calls side by side holds it, the rows are cut into calls of at most 32, `lanes`
         of them at a time enqueued side by side, each on its own stream with its own workspace
         (peers of a level never see each other, so the calls are independent; they share the weights
         and the KV cache and write different slots, of the same page too where a call ends inside one:
@@ -183,11 +191,18 @@ class Target:
         tk = torch.full((n, k), -7, dtype=torch.int32, device=dev)
         tp = torch.zeros((n, k), dtype=torch.float32, device=dev)
         cur = torch.cuda.current_stream(dev)
+        pieces = level_pieces(n, lanes)
+        if n > LEVEL_ONE_PASS_ROWS and pieces[0][1] > 8 and self._level_ws is not None:
+            rows = B.CardTreeRows(tok.data_ptr(), pos.data_ptr(), int(first_slot), mask.data_ptr(), words, int(mask_base))
+            _check(B.card_draft_level_wide(self.cfg, self.packed, self.kv(-1), ctx_len, rows, n, pieces[0][1], k, self._level_ws,
+                                           cur.cuda_stream, tk, tp), "card_draft_level_wide")
+            cur.synchronize()
+            return {"topk_tokens": tk, "topk_probs": tp}
         ready = torch.cuda.Event()
         ready.record(cur)
         done = []
         try:
-            for i, (c0, c1) in enumerate(level_pieces(n, lanes)):
+            for i, (c0, c1) in enumerate(pieces):
                 lane = i % lanes
                 st = self._lane_streams[lane]
                 if i < lanes:

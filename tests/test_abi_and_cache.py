@@ -74,6 +74,14 @@ def test_argument_errors_are_caught_on_the_host():
     assert piece(8, 100, 107) == card.CARD_ERANGE  # the level ends before the piece does
     assert piece(8, 101, 120) == card.CARD_ERANGE and piece(8, 99, 120) == card.CARD_ERANGE  # begins behind it, or in the context
     assert piece(8, 100, 257) == card.CARD_ECAPACITY
+    # a wide level is refused for what its calls would be refused for, and for calls of eight rows and less
+    wide = lambda n, per, k=4, ws=0x1000, r=rows: card.card_draft_level_wide(cfg, 0x1000, kv, 100, r, n, per, k, ws, None, 0x1000, 0x1000)  # noqa: E731
+    assert wide(0, 32) == wide(40, 8) == wide(40, 33) == wide(40, 32, 0) == wide(40, 32, 17) == card.CARD_ERANGE
+    assert wide(157, 32) == card.CARD_ECAPACITY and wide(40, 32, 4, 0x1008) == card.CARD_EINVAL
+    assert wide(40, 32, 4, 0x1000, card.CardTreeRows(0x1000, 0x1000, 99, 0x1000, 8, 96)) == card.CARD_ERANGE  # in the context
+    assert wide(40, 32, 4, 0x1000, card.CardTreeRows(0x1000, 0x1000, 100, 0x1000, 1, 96)) == card.CARD_ERANGE  # behind the mask
+    assert wide(40, 32, 4, 0x1000, card.CardTreeRows(0x1000, 0x1000, 100, 0x1000, 8, 90)) == card.CARD_EINVAL
+    assert card.card_level_workspace_bytes(cfg) % 1024 == 0 and card.card_level_workspace_bytes(cfg) > 0
     # a page pool of 4 GiB per layer: no step can use it, so no prompt fills it
     big = card.CardKV(0x1000, 0x1000, 0x1000, 2 ** 32 // (cfg.n_kv_heads * 16 * cfg.head_dim * 2), -1)
     assert card.card_verify(cfg, 0x1000, big, 0, 0x1000, 8, 0x1000, None, 0x1000) == card.CARD_EINVAL

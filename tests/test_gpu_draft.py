@@ -369,6 +369,21 @@ def test_a_wide_level_from_any_slot_leaves_what_calls_in_a_row_leave(first, n, l
     _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), MID, first, n)
 
 
+# several passes (24 and 16 rows per call, the last of eight and less), two row tiles of which the second has one row, one pass
+# of exactly eight row tiles; the widest k
+@pytest.mark.parametrize("shape,first,n,lanes,k", [(MID, 87, 200, 3, 16), (TINY, 80, 150, 4, 1), (MID, 81, 49, 2, 7), (MID, 80, 128, 2, 16),
+                                                   (MID, 95, 33, 3, 5)])
+def test_one_pass_over_a_wide_level_equals_its_calls(shape, first, n, lanes, k):
+    tgts, want, toks, rows, mask_base, pieces = _level_twice(shape, 26, 70, first, n, k, lanes)
+    assert pieces[0][1] > 8
+    res = tgts[1].draft_level_wide(70, toks, [71] * n, first, rows, mask_base, k)
+    _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), shape, first, n)
+    # side by side, where there is no room for the pass's workspace: the same
+    tgts[1]._level_ws = None
+    res = tgts[1].draft_level_wide(70, toks, [71] * n, first, rows, mask_base, k)
+    _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), shape, first, n)
+
+
 def test_a_wide_level_with_a_refused_piece_leaves_nothing_running():
     """The pieces in front of a refused one work on tensors of the call: it ends behind them."""
     import paper_2508_04462_amd as card
