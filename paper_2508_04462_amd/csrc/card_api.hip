@@ -309,24 +309,37 @@ int draft_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv,
 // ---- prompt pass (card_prompt.hip) -----------------------------------------------------------------
 constexpr int kPromptMaxRows = 1024;  // rows per pass: the chip is full (more rows per pass measured no gain)
 
-// Into how many K ranges a product is cut: the count with the least estimated time.  A workgroup's
-// time goes with its k-steps, plus about six for filling and draining: 0.52 us per step alone on a compute
-// unit, 0.88 with a second one beside it; every K range writes and reads the product once more in fp32
-// (6 TB/s), and a cut gate/up product needs a kernel of its own behind it.  Against the fastest of S = 1, 2, 3, 4,
-// 6, 8, 12, 16 on the 1B, 7B, 8B and 70B shapes with 48-1000 rows (96 products, each with the kernel behind it): within 5 %
-// in 82 % of them, within 10 % in 93 %, at worst 19 % slower (70B gate/up, 48 rows: 3 ranges 193 us, one 163).
-int prompt_splits(int Nt, int Ks, int mts, bool swiglu) {
-    const int64_t blocks = int64_t(ceil_div(Nt, kPgWaves * kPgN)) * ceil_div(mts, kPgTiles);
+// How a product is run: workgroups of `waves` wavefronts on 4 * waves weight tiles x `tiles` row tiles, K in `splits` ranges.
+struct PromptPlan {
+    int waves, tiles, splits;
+};
+// The plan with the least estimated time.  A workgroup's time goes with its k-steps, plus 5-6 for filling and draining:
+// of four wavefronts 0.43 us a step alone on a compute unit, 0.75 with a second one beside it (512 at a time, a third of a last
+// round that is not full is lost); of eight, one per compute unit, 0.70 us with four row tiles and 1.16 with seven, in whole rounds
+// of 256.  Every K range writes the product once more in fp32 (4.4 TB/s) and the next kernel reads it (5 TB/s); a cut
+// gate/up product needs a kernel of its own behind it (4 us).
+// Against the fastest of all plans with 1, 2, ... 8, 12 or 16 ranges on the 1B, 7B, 8B and 70B shapes with 16-1024 rows (240 products, with what the
+// next kernel pays): within 5 % in 95 % of them, at worst 9 % slower (7B gate/up, 64 rows: 55 us, another plan 50).  The wide
+// workgroups read less of the activations and weights per matrix instruction: from 200 rows on they give 3-8 %.
+PromptPlan prompt_plan(int Nt, int Ks, int mts, bool swiglu) {
     const int turns = ceil_div(Ks, kPgUnroll);
-    int best = 1;
+    PromptPlan best = {4, 4, 1};
     double best_us = 1e30;
-    for (int s = 1; s <= 16 && (s == 1 || turns / s >= 2); ++s) {
-        const int64_t wgs = blocks * s;
-        double us = (ceil_div(turns, s) * kPgUnroll + 6) * (wgs <= 256 ? 0.52 : 0.88 * std::max(1.0, double(wgs) / 512));
-        if (!swiglu || s > 1) us += double(s) * Nt * mts * 2048.0 / 6e6 + (swiglu ? 4.0 : 0.0);
-        if (us < best_us) {
-            best_us = us;
-            best = s;
+    for (const PromptPlan& v : {PromptPlan{4, 4, 0}, PromptPlan{8, 4, 0}, PromptPlan{8, 7, 0}}) {
+        if (v.tiles > 4 && mts <= 4) continue;
+        const int64_t blocks = int64_t(ceil_div(Nt, v.waves * kPgN)) * ceil_div(mts, v.tiles);
+        for (int s = 1; s <= 16 && (s == 1 || turns / s >= 2); ++s) {
+            const int64_t wgs = blocks * s;
+            const double steps = ceil_div(turns, s) * kPgUnroll;
+            double us;
+            if (v.waves == 8) us = (steps + 4.8) * (v.tiles == 4 ? 0.70 : 1.16) * ceil_div(wgs, 256);
+            else if (wgs <= 256) us = (steps + 6) * 0.43;
+            else us = (steps + 6) * 0.75 * std::max(1.0, 0.68 * double(wgs) / 512 + 0.32 * ceil_div(wgs, 512));
+            if (!swiglu || s > 1) us += double(s) * Nt * mts * 1024.0 * (1 / 4.4e6 + 1 / 5e6) + (swiglu ? 4.0 : 0.0);
+            if (us < best_us) {
+                best_us = us;
+                best = {v.waves, v.tiles, s};
+            }
         }
     }
     return best;
@@ -358,23 +371,29 @@ PromptLayout prompt_layout(const card_model_cfg* cfg, const Layout& L, int rows)
     size_t part = 0;
     for (int m = 1; m <= p.mcap; ++m)
         for (const MatDesc* d : {&L.qkv, &L.wo, &L.gu, &L.wd}) {
-            const int s = prompt_splits(d->Nt, d->Ks, m, d == &L.gu);
-            if (d != &L.gu || s > 1) part = std::max(part, size_t(s) * d->Nt * align_up(m, kPgTiles) * 1024);
+            const int s = prompt_plan(d->Nt, d->Ks, m, d == &L.gu).splits;
+            if (d != &L.gu || s > 1) part = std::max(part, size_t(s) * d->Nt * m * 1024);
         }
     p.part = take(part);
     p.bytes = w;
     return p;
 }
 
-// The product of the row tiles [mt0, g.mts).
-void prompt_gemm(PgemmArgs g, PgemmEpi epi, int mt0, hipStream_t st) {
-    g.nblk = ceil_div(g.Nt, kPgWaves * kPgN);
-    g.mb0 = mt0 / kPgTiles;
-    g.mblk = ceil_div(g.mts, kPgTiles) - g.mb0;
-    const dim3 grid(uint32_t(ceil_div(int64_t(g.nblk) * g.mblk * g.splits, 8) * 8)), block(kPgWaves * 64);
-    if (epi == PG_ARGMAX) hipLaunchKernelGGL(k_prompt_gemm<PG_ARGMAX>, grid, block, 0, st, g);
-    else if (epi == PG_SWIGLU) hipLaunchKernelGGL(k_prompt_gemm<PG_SWIGLU>, grid, block, 0, st, g);
-    else hipLaunchKernelGGL(k_prompt_gemm<PG_PART>, grid, block, 0, st, g);
+// The product of the row tiles [g.mt0, g.mts).
+template <int EPI>
+void prompt_gemm(PgemmArgs g, const PromptPlan& plan, hipStream_t st) {
+    g.splits = plan.splits;
+    g.nblk = ceil_div(g.Nt, plan.waves * kPgN);
+    g.mblk = ceil_div(g.mts - g.mt0, plan.tiles);
+    const dim3 grid(uint32_t(ceil_div(int64_t(g.nblk) * g.mblk * g.splits, 8) * 8)), block(uint32_t(plan.waves) * 64);
+    if constexpr (EPI != PG_ARGMAX) {  // (one row tile)
+        if (plan.waves == 8) {
+            if (plan.tiles == 4) hipLaunchKernelGGL((k_prompt_gemm<EPI, 8, 4>), grid, block, 0, st, g);
+            else hipLaunchKernelGGL((k_prompt_gemm<EPI, 8, 7>), grid, block, 0, st, g);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_prompt_gemm<EPI, 4, 4>), grid, block, 0, st, g);
 }
 
 // One pass: `rows` tokens at positions ctx_len .. (a multiple of 16).  next_token: where the arg-max behind the
@@ -427,8 +446,8 @@ int prompt_pass(const card_model_cfg* cfg, const Layout& L, const PromptLayout& 
         g.nwg = nwg;
         g.x = in;
         g.mts = mts;
-        g.mp0 = e.mp0 = mt0 / kPgTiles * kPgTiles;  // (a tile that goes on alone may be cut many ways: its partials get few rows)
-        g.mcap = e.mcap = mpad - g.mp0;
+        g.mt0 = e.mp0 = mt0;  // (a tile that goes on alone may be cut many ways: its partials get few rows)
+        g.mcap = e.mcap = mts - mt0;
         g.part = const_cast<float*>(e.part);
         g.ss = e.ss;
         g.ss_groups = P.groups;
@@ -439,16 +458,20 @@ int prompt_pass(const card_model_cfg* cfg, const Layout& L, const PromptLayout& 
         g.row = rows - 1;
         g.V = cfg->vocab;
         g.best = e.best;
-        g.splits = epi == PG_ARGMAX ? 1 : prompt_splits(m.Nt, m.Ks, mts - mt0, epi == PG_SWIGLU);
-        e.splits = g.splits;
+        const PromptPlan plan = epi == PG_ARGMAX ? PromptPlan{4, 4, 1} : prompt_plan(m.Nt, m.Ks, mts - mt0, epi == PG_SWIGLU);
+        e.splits = plan.splits;
         e.Nt = m.Nt;
-        if (epi == PG_SWIGLU && g.splits > 1) {
-            prompt_gemm(g, PG_PART, mt0, st);
-            e.mt0 = mt0;
-            hipLaunchKernelGGL(k_prompt_swiglu, dim3(uint32_t(ceil_div(m.Nt, 2 * kPgWaves)), uint32_t(mts - mt0)), dim3(256), 0, st, e, act,
-                               L.wd.Ks);
+        if (epi == PG_ARGMAX) {
+            prompt_gemm<PG_ARGMAX>(g, plan, st);
+        } else if (epi == PG_SWIGLU && plan.splits == 1) {
+            prompt_gemm<PG_SWIGLU>(g, plan, st);
         } else {
-            prompt_gemm(g, epi, mt0, st);
+            prompt_gemm<PG_PART>(g, plan, st);
+            if (epi == PG_SWIGLU) {
+                e.mt0 = mt0;
+                hipLaunchKernelGGL(k_prompt_swiglu, dim3(uint32_t(ceil_div(m.Nt, 2 * kPgWaves)), uint32_t(mts - mt0)), dim3(256), 0, st, e,
+                                   act, L.wd.Ks);
+            }
         }
     };
     const auto resid = [&](const float* next_gain, int mt0) {

@@ -139,7 +139,8 @@ enum LvEpi { LV_PART = 0, LV_SWIGLU = 1, LV_LOGITS = 2 };
 // The others walk all of K.
 template <int EPI, int N>
 __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
-    constexpr int MT = kPgTiles, KB = 2, U = 4, DA = 4, DB = 2;
+    constexpr int MT = kPgTiles, KB = 2, U = 4, DA = 8, DB = 4;
+    static_assert(DA % U == 0 && DA == KB * DB && U == 2 * KB, "static ring indices");
     constexpr int XF = KB * 2 * MT, XW = XF / kPgWaves;
     constexpr bool FULL = EPI != LV_PART;
     __shared__ uint4v xs[2][XF][64];
@@ -190,14 +191,16 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
     for (int i = 0; i < N; ++i) tl[i].init(order, min(v0 + i, a.Nt - 1));
     uint32_t woff[N];
     Cursor ca = {-1, 0, 0, 0}, cb = {-1, 0, 0, 0};
-    auto load_a = [&](bf16x8 (&r)[N]) {
-        if (ca.left == 0 && next(ca)) {
+    // (`first`: the k-step is the first of a turn; chains begin with turns)
+    auto load_a = [&](bf16x8 (&r)[N], bool first) {
+        if (first && ca.left == 0 && next(ca)) {
             int w = 0;
             while (w + 1 < kStreamWaves && ca.s >= ((w + 1) * a.Ks) / kStreamWaves) ++w;
 #pragma unroll
             for (int i = 0; i < N; ++i) woff[i] = tl[i].at(ca.s, (w * a.Ks) / kStreamWaves, ((w + 1) * a.Ks) / kStreamWaves);
         }
-        const int voff = ca.left > 0 && ca.s < ca.e ? lane * 16 : kOutOfRange;
+        int voff = ca.left > 0 && ca.s < ca.e ? lane * 16 : kOutOfRange;
+        asm volatile("" : "+v"(voff));  // (one load here, not one per way to this offset: the second would wait for the first)
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             r[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wr, voff, int(woff[i]), 0));
@@ -208,13 +211,13 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
     };
     const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x + px_frag(a.Ks, 0, mt0), uint32_t(a.Ks) * (kPgTiles * 2048));
     const int xoff = (wave * XW * 64 + lane) * 16;
-    auto load_b = [&](uint4v (&r)[XW]) {
-        if (cb.left == 0) next(cb);
+    auto load_b = [&](uint4v (&r)[XW], bool first) {
+        if (first && cb.left == 0) next(cb);
 #pragma unroll
         for (int q = 0; q < XW; ++q) {
-            const int s = cb.s + (wave * XW + q) / (2 * MT);
-            r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, cb.left > 0 && s < cb.e ? xoff + q * 1024 : kOutOfRange,
-                                                         cb.s * (kPgTiles * 2048), 0);
+            int voff = cb.left > 0 && cb.s + (wave * XW + q) / (2 * MT) < cb.e ? xoff + q * 1024 : kOutOfRange;
+            asm volatile("" : "+v"(voff));
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff, cb.s * (kPgTiles * 2048), 0);
         }
         cb.s += KB;
         cb.left -= cb.left > 0 ? KB : 0;
@@ -237,51 +240,60 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
         for (int j = 0; j < MT; ++j) acc[i][j] = tot[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     bf16x8 wa[DA][N];
     uint4v xb[DB][XW];
-    load_b(xb[0]);
+    load_b(xb[0], true);
 #pragma unroll
-    for (int q = 0; q + 1 < DA; ++q) load_a(wa[q]);
+    for (int q = 0; q + 1 < DA; ++q) load_a(wa[q], q % U == 0);
     store_b(0, xb[0]);
 #pragma unroll
-    for (int q = 1; q <= DB; ++q) load_b(xb[q % DB]);
+    for (int q = 1; q <= DB; ++q) load_b(xb[q % DB], q % 2 == 0);
     sync();
-    for (int c = 0; c < n_chains; ++c) {
+    int c = -1, turns = 0, total_turns = 0;  // the chain that is being multiplied, what is left of it
+    for (int i = 0; i < n_chains; ++i) {
         int b, e;
-        chain(c, b, e);
-        for (int s = b; s < e; s += U) {
+        chain(i, b, e);
+        total_turns += (e - b + U - 1) / U;
+    }
+    auto next_chain = [&]() {
+        while (turns == 0 && c + 1 < n_chains) {
+            int b, e;
+            chain(++c, b, e);
+            turns = (e - b + U - 1) / U;
+            if (FULL && turns == 0) {
 #pragma unroll
-            for (int h = 0; h < DB; ++h) {
-#pragma unroll
-                for (int k = 0; k < KB; ++k) {
-                    const int u = h * KB + k;
-                    load_a(wa[(u + DA - 1) % DA]);
-#pragma unroll
-                    for (int j = 0; j < MT; ++j) {
-                        const bf16x8 bh = __builtin_bit_cast(bf16x8, xs[h][(k * MT + j) * 2][lane]);
-                        const bf16x8 bl = __builtin_bit_cast(bf16x8, xs[h][(k * MT + j) * 2 + 1][lane]);
-#pragma unroll
-                        for (int i = 0; i < N; ++i)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bh, acc[i][j], 0, 0, 0);
-#pragma unroll
-                        for (int i = 0; i < N; ++i)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bl, acc[i][j], 0, 0, 0);
-                    }
-                }
-                store_b(h ^ 1, xb[h ^ 1]);
-                load_b(xb[h ^ 1]);
-                sync();
+                for (int i = 0; i < N; ++i) pkq[wave][c][i][lane] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
         }
-        // the chain's end.  (A packed tile's quarter is one chain in the grouped down-projection too.)
+    };
+    next_chain();
+    for (int t = 0; t < total_turns; t += DA / U) {  // (a turn behind the last one multiplies zeros)
 #pragma unroll
-        for (int j = 0; j < MT; ++j) {
-            const bool packed = (pk >> j) & 1u;
-            if (FULL || !packed) {
+        for (int tt = 0; tt < DA / U; ++tt) {
 #pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    if (FULL && packed) pkq[wave][c][i][lane] = acc[i][j];
-                    tot[i][j] += acc[i][j];
-                    acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int h = 0; h < 2; ++h) {
+                const int half = tt * 2 + h;
+                px_half_turn<N, MT, KB>(xs[h], lane, acc, [&](int k) -> const bf16x8(&)[N] { return wa[(half * KB + k) % DA]; }, [&](int k) {
+                    const int u = half * KB + k + DA - 1;
+                    load_a(wa[u % DA], u % U == 0);
+                });
+                store_b(h ^ 1, xb[(half + 1) % DB]);
+                load_b(xb[(half + 1) % DB], (half + 1 + DB) % 2 == 0);
+                sync();
+            }
+            // the chain's end.  (A packed tile's quarter is one chain in the grouped down-projection too.)
+            if (turns > 0 && --turns == 0) {
+#pragma unroll
+                for (int j = 0; j < MT; ++j) {
+                    const bool packed = (pk >> j) & 1u;
+                    if (FULL || !packed) {
+#pragma unroll
+                        for (int i = 0; i < N; ++i) {
+                            if (FULL && packed) pkq[wave][c][i][lane] = acc[i][j];
+                            tot[i][j] += acc[i][j];
+                            acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        }
+                    }
                 }
+                next_chain();
             }
         }
     }

@@ -22,11 +22,11 @@
 
 namespace card {
 
-constexpr int kPgTiles = 4;      // row tiles per block of the activation layout and per workgroup
+constexpr int kPgTiles = 4;      // row tiles per block of the activation layout
 constexpr int kPgGroup = 64;     // residual columns per partial sum of squares
-constexpr int kPgWaves = 4;      // wavefronts per workgroup of the product kernel
+constexpr int kPgWaves = 4;      // wavefronts per workgroup of the small kernels
 constexpr int kPgN = 4;          // weight tiles per wavefront
-constexpr int kPgUnroll = 4;     // k-steps per turn of the product kernel's rings
+constexpr int kPgUnroll = 4;     // k-steps per turn of the product kernel
 
 // element offset of (k-step s, row tile mt) of an activation with Ks k-steps: hi fragment, lo 512 behind
 __device__ __forceinline__ size_t px_frag(int Ks, int s, int mt) {
@@ -76,9 +76,8 @@ struct PgemmArgs {
     uint32_t bytes;
     int32_t Nt, Ks, NB, nwg;  // tiles, k-steps, batch width and grid of the stream order
     const __bf16* x;     // activations [blocks][Ks][kPgTiles][2][64][8]
-    int32_t mts;         // row tiles in use
-    int32_t mp0, mcap;   // first row tile of the partials and how many they have room for
-    int32_t mb0;         // first block of row tiles
+    int32_t mts;         // end of the row tiles in use
+    int32_t mt0, mcap;   // first row tile, and how many the partials have room for
     int32_t nblk, mblk, splits;
     float* part;         // [splits][Nt][mcap][64][4]
     // SwiGLU
@@ -128,27 +127,49 @@ struct PgTile {
     }
 };
 
-// One workgroup: 16 weight tiles (four per wavefront, straight from memory into registers: no
-// other wavefront needs them) x four row tiles (staged through LDS: all four need them), a range of K.
-// Per k-step a wavefront issues 32 matrix instructions (high and low halves) on four weight and eight
-// activation fragments; two workgroups per compute unit, so one's barriers and loads hide behind the
-// other's matrix instructions.
-// Loads in flight: a k-step's matrix instructions take 0.21 us, a load 0.5-1 us, so three steps of
-// weights and four of activations are ahead in registers.  All loads are unconditional (out of range behind
-// the end: zeros, no memory access), so that the compiler's waits leave the others in flight.
-// Measured on gate/up of the 8B shape, 1000 rows (1792 workgroups, 128 k-steps, 474 GFLOP issued, halves
-// counted): 375-393 us from session to session, 1.2-1.26 PFLOP/s.  24 KiB per workgroup and k-step come from L2,
-// 14-15 TB/s, 56-59 GB/s per compute unit.  In one session, 393 us: one step of weights ahead 393 (the depth
-// no longer matters with two k-steps per barrier), eight row tiles per workgroup 588 (a third fewer bytes, but 58
-// registers spill).  The 32x32x16 instruction on the same tiles: no gain.
-template <int EPI>
-__global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
-    constexpr int MT = kPgTiles;
-    constexpr int KB = 2;                                // k-steps between two barriers
-    constexpr int XF = KB * 2 * MT, XW = XF / kPgWaves;  // their activation fragments, per wavefront
-    constexpr int DA = 4, DB = 2;  // register stages: weights of a k-step, activations of KB k-steps
-    constexpr int U = kPgUnroll;
-    static_assert(U % DA == 0 && U == KB * DB && DB == 2, "static ring indices");
+// The matrix instructions of KB k-steps on a wavefront's N weight tiles (weights(k)) and MT row tiles, whose halves lie in LDS.
+// A row tile's fragments are read PX_AHEAD steps before they are used: left to itself the compiler reads them right in front of their first
+// use, and a wavefront then waits for LDS four times a k-step.  before(k) runs in front of k-step k.
+template <int N, int MT, int KB, typename W, typename F>
+__device__ __forceinline__ void px_half_turn(const uint4v (&x)[KB * MT * 2][64], int lane, floatx4 (&acc)[N][MT], W&& weights, F&& before) {
+    constexpr int J = N >= 4 ? 1 : 2;      // row tiles per step: at least four independent instructions in a row
+    constexpr int STEPS = KB * MT / J, AHEAD = N == 1 || (N >= 4 && MT < 8) ? 2 : 1;
+    static_assert(MT % J == 0 && STEPS >= AHEAD, "steps");
+    bf16x8 fr[STEPS][2 * J];
+    auto read = [&](int i) {
+#pragma unroll
+        for (int q = 0; q < 2 * J; ++q) fr[i][q] = __builtin_bit_cast(bf16x8, x[i * 2 * J + q][lane]);
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) read(i);
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        const int k = i * J / MT;
+        if (i * J % MT == 0) before(k);
+        if (i + AHEAD < STEPS) read(i + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+        const bf16x8(&w)[N] = weights(k);
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int q = 0; q < J; ++q)
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    floatx4& c = acc[n][(i * J + q) % MT];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[n], fr[i][2 * q + half], c, 0, 0, 0);
+                }
+    }
+}
+
+// One workgroup of W wavefronts: 4 W weight tiles (four per wavefront, straight from memory into registers: no
+// other wavefront needs them) x MT row tiles (staged through LDS: all of them need them), a range of K.
+// Per k-step a wavefront issues 8 MT matrix instructions (high and low halves).  W = 8 fills a compute unit with one
+// workgroup, W = 4 with two; either way two wavefronts share a SIMD.
+template <int EPI, int W, int MT>
+__global__ __launch_bounds__(W * 64, 2) void k_prompt_gemm(PgemmArgs a) {
+    constexpr int KB = kPgUnroll;                 // k-steps between two barriers, and in the ring of weights
+    constexpr int XF = KB * 2 * MT, XW = XF / W;  // their activation fragments, per wavefront
+    static_assert(XF % W == 0, "fragments dealt evenly");
     __shared__ uint4v xs[2][XF][64];
     __shared__ __align__(8) float scale[MT * 16];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -159,9 +180,9 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
     const int L = int(blockIdx.x & 7) * per + int(blockIdx.x >> 3);
     if (int(blockIdx.x >> 3) >= per || L >= total) return;
     const int mb = L % a.mblk, sp = (L / a.mblk) % a.splits, nb = L / (a.mblk * a.splits);
-    const int kc = (a.Ks + U - 1) / U;  // K in whole turns of the rings
-    const int k0 = kc * sp / a.splits * U, k1 = kc * (sp + 1) / a.splits * U;
-    const int v0 = (nb * kPgWaves + wave) * kPgN, mt0 = (a.mb0 + mb) * MT;
+    const int kc = (a.Ks + KB - 1) / KB;  // K in whole turns
+    const int k0 = kc * sp / a.splits * KB, k1 = kc * (sp + 1) / a.splits * KB, ke = min(k1, a.Ks);
+    const int v0 = (nb * W + wave) * kPgN, mt0 = a.mt0 + mb * MT;
 
     const __amdgpu_buffer_rsrc_t wr = make_rsrc(a.w, a.bytes);
     PgTile tl[kPgN];
@@ -178,7 +199,8 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
 #pragma unroll
             for (int i = 0; i < kPgN; ++i) woff[i] = tl[i].at(sa, s0, seg_end);
         }
-        const int voff = sa < min(k1, a.Ks) ? lane * 16 : kOutOfRange;
+        int voff = sa < ke ? lane * 16 : kOutOfRange;
+        asm volatile("" : "+v"(voff));  // (one load here, not one per way to this offset: the second would wait for the first)
 #pragma unroll
         for (int i = 0; i < kPgN; ++i) {
             r[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wr, voff, int(woff[i]), 0));
@@ -186,20 +208,30 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
         }
         ++sa;
     };
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x + px_frag(a.Ks, 0, mt0), uint32_t(a.Ks) * (kPgTiles * 2048));
-    const int xoff = (wave * XW * 64 + lane) * 16;  // (the fragments of consecutive k-steps are contiguous)
+    // fragment f of a turn: k-step f / (2 MT), row tile f / 2 % MT, half f % 2; the wavefront brings XW consecutive ones
+    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, uint32_t(a.Ks) * uint32_t((a.mts + kPgTiles - 1) / kPgTiles * kPgTiles) * 2048u);
+    uint32_t xoff[XW];
+    int xstep[XW];
+#pragma unroll
+    for (int q = 0; q < XW; ++q) {
+        const int f = wave * XW + q, mt = mt0 + f / 2 % MT;
+        xstep[q] = mt < a.mts ? f / (2 * MT) : 1 << 24;  // (no such row tile: no such k-step)
+        xoff[q] = uint32_t(px_frag(a.Ks, f / (2 * MT), mt)) * 2u + uint32_t(f & 1) * 1024u;
+    }
     int sb = k0;
-    auto load_b = [&](uint4v (&r)[XW]) {
+    uint4v xb[XW];
+    auto load_b = [&]() {
 #pragma unroll
         for (int q = 0; q < XW; ++q) {
-            const int voff = sb + (wave * XW + q) / (2 * MT) < min(k1, a.Ks) ? xoff + q * 1024 : kOutOfRange;
-            r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff, sb * (kPgTiles * 2048), 0);
+            int voff = sb + xstep[q] < ke ? lane * 16 : kOutOfRange;
+            asm volatile("" : "+v"(voff));
+            xb[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff, int(xoff[q] + uint32_t(sb) * (kPgTiles * 2048u)), 0);
         }
         sb += KB;
     };
-    auto store_b = [&](int buf, const uint4v (&r)[XW]) {
+    auto store_b = [&](int buf) {
 #pragma unroll
-        for (int q = 0; q < XW; ++q) xs[buf][wave * XW + q][lane] = r[q];
+        for (int q = 0; q < XW; ++q) xs[buf][wave * XW + q][lane] = xb[q];
     };
 
     floatx4 acc[kPgN][MT];
@@ -207,14 +239,11 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
     for (int i = 0; i < kPgN; ++i)
 #pragma unroll
         for (int j = 0; j < MT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 wa[DA][kPgN];
-    uint4v xb[DB][XW];
-    load_b(xb[0]);
+    bf16x8 wa[KB][kPgN];
+    load_b();
 #pragma unroll
-    for (int q = 0; q + 1 < DA; ++q) load_a(wa[q]);
-    store_b(0, xb[0]);
-#pragma unroll
-    for (int q = 1; q <= DB; ++q) load_b(xb[q % DB]);
+    for (int q = 0; q + 1 < KB; ++q) load_a(wa[q]);
+    store_b(0);
     auto sync = [&]() {  // LDS writes done, everybody here; loads stay in flight
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(kWaitLds);
@@ -222,45 +251,28 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
         asm volatile("" ::: "memory");
     };
     sync();
-    // Half turn h: multiply LDS buffer h; the weights DA - 1 k-steps on are requested, the activations of
-    // the next half turn go to the other buffer (everybody has left it at the last barrier) and their
-    // registers take those DB half turns behind it
-    for (int s = k0; s < k1; s += U) {
-#pragma unroll
-        for (int h = 0; h < DB; ++h) {
-#pragma unroll
-            for (int k = 0; k < KB; ++k) {
-                const int u = h * KB + k;
-                load_a(wa[(u + DA - 1) % DA]);
-#pragma unroll
-                for (int j = 0; j < MT; ++j) {
-                    const bf16x8 bh = __builtin_bit_cast(bf16x8, xs[h][(k * MT + j) * 2][lane]);
-                    const bf16x8 bl = __builtin_bit_cast(bf16x8, xs[h][(k * MT + j) * 2 + 1][lane]);
-#pragma unroll
-                    for (int i = 0; i < kPgN; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bh, acc[i][j], 0, 0, 0);
-#pragma unroll
-                    for (int i = 0; i < kPgN; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[u % DA][i], bl, acc[i][j], 0, 0, 0);
-                }
-            }
-            store_b(h ^ 1, xb[h ^ 1]);
-            load_b(xb[h ^ 1]);
-            sync();
-        }
+    // A turn: request the next one's activations, multiply this one's (requesting weights KB - 1 k-steps on), then put
+    // the next one's into the other LDS buffer, which everybody left at the last barrier.
+    for (int s = k0, h = 0; s < k1; s += KB, h ^= 1) {
+        load_b();
+        px_half_turn<kPgN, MT, KB>(xs[h], lane, acc, [&](int k) -> const bf16x8(&)[kPgN] { return wa[k]; },
+                                   [&](int k) { load_a(wa[(k + KB - 1) % KB]); });
+        store_b(h ^ 1);
+        sync();
     }
 
     if constexpr (EPI == PG_PART) {
 #pragma unroll
         for (int i = 0; i < kPgN; ++i) {
             if (v0 + i >= a.Nt) continue;
-            float* p = a.part + ((size_t(sp) * a.Nt + tl[i].t) * a.mcap + mt0 - a.mp0) * 256 + lane * 4;
+            float* p = a.part + ((size_t(sp) * a.Nt + tl[i].t) * a.mcap + mt0 - a.mt0) * 256 + lane * 4;
 #pragma unroll
             for (int j = 0; j < MT; ++j)
                 if (mt0 + j < a.mts) *reinterpret_cast<floatx4*>(p + j * 256) = acc[i][j];
         }
     } else if constexpr (EPI == PG_SWIGLU) {
-        for (int e = tid; e < MT * 64; e += kPgWaves * 64) {
+        for (int e = tid; e < MT * 64; e += W * 64) {
+            if (mt0 + (e >> 6) >= a.mts) continue;
             const float sc = px_row_scale<4>(a.ss + size_t(mt0 * 16 + (e >> 2)) * a.ss_groups, a.ss_groups, e & 3, a.inv_d, a.eps);
             if ((e & 3) == 0) scale[e >> 2] = sc;
         }
@@ -298,7 +310,7 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_prompt_gemm(PgemmArgs a) {
         sync();
         if (tid == 0) {
 #pragma unroll
-            for (int w = 1; w < kPgWaves; ++w) best = wb[w] > best ? wb[w] : best;
+            for (int w = 1; w < W; ++w) best = wb[w] > best ? wb[w] : best;
             __hip_atomic_fetch_max(a.best, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
