@@ -547,23 +547,27 @@ LevelLayout level_layout(const card_model_cfg* cfg, const Layout& L) {
     return p;
 }
 
-template <int EPI>
+template <int EPI, int N, int MT>
 void level_gemm(LvGemmArgs g, hipStream_t st) {
-    g.mblk = ceil_div(g.n_tiles, kPgTiles);
-    const int splits = EPI == LV_PART ? 4 : 1;
-    const auto grid = [&](int n) {
-        g.nblk = ceil_div(g.Nt, kPgWaves * n);
-        return dim3(uint32_t(ceil_div(int64_t(g.nblk) * splits * g.mblk, 8) * 8));
+    g.nblk = ceil_div(g.Nt, kLvWaves * N);
+    g.mblk = ceil_div(g.n_tiles, MT);
+    const int64_t wgs = int64_t(g.nblk) * g.mblk * (EPI == LV_PART ? 4 : 1);
+    hipLaunchKernelGGL((k_level_gemm<EPI, N, MT>), dim3(uint32_t(ceil_div(wgs, 8) * 8)), dim3(kLvWaves * 64), 0, st, g);
+}
+template <int EPI>
+void level_product(const LvGemmArgs& g, hipStream_t st) {
+    // whole rounds of 256 workgroups, times what they bring into a compute unit per k-step
+    const auto rounds = [&](int n, int mt) {
+        return ceil_div(int64_t(ceil_div(g.Nt, kLvWaves * n)) * ceil_div(g.n_tiles, mt) * (EPI == LV_PART ? 4 : 1), 256) * (kLvWaves * n + 2 * mt);
     };
     if constexpr (EPI == LV_PART) {
-        if (ceil_div(g.Nt, kPgWaves * 2) * splits * g.mblk < 256) {
-            const dim3 gr = grid(1);
-            hipLaunchKernelGGL((k_level_gemm<EPI, 1>), gr, dim3(kPgWaves * 64), 0, st, g);
-            return;
-        }
+        if (rounds(1, 2) <= rounds(2, 2)) level_gemm<EPI, 1, 2>(g, st);
+        else level_gemm<EPI, 2, 2>(g, st);
+    } else {
+        if (g.n_tiles > 4 && rounds(2, 8) < std::min(rounds(1, 4), rounds(2, 4))) level_gemm<EPI, 2, 8>(g, st);
+        else if (rounds(1, 4) <= rounds(2, 4)) level_gemm<EPI, 1, 4>(g, st);
+        else level_gemm<EPI, 2, 4>(g, st);
     }
-    const dim3 gr = grid(2);
-    hipLaunchKernelGGL((k_level_gemm<EPI, 2>), gr, dim3(kPgWaves * 64), 0, st, g);
 }
 
 // The rows of `e.t` (of the n_rows of the level) through the model.
@@ -607,23 +611,23 @@ int level_pass(const card_model_cfg* cfg, const Layout& L, const LevelLayout& P,
     const size_t pool_layer = size_t(kv->n_pages) * cfg->n_kv_heads * 16 * h;
     for (int l = 0; l < cfg->n_layers; ++l) {
         const char* lb = packed + L.layer0_off + size_t(l) * L.layer_stride;
-        level_gemm<LV_PART>(product(L.qkv, lb, e.xf), st);
+        level_product<LV_PART>(product(L.qkv, lb, e.xf), st);
         e.kpool = static_cast<__bf16*>(kv->k_pages) + size_t(l) * pool_layer;
         e.vpool = static_cast<__bf16*>(kv->v_pages) + size_t(l) * pool_layer;
         hipLaunchKernelGGL(k_level_qkv, dim3(uint32_t(ceil_div(L.qkv.Nt, 4)), uint32_t(e.n_tiles)), dim3(256), 0, st, e);
         if (h == 128) hipLaunchKernelGGL(k_level_attn<128>, dim3(uint32_t(tasks)), dim3(256), 0, st, e);
         else hipLaunchKernelGGL(k_level_attn<64>, dim3(uint32_t(tasks)), dim3(256), 0, st, e);
-        level_gemm<LV_PART>(product(L.wo, lb, e.att), st);
+        level_product<LV_PART>(product(L.wo, lb, e.att), st);
         e.gain = gain(l, true);
         hipLaunchKernelGGL(k_level_resid<false>, cols, dim3(256), 0, st, e);
-        level_gemm<LV_SWIGLU>(product(L.gu, lb, e.xf), st);
+        level_product<LV_SWIGLU>(product(L.gu, lb, e.xf), st);
         LvGemmArgs g = product(L.wd, lb, reinterpret_cast<const __bf16*>(ws + P.act));
         g.grouped = (nwg & 7) == 0 && (L.wd.Nt & 3) == 0;
-        level_gemm<LV_PART>(g, st);
+        level_product<LV_PART>(g, st);
         e.gain = gain(l + 1, false);
         hipLaunchKernelGGL(k_level_resid<false>, cols, dim3(256), 0, st, e);
     }
-    level_gemm<LV_LOGITS>(product(L.lm, packed, e.xf), st);
+    level_product<LV_LOGITS>(product(L.lm, packed, e.xf), st);
     LvTopkArgs t = {};
     t.logits = reinterpret_cast<const float*>(ws + P.logits);
     t.ldl = L.lm.Nt * 16;

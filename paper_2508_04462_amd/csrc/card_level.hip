@@ -23,6 +23,7 @@
 namespace card {
 
 constexpr int kLvTiles = 8;  // row tiles of a pass
+constexpr int kLvWaves = 8;  // wavefronts per workgroup of the product kernel
 
 // Rows [row0, row0 + n) of the level, n <= 16, all of one call.
 struct LvTile {
@@ -132,20 +133,21 @@ struct LvGemmArgs {
 
 enum LvEpi { LV_PART = 0, LV_SWIGLU = 1, LV_LOGITS = 2 };
 
-// As k_prompt_gemm (weights of a wavefront's N tiles straight into registers, four row tiles of activations through LDS
-// for all four wavefronts), but K is walked in the verify kernel's chains: at the end of each the accumulators are
+// As k_prompt_gemm (weights of a wavefront's N tiles straight into registers, MT row tiles of activations through LDS
+// for all eight wavefronts), but K is walked in the verify kernel's chains: at the end of each the accumulators are
 // added to the running sums and start again from zero.  LV_PART: a workgroup takes one quarter of K (one chain, or the four of
 // the grouped down-projection), the next kernel adds the quarters; narrow matrices then still fill the chip.
 // The others walk all of K.
-template <int EPI, int N>
-__global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
-    constexpr int MT = kPgTiles, KB = 2, U = 4, DA = 8, DB = 4;
-    static_assert(DA % U == 0 && DA == KB * DB && U == 2 * KB, "static ring indices");
-    constexpr int XF = KB * 2 * MT, XW = XF / kPgWaves;
+template <int EPI, int N, int MT>
+__global__ __launch_bounds__(kLvWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
+    // k-steps between two barriers (a "turn"), turns in the rings of registers, weights in the ring
+    constexpr int KB = MT > 4 ? 2 : 4, UT = 2, DA = KB * UT;
+    constexpr int XF = KB * 2 * MT, XW = XF / kLvWaves;
+    static_assert(XF % kLvWaves == 0 && UT == 2, "fragments dealt evenly; turn u reads LDS buffer u & 1");
     constexpr bool FULL = EPI != LV_PART;
     __shared__ uint4v xs[2][XF][64];
     __shared__ __align__(16) float scale[FULL ? MT * 16 : 4];
-    __shared__ floatx4 pkq[FULL ? kPgWaves : 1][4][N][64];  // a packed tile's four quarters
+    __shared__ floatx4 pkq[FULL ? kLvWaves : 1][4][N][64];  // a packed tile's four quarters
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int splits = FULL ? 1 : 4;
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
     const int L = int(blockIdx.x & 7) * per + int(blockIdx.x >> 3);
     if (int(blockIdx.x >> 3) >= per || L >= total) return;
     const int mb = L % a.mblk, sp = (L / a.mblk) % splits, nb = L / (a.mblk * splits);
-    const int v0 = (nb * kPgWaves + wave) * N, mt0 = mb * MT;
+    const int v0 = (nb * kLvWaves + wave) * N, mt0 = mb * MT;
     const uint32_t pk = (a.pk_tiles >> mt0) & ((1u << MT) - 1u);
     const int q0 = (sp * a.Ks) / kStreamWaves, qlen = ((sp + 1) * a.Ks) / kStreamWaves - q0;
     const int n_chains = FULL ? kStreamWaves : (a.grouped ? 4 : 1);
@@ -178,7 +180,7 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
             chain(++c.i, b, e);
             c.s = b;
             c.e = e;
-            c.left = (e - b + U - 1) / U * U;
+            c.left = (e - b + KB - 1) / KB * KB;
             moved = true;
         }
         return moved;
@@ -209,15 +211,23 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
         ++ca.s;
         ca.left -= ca.left > 0 ? 1 : 0;
     };
-    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x + px_frag(a.Ks, 0, mt0), uint32_t(a.Ks) * (kPgTiles * 2048));
-    const int xoff = (wave * XW * 64 + lane) * 16;
-    auto load_b = [&](uint4v (&r)[XW], bool first) {
-        if (first && cb.left == 0) next(cb);
+    // fragment f of a turn: k-step f / (2 MT), row tile f / 2 % MT, half f % 2; the wavefront brings XW consecutive ones
+    const __amdgpu_buffer_rsrc_t xr = make_rsrc(a.x, uint32_t(a.Ks) * uint32_t((a.n_tiles + kPgTiles - 1) / kPgTiles * kPgTiles) * 2048u);
+    uint32_t xoff[XW];
+    int xstep[XW];
+#pragma unroll
+    for (int q = 0; q < XW; ++q) {
+        const int f = wave * XW + q, mt = mt0 + f / 2 % MT;
+        xstep[q] = mt < a.n_tiles ? f / (2 * MT) : 1 << 24;  // (no such row tile: no such k-step)
+        xoff[q] = uint32_t(px_frag(a.Ks, f / (2 * MT), mt)) * 2u + uint32_t(f & 1) * 1024u;
+    }
+    auto load_b = [&](uint4v (&r)[XW]) {
+        if (cb.left == 0) next(cb);
 #pragma unroll
         for (int q = 0; q < XW; ++q) {
-            int voff = cb.left > 0 && cb.s + (wave * XW + q) / (2 * MT) < cb.e ? xoff + q * 1024 : kOutOfRange;
+            int voff = cb.left > 0 && cb.s + xstep[q] < cb.e ? lane * 16 : kOutOfRange;
             asm volatile("" : "+v"(voff));
-            r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff, cb.s * (kPgTiles * 2048), 0);
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(xr, voff, int(xoff[q] + uint32_t(cb.s) * (kPgTiles * 2048u)), 0);
         }
         cb.s += KB;
         cb.left -= cb.left > 0 ? KB : 0;
@@ -239,25 +249,25 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
 #pragma unroll
         for (int j = 0; j < MT; ++j) acc[i][j] = tot[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     bf16x8 wa[DA][N];
-    uint4v xb[DB][XW];
-    load_b(xb[0], true);
+    uint4v xb[UT][XW];
+    load_b(xb[0]);
 #pragma unroll
-    for (int q = 0; q + 1 < DA; ++q) load_a(wa[q], q % U == 0);
+    for (int q = 0; q + 1 < DA; ++q) load_a(wa[q], q % KB == 0);
     store_b(0, xb[0]);
 #pragma unroll
-    for (int q = 1; q <= DB; ++q) load_b(xb[q % DB], q % 2 == 0);
+    for (int q = 1; q <= UT; ++q) load_b(xb[q % UT]);
     sync();
     int c = -1, turns = 0, total_turns = 0;  // the chain that is being multiplied, what is left of it
     for (int i = 0; i < n_chains; ++i) {
         int b, e;
         chain(i, b, e);
-        total_turns += (e - b + U - 1) / U;
+        total_turns += (e - b + KB - 1) / KB;
     }
     auto next_chain = [&]() {
         while (turns == 0 && c + 1 < n_chains) {
             int b, e;
             chain(++c, b, e);
-            turns = (e - b + U - 1) / U;
+            turns = (e - b + KB - 1) / KB;
             if (FULL && turns == 0) {
 #pragma unroll
                 for (int i = 0; i < N; ++i) pkq[wave][c][i][lane] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -265,20 +275,15 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
         }
     };
     next_chain();
-    for (int t = 0; t < total_turns; t += DA / U) {  // (a turn behind the last one multiplies zeros)
+    for (int t = 0; t < total_turns; t += UT) {  // (a turn behind the last one multiplies zeros)
 #pragma unroll
-        for (int tt = 0; tt < DA / U; ++tt) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int half = tt * 2 + h;
-                px_half_turn<N, MT, KB>(xs[h], lane, acc, [&](int k) -> const bf16x8(&)[N] { return wa[(half * KB + k) % DA]; }, [&](int k) {
-                    const int u = half * KB + k + DA - 1;
-                    load_a(wa[u % DA], u % U == 0);
-                });
-                store_b(h ^ 1, xb[(half + 1) % DB]);
-                load_b(xb[(half + 1) % DB], (half + 1 + DB) % 2 == 0);
-                sync();
-            }
+        for (int u = 0; u < UT; ++u) {
+            px_half_turn<N, MT, KB>(xs[u & 1], lane, acc, [&](int k) -> const bf16x8(&)[N] { return wa[u * KB + k]; }, [&](int k) {
+                load_a(wa[(u * KB + k + DA - 1) % DA], (k + DA - 1) % KB == 0);
+            });
+            store_b((u + 1) & 1, xb[(u + 1) % UT]);
+            load_b(xb[(u + 1) % UT]);
+            sync();
             // the chain's end.  (A packed tile's quarter is one chain in the grouped down-projection too.)
             if (turns > 0 && --turns == 0) {
 #pragma unroll
@@ -308,7 +313,7 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
                 if (mt0 + j < a.n_tiles) *reinterpret_cast<floatx4*>(p + j * 256) = (pk >> j) & 1u ? acc[i][j] : tot[i][j];
         }
     } else {
-        for (int e = tid; e < MT * 16 * 8; e += kPgWaves * 64) {
+        for (int e = tid; e < MT * 16 * 8; e += kLvWaves * 64) {
             const int row = mt0 * 16 + (e >> 3);
             if (mt0 + (e >> 7) < a.n_tiles) {
                 const float sc = lv_row_scale(a.ss + size_t(row) * a.n_part, a.n_part, e & 7, a.inv_d, a.eps);
@@ -325,18 +330,19 @@ __global__ __launch_bounds__(kPgWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
 #pragma unroll
                 for (int i = 0; i < N; ++i)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) tot[i][j] += pkq[wave][c][i][min(lane + 8, 63)];
+                    for (int q = 0; q < 4; ++q) tot[i][j] += pkq[wave][q][i][min(lane + 8, 63)];
             }
             const float sc = scale[j * 16 + m];
             if constexpr (EPI == LV_SWIGLU) {
+                // (one tile: the lanes from 32 on get what the others have)
 #pragma unroll
                 for (int i = 0; i < N; i += 2) {
-                    const int ta = tl[i].t, tb = tl[i + 1].t;
+                    const int i1 = N > 1 ? i + 1 : i;
                     float v[4];
                     const bool low = lane < 32;
-                    px_swiglu_values(lane, sc, tot[i][j], tot[i + 1][j], v);
-                    const int t = low ? ta : tb;
-                    if (v0 + i + (low ? 0 : 1) >= a.Nt || (packed && m >= 8)) continue;
+                    px_swiglu_values(lane, sc, tot[i][j], tot[i1][j], v);
+                    const int t = low ? tl[i].t : tl[i1].t;
+                    if (v0 + (low ? i : i + 1) >= (N > 1 || low ? a.Nt : 0) || (packed && m >= 8)) continue;
                     const int k = t * 8 + ((lane >> 4) & 1) * 4;
                     lv_store<4>(a.act, a.Ks_out, mt0 + j, packed, m, k, v);
                     const float z[4] = {0.f, 0.f, 0.f, 0.f};

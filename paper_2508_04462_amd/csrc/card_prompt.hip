@@ -132,7 +132,7 @@ struct PgTile {
 // use, and a wavefront then waits for LDS four times a k-step.  before(k) runs in front of k-step k.
 template <int N, int MT, int KB, typename W, typename F>
 __device__ __forceinline__ void px_half_turn(const uint4v (&x)[KB * MT * 2][64], int lane, floatx4 (&acc)[N][MT], W&& weights, F&& before) {
-    constexpr int J = N >= 4 ? 1 : 2;      // row tiles per step: at least four independent instructions in a row
+    constexpr int J = N >= 4 ? 1 : 2;      // row tiles per step: at least four independent instructions in a row (two of N = 1)
     constexpr int STEPS = KB * MT / J, AHEAD = N == 1 || (N >= 4 && MT < 8) ? 2 : 1;
     static_assert(MT % J == 0 && STEPS >= AHEAD, "steps");
     bf16x8 fr[STEPS][2 * J];
