@@ -384,6 +384,13 @@ def test_one_pass_over_a_wide_level_equals_its_calls(shape, first, n, lanes, k):
     _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), shape, first, n)
 
 
+def test_lanes_are_refused_where_no_share_of_the_gpu_was_given():
+    import paper_2508_04462_amd as card
+
+    with pytest.raises(ValueError):  # (a small model's own choice of a grid is no such share)
+        card.Target(TINY, 128).enable_lanes(2)
+
+
 def test_a_wide_level_with_a_refused_piece_leaves_nothing_running():
     """The pieces in front of a refused one work on tensors of the call: it ends behind them."""
     import paper_2508_04462_amd as card
