@@ -31,6 +31,40 @@ __device__ __forceinline__ void split_bf16(float v, __bf16& hi, __bf16& lo) {
     hi = static_cast<__bf16>(v);
     lo = static_cast<__bf16>(v - static_cast<float>(hi));
 }
+// Reductions over the four rows of sixteen lanes of a wavefront (lanes l, l ^ 16, l ^ 32, l ^ 48), the same in all of them: register
+// swaps.  A shuffle goes through LDS, 100 clocks and more each beside the weight stream: four of them stood in every round of an
+// attention task, three in front of an RMSNorm scale, one in a residual epilogue (verify step, same states, us with shuffles / without:
+// 1B decode 902 / 899, 8B r = 8 3246 / 3241, 7B r = 32 4370 / 4337, r = 13 3310 / 3297, 32 tree rows of the 1B shape 1279 / 1271).
+template <typename F>
+__device__ __forceinline__ float across_rows(float v, F&& op) {
+    typedef __attribute__((ext_vector_type(2))) unsigned int pair;
+    const uint32_t u = __float_as_uint(v);
+    const pair p = __builtin_bit_cast(pair, __builtin_amdgcn_permlane16_swap(u, u, false, false));  // rows (0, 0, 2, 2) and (1, 1, 3, 3)
+    v = op(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    const uint32_t w = __float_as_uint(v);
+    const pair q = __builtin_bit_cast(pair, __builtin_amdgcn_permlane32_swap(w, w, false, false));  // the halves
+    return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+__device__ __forceinline__ float max_across_rows(float v) {
+    return across_rows(v, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float sum_across_rows(float v) {
+    return across_rows(v, [](float a, float b) { return a + b; });
+}
+// Sum over a group of LPR neighbouring lanes (2, 4 or 8, all of them active), the same in all of them; register moves again.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    const int i = int(__float_as_uint(v));
+    return v + __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false)));
+}
+template <int LPR>
+__device__ __forceinline__ float group_sum(float v) {
+    static_assert(LPR == 2 || LPR == 4 || LPR == 8, "part of a row of lanes");
+    v = dpp_add<0xB1>(v);                            // lane ^ 1
+    if constexpr (LPR > 2) v = dpp_add<0x4E>(v);     // lane ^ 2
+    if constexpr (LPR > 4) v = dpp_add<0x141>(v);    // mirrored in eight: the other four
+    return v;
+}
 // Largest of a group of LPR neighbouring lanes' values (8 or 16, all of them active): register moves
 // inside a row of sixteen lanes, no trip through LDS.
 template <int CTRL>

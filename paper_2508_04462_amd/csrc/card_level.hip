@@ -108,8 +108,7 @@ __device__ __forceinline__ float lv_row_scale(const float* ss, int n_part, int s
         const floatx4 v = *reinterpret_cast<const floatx4*>(ss + 4 * g);
         sq += (v[0] + v[1]) + (v[2] + v[3]);
     }
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) sq += __shfl_xor(sq, o);
+    sq = group_sum<8>(sq);
     return 1.0f / sqrtf(sq * inv_d + eps);
 }
 

@@ -524,8 +524,7 @@ __device__ __forceinline__ void px_two_pages(const bf16x8 (&ka)[H / 32], const b
         if (oka[v]) pmax = fmaxf(pmax, sa[v]);
         if (okb[v]) pmax = fmaxf(pmax, sb[v]);
     }
-    pmax = fmaxf(pmax, __shfl_xor(pmax, 16));
-    pmax = fmaxf(pmax, __shfl_xor(pmax, 32));
+    pmax = max_across_rows(pmax);
     const float mnew = fmaxf(mx, pmax);
     const float alpha = __builtin_amdgcn_exp2f(mx - mnew);
     float psum = 0.f;
@@ -543,8 +542,7 @@ __device__ __forceinline__ void px_two_pages(const bf16x8 (&ka)[H / 32], const b
         pbh[v] = __builtin_bit_cast(short, hi);
         pbl[v] = __builtin_bit_cast(short, lo);
     }
-    psum += __shfl_xor(psum, 16);
-    psum += __shfl_xor(psum, 32);
+    psum = sum_across_rows(psum);
     sum = sum * alpha + psum;
     mx = mnew;
     weights_done();

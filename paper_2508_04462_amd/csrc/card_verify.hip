@@ -783,8 +783,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                         const float4 v = *reinterpret_cast<const float4*>(ea.ss_in + size_t(ss_row) * n_part + 4 * g);
                         sq += (v.x + v.y) + (v.z + v.w);
                     }
-#pragma unroll
-                for (int o = 1; o < SSL; o <<= 1) sq += __shfl_xor(sq, o);
+                sq = group_sum<SSL>(sq);
                 if (ss_sub == 0 && ss_row < r) sm.row_scale[ss_row] = 1.0f / sqrtf(sq * a.inv_d + a.eps);
             }
         }
@@ -893,7 +892,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                 st_dev_f32x8(ea.xres_new, uint32_t(m) * a.d + n0, nv);
                 st_dev_frag8(ea.xfrag_new, frag_index(n0, m, rp), gv);
             }
-            ssum += __shfl_xor(ssum, 1);
+            ssum = group_sum<2>(ssum);
             if (on && c == 0) st_agent(ea.ss_new + size_t(m) * (a.d >> 4) + (tile0 + i * t_inner), ssum);
             static_assert(NBS * 2 * kMaxR <= kMegaThreads, "one pass");
         } else if constexpr (EPI == ME_SWIGLU) {
@@ -1446,8 +1445,7 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
                 if (oka[v]) pmax = fmaxf(pmax, sa[v]);
                 if (okb[v]) pmax = fmaxf(pmax, sb[v]);
             }
-            pmax = fmaxf(pmax, __shfl_xor(pmax, 16));
-            pmax = fmaxf(pmax, __shfl_xor(pmax, 32));
+            pmax = max_across_rows(pmax);
             const float mnew = fmaxf(mx, pmax);
             const float alpha = __builtin_amdgcn_exp2f(mx - mnew);
             float pa[4], pb[4], psum = 0.f;
@@ -1457,8 +1455,7 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
                 pb[v] = okb[v] ? __builtin_amdgcn_exp2f(sb[v] - mnew) : 0.f;
                 psum += pa[v] + pb[v];
             }
-            psum += __shfl_xor(psum, 16);
-            psum += __shfl_xor(psum, 32);
+            psum = sum_across_rows(psum);
             sum = sum * alpha + psum;
             mx = mnew;
             short4v pah, pal, pbh, pbl;
@@ -1641,7 +1638,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
                 st_dev_f32x8(a.xres, uint32_t(m) * a.d + n0, nv);
                 st_dev_frag8(a.xfrag, frag_index(n0, m, a.rp), gv);
             }
-            ssum += __shfl_xor(ssum, 1);
+            ssum = group_sum<2>(ssum);
             if (on && c == 0) st_agent(a.ss + size_t(m) * n_dt + t, ssum);
         }
         // rotation table in fp64 (long contexts stay exact), spread over the grid
