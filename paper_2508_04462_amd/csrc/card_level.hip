@@ -457,8 +457,8 @@ __global__ __launch_bounds__(256) void k_level_qkv(LvArgs a) {
         float o2[2][2];  // [which half of the head][pair]
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            o2[0][q] = v[2 * q] * cp[q] - v[2 * q + 1] * sp[q];
-            o2[1][q] = v[2 * q + 1] * cp[q] + v[2 * q] * sp[q];
+            o2[0][q] = rotate_first(v[2 * q], v[2 * q + 1], cp[q], sp[q]);
+            o2[1][q] = rotate_second(v[2 * q], v[2 * q + 1], cp[q], sp[q]);
         }
         if (is_q) {
             const int kvh = head / a.G, gl = head % a.G;

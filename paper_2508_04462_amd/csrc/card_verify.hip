@@ -115,7 +115,10 @@ struct __align__(16) MegaSmem {
     float tile[2048];        // reduced outputs of one batch: [NB*16 rows][16*MT columns]
     float row_scale[kMaxR];
     float wgt[(kMegaWaves + 3) * 16];
-    unsigned long long part_best[512];
+    union {
+        unsigned long long part_best[512];  // vocabulary phase
+        float rope[kMaxR * 16];             // before: (cos, sin) of the eight pairs of the workgroup's QKV tiles, per row
+    };
     unsigned long long wg_best[kMaxR];
     uint4v dump[64];             // where a producer writes ring slots that hold no fragment (end of the stream)
     uint32_t tail[kMegaWaves];   // fragments pushed so far (written by the producer)
@@ -566,6 +569,13 @@ struct EpiArgs {
     LmState* lm;
 };
 
+// Whether all QKV tiles of a workgroup (every nwg-th, shifted by half the grid in odd layers) lie at the same place in their heads
+// of H / 16 tiles.  Their rotation factors then stay in LDS: loaded in every epilogue, they come behind the pages that attention
+// has just requested, a memory latency on the way to the barrier (1B decode 900 -> 888 us, 8B r = 8 3246 -> 3236, 7B r = 32 4334 -> 4309; in the
+// kernels for 9-16 rows and for more than eight tree rows no gain: 3302 -> 3315, 1291 -> 1301, so these load them as before).
+template <int H>
+__device__ __forceinline__ bool rope_in_lds(const MegaArgs& a) { return a.nwg % (H / 8) == 0; }
+
 struct NoHook {
     __device__ __forceinline__ void operator()() const {}
 };
@@ -589,7 +599,7 @@ struct NoHook {
 // so the four workgroups hand their blocks over in memory and the last one to arrive adds the four
 // (always in the order of the quarters, whoever comes last) and runs the epilogue for all four
 // tiles.
-template <int NB, int MT, int EPI, bool PK, typename Hook = NoHook, bool GRP4 = false>
+template <int H, int NB, int MT, int EPI, bool PK, bool ROPE_LDS = false, typename Hook = NoHook, bool GRP4 = false>
 __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P, const __bf16* xf, uint32_t xf_bytes,
                                            const EpiArgs& ea, FifoC& fc, MegaSmem& sm, int wave, int lane,
                                            uint32_t& cgen, Hook after_k = Hook()) {
@@ -1018,7 +1028,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
             // head and row 2p+1 its rotation partner p + h/2.  Work item: (tile, row m, which half).
             const int which = tid & 1, m = (tid >> 1) % kMaxR, i = tid / (2 * kMaxR);
             if (i < nvalid_s && m < r) {
-                const int h = a.h, half = h >> 1;
+                const int h = ROPE_LDS ? H : a.h, half = h >> 1;
                 const int prow = (tile0 + i * a.nwg) * 16;
                 const float sc = sm.row_scale[m];
                 const int page = sm.row_page[m], tk = (a.slot0 + m) & 15;
@@ -1026,13 +1036,28 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     const bool is_q = prow < a.qd;
                     const int rel = is_q ? prow : prow - a.qd;
                     const int head = rel / h, p0 = (rel % h) >> 1;  // eight pairs p0 .. p0+7 (p0 % 8 == 0)
+                    // factors of the eight pairs: from LDS where all tiles of the workgroup have the same ones
+                    float cos8[8], sin8[8];
+                    if (ROPE_LDS && rope_in_lds<H>(a)) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            cos8[e] = sm.rope[m * 16 + e];
+                            sin8[e] = sm.rope[m * 16 + 8 + e];
+                        }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            cos8[e] = a.rope[m * half + p0 + e];
+                            sin8[e] = a.rope[kMaxR * half + m * half + p0 + e];
+                        }
+                    }
                     float ov[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         const float z0 = sm.tile[(i * 16 + 2 * e) * COLS + m] * sc;
                         const float z1 = sm.tile[(i * 16 + 2 * e + 1) * COLS + m] * sc;
-                        const float cs = a.rope[m * half + p0 + e], sn = a.rope[kMaxR * half + m * half + p0 + e];
-                        ov[e] = which == 0 ? z0 * cs - z1 * sn : z1 * cs + z0 * sn;
+                        const float cs = cos8[e], sn = sin8[e];
+                        ov[e] = which == 0 ? rotate_first(z0, z1, cs, sn) : rotate_second(z0, z1, cs, sn);
                     }
                     const int j0 = p0 + which * half;  // first of eight consecutive head elements
                     if (is_q) {
@@ -1056,7 +1081,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
             const int jj = (tid & 1) * 8 + ((tid >> 1) & 7);
             const bool v_lane = ((tid >> 1) % kMaxR) < 8;
             if (i < nvalid_s && v_lane && (tile0 + i * a.nwg) * 16 >= a.qd + a.kvd) {
-                const int h = a.h;
+                const int h = ROPE_LDS ? H : a.h;
                 const int rel = (tile0 + i * a.nwg) * 16 - a.qd - a.kvd + jj;
                 const int head = rel / h, jg = rel % h;
                 int m2 = 0;
@@ -1657,6 +1682,12 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
 
     int pid0[8];
     attn_page_ids<H>(a, wave, wg, pid0);
+    constexpr bool ROPE_LDS = PK || (MT == 2 && !DR);
+    if (ROPE_LDS && rope_in_lds<H>(a)) {  // (read behind the barriers of the first QKV reduction)
+        const int p0 = wg * 16 % H / 2;
+        for (int e = tid; e < a.r * 16; e += kMegaThreads)
+            sm.rope[e] = a.rope[((e & 15) >> 3) * (kMaxR * H / 2) + (e >> 4) * (H / 2) + p0 + (e & 7)];
+    }
     const size_t xres_stride = size_t(kMaxR) * a.d, ss_stride = size_t(n_dt) * kMaxR;
 #define CARD_TS(i)                                                                  \
     if (a.ts && l == a.ts_layer && tid == 0) a.ts[size_t(wg) * 32 + (i)] = wall_clock64();
@@ -1692,7 +1723,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         };
         CARD_TS(0)
         ea.ts0 = 21;
-        gemm_phase<kNbQkv, MT, PC ? ME_QKV_PIECE : ME_QKV, PK>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
+        gemm_phase<H, kNbQkv, MT, PC ? ME_QKV_PIECE : ME_QKV, PK, ROPE_LDS>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
                                           sm, wave, lane, cgen, preload);
         CARD_TS(1)
         store_wait();
@@ -1713,7 +1744,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ss_new = a.ss + v1 * ss_stride;
         ea.gain_next = reinterpret_cast<const float*>(lb + a.g_ffn_off);
         ea.ts0 = 24;
-        gemm_phase<kNbOne, MT, ME_RESID, PK>(a, p_wo, a.attfrag + size_t(l) * a.attfrag_stride,
+        gemm_phase<H, kNbOne, MT, ME_RESID, PK>(a, p_wo, a.attfrag + size_t(l) * a.attfrag_stride,
                                             uint32_t(a.attfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         CARD_TS(5)
         store_wait();
@@ -1725,7 +1756,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ss_in = a.ss + v1 * ss_stride;
         ea.actfrag = a.actfrag + size_t(l) * a.actfrag_stride;
         ea.ts0 = 0;
-        gemm_phase<kNbWide, MT, ME_SWIGLU, PK>(a, p_gu, a.xfrag + v1 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea,
+        gemm_phase<H, kNbWide, MT, ME_SWIGLU, PK>(a, p_gu, a.xfrag + v1 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea,
                                               fc, sm, wave, lane, cgen);
         CARD_TS(7)
         store_wait();
@@ -1743,13 +1774,13 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ts0 = 27;
         if constexpr (!PK) {
             if (down_grouped(a))
-                gemm_phase<4, MT, ME_RESID, false, NoHook, true>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
+                gemm_phase<H, 4, MT, ME_RESID, false, false, NoHook, true>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
                                                                  uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
             else
-                gemm_phase<kNbOne, MT, ME_RESID, false>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
+                gemm_phase<H, kNbOne, MT, ME_RESID, false>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
                                                         uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         } else {
-            gemm_phase<kNbOne, MT, ME_RESID, PK>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
+            gemm_phase<H, kNbOne, MT, ME_RESID, PK>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
                                                 uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         }
         CARD_TS(9)
@@ -1765,7 +1796,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ss_in = a.ss + size_t(2 * a.L) * ss_stride;
         LmState lm = {{0ull, 0ull}, -1e30f, 0.f};
         ea.lm = &lm;
-        gemm_phase<kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK>(a, p_lm, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
+        gemm_phase<H, kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK>(a, p_lm, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
                                           uint32_t(a.xfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         if (!DR && tid < a.r && sm.wg_best[tid] != 0ull)
             __hip_atomic_fetch_max(&a.best[tid], sm.wg_best[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
