@@ -352,6 +352,13 @@ __device__ __forceinline__ PhasePlan stream_phase(const MegaArgs& a, int ph, int
     return plan_phase(reinterpret_cast<const bf16x8*>(lb + a.wd.off), a.wd.Nt, a.wd.Ks, wg, nwg, ((l + 1) & 1) * half, wave);
 }
 
+// The consumers' plan of the next phase is made while the barrier in front of it is still to come: its divisions (a few hundred
+// clocks) would stand between the release and the first activation loads otherwise (8B r = 8 3233 -> 3203 us, 7B r = 32 4313 -> 4291, r = 13
+// 3301 -> 3290, 70B widths 2736 -> 2730, 1B decode 888 -> 891).
+__device__ __forceinline__ void made_here(const PhasePlan& p) {
+    asm volatile("" ::"s"(p.first), "s"(p.bytes), "s"(p.cnt), "s"(p.s0), "s"(p.s1), "s"(p.t_first));
+}
+
 // ---- producer ----------------------------------------------------------------------------------
 // Walks the stream of wavefront pair w: kRing loads in flight in a static register ring, each
 // arrival written to the next FIFO slot (LDS addresses are dynamic, register indices are not).
@@ -1691,6 +1698,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
     const size_t xres_stride = size_t(kMaxR) * a.d, ss_stride = size_t(n_dt) * kMaxR;
 #define CARD_TS(i)                                                                  \
     if (a.ts && l == a.ts_layer && tid == 0) a.ts[size_t(wg) * 32 + (i)] = wall_clock64();
+    PhasePlan p_qkv = stream_phase<!PK>(a, SP_QKV, wg, wave);
     for (int l = 0; l < a.L; ++l) {
         const char* lb = layer_base(l);
         const int v0 = 2 * l, v1 = 2 * l + 1, v2 = 2 * l + 2;
@@ -1701,7 +1709,6 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         // QKV (+norm scale, rotation, KV write).  Pages that hold only old context do not depend
         // on this phase: their loads are issued as soon as the k-loop is over, ahead of the
         // epilogue's stores, and land while the barrier in front of attention is crossed.
-        const PhasePlan p_qkv = stream_phase<!PK>(a, 4 * l + SP_QKV, wg, wave);
         ea.ss_in = a.ss + v0 * ss_stride;
         ea.qfrag = a.qfrag + size_t(l) * a.qfrag_stride;
         ea.kpool = a.kpool + size_t(l) * a.pool_layer_elems;
@@ -1732,12 +1739,13 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         CARD_TS(2)
         attn_phase<H, DR, PC>(a, l, sm, wave, lane, wg, bf, pid0, loaded, cgen);
         CARD_TS(3)
+        const PhasePlan p_wo = stream_phase<!PK>(a, 4 * l + SP_WO, wg, wave);
+        made_here(p_wo);
         store_wait();
         grid_wait(a, gen, sm, cgen);
         CARD_TS(4)
 
         // O-projection + residual -> version v1, gained with the FFN norm's gain
-        const PhasePlan p_wo = stream_phase<!PK>(a, 4 * l + SP_WO, wg, wave);
         ea.xres_old = a.xres + v0 * xres_stride;
         ea.xres_new = a.xres + v1 * xres_stride;
         ea.xfrag_new = a.xfrag + v1 * a.xfrag_stride;
@@ -1747,24 +1755,26 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         gemm_phase<H, kNbOne, MT, ME_RESID, PK>(a, p_wo, a.attfrag + size_t(l) * a.attfrag_stride,
                                             uint32_t(a.attfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         CARD_TS(5)
+        const PhasePlan p_gu = stream_phase<!PK>(a, 4 * l + SP_GU, wg, wave);
+        made_here(p_gu);
         store_wait();
         grid_wait(a, gen, sm, cgen);
         CARD_TS(6)
 
         // gate/up + SwiGLU
-        const PhasePlan p_gu = stream_phase<!PK>(a, 4 * l + SP_GU, wg, wave);
         ea.ss_in = a.ss + v1 * ss_stride;
         ea.actfrag = a.actfrag + size_t(l) * a.actfrag_stride;
         ea.ts0 = 0;
         gemm_phase<H, kNbWide, MT, ME_SWIGLU, PK>(a, p_gu, a.xfrag + v1 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea,
                                               fc, sm, wave, lane, cgen);
         CARD_TS(7)
+        const PhasePlan p_wd = stream_phase<!PK>(a, 4 * l + SP_WD, wg, wave);
+        made_here(p_wd);
         store_wait();
         grid_wait(a, gen, sm, cgen);
         CARD_TS(8)
 
         // down + residual -> version v2, gained with the next norm's gain
-        const PhasePlan p_wd = stream_phase<!PK>(a, 4 * l + SP_WD, wg, wave);
         ea.xres_old = a.xres + v1 * xres_stride;
         ea.xres_new = a.xres + v2 * xres_stride;
         ea.xfrag_new = a.xfrag + v2 * a.xfrag_stride;
@@ -1784,6 +1794,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
                                                 uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         }
         CARD_TS(9)
+        p_qkv = stream_phase<!PK>(a, 4 * (l + 1) + SP_QKV, wg, wave);  // (behind the last layer the vocabulary head's)
+        made_here(p_qkv);
         store_wait();
         grid_wait(a, gen, sm, cgen);
         CARD_TS(10)
@@ -1791,12 +1803,11 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
 
     // vocabulary head + arg-max
     {
-        const PhasePlan p_lm = stream_phase<!PK>(a, 4 * a.L, wg, wave);
         EpiArgs ea = {};
         ea.ss_in = a.ss + size_t(2 * a.L) * ss_stride;
         LmState lm = {{0ull, 0ull}, -1e30f, 0.f};
         ea.lm = &lm;
-        gemm_phase<H, kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK>(a, p_lm, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
+        gemm_phase<H, kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK>(a, p_qkv, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
                                           uint32_t(a.xfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         if (!DR && tid < a.r && sm.wg_best[tid] != 0ull)
             __hip_atomic_fetch_max(&a.best[tid], sm.wg_best[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
