@@ -137,6 +137,9 @@ enum LvEpi { LV_PART = 0, LV_SWIGLU = 1, LV_LOGITS = 2 };
 // added to the running sums and start again from zero.  LV_PART: a workgroup takes one quarter of K (one chain, or the four of
 // the grouped down-projection), the next kernel adds the quarters; narrow matrices then still fill the chip.
 // The others walk all of K.
+// Bound by the bytes that enter a compute unit (57 GB/s of weights and activations together): 0.15 us per k-step for eight weight tiles
+// and 0.07 for two row tiles.  1B shape, 100 rows, us: QKV 10.4 (N = 2, MT = 2; four wavefronts on four row tiles 11.8), O and down 12.9 on
+// average (N = 1, MT = 2; 13.9), gate/up 27.9 (N = 1, MT = 4; 28.6), vocabulary 131 (N = 2, MT = 8; 174).
 template <int EPI, int N, int MT>
 __global__ __launch_bounds__(kLvWaves * 64, 2) void k_level_gemm(LvGemmArgs a) {
     // k-steps between two barriers (a "turn"), turns in the rings of registers, weights in the ring

@@ -128,8 +128,8 @@ struct PgTile {
 };
 
 // The matrix instructions of KB k-steps on a wavefront's N weight tiles (weights(k)) and MT row tiles, whose halves lie in LDS.
-// A row tile's fragments are read PX_AHEAD steps before they are used: left to itself the compiler reads them right in front of their first
-// use, and a wavefront then waits for LDS four times a k-step.  before(k) runs in front of k-step k.
+// A row tile's fragments are read AHEAD steps before they are used: left to itself the compiler reads them right in front of their first
+// use, and a wavefront then waits for LDS four times a k-step (gate/up of the 1B shape, 203 rows: 39.7 -> 35.3 us).  before(k) runs in front of k-step k.
 template <int N, int MT, int KB, typename W, typename F>
 __device__ __forceinline__ void px_half_turn(const uint4v (&x)[KB * MT * 2][64], int lane, floatx4 (&acc)[N][MT], W&& weights, F&& before) {
     constexpr int J = N >= 4 ? 1 : 2;      // row tiles per step: at least four independent instructions in a row (two of N = 1)
@@ -165,6 +165,10 @@ __device__ __forceinline__ void px_half_turn(const uint4v (&x)[KB * MT * 2][64],
 // other wavefront needs them) x MT row tiles (staged through LDS: all of them need them), a range of K.
 // Per k-step a wavefront issues 8 MT matrix instructions (high and low halves).  W = 8 fills a compute unit with one
 // workgroup, W = 4 with two; either way two wavefronts share a SIMD.
+// A compute unit brings in about 57 GB/s of weights (HBM) and activations (L2) together, so wide workgroups pay by what they do not
+// read again: per k-step 46 KiB for 448 matrix instructions at 8 x 7, 24 for 128 at 4 x 4.  Measured on the 8B shape, 1000 rows, us,
+// 4 x 4 / 8 x 4 / 8 x 7: gate/up 371 / 381 / 326 (1.45 PFLOP/s issued, halves counted), QKV 88 / 90 / 82, O 58 / 55 / 62, down
+// 180 / 166 / 174; with zeros as operands gate/up takes 276: the card's power.  Eight row tiles spill (383).
 template <int EPI, int W, int MT>
 __global__ __launch_bounds__(W * 64, 2) void k_prompt_gemm(PgemmArgs a) {
     constexpr int KB = kPgUnroll;                 // k-steps between two barriers, and in the ring of weights
