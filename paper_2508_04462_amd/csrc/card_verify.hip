@@ -1386,9 +1386,10 @@ __device__ __forceinline__ void attn_page_ids(const MegaArgs& a, int wave, int w
 
 // TREE: draft-side rows with mask rows.  PIECE: of a level whose other rows are forwarded by calls that may run at the
 // same time: the last pages of the walk are shared with them.
-template <int H, bool TREE, bool PIECE>
-__device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSmem& sm, int wave, int lane, int wg,
-                                           AttnBufs<H>& bf, const int (&pid0)[8], bool (&loaded)[8], uint32_t& cgen) {
+// EARLY: the workgroup's first task, and which row the lane has in it, come with the call.
+template <int H, bool TREE, bool PIECE, bool EARLY>
+__device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSmem& sm, int wave, int lane, int wg, const AttnTask& first,
+                                           int first_row, AttnBufs<H>& bf, const int (&pid0)[8], bool (&loaded)[8], uint32_t& cgen) {
     constexpr int ST = H / 32, HT = H / 16, PART = 16 * (H + 2), NBUF = AttnBufs<H>::N;
     const int tid = threadIdx.x;
     const int R = a.G * a.r;
@@ -1397,11 +1398,11 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
     const __bf16* vpool = a.vpool + size_t(layer) * a.pool_layer_elems;
     const int n_tasks = a.Hkv * a.row_tiles * a.a_splits;
     for (int task = wg; task < n_tasks; task += a.nwg) {
-        const AttnTask t = attn_task(a, task);
+        const AttnTask t = EARLY && task == wg ? first : attn_task(a, task);
         const int kvh = t.kvh, rt = t.rt;
         const int rho = rt * 16 + col;
         const bool row_ok = rho < R;
-        const int mrow = row_ok ? rho / a.G : -1;
+        const int mrow = EARLY && task == wg ? first_row : (row_ok ? rho / a.G : -1);
         const int limit = a.slot0 + mrow;  // chain: last visible slot of this lane's row
         // tree rows: the lane's mask row (rows beyond R read row 0 and are dropped by mrow < 0)
         const uint32_t* mrow_mask = TREE ? a.tmask + size_t(mrow < 0 ? 0 : mrow) * a.tmask_words : nullptr;
@@ -1733,11 +1734,22 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         gemm_phase<H, kNbQkv, MT, PC ? ME_QKV_PIECE : ME_QKV, PK, ROPE_LDS>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
                                           sm, wave, lane, cgen, preload);
         CARD_TS(1)
+        // As with the plans, the first task's divisions in front of the barrier (1B decode 892 -> 885 us, 7B r = 32 4330 -> 4286, 8B r = 8
+        // 3232 -> 3228; in the kernels for 9-16 rows and for tree rows 0.2-0.3 % slower, so not there).
+        constexpr bool EARLY = ROPE_LDS;
+        AttnTask first = {};
+        int first_row = -1;
+        if constexpr (EARLY) {
+            first = attn_task(a, wg);
+            const int rho = first.rt * 16 + (lane & 15);
+            first_row = rho < a.G * a.r ? rho / a.G : -1;
+            asm volatile("" ::"s"(first.kvh), "s"(first.rt), "s"(first.split), "s"(first.pg0), "s"(first.pg1), "v"(first_row));
+        }
         store_wait();
         CARD_TS(12)
         grid_wait(a, gen, sm, cgen);
         CARD_TS(2)
-        attn_phase<H, DR, PC>(a, l, sm, wave, lane, wg, bf, pid0, loaded, cgen);
+        attn_phase<H, DR, PC, EARLY>(a, l, sm, wave, lane, wg, first, first_row, bf, pid0, loaded, cgen);
         CARD_TS(3)
         const PhasePlan p_wo = stream_phase<!PK>(a, 4 * l + SP_WO, wg, wave);
         made_here(p_wo);
