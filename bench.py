@@ -180,7 +180,7 @@ def cpu_baseline(shape, seed: int, ctx: int, r: int, cand):
 class Rig:
     """A target model of one shape with its weights, and the pieces the timed loops need."""
 
-    def __init__(self, shape, seed, max_ctx, grid_wgs=0):
+    def __init__(self, shape, seed, max_ctx):
         import torch
 
         import paper_2508_04462_amd as card
@@ -188,7 +188,7 @@ class Rig:
 
         self.card, self.torch = card, torch
         self.shape, self.seed = shape, seed
-        self.tgt = card.Target(shape, max_ctx + 64, max_r=32, grid_wgs=grid_wgs)
+        self.tgt = card.Target(shape, max_ctx + 64, max_r=32)
         load_synthetic_weights(self.tgt, shape, seed)
         self.ctx = None
         self.g0 = None
@@ -624,9 +624,7 @@ def main():
         print(json.dumps(draft_level_entry(args, False, probe_levels=3)))
         return
     sweep_ctx = 0 if args.sweep == "none" or args.shape != "llama8b" else (512 if args.sweep == "quick" else 32768)
-    # (a timeline is one of all compute units, also for a small model)
-    grid = torch.cuda.get_device_properties(dev).multi_processor_count if args.timeline is not None else 0
-    rig = Rig(shape, args.seed, max(ctx, sweep_ctx), min(grid, 256))
+    rig = Rig(shape, args.seed, max(ctx, sweep_ctx))
     rig.set_context(ctx)
     try:
         cands = rig.planted(r)  # planted-prefix invariant on the path being timed

@@ -61,7 +61,8 @@ typedef struct card_model_cfg {
                          256); a smaller number leaves the other compute units to kernels the
                          caller runs beside it (the draft model of the paper runs in parallel
                          with the target: CARD Design, first paragraph).  The packed weight
-                         order depends on it: pack and verify with the same value.            */
+                         order depends on it: pack and verify with the same value.  (Workgroups
+                         of either that a small model has no work for are not launched.)      */
 } card_model_cfg;
 
 /* Tensors of the canonical (caller-side) weight set. Matrices are bf16, row-major

@@ -56,6 +56,7 @@ struct MegaArgs {
     float eps, inv_d, theta, inv_sqrt_h;
     const char* wbase;
     const uint32_t* stamp;  // {magic, grid size} the weights were laid out for
+    int32_t grid;           // the grid size that has to be: nwg, or more where the last positions of that grid have nothing to do
     size_t embed_off, g_final_off, layer0_off, layer_stride, g_attn_off, g_ffn_off;
     MatDesc qkv, wo, gu, wd, lm;  // lm.off absolute, the others relative to the layer base
     __bf16* kpool;
@@ -1642,6 +1643,12 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         return;
     }
 
+    // Flags of positions that this call leaves out keep up with the epochs: behind by 2^31 (262144 calls), one would look
+    // ahead of a later call that needs it.
+    if (tid < kFlagCopies)
+        for (int p = wg + nwg; p < a.grid; p += nwg)
+            __hip_atomic_store(&a.flags[tid * 256 + p], sm.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
     uint32_t gen = 0, cgen = 0;
     FifoC fc = {0u, 0u, 0u, false, 0u};
     const int n_dt = a.d >> 4;  // 16-column tiles of the residual stream
@@ -1917,7 +1924,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
             int j = 0;
             while (j < a.r && a.cand[j] == sm.pred[j]) ++j;
             // weights laid out for another grid size would stream in the wrong order
-            const bool bad_layout = a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(nwg);
+            const bool bad_layout = a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.grid);
             // a token id outside the vocabulary was clamped by the embedding gather: the step is void
             bool bad_token = false;
             for (int i = 0; i < a.r; ++i) bad_token = bad_token || a.cand[i] < 0 || a.cand[i] >= a.V;

@@ -20,21 +20,6 @@ def make_cfg(shape, max_ctx: int, max_r: int = 32, grid_wgs: int = 0) -> B.CardM
 # (2 layers of 256 columns: 144 / 167); 33 tokens: 1367 / 2128, 4587 / 6879, 4442 / 6924, 3562 / 5872 (147 / 315).
 PROMPT_MIN_TOKENS = 33
 
-def _small_model_grid(cfg: B.CardModelCfg) -> int:
-    """Workgroups of a model that has the GPU for itself (0: all compute units).  A small model's step is a chain of grid-wide
-    hand-overs, and those are cheaper among fewer workgroups, as long as these stream the weights fast enough.
-    us per step, all 256 / the grid chosen (and others), 4 rows: 1.4 MB of weights per layer 79 / 70
-    (64: 71, 32: 70), 5.7 MB 124 / 110 (64: 111, 32: 117), 6.3 MB 146 / 130 (64: 130, 32: 137), 14 MB 216 / 197 (128: 199, 64: 209),
-    24 MB 229 / 220 (192: 225, 96: 223), 31 MB 229 / 212 (192: 222, 96: 221); 90 MB 155 (192: 150, 128: 157), 121 MB 904 (224: 910, 128:
-    1012).  Long contexts want all compute units for attention: 32 rows behind 2000 tokens 113 / 103, 181 / 169, 330 / 312, 350 / 342,
-    behind 4000 118 / 109, 188 / 192, 348 / 340, 365 / 368, behind 16 000 135 / 151, 210 / 326, 436 / 551, 439 / 524."""
-    if cfg.max_ctx > 2304:
-        return 0
-    d, h = cfg.d_model, cfg.head_dim
-    layer = 2 * (d * h * (2 * cfg.n_q_heads + 2 * cfg.n_kv_heads) + 3 * d * cfg.d_ffn)
-    return 48 if layer < 10e6 else 96 if layer < 19e6 else 128 if layer < 50e6 else 0
-
-
 # Levels of more rows than this go through card_draft_level_wide instead of calls side by side.
 LEVEL_ONE_PASS_ROWS = 32
 
@@ -76,11 +61,6 @@ class Target:
             raise RuntimeError("libcard needs a GPU: there is no CPU path")
         self.device = torch.device(device)
         self.cfg = make_cfg(shape, max_ctx, max_r, grid_wgs)
-        self._whole_gpu = grid_wgs == 0  # nothing else is meant to run beside it
-        if self._whole_gpu:
-            cus = torch.cuda.get_device_properties(self.device).multi_processor_count
-            grid = _small_model_grid(self.cfg)
-            self.cfg.grid_wgs = grid if grid < cus else 0
         wbytes = B.card_packed_weight_bytes(self.cfg)
         if wbytes == 0:
             raise B.CardError(B.CARD_EINVAL, "card_packed_weight_bytes")
@@ -179,7 +159,7 @@ class Target:
         created with grid_wgs set so that lanes * grid_wgs workgroups fit the GPU: every call of a
         level then runs on its own share of the compute units."""
         cus = torch.cuda.get_device_properties(self.device).multi_processor_count
-        if self._whole_gpu or lanes * self.cfg.grid_wgs > cus:
+        if self.cfg.grid_wgs <= 0 or lanes * self.cfg.grid_wgs > cus:
             raise ValueError("lanes * grid_wgs must fit the compute units")
         self._lane_ws = [self.workspace]
         for _ in range(lanes - 1):
@@ -249,7 +229,7 @@ class Target:
         (PROMPT_MIN_TOKENS), and wherever grid_wgs is given, whether or not something runs beside the
         model at that time (card_prompt's kernels spread over all compute units)."""
         n = len(tokens)
-        if (chunk >= 32 and self._whole_gpu and PROMPT_MIN_TOKENS <= n <= self.cfg.max_ctx
+        if (chunk >= 32 and self.cfg.grid_wgs == 0 and PROMPT_MIN_TOKENS <= n <= self.cfg.max_ctx
                 and self._prompt_workspace(min(n, 1024))):
             # `out` as a step leaves it: all n tokens taken, the next one, their slots; or, where a token id lies outside
             # the vocabulary (it is forwarded as the nearest one inside), as a failed step leaves it

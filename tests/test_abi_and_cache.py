@@ -94,17 +94,6 @@ def test_argument_errors_are_caught_on_the_host():
     assert card.card_strerror(card.CARD_ECAPACITY) == "KV cache capacity exceeded"
 
 
-def test_small_models_with_short_contexts_get_smaller_grids():
-    from paper_2508_04462_amd.runtime import _small_model_grid
-
-    shape = lambda d, f: ci.ModelShape("s", 1, d, d // 64, d // 64, 64, f, 100, ctx=64, r=4)  # noqa: E731
-    grids = [_small_model_grid(card.make_cfg(shape(d, f), 2048)) for d, f in ((256, 688), (768, 2048), (1024, 4096), (2048, 8192))]
-    assert grids == [48, 96, 128, 0]
-    assert _small_model_grid(card.make_cfg(shape(256, 688), 2320)) == 0
-    for name in ("llama1b", "llama8b", "qwen7b", "llama70b"):
-        assert _small_model_grid(card.make_cfg(ci.SHAPES[name], 1024)) == 0
-
-
 # ------------------------------------------------------------------------------- candidate cache
 
 
