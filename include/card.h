@@ -349,7 +349,8 @@ int card_cache_read_level(const card_cache* c, int32_t level, int32_t* tokens, i
  * rows in a page that it opens, and reads the pages of earlier slots through caches that another
  * call's stores do not reach.  Results, without the logits ever being stored: per row the k <= 16 most probable tokens (most probable first, equal
  * logits by ascending token id) and their probabilities under softmax over the whole vocabulary.
- * logits_dev (optional, test use): fp32 [n_rows][vocab].  Errors as card_verify.
+ * logits_dev (optional, test use): fp32 [n_rows][vocab].  Every token is -1 and every probability 0 if the weights were
+ * packed for another grid size.  Errors as card_verify.
  *
  * card_draft_level_piece: one of several calls that forward a level, in any order or at the same
  * time.  The level owns the slots [level_first, level_end) (ctx_len <= level_first <= first_slot,

@@ -649,6 +649,7 @@ int level_pass(const card_model_cfg* cfg, const Layout& L, const LevelLayout& P,
     t.nwg = nwg;
     t.n_tiles = e.n_tiles;
     t.k = k;
+    t.stamp = reinterpret_cast<const uint32_t*>(packed + L.stamp_off);
     std::copy(e.t, e.t + kLvTiles, t.t);
     t.lse = reinterpret_cast<float*>(ws + P.lse);
     t.best = reinterpret_cast<unsigned long long*>(ws + P.best);

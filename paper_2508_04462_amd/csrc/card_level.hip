@@ -696,6 +696,7 @@ __global__ __launch_bounds__(256, 2) void k_level_attn(LvArgs a) {
 struct LvTopkArgs {
     const float* logits;  // [n_tiles * 16][ldl]
     int32_t ldl, V, Nt, nwg, n_tiles, k;
+    const uint32_t* stamp;  // {magic, grid size} the weights were laid out for
     LvTile t[kLvTiles];
     float* lse;                  // [n_tiles * 16][nwg][2] (max, sum of exp) of the columns of each position of the stream order
     unsigned long long* best;    // [n_tiles * 16][16 * nwg] largest key of each lane's columns
@@ -835,6 +836,7 @@ __global__ __launch_bounds__(256) void k_level_topk(LvTopkArgs a) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) mine[c] = key_of(tid + c * 256);
     prev = ~0ull;
+    const bool bad_layout = a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.nwg);
     for (int j = 0; j < a.k; ++j) {
         unsigned long long best = 0ull;
 #pragma unroll
@@ -848,8 +850,9 @@ __global__ __launch_bounds__(256) void k_level_topk(LvTopkArgs a) {
             const uint32_t kb = uint32_t(best >> 32);
             const float logit = __uint_as_float((kb & 0x80000000u) ? (kb & 0x7fffffffu) : ~kb);
             const size_t at = size_t(T.row0 + (row & 15)) * a.k + j;
-            a.tok[at] = best != 0ull ? int(0xffffffffu - uint32_t(best & 0xffffffffull)) : -1;
-            a.prob[at] = best != 0ull ? __expf(logit - lse) : 0.f;
+            const bool is = best != 0ull && !bad_layout;
+            a.tok[at] = is ? int(0xffffffffu - uint32_t(best & 0xffffffffull)) : -1;
+            a.prob[at] = is ? __expf(logit - lse) : 0.f;
         }
         prev = best;
     }

@@ -1859,6 +1859,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         // Rows are merged by one workgroup each: thread t holds workgroup t's sorted list of topk keys (in
         // sixteen places) for the row and its (max, sum) pair; the log-sum-exp folds the pairs, then k rounds of
         // "largest list head in the workgroup" emit the row's k best tokens with their probabilities.
+        const bool bad_layout = a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.grid);  // no token then, as behind the last one
         for (int m = wg; m < a.r; m += nwg) {
             unsigned long long mine[16];
             float pm = -1e30f, ps = 0.f;
@@ -1906,8 +1907,9 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
                 if (tid == 0) {
                     const uint32_t kb = uint32_t(best >> 32);
                     const float logit = __uint_as_float((kb & 0x80000000u) ? (kb & 0x7fffffffu) : ~kb);
-                    a.topk_tok[m * a.topk + j] = best != 0ull ? int(0xffffffffu - uint32_t(best & 0xffffffffull)) : -1;
-                    a.topk_prob[m * a.topk + j] = best != 0ull ? __expf(logit - lse) : 0.f;
+                    const bool is = best != 0ull && !bad_layout;
+                    a.topk_tok[m * a.topk + j] = is ? int(0xffffffffu - uint32_t(best & 0xffffffffull)) : -1;
+                    a.topk_prob[m * a.topk + j] = is ? __expf(logit - lse) : 0.f;
                 }
             }
             cbar(sm, cgen);

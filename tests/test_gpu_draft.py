@@ -322,6 +322,34 @@ def _level_twice(shape, seed, ctx_len, first, n, k, lanes):
     return tgts, want, toks, rows, mask_base, pieces
 
 
+def _forward_level(route, tgt, blob, toks, rows, mask_base, first, n, k, per=None):
+    """A level behind 70 tokens by the entry points themselves, one call after the other."""
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd.runtime import level_pieces
+
+    dev, words = tgt.device, len(rows[0])
+    tok = torch.tensor(toks, dtype=torch.int32, device=dev)
+    pos = torch.full((n,), 71, dtype=torch.int32, device=dev)
+    mask = torch.tensor([[w - (1 << 32) if w >= 1 << 31 else w for w in row] for row in rows], dtype=torch.int32, device=dev)
+    tk = torch.full((n, k), -7, dtype=torch.int32, device=dev)
+    tp = torch.full((n, k), -7.0, dtype=torch.float32, device=dev)
+    args = lambda a: card.CardTreeRows(tok[a:].data_ptr(), pos[a:].data_ptr(), first + a, mask[a:].data_ptr(), words, mask_base)  # noqa: E731
+    pieces = level_pieces(n, 2)
+    if route == "one pass":
+        ws = torch.empty(card.card_level_workspace_bytes(tgt.cfg), dtype=torch.uint8, device=dev).fill_(0xFF)
+        assert card.card_draft_level_wide(tgt.cfg, blob, tgt.kv(-1), 70, args(0), n, per or max(16, pieces[0][1]), k, ws, tgt._stream(),
+                                          tk, tp) == card.CARD_OK
+    elif route == "call":
+        assert card.card_draft_level(tgt.cfg, blob, tgt.kv(-1), 70, args(0), n, k, tgt.workspace, tgt._stream(), tk, tp,
+                                     None) == card.CARD_OK
+    else:
+        for a, b in pieces:
+            assert card.card_draft_level_piece(tgt.cfg, blob, tgt.kv(-1), 70, args(a), b - a, first, first + n, k, tgt.workspace,
+                                               tgt._stream(), tk[a:b], tp[a:b], None) == card.CARD_OK
+    torch.cuda.synchronize()
+    return tk.cpu(), tp.cpu()
+
+
 def _same_level(tgts, want, got, shape, first, n):
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
     end = (first + n + 15) // 16 * 16
@@ -389,6 +417,24 @@ def test_lanes_are_refused_where_no_share_of_the_gpu_was_given():
 
     with pytest.raises(ValueError):  # (a small model's own choice of a grid is no such share)
         card.Target(TINY, 128).enable_lanes(2)
+
+
+@pytest.mark.parametrize("n", [5, 12, 32, 100])
+def test_draft_calls_give_no_candidates_for_weights_packed_for_another_grid(n):
+    """As a verification step reports it: a level in one call (up to 32 rows), in pieces, in one pass."""
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd.synthetic import load_synthetic_weights
+
+    tgts, want, toks, rows, mask_base, _ = _level_twice(MID, 27, 70, 80, n, 5, 2)
+    tgt, other = tgts[1], card.Target(MID, 320, grid_wgs=128)
+    load_synthetic_weights(other, MID, 27, 0.2)
+    for route in ("call", "pieces", "one pass")[n > 32:]:
+        tk, tp = _forward_level(route, tgt, other.packed, toks, rows, mask_base, 80, n, 5)
+        assert (tk == -1).all() and (tp == 0).all()
+        tk, tp = _forward_level(route, tgt, tgt.packed, toks, rows, mask_base, 80, n, 5)
+        assert (tk >= 0).all() and (tp > 0).all()
+        if route == "pieces":
+            assert torch.equal(tk, want[0]) and torch.equal(tp, want[1])
 
 
 def test_a_wide_level_with_a_refused_piece_leaves_nothing_running():
