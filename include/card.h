@@ -359,8 +359,8 @@ int card_cache_read_level(const card_cache* c, int32_t level, int32_t* tokens, i
  *
  * card_draft_level_wide: a level of any width in one call, the weights streamed once per 128 rows instead of
  * once per call.  Same results, bit for bit, as card_draft_level_piece calls of rows_per_call rows each (the last
- * may be shorter; 8 < rows_per_call <= max_r), whose errors it reports before anything is enqueued.  It spreads over all
- * compute units that are free, whatever grid_wgs says.  workspace_dev: card_level_workspace_bytes, aligned to 16 bytes, no
+ * may be shorter; 8 < rows_per_call <= max_r), whose errors it reports before anything is enqueued.  Its kernels spread
+ * over all compute units, whatever grid_wgs says: a verification step that starts meanwhile gets its workgroups only as these end.  workspace_dev: card_level_workspace_bytes, aligned to 16 bytes, no
  * preparation; not shared with a call that may run at the same time.
  *
  * card_cache_select, eqs. (3)-(7): scores every (parent i, its j-th token) pair

@@ -20,7 +20,10 @@ def make_cfg(shape, max_ctx: int, max_r: int = 32, grid_wgs: int = 0) -> B.CardM
 # (2 layers of 256 columns: 144 / 167); 33 tokens: 1367 / 2128, 4587 / 6879, 4442 / 6924, 3562 / 5872 (147 / 315).
 PROMPT_MIN_TOKENS = 33
 
-# Levels of more rows than this go through card_draft_level_wide instead of calls side by side.
+# Levels of more rows than this go through card_draft_level_wide instead of calls side by side, where the lanes have the whole
+# GPU: whatever takes more than one call on one lane.  us in one pass / side by side on two lanes, 1024 tokens: 1B shape 33 rows 1543 / 1725, 48 rows
+# 1611 / 1708, 64 rows 1616 / 1787, 100 rows 1781 / 3358; 33 rows of 8 layers of the 8B shape 1479 / 2198, of the 7B shape 1657 / 2379, of 3 layers of
+# 70B 1681 / 2900; 1B shape on four lanes 33 rows 1562 / 2220, 64 rows 1642 / 4144.
 LEVEL_ONE_PASS_ROWS = 32
 
 _LANE_STREAMS: Dict[str, list] = {}
@@ -157,7 +160,9 @@ class Target:
     def enable_lanes(self, lanes: int) -> None:
         """Prepare `lanes` workspaces and streams for draft_level_wide.  The model must have been
         created with grid_wgs set so that lanes * grid_wgs workgroups fit the GPU: every call of a
-        level then runs on its own share of the compute units."""
+        level then runs on its own share of the compute units, and other kernels may run on what the lanes
+        leave.  Where they leave nothing, wide levels may also go through card_draft_level_wide, whose kernels
+        spread over the whole GPU: its workspace is taken here."""
         cus = torch.cuda.get_device_properties(self.device).multi_processor_count
         if self.cfg.grid_wgs <= 0 or lanes * self.cfg.grid_wgs > cus:
             raise ValueError("lanes * grid_wgs must fit the compute units")
@@ -167,16 +172,18 @@ class Target:
             _check(B.card_workspace_init(self.cfg, ws, self._stream()), "card_workspace_init")
             self._lane_ws.append(ws)
         self._lane_streams = _lane_streams(self.device, lanes)
-        try:
-            self._level_ws = torch.empty(B.card_level_workspace_bytes(self.cfg), dtype=torch.uint8, device=self.device)
-        except torch.cuda.OutOfMemoryError:  # a full device: levels go through calls side by side
-            self._level_ws = None
+        self._level_ws = None
+        if lanes * self.cfg.grid_wgs == cus:
+            try:
+                self._level_ws = torch.empty(B.card_level_workspace_bytes(self.cfg), dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:  # a full device: levels go through calls side by side
+                pass
         torch.cuda.current_stream(self.device).synchronize()
 
     def draft_level_wide(self, ctx_len: int, tokens: Sequence[int], positions: Sequence[int], first_slot: int,
                          mask_rows: Sequence[Sequence[int]], mask_base: int, k: int) -> Dict:
-        """card_draft_level for a level of any width: in one pass over the weights (card_draft_level_wide), or, where one round of
-        calls side by side holds it, the rows are cut into calls of at most 32, `lanes`
+        """card_draft_level for a level of any width.  More than 32 rows of a model whose lanes have all compute units go in one
+        pass over the weights (card_draft_level_wide).  Else the rows are cut into calls of at most 32, `lanes`
         of them at a time enqueued side by side, each on its own stream with its own workspace
         (peers of a level never see each other, so the calls are independent; they share the weights
         and the KV cache and write different slots, of the same page too where a call ends inside one:

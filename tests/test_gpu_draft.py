@@ -412,6 +412,20 @@ def test_one_pass_over_a_wide_level_equals_its_calls(shape, first, n, lanes, k):
     _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), shape, first, n)
 
 
+@pytest.mark.parametrize("lanes", [2, 3, 4])
+def test_a_wide_level_keeps_to_the_compute_units_of_its_lanes(lanes, monkeypatch):
+    """The pass whose kernels spread over the whole GPU is taken only where the lanes (of 64 workgroups) have all of it."""
+    from paper_2508_04462_amd import binding
+
+    tgts, want, toks, rows, mask_base, _ = _level_twice(MID, 28, 70, 80, 100, 5, lanes)
+    one_pass, calls = binding.card_draft_level_wide, []
+    monkeypatch.setattr(binding, "card_draft_level_wide", lambda *a: calls.append(1) or one_pass(*a))
+    res = tgts[1].draft_level_wide(70, toks, [71] * 100, 80, rows, mask_base, 5)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert len(calls) == (1 if lanes * 64 == cus else 0)
+    _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), MID, 80, 100)
+
+
 def test_lanes_are_refused_where_no_share_of_the_gpu_was_given():
     import paper_2508_04462_amd as card
 
