@@ -264,6 +264,7 @@ def test_a_wide_level_in_calls_side_by_side_equals_the_calls_one_after_the_other
     tgt = card.Target(shape, 320, max_r=32, grid_wgs=64)
     load_synthetic_weights(tgt, shape, seed, 0.2)
     tgt.enable_lanes(4)
+    tgt._level_ws = None  # (no room for the one-pass route's workspace)
     ctx = ci.uniform_tokens(seed, "ctx_tokens", 0, ctx_len, shape.vocab).tolist()
     tgt.prefill(ctx)
     rng = np.random.default_rng(seed)
@@ -291,10 +292,10 @@ def test_a_wide_level_in_calls_side_by_side_equals_the_calls_one_after_the_other
     assert (out["wide"][0] >= 0).all()
 
 
-def _level_twice(shape, seed, ctx_len, first, n, k, lanes):
+def _level_twice(shape, seed, ctx_len, first, n, k, lanes, grid=64, per=None):
     """Roots from the last page in use on, and a level of n nodes behind them from slot `first`, on two models with the same weights whose pools
-    start as 0xFF bytes (NaN patterns): forwarded in a row on the first; -> both models, the row call's results, and the
-    level's arguments."""
+    start as 0xFF bytes (NaN patterns): forwarded in a row on the first, in calls of `per` rows or as `lanes` lanes would cut it; -> both
+    models, the row call's results, and the level's arguments."""
     import paper_2508_04462_amd as card
     from paper_2508_04462_amd.runtime import level_pieces
     from paper_2508_04462_amd.synthetic import load_synthetic_weights
@@ -309,14 +310,18 @@ def _level_twice(shape, seed, ctx_len, first, n, k, lanes):
     assert st == card.CARD_OK
     tgts = []
     for _ in range(2):
-        tgt = card.Target(shape, 320, max_r=32, grid_wgs=64, pool_fill=0xFF)
-        load_synthetic_weights(tgt, shape, seed, 0.2)
-        tgt.enable_lanes(lanes)
+        tgt = card.Target(shape, 320, max_r=32, grid_wgs=grid, pool_fill=0xFF)
+        if tgts:
+            tgt.packed.copy_(tgts[0].packed)
+        else:
+            load_synthetic_weights(tgt, shape, seed, 0.2)
+        if lanes:
+            tgt.enable_lanes(lanes)
         tgt.prefill(ctx)
         tgt.draft_level(ctx_len, list(range(5, 5 + roots)), [ctx_len] * roots, base, root_rows, mask_base, k)
         tgts.append(tgt)
     toks = ci.uniform_tokens(seed, "ctx_tokens", 1, n, shape.vocab).tolist()
-    pieces = level_pieces(n, lanes)
+    pieces = [(a, min(n, a + per)) for a in range(0, n, per)] if per else level_pieces(n, lanes)
     parts = [tgts[0].draft_level(ctx_len, toks[a:b], [ctx_len + 1] * (b - a), first + a, rows[a:b], mask_base, k) for a, b in pieces]
     want = tuple(torch.cat([p[key].cpu() for p in parts]) for key in ("topk_tokens", "topk_probs"))
     return tgts, want, toks, rows, mask_base, pieces
@@ -388,11 +393,14 @@ def test_pieces_of_a_level_in_any_order(shape, first, n):
     _same_level(tgts, want, (tk.cpu(), tp.cpu()), shape, first, n)
 
 
-@pytest.mark.parametrize("lanes", [2, 4])
+@pytest.mark.parametrize("lanes,one_pass", [(2, False), (4, False), (4, True)])
 @pytest.mark.parametrize("first,n", LEVELS)
-def test_a_wide_level_from_any_slot_leaves_what_calls_in_a_row_leave(first, n, lanes):
-    """Pieces side by side that share a page, on pools that nobody has written these slots of before."""
+def test_a_wide_level_from_any_slot_leaves_what_calls_in_a_row_leave(first, n, lanes, one_pass):
+    """Pieces side by side that share a page, and one pass (more than 32 rows), on pools that nobody has written these slots of before."""
     tgts, want, toks, rows, mask_base, _ = _level_twice(MID, 24, 70, first, n, 5, lanes)
+    assert (tgts[1]._level_ws is not None) == (lanes == 4)
+    if not one_pass:
+        tgts[1]._level_ws = None
     res = tgts[1].draft_level_wide(70, toks, [71] * n, first, rows, mask_base, 5)
     _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), MID, first, n)
 
@@ -403,13 +411,8 @@ def test_a_wide_level_from_any_slot_leaves_what_calls_in_a_row_leave(first, n, l
                                                    (MID, 95, 33, 3, 5)])
 def test_one_pass_over_a_wide_level_equals_its_calls(shape, first, n, lanes, k):
     tgts, want, toks, rows, mask_base, pieces = _level_twice(shape, 26, 70, first, n, k, lanes)
-    assert pieces[0][1] > 8
-    res = tgts[1].draft_level_wide(70, toks, [71] * n, first, rows, mask_base, k)
-    _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), shape, first, n)
-    # side by side, where there is no room for the pass's workspace: the same
-    tgts[1]._level_ws = None
-    res = tgts[1].draft_level_wide(70, toks, [71] * n, first, rows, mask_base, k)
-    _same_level(tgts, want, (res["topk_tokens"].cpu(), res["topk_probs"].cpu()), shape, first, n)
+    got = _forward_level("one pass", tgts[1], tgts[1].packed, toks, rows, mask_base, first, n, k, pieces[0][1])
+    _same_level(tgts, want, got, shape, first, n)
 
 
 @pytest.mark.parametrize("lanes", [2, 3, 4])
@@ -456,7 +459,7 @@ def test_a_wide_level_with_a_refused_piece_leaves_nothing_running():
     import paper_2508_04462_amd as card
 
     tgts, _, toks, rows, mask_base, pieces = _level_twice(MID, 25, 70, 80, 100, 5, 2)
-    assert len(pieces) == 4
+    assert len(pieces) == 4 and tgts[1]._level_ws is None  # (side by side: one pass is refused before anything runs)
     short = [row[:3] for row in rows]  # 96 slots from mask_base = 64: the last pieces' lie behind them
     with pytest.raises(card.CardError) as e:
         tgts[1].draft_level_wide(70, toks, [71] * 100, 80, short, mask_base, 5)
