@@ -415,6 +415,28 @@ def test_one_pass_over_a_wide_level_equals_its_calls(shape, first, n, lanes, k):
     _same_level(tgts, want, got, shape, first, n)
 
 
+# Every tile choice of the pass's products, and vocabularies of many tiles per lane.  Weight tiles x row tiles per wavefront of QKV | O and
+# down | gate/up | vocabulary:
+WIDTHS = [
+    ("llama1b", 2, 100, 32, 8, 128),   # 2x2 | 1x2 | 1x4 | 2x8, the last call of four rows
+    ("llama1b", 1, 28, 24, 16, 48),    # 1x2 | 1x2 | 1x4 | 2x4, four rows; 41 tiles per lane: more columns than the top-k keeps in registers
+    ("llama8b", 2, 100, 32, 8, 256),   # 1x2 | 2x2 | 2x4 | 2x8, four rows
+    ("llama8b", 1, 60, 32, 3, 128),    # 2x2 | 1x2 | 1x4 | 2x4
+    ("qwen7b", 2, 53, 24, 8, 128),     # 2x2 | 2x2 | 2x8 | 2x8, five rows
+    ("qwen7b", 1, 32, 24, 1, 200),     # 2x2 | 1x2 | 2x4 | 2x4, eight rows
+    ("llama70b", 1, 114, 32, 5, 256),  # 1x2 | 2x2 | 2x8 | 2x8, the last call of 18
+]
+
+
+@pytest.mark.parametrize("model,layers,n,per,k,grid", WIDTHS, ids=[f"{w[0]}-{w[2]}" for w in WIDTHS])
+def test_one_pass_over_a_wide_level_of_real_widths_equals_its_calls(model, layers, n, per, k, grid):
+    shape, first = ci.SHAPES[model].with_layers(layers), 85
+    tgts, want, toks, rows, mask_base, _ = _level_twice(shape, 29, 70, first, n, k, 0, grid, per)
+    got = _forward_level("one pass", tgts[1], tgts[1].packed, toks, rows, mask_base, first, n, k, per)
+    assert (got[0] >= 0).all()
+    _same_level(tgts, want, got, shape, first, n)
+
+
 @pytest.mark.parametrize("lanes", [2, 3, 4])
 def test_a_wide_level_keeps_to_the_compute_units_of_its_lanes(lanes, monkeypatch):
     """The pass whose kernels spread over the whole GPU is taken only where the lanes (of 64 workgroups) have all of it."""
