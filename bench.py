@@ -437,7 +437,8 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
     1B-shaped draft on the whole GPU builds cache levels of K = 100 nodes, top-8 per node, below a
     root behind 1024 tokens of context.  A level is forwarded in ceil(K / 32) calls of the
     draft-mode kernel (tree positions, slots, ancestor mask; per-row top-k and log-sum-exp fused
-    into the vocabulary phase), then card_cache_select takes the global top-K of the K * k path
+    into the vocabulary phase) or, lanes > 1, as draft_level_wide forwards it on that many lanes: in one pass
+    over the weights per 128 rows; then card_cache_select takes the global top-K of the K * k path
     scores.  Timed: level 2 onwards (parents spread over the level above), host synchronisation
     after every call included.  probe_levels > 0: no timing, that many levels (for counter runs)."""
     import numpy as np
@@ -445,13 +446,14 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
 
     import card_inputs as ci
     import paper_2508_04462_amd as card
+    from paper_2508_04462_amd.runtime import level_pieces
     from paper_2508_04462_amd.synthetic import load_synthetic_weights
 
     shape = ci.ModelShape("tiny-draft", 1, 128, 2, 1, 64, 344, 1024) if quick else ci.SHAPES["llama1b"]
     ctx_len, K, k = (64, 40, 4) if quick else (1024, 100, 8)
-    n_levels = probe_levels if probe_levels else (2 if quick else 4)
+    n_levels = probe_levels if probe_levels else 4  # (from the third on of K nodes)
     grid = 0
-    if lanes > 1:  # the calls of a level side by side, each on its share of the compute units
+    if lanes > 1:  # the lanes have all compute units
         grid = torch.cuda.get_device_properties(0).multi_processor_count // lanes // 8 * 8
     dr = card.Target(shape, ctx_len + 16 + K * (n_levels + 1) + 64, max_r=32, grid_wgs=grid)
     load_synthetic_weights(dr, shape, args.seed + 100)
@@ -470,17 +472,14 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
         n = len(tokens)
         tk = torch.empty((n, k), dtype=torch.int32, device=dev)
         tp = torch.empty((n, k), dtype=torch.float32, device=dev)
-        calls = 0
         if lanes > 1 and n > 1:
             res = dr.draft_level_wide(ctx_len, tokens, [position] * n, first, rows, mask_base, k)
             tk, tp = res["topk_tokens"], res["topk_probs"]
-            calls = (n + 31) // 32
         else:
             for c0 in range(0, n, 32):
                 c1 = min(n, c0 + 32)
                 res = dr.draft_level(ctx_len, tokens[c0:c1], [position] * (c1 - c0), first + c0, rows[c0:c1], mask_base, k)
                 tk[c0:c1], tp[c0:c1] = res["topk_tokens"], res["topk_probs"]
-                calls += 1
         ot = torch.empty(K, dtype=torch.int32, device=dev)
         os_ = torch.empty(K, dtype=torch.float32, device=dev)
         op = torch.empty(K, dtype=torch.int32, device=dev)
@@ -488,20 +487,20 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
         if cnt < 0:
             raise card.CardError(cnt, "card_cache_select")
         torch.cuda.synchronize()
-        return rows, ot[:cnt].tolist(), op[:cnt].tolist(), os_[:cnt].clone(), calls
+        return rows, ot[:cnt].tolist(), op[:cnt].tolist(), os_[:cnt].clone()
 
     # level 0: the root alone; its children are level 1
-    rows, toks, pars, sigma, _ = forward([root], [-1], None, ctx_len, ctx_len, torch.ones(1, dtype=torch.float32, device=dev))
-    first, times, calls = ctx_len + 1, [], 0
+    rows, toks, pars, sigma = forward([root], [-1], None, ctx_len, ctx_len, torch.ones(1, dtype=torch.float32, device=dev))
+    first, times = ctx_len + 1, []
     for l in range(1, n_levels + 1):
         t0 = time.perf_counter()
-        rows, ntoks, npars, nsigma, c = forward(toks, pars, rows, first, ctx_len + l, sigma)
+        rows, ntoks, npars, nsigma = forward(toks, pars, rows, first, ctx_len + l, sigma)
         if l >= 2 or n_levels == 1:
             times.append((time.perf_counter() - t0) * 1e3)
-            calls = c
         first += len(toks)
         n_nodes = len(toks)
         toks, pars, sigma = ntoks, npars, nsigma
+    one_pass = lanes > 1 and dr.level_in_one_pass(n_nodes)
     dr = None
     gc.collect()
     torch.cuda.empty_cache()
@@ -509,11 +508,23 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
         return {"draft_probe": True, "levels": n_levels, "K": K, "k": k}
     ms = float(np.median(times))
     params = shape.streamed_weight_bytes() // 2
-    rows_issued = 32 * (n_nodes // 32) + (0 if n_nodes % 32 == 0 else (8 if n_nodes % 32 <= 8 else 16 if n_nodes % 32 <= 16 else 32))
-    return {"kind": "draft_level", "draft": shape.name, "ctx": ctx_len, "K": n_nodes, "k": k, "calls_per_level": calls,
-            "calls_side_by_side": lanes, "workgroups_per_call": grid if grid else "all compute units",
-            "ms_per_level": ms, "ms_per_call": ms / calls, "nodes_per_s": n_nodes / (ms * 1e-3),
-            "hbm_frac": calls * (shape.streamed_weight_bytes() + shape.kv_bytes(ctx_len)) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+    calls = [b - a for a, b in level_pieces(n_nodes, lanes)] if lanes > 1 else [min(32, n_nodes - a) for a in range(0, n_nodes, 32)]
+    if one_pass:
+        # whole calls of the cut that the pass reproduces, eight tiles of 16 rows per pass over the weights
+        tiles = [(r + 15) // 16 for r in calls]
+        streams, room = 0, 0
+        for t in tiles:
+            if t > room:
+                streams, room = streams + 1, 8
+            room -= t
+        rows_issued = 16 * sum(tiles)
+    else:
+        streams = len(calls)
+        rows_issued = sum(8 if r <= 8 else 16 if r <= 16 else 32 for r in calls)
+    how = {"route": "one pass" if one_pass else "calls", "lanes": lanes, "weight_streams_per_level": streams}
+    return {"kind": "draft_level", "draft": shape.name, "ctx": ctx_len, "K": n_nodes, "k": k, **how,
+            "ms_per_level": ms, "nodes_per_s": n_nodes / (ms * 1e-3),
+            "hbm_frac": streams * (shape.streamed_weight_bytes() + shape.kv_bytes(ctx_len)) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             # matrix-pipe work issued: two instructions (high and low activation halves) per weight
             # fragment and 16-row tile, padded rows included, against the dense bf16 peak
             "mfma_tflops_issued": 2 * 2 * rows_issued * params / (ms * 1e-3) / 1e12,
@@ -556,7 +567,7 @@ def run_sweep(args, rig8b):
         section("cache loop", lambda: out.append(cache_loop(rig8b, 8, 0.6, 16)))
         section("concurrent loop", lambda: out.extend(concurrent_loop_entries(args, state["decode_tps"], True)))
         section("draft level", lambda: out.append(draft_level_entry(args, True)))
-        section("draft level, two calls side by side", lambda: out.append(draft_level_entry(args, True, lanes=2)))
+        section("draft level, two lanes", lambda: out.append(draft_level_entry(args, True, lanes=2)))
         return out
     rig8b.close()
 
@@ -597,7 +608,7 @@ def run_sweep(args, rig8b):
     section("llama70b r sweep", llama70b)
     section("concurrent loop", lambda: out.extend(concurrent_loop_entries(args, state["decode_tps"], False)))
     section("draft level", lambda: out.append(draft_level_entry(args, False)))
-    section("draft level, two calls side by side", lambda: out.append(draft_level_entry(args, False, lanes=2)))
+    section("draft level, two lanes", lambda: out.append(draft_level_entry(args, False, lanes=2)))
     return out
 
 

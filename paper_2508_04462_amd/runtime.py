@@ -180,6 +180,10 @@ class Target:
                 pass
         torch.cuda.current_stream(self.device).synchronize()
 
+    def level_in_one_pass(self, n: int) -> bool:
+        """Whether draft_level_wide forwards n nodes in one pass over the weights (else in calls side by side)."""
+        return n > LEVEL_ONE_PASS_ROWS and level_pieces(n, len(self._lane_ws))[0][1] > 8 and self._level_ws is not None
+
     def draft_level_wide(self, ctx_len: int, tokens: Sequence[int], positions: Sequence[int], first_slot: int,
                          mask_rows: Sequence[Sequence[int]], mask_base: int, k: int) -> Dict:
         """card_draft_level for a level of any width.  More than 32 rows of a model whose lanes have all compute units go in one
@@ -199,7 +203,7 @@ class Target:
         tp = torch.zeros((n, k), dtype=torch.float32, device=dev)
         cur = torch.cuda.current_stream(dev)
         pieces = level_pieces(n, lanes)
-        if n > LEVEL_ONE_PASS_ROWS and pieces[0][1] > 8 and self._level_ws is not None:
+        if self.level_in_one_pass(n):
             rows = B.CardTreeRows(tok.data_ptr(), pos.data_ptr(), int(first_slot), mask.data_ptr(), words, int(mask_base))
             _check(B.card_draft_level_wide(self.cfg, self.packed, self.kv(-1), ctx_len, rows, n, pieces[0][1], k, self._level_ws,
                                            cur.cuda_stream, tk, tp), "card_draft_level_wide")

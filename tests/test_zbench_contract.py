@@ -51,8 +51,13 @@ def test_short_run_prints_one_json_line_with_the_contract_fields(monkeypatch, ca
     assert conc and all("error" in e or (e["text_equals_plain_decode"] and e["accepted_tokens_per_s"] > 0) for e in conc)
     pts = [e for e in pts if e.get("kind") != "concurrent_loop"]
     dl = [e for e in sw if e.get("kind") == "draft_level"]
-    assert len(dl) == 2 and all(e["ms_per_level"] > 0 and e["calls_per_level"] == (e["K"] + 31) // 32 for e in dl)
-    assert sorted(e["calls_side_by_side"] for e in dl) == [1, 2]
+    assert len(dl) == 2 and all(e["ms_per_level"] > 0 and e["K"] == 40 for e in dl)
+    # the weights are streamed once per call of 32 rows, and once by the pass; the fractions of the peaks are of what was moved and issued
+    assert [(e["route"], e["lanes"], e["weight_streams_per_level"]) for e in dl] == [("calls", 1, 2), ("one pass", 2, 1)]
+    per_stream = [e["hbm_frac"] * e["ms_per_level"] / e["weight_streams_per_level"] for e in dl]
+    assert abs(per_stream[0] - per_stream[1]) <= 1e-9 * per_stream[0]
+    issued = [e["mfma_tflops_issued"] / e["model_tflops"] * e["K"] / 2 for e in dl]  # rows
+    assert [round(i, 6) for i in issued] == [32 + 8, 16 + 16 + 16]  # calls of 32 and 8 rows; tiles of calls of 24 and 16 rows
     loops = [e for e in sw if e.get("kind") == "cache_loop"]
     assert loops and all("error" in e or (e["accepted_tokens_per_s"] > 0 and 1.0 <= e["mean_accepted_len"] <= e["r"])
                          for e in loops)
