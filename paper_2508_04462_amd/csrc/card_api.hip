@@ -359,7 +359,7 @@ PromptPlan prompt_plan(int Nt, int Ks, int mts, bool swiglu) {
 }
 
 struct PromptLayout {
-    size_t x, xf, ss, att, act, q, rope, best, part, bytes;
+    size_t x, xf, ss, att, act, q, rope, best, part;  // part: the last one, of prompt_part_bytes
     int mcap, groups;
 };
 PromptLayout prompt_layout(const card_model_cfg* cfg, const Layout& L, int rows) {
@@ -381,15 +381,18 @@ PromptLayout prompt_layout(const card_model_cfg* cfg, const Layout& L, int rows)
     p.q = take(cap * cfg->n_q_heads * h * 4);
     p.rope = take(cap * h * 4);
     p.best = take(8);
+    p.part = w;
+    return p;
+}
+// Room for the partial products of up to mcap row tiles (256 plans per 1024 rows: for the size query, not for each prompt).
+size_t prompt_part_bytes(const Layout& L, int mcap) {
     size_t part = 0;
-    for (int m = 1; m <= p.mcap; ++m)
+    for (int m = 1; m <= mcap; ++m)
         for (const MatDesc* d : {&L.qkv, &L.wo, &L.gu, &L.wd}) {
             const int s = prompt_plan(d->Nt, d->Ks, m, d == &L.gu).splits;
             if (d != &L.gu || s > 1) part = std::max(part, size_t(s) * d->Nt * m * 1024);
         }
-    p.part = take(part);
-    p.bytes = w;
-    return p;
+    return part;
 }
 
 // The product of the row tiles [g.mt0, g.mts).
@@ -938,7 +941,8 @@ int card_verify_debug_logits(const card_model_cfg* cfg, const void* packed_weigh
 size_t card_prompt_workspace_bytes(const card_model_cfg* cfg, int32_t rows) {
     const Layout L = make_layout(cfg);
     if (!L.ok || rows < 1) return 0;
-    return prompt_layout(cfg, L, std::min(rows, kPromptMaxRows)).bytes;
+    const PromptLayout P = prompt_layout(cfg, L, std::min(rows, kPromptMaxRows));
+    return align_up(P.part + prompt_part_bytes(L, P.mcap), 1024);
 }
 
 int card_prompt(const card_model_cfg* cfg, const void* packed_weights_dev, const card_kv* kv, int32_t ctx_len,
