@@ -88,7 +88,9 @@ def phase_timeline(rig, ctx, r, cand, layer):
         out["phases"][n] = round(float(np.median(t[:, i + 1] - t[:, i])), 2)
         out["boundary_spread"][n] = round(float(t[:, i + 1].max() - t[:, i + 1].min()), 2)
     out["layer_total"] = round(float(np.median(t[:, 10] - t[:, 0])), 2)
+    whole = t
     for tag, s0 in (("qkv", 21), ("o_proj", 24), ("down", 27)):
+        t = whole[whole[:, s0 + 1] > 0]  # (workgroups with a tile)
         d = {"first_activations_after": round(float(np.median(t[:, s0] - t[:, {21: 0, 24: 4, 27: 8}[s0]])), 2),
              "k_loop": round(float(np.median(t[:, s0 + 1] - t[:, s0])), 2)}
         if s0 != 27:
@@ -98,7 +100,7 @@ def phase_timeline(rig, ctx, r, cand, layer):
             d["of_which_page_preload_issue"] = round(float(np.median(t[:, 16] - t[:, 11])), 2)
             d["stores_acknowledged_after"] = round(float(np.median(t[:, 12] - t[:, 1])), 2)
         out[tag + "_detail"] = d
-    att = t[t[:, 13] > 0]
+    att = whole[whole[:, 13] > 0]
     if len(att):
         out["attention_detail"] = {
             "workgroups_with_a_task": int(len(att)),

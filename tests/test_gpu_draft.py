@@ -425,6 +425,7 @@ WIDTHS = [
     ("qwen7b", 2, 53, 24, 8, 128),     # 2x2 | 2x2 | 2x8 | 2x8, five rows
     ("qwen7b", 1, 32, 24, 1, 200),     # 2x2 | 1x2 | 2x4 | 2x4, eight rows
     ("llama70b", 1, 114, 32, 5, 256),  # 1x2 | 2x2 | 2x8 | 2x8, the last call of 18
+    ("tiny", 2, 53, 24, 6, 256),       # 1x2 | 1x2 | 1x4 | 1x4; calls that leave out the workgroups without work
 ]
 
 

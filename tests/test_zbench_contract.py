@@ -78,3 +78,5 @@ def test_timeline_probe_reports_the_ten_phases_of_a_layer(monkeypatch, capsys):
     assert all(v >= 0 for v in t["phases"].values())  # the stamps of a workgroup are in order
     assert 0 < t["layer_total"] < 1000 and abs(sum(t["phases"].values()) - t["layer_total"]) < 0.2 * t["layer_total"] + 1
     assert t["attention_detail"]["workgroups_with_a_task"] >= 1
+    # medians of the workgroups that have a tile (16 of them in the O-projection)
+    assert all(0 <= v < 1000 for tag in ("qkv", "o_proj", "down") for v in t[f"{tag}_detail"].values())
