@@ -31,7 +31,8 @@ __device__ __forceinline__ void split_bf16(float v, __bf16& hi, __bf16& lo) {
     hi = static_cast<__bf16>(v);
     lo = static_cast<__bf16>(v - static_cast<float>(hi));
 }
-// Rotary embedding of a pair: which product is rounded before the sum is fixed here, so that every kernel's K has the same bits.
+// Rotary embedding of a pair: which product is rounded before the sum is fixed here, so that the verify kernels and the wide levels (which
+// promise each other's bits) write the same K.  (The prompt pass sums its products in another order anyway.)
 __device__ __forceinline__ float rotate_first(float z0, float z1, float cs, float sn) { return fmaf(z0, cs, -(z1 * sn)); }
 __device__ __forceinline__ float rotate_second(float z0, float z1, float cs, float sn) { return fmaf(z1, cs, z0 * sn); }
 // Reductions over the four rows of sixteen lanes of a wavefront (lanes l, l ^ 16, l ^ 32, l ^ 48), the same in all of them: register

@@ -167,8 +167,8 @@ __device__ __forceinline__ void px_half_turn(const uint4v (&x)[KB * MT * 2][64],
 // workgroup, W = 4 with two; either way two wavefronts share a SIMD.
 // A compute unit brings in about 57 GB/s of weights (HBM) and activations (L2) together, so wide workgroups pay by what they do not
 // read again: per k-step 46 KiB for 448 matrix instructions at 8 x 7, 24 for 128 at 4 x 4.  Measured on the 8B shape, 1000 rows, us,
-// 4 x 4 / 8 x 4 / 8 x 7: gate/up 371 / 381 / 326 (1.45 PFLOP/s issued, halves counted), QKV 88 / 90 / 82, O 58 / 55 / 62, down
-// 180 / 166 / 174; with zeros as operands gate/up takes 276: the card's power.  Eight row tiles spill (383).
+// 4 x 4 / 8 x 4 / 8 x 7: gate/up 371 / 381 / 326 (1.45 PFLOP/s issued, halves counted; in other sessions 338-348), QKV 88 / 90 / 82, O 58 /
+// 55 / 62, down 180 / 166 / 174; with zeros as operands gate/up takes 276: the card's power.  Eight row tiles spill (383).
 template <int EPI, int W, int MT>
 __global__ __launch_bounds__(W * 64, 2) void k_prompt_gemm(PgemmArgs a) {
     constexpr int KB = kPgUnroll;                 // k-steps between two barriers, and in the ring of weights

@@ -16,8 +16,8 @@ def make_cfg(shape, max_ctx: int, max_r: int = 32, grid_wgs: int = 0) -> B.CardM
 
 
 # Prompts of at least this many tokens go through card_prompt: whatever takes more than one verify call.  us by
-# card_prompt / by verify calls, 20 tokens: 1B shape 1321 / 1152, 7B 4326 / 3621, 8B 4488 / 3629, 8 layers of 70B 3397 / 3009
-# (2 layers of 256 columns: 144 / 167); 33 tokens: 1367 / 2128, 4587 / 6879, 4442 / 6924, 3562 / 5872 (147 / 315).
+# card_prompt / by verify calls, 20 tokens: 1B shape 1303 / 1122, 7B 4016 / 3532, 8B 4326 / 3514, 8 layers of 70B 3236 / 2992,
+# 2 layers of 256 columns 181 / 165; 33 tokens: 1358 / 2073, 4232 / 6734, 4394 / 6749, 3355 / 5837, 174 / 295.
 PROMPT_MIN_TOKENS = 33
 
 # Levels of more rows than this go through card_draft_level_wide instead of calls side by side, where the lanes have the whole
