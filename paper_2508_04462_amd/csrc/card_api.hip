@@ -217,7 +217,7 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.F = cfg->d_ffn;
     a.V = cfg->vocab;
     a.r = r;
-    a.rp = (r + 7) / 8 * 8;
+    a.rp = r;
     a.ctx_len = ctx_len;
     a.eps = cfg->rms_eps;
     a.inv_d = 1.0f / float(cfg->d_model);
