@@ -749,16 +749,16 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
 #pragma unroll
                         for (int k = 0; k < GRP; ++k) fr[k / NB][k % NB] = __builtin_bit_cast(bf16x8, grp[k * 64]);
                     } else {
+                        // The same, slot by slot (the group wraps, or a narrow batch).  Every slot is read, needed or not: a read
+                        // under a condition and zeros where it does not hold cost 16-19 registers, which spilled in the kernels of two
+                        // row tiles (32 tree rows of the 1B shape 1278 -> 1252 us, 8B r = 5 at 32 700 tokens 671 -> 668; others within 0.6 %).
 #pragma unroll
                         for (int u = 0; u < SG; ++u)
 #pragma unroll
                             for (int i = 0; i < NB; ++i) {
-                                fr[u][i] = __builtin_bit_cast(bf16x8, uint4v{0u, 0u, 0u, 0u});
-                                if (u < nvs && i < nvalid) {
-                                    uint32_t sl = fc.pos + uint32_t(u * nvalid + i);
-                                    sl = sl >= uint32_t(kFifo) ? sl - uint32_t(kFifo) : sl;
-                                    fr[u][i] = __builtin_bit_cast(bf16x8, sm.fifo[wave][sl][lane]);
-                                }
+                                uint32_t sl = fc.pos + uint32_t(u * nvalid + i);
+                                sl = sl >= uint32_t(kFifo) ? sl - uint32_t(kFifo) : sl;
+                                fr[u][i] = __builtin_bit_cast(bf16x8, sm.fifo[wave][sl][lane]);
                             }
                     }
                     // LDS runs a wavefront's instructions in order: the slots are read before this lands
@@ -769,6 +769,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                     lds_post(&sm.head[wave], fc.head);
 #pragma unroll
                     for (int u = 0; u < SG; ++u) {
+                        if (u >= nvs) break;  // (behind the wavefront's share: neither weights nor activations)
                         const int slot = gg * SG + u;
 #pragma unroll
                         for (int i = 0; i < NB; ++i)
