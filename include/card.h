@@ -63,6 +63,11 @@ typedef struct card_model_cfg {
                          with the target: CARD Design, first paragraph).  The packed weight
                          order depends on it: pack and verify with the same value.  (Workgroups
                          of either that a small model has no work for are not launched.)      */
+    int32_t coded;    /* 1: the packed weights hold a second, coded copy of the matrices behind
+                         the first, 12 bits per weight and exact, which verification and draft
+                         calls of up to 32 rows read instead: a quarter fewer bytes per step, twice
+                         the memory (card_packed_weight_bytes).  Pack and call with the same
+                         value, or call with 0 on weights packed with 1.  0: no such copy         */
 } card_model_cfg;
 
 /* Tensors of the canonical (caller-side) weight set. Matrices are bf16, row-major

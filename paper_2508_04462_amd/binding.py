@@ -28,6 +28,7 @@ class CardModelCfg(C.Structure):
         ("n_kv_heads", C.c_int32), ("head_dim", C.c_int32), ("d_ffn", C.c_int32),
         ("vocab", C.c_int32), ("rope_theta", C.c_float), ("rms_eps", C.c_float),
         ("kv_block", C.c_int32), ("max_ctx", C.c_int32), ("max_r", C.c_int32), ("grid_wgs", C.c_int32),
+        ("coded", C.c_int32),
     ]
 
 

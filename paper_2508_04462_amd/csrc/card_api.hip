@@ -97,22 +97,26 @@ int grid_size(const card_model_cfg* cfg) {
 // workgroup per compute unit, so on an otherwise idle device the dispatcher places all of them.
 // Should other work hold compute units for longer than the kernel's bounded waits, the step ends
 // with accepted_len = -1 instead of hanging.
-template <int MT, int H, bool PK, bool DR, bool PC = false>
-int launch_mega(MegaArgs& a, hipStream_t st) {
+template <int MT, int H, bool PK, bool DR, bool PC, bool CODED>
+int launch_kernel(MegaArgs& a, hipStream_t st) {
     static std::atomic<int> fits[kMaxDevices];  // 0 unknown, 1 yes, -1 no
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return CARD_EDEVICE;
     int f = fits[dev].load(std::memory_order_relaxed);
     if (f == 0) {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify<MT, H, PK, DR, PC>, kBlockThreads, 0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_verify<MT, H, PK, DR, PC, CODED>, kBlockThreads, 0) != hipSuccess)
             return CARD_EDEVICE;
         f = per_cu >= 1 ? 1 : -1;
         fits[dev].store(f, std::memory_order_relaxed);
     }
     if (f < 0 || a.nwg > cu_count()) return CARD_EDEVICE;
-    hipLaunchKernelGGL((k_verify<MT, H, PK, DR, PC>), dim3(a.nwg), dim3(kBlockThreads), 0, st, a);
+    hipLaunchKernelGGL((k_verify<MT, H, PK, DR, PC, CODED>), dim3(a.nwg), dim3(kBlockThreads), 0, st, a);
     return launch_status();
+}
+template <int MT, int H, bool PK, bool DR, bool PC = false>
+int launch_mega(MegaArgs& a, hipStream_t st) {
+    return a.cbase ? launch_kernel<MT, H, PK, DR, PC, true>(a, st) : launch_kernel<MT, H, PK, DR, PC, false>(a, st);
 }
 
 // Scratch of the entry point that allocates nothing: what card_verify takes as `workspace_dev`,
@@ -236,6 +240,24 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.gu = L.gu;
     a.wd = L.wd;
     a.lm = L.lm;
+    if (cfg->coded) {
+        a.cbase = a.wbase + L.coded_off;
+        a.c_layer0_off = L.c_layer0_off;
+        a.c_layer_stride = L.c_layer_stride;
+        a.c_code_off = L.c_code_off;
+        a.c_lm_code_off = L.c_lm_code_off;
+        a.c_stamp = reinterpret_cast<const uint32_t*>(a.cbase + L.c_stamp_off);
+        const auto desc = [&](CodedDesc c, const MatDesc& m) {
+            c.fl_run = flag_run_words(m.Nt, m.Ks, m.NB, grid);
+            c.fl2_run = grouped_run_words(m.Nt, m.Ks, grid);
+            return c;
+        };
+        a.c_qkv = desc(L.c_qkv, L.qkv);
+        a.c_wo = desc(L.c_wo, L.wo);
+        a.c_gu = desc(L.c_gu, L.gu);
+        a.c_wd = desc(L.c_wd, L.wd);
+        a.c_lm = desc(L.c_lm, L.lm);
+    }
     a.kpool = static_cast<__bf16*>(kv->k_pages);
     a.vpool = static_cast<__bf16*>(kv->v_pages);
     a.pool_layer_elems = size_t(kv->n_pages) * cfg->n_kv_heads * 16 * h;
@@ -718,14 +740,16 @@ int card_weights_pack_tensor(const card_model_cfg* cfg, int32_t tensor, int32_t 
         return hipMemcpyAsync(dst, src_dev, bytes, hipMemcpyDeviceToDevice, st) == hipSuccess ? CARD_OK
                                                                                                : CARD_EDEVICE;
     };
-    auto pack = [&](char* dst, const MatDesc& m, int src_rows, int n_rows, int prow0, int map) {
+    // coded copy: of the vocabulary head or of the layer
+    char* cb = pb + L.coded_off;
+    char* clb = per_layer ? cb + L.c_layer0_off + size_t(layer) * L.c_layer_stride : cb;
+    auto pack = [&](char* dst, const MatDesc& m, int src_rows, int n_rows, int prow0, int map, const CodedDesc& c, int which) {
         PackArgs a = {};
         a.src = static_cast<const __bf16*>(src_dev);
         a.dst = reinterpret_cast<__bf16*>(dst + m.off);
         a.src_rows = src_rows;
         a.K = m.K;
         a.Ks = m.Ks;
-        a.n_rows = n_rows;
         a.prow0 = prow0;
         a.map = map;
         a.head_dim = h;
@@ -733,12 +757,28 @@ int card_weights_pack_tensor(const card_model_cfg* cfg, int32_t tensor, int32_t 
         a.NB = m.NB;
         a.nwg = grid_size(cfg);
         if (a.nwg <= 0) return int(CARD_EDEVICE);
-        // whoever verifies with these weights must run the grid they were laid out for
-        if (hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(pb + L.stamp_off), int(kStampMagic), 1, st) != hipSuccess ||
-            hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(pb + L.stamp_off + 4), a.nwg, 1, st) != hipSuccess)
-            return int(CARD_EDEVICE);
-        const int64_t total = int64_t(n_rows) * m.Ks * 4;
-        hipLaunchKernelGGL(k_pack, dim3(uint32_t((total + 255) / 256)), dim3(256), 0, st, a);
+        const bool half = map == MAP_GATE || map == MAP_UP;  // eight rows of every tile
+        a.t0 = half ? 0 : prow0 / 16;
+        a.tiles = half ? m.Nt : n_rows / 16;
+        a.stamp = reinterpret_cast<uint32_t*>(pb + L.stamp_off);
+        if (cfg->coded) {
+            uint32_t* code = reinterpret_cast<uint32_t*>(clb + (per_layer ? L.c_code_off : L.c_lm_code_off));
+            a.planes = clb + c.off;
+            a.coded_stamp = reinterpret_cast<uint32_t*>(cb + L.c_stamp_off);
+            a.fl = reinterpret_cast<unsigned long long*>(clb + (map == MAP_UP ? c.fl2 : c.fl));
+            // (only grids that can take it in groups: elsewhere a run of the grouped order has no room of its own)
+            if (tensor == CARD_T_WD && (m.Nt & 3) == 0 && ((a.nwg & 7) == 0 || m.Nt <= a.nwg))
+                a.gfl = reinterpret_cast<unsigned long long*>(clb + c.fl2);
+            a.base4 = code + which;
+            a.counts = code + kCodeCounts + 128 * which;
+        }
+        hipLaunchKernelGGL(k_pack_begin, dim3(1), dim3(128), 0, st, a);
+        if (cfg->coded) {
+            const int64_t pieces = (int64_t(src_rows) * m.K / 8 + 255) / 256;
+            hipLaunchKernelGGL(k_pack_count, dim3(uint32_t(std::min<int64_t>(pieces, 1024))), dim3(256), 0, st, a);
+            hipLaunchKernelGGL(k_pack_base, dim3(1), dim3(128), 0, st, a);
+        }
+        hipLaunchKernelGGL(k_pack, dim3(uint32_t((int64_t(a.tiles) * m.Ks + 3) / 4)), dim3(256), 0, st, a);
         return launch_status();
     };
     switch (tensor) {
@@ -746,17 +786,17 @@ int card_weights_pack_tensor(const card_model_cfg* cfg, int32_t tensor, int32_t 
         case CARD_T_G_FINAL: return copy(pb + L.g_final_off, size_t(d) * 4);
         case CARD_T_G_ATTN: return copy(lb + L.g_attn_off, size_t(d) * 4);
         case CARD_T_G_FFN: return copy(lb + L.g_ffn_off, size_t(d) * 4);
-        case CARD_T_WQ: return pack(lb, L.qkv, qd, qd, 0, MAP_ROPE);
-        case CARD_T_WK: return pack(lb, L.qkv, kvd, kvd, qd, MAP_ROPE);
-        case CARD_T_WV: return pack(lb, L.qkv, kvd, kvd, qd + kvd, MAP_IDENT);
-        case CARD_T_WO: return pack(lb, L.wo, d, L.wo.Nt * 16, 0, MAP_IDENT);
-        case CARD_T_WG: return pack(lb, L.gu, cfg->d_ffn, cfg->d_ffn, 0, MAP_GATE);
-        case CARD_T_WU: return pack(lb, L.gu, cfg->d_ffn, cfg->d_ffn, 0, MAP_UP);
-        case CARD_T_WD: return pack(lb, L.wd, d, L.wd.Nt * 16, 0, MAP_IDENT);
+        case CARD_T_WQ: return pack(lb, L.qkv, qd, qd, 0, MAP_ROPE, L.c_qkv, CT_Q);
+        case CARD_T_WK: return pack(lb, L.qkv, kvd, kvd, qd, MAP_ROPE, L.c_qkv, CT_K);
+        case CARD_T_WV: return pack(lb, L.qkv, kvd, kvd, qd + kvd, MAP_IDENT, L.c_qkv, CT_V);
+        case CARD_T_WO: return pack(lb, L.wo, d, L.wo.Nt * 16, 0, MAP_IDENT, L.c_wo, CT_O);
+        case CARD_T_WG: return pack(lb, L.gu, cfg->d_ffn, cfg->d_ffn, 0, MAP_GATE, L.c_gu, CT_G);
+        case CARD_T_WU: return pack(lb, L.gu, cfg->d_ffn, cfg->d_ffn, 0, MAP_UP, L.c_gu, CT_U);
+        case CARD_T_WD: return pack(lb, L.wd, d, L.wd.Nt * 16, 0, MAP_IDENT, L.c_wd, CT_D);
         default: {
             MatDesc m = L.lm;
             m.off = 0;
-            return pack(pb + L.lm_off, m, cfg->vocab, L.lm.Nt * 16, 0, MAP_IDENT);
+            return pack(pb + L.lm_off, m, cfg->vocab, L.lm.Nt * 16, 0, MAP_IDENT, L.c_lm, 0);
         }
     }
 }

@@ -12,6 +12,39 @@ typedef __attribute__((ext_vector_type(4))) short short4v;
 typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(4))) unsigned int uint4v;
 
+// ---- weights in three planes (CodedDesc) --------------------------------------------------------------
+// Eight weights of a lane as they are stored: low bytes, high nibbles, rest nibbles.  Bits 8-14 of a weight are (base + c) ^ (rest << 3),
+// where base + c <= 127: any value has one c and one rest.  The nibbles of weights 0-3 lie in byte i as the byte that they
+// become needs them (sign in bit 7, c in bits 0-2; rest in bits 3-6), those of weights 4-7 likewise, but four bits further left.
+__device__ __forceinline__ uint32_t rotate_right4(uint32_t v) { return __builtin_amdgcn_alignbit(v, v, 4); }
+__device__ __forceinline__ uint32_t high_bytes(uint32_t high, uint32_t rest, uint32_t base4) {
+    return ((high & 0x87878787u) + base4) ^ (rest & 0x78787878u);  // (no carry: base + c < 128)
+}
+// low bytes and high bytes of eight weights -> the weights
+__device__ __forceinline__ uint4v join_weights(uint4v v) {
+    return uint4v{__builtin_amdgcn_perm(v[2], v[0], 0x05010400u), __builtin_amdgcn_perm(v[2], v[0], 0x07030602u),
+                                             __builtin_amdgcn_perm(v[3], v[1], 0x05010400u), __builtin_amdgcn_perm(v[3], v[1], 0x07030602u)};
+}
+// {low, low, high, rest} as loaded -> the weights
+__device__ __forceinline__ uint4v decode_weights(uint4v v, uint32_t base4) {
+    return join_weights(uint4v{v[0], v[1], high_bytes(v[2], v[3], base4), high_bytes(rotate_right4(v[2]), rotate_right4(v[3]), base4)});
+}
+// and back
+__device__ __forceinline__ uint4v encode_weights(bf16x8 w, uint32_t base) {
+    const uint4v d = __builtin_bit_cast(uint4v, w);
+    uint4v out = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t x = (d[e >> 1] >> ((e & 1) * 16)) & 0xffffu, h = (x >> 8) & 127u;
+        const uint32_t c = (h - base) & 7u, rest = ((base + c) ^ h) >> 3;
+        const uint32_t hb = ((x >> 15) << 7 | c) << ((e & 3) * 8), rb = rest << ((e & 3) * 8 + 3);
+        out[e >> 2] |= (x & 255u) << ((e & 3) * 8);
+        out[2] |= e < 4 ? hb : (hb << 4 | hb >> 28);
+        out[3] |= e < 4 ? rb : (rb << 4 | rb >> 28);
+    }
+    return out;
+}
+
 // Data handed from one workgroup to another inside a kernel goes through device-scope accesses:
 // the store writes through the compute die's own L2, the load bypasses it.  (A full device fence
 // would write back and invalidate the whole L2 on every call - tens of microseconds.)

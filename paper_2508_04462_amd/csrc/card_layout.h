@@ -16,6 +16,7 @@ constexpr int kKvBlock = 16;
 constexpr int kNbQkv = 2, kNbOne = 1, kNbWide = 8;
 constexpr int kFlagCopies = 32;  // copies of the barrier flags (256 words each): pollers spread over them
 constexpr uint32_t kStampMagic = 0x43415244u;  // "CARD"
+constexpr uint32_t kCodedMagic = 0x43415245u;  // stamp of the coded copy
 constexpr uint32_t kWsMagic = 0x57534b31u;     // workspace control words initialised ("WSK1"), word kBarMagic
 // words of the barrier block: [1] exit counter, [2] error flag, [3] barrier epoch, [4] magic
 constexpr int kBarExit = 1, kBarError = 2, kBarEpoch = 3, kBarMagic = 4;
@@ -68,12 +69,77 @@ CARD_HD inline int64_t stream_frag_index(int32_t Nt, int32_t Ks, int32_t NB, int
     return r.first + int64_t(b) * NB * (r.s1 - r.s0) + int64_t(s - r.s0) * nv + i;
 }
 
+// ---- the coded copy of the matrices (card_model_cfg.coded) -----------------------------------------------
+// The verify kernel's steps are bound by the bytes of the weights, and of a bf16 weight's sixteen bits four are nearly always
+// known: weights, trained or normally distributed, spread over few exponents.  A coded matrix holds its fragments (in stream order, n = Nt * Ks of
+// them) in three planes:
+//   low  512 B at f * 512:                bits 0-7 of the lane's eight weights
+//   high 256 B at n * 512 + f * 256:      four bits each: the sign, and the low three bits c of bits 8-14 less `base`
+//   rest 256 B at n * 768 + f * 256:      four bits each: what is left of bits 8-14, zero for the weights whose
+//                                         exponent is one of the sixteen from 2 * base on
+// The base is that of the tensor, chosen when it is packed as the one that leaves out fewest weights.  The kernel reads a
+// fragment's rest only where a bit per fragment says that it holds something: 12 bits per weight instead of 16,
+// lossless, for any bit pattern.  (6 % of the fragments have a rest if the weights are normally distributed.)
+struct CodedDesc {
+    size_t off;  // of the planes, from the coded layer's base (vocabulary head: from the copy's)
+    size_t fl;   // of the bits that say which fragments have a rest, in stream order (stream_flag)
+    size_t fl2;  // gate/up: those of the up rows (`fl`: of the gate rows); down-projection: those in grouped order (grouped_flag)
+    int32_t fl_run, fl2_run;  // words of 64 bits per run (filled in for the grid in use)
+};
+// The bits in stream order: every run (pair w of position p: number 4 p + w) has its own words, every batch of a run begins with a word.
+// As the verify kernel's down-projection for more than eight rows takes them (four positions share their tiles: position 4 g + q takes
+// quarter q of K of all four, pair w the w-th quarter of that, the four tiles of a k-step in turn): "grouped".
+struct FlagPlace {
+    int64_t word;
+    int32_t bit;
+};
+CARD_HD inline int32_t flag_words(int32_t bits) { return (bits + 63) / 64; }
+CARD_HD inline int32_t flag_run_words(int32_t Nt, int32_t Ks, int32_t NB, int32_t nwg) {
+    const int32_t cnt = (Nt + nwg - 1) / nwg, wide = cnt < NB ? cnt : NB;
+    return (cnt + NB - 1) / NB * flag_words(wide * ((Ks + kStreamWaves - 1) / kStreamWaves));
+}
+CARD_HD inline int32_t grouped_run_words(int32_t Nt, int32_t Ks, int32_t nwg) {
+    const int32_t quarter = (Ks + 3) / 4, steps = (quarter + 3) / 4;
+    return (Nt + nwg - 1) / nwg * flag_words(4 * steps);
+}
+CARD_HD inline FlagPlace stream_flag(int32_t Nt, int32_t Ks, int32_t NB, int32_t nwg, int32_t t, int32_t s) {
+    const int32_t p = t % nwg, j = t / nwg;
+    int32_t w = 0;
+    while (w + 1 < kStreamWaves && s >= ((w + 1) * Ks) / kStreamWaves) ++w;
+    const StreamRun r = stream_run(Nt, Ks, nwg, p, w);
+    const int32_t b = j / NB, steps = r.s1 - r.s0, nv = r.cnt - b * NB < NB ? r.cnt - b * NB : NB;
+    const int32_t at = (s - r.s0) * nv + j % NB;
+    return {int64_t(p * kStreamWaves + w) * flag_run_words(Nt, Ks, NB, nwg) + b * flag_words(NB * steps) + at / 64, at % 64};
+}
+CARD_HD inline FlagPlace grouped_flag(int32_t Nt, int32_t Ks, int32_t nwg, int32_t t, int32_t s) {
+    const int32_t p = t % nwg, j = t / nwg;
+    int32_t q = 0, w = 0;
+    while (q < 3 && s >= ((q + 1) * Ks) / 4) ++q;
+    const int32_t q0 = (q * Ks) / 4, len = ((q + 1) * Ks) / 4 - q0;
+    while (w < 3 && s >= q0 + ((w + 1) * len) / 4) ++w;
+    const int32_t s0 = q0 + (w * len) / 4, steps = q0 + ((w + 1) * len) / 4 - s0;
+    const int32_t at = (s - s0) * 4 + (p & 3);
+    return {int64_t(((p & ~3) + q) * kStreamWaves + w) * grouped_run_words(Nt, Ks, nwg) + j * flag_words(4 * steps) + at / 64, at % 64};
+}
+// Room for them on any grid of up to 256 workgroups.  (The kernel reads a word ahead.)
+inline size_t flag_bytes(int32_t Nt, int32_t Ks, int32_t NB) {
+    const size_t steps = (Ks + kStreamWaves - 1) / kStreamWaves;
+    return (4 * ((size_t(Nt) + 256 * size_t(NB)) * steps / 64 + size_t(Nt) / NB + 520) + 8) * 8;
+}
+inline size_t grouped_bytes(int32_t Nt, int32_t Ks) { return (4 * (size_t(Nt) + 260) * ((size_t(Ks) + 15) / 16 / 16 + 2) + 8) * 8; }
+// Words of a layer's `code` block: a base per tensor (four times in its bytes), then 128 counters per tensor (packing only).
+enum CodeTensor { CT_Q = 0, CT_K = 1, CT_V = 2, CT_O = 3, CT_G = 4, CT_U = 5, CT_D = 6 };
+constexpr int kCodeCounts = 64;  // first counter (tensor i: 128 i behind it)
+
 struct Layout {
     bool ok;
     // packed weights
     size_t embed_off, lm_off, g_final_off, stamp_off, layer0_off, layer_stride, weight_bytes;
     MatDesc qkv, wo, gu, wd, lm;  // layer matrices relative to the layer base; lm absolute
     size_t g_attn_off, g_ffn_off; // relative to the layer base
+    // coded copy: where it begins in the blob (behind everything else), from there: the vocabulary head's planes and code block, the stamp, the layers
+    CodedDesc c_qkv, c_wo, c_gu, c_wd, c_lm;
+    size_t coded_off, c_stamp_off, c_lm_code_off, c_layer0_off, c_layer_stride, c_code_off;  // c_code_off: in a layer
     size_t ws_bytes;
     // workspace of the persistent kernel (byte offsets) and strides in elements
     size_t m_xres_off, m_xfrag_off, m_ss_off, m_qfrag_off, m_attfrag_off, m_actfrag_off, m_apart_off, m_bar_off,
@@ -110,6 +176,7 @@ inline bool cfg_valid(const card_model_cfg* c) {
     if (c->max_r < 1 || c->max_r > kMaxR) return false;
     if (!(c->rope_theta > 0.f) || !(c->rms_eps >= 0.f)) return false;
     if (c->grid_wgs < 0 || c->grid_wgs > 256) return false;
+    if (c->coded != 0 && c->coded != 1) return false;
     return true;
 }
 
@@ -143,6 +210,34 @@ inline Layout make_layout(const card_model_cfg* c) {
     lo = align_up(lo + size_t(d) * 4, 1024);
     L.layer_stride = lo;
     L.weight_bytes = L.layer0_off + size_t(c->n_layers) * L.layer_stride;
+    L.coded_off = align_up(L.weight_bytes, 1024);
+    {
+        size_t at = 0;
+        auto coded = [&](const MatDesc& m, int sets, bool grouped) {
+            CodedDesc c = {};
+            c.off = at;
+            at += m.bytes();
+            c.fl = at;
+            at = align_up(at + flag_bytes(m.Nt, m.Ks, m.NB), 1024);
+            c.fl2 = at;
+            if (grouped) at = align_up(at + grouped_bytes(m.Nt, m.Ks), 1024);
+            else if (sets > 1) at = align_up(at + flag_bytes(m.Nt, m.Ks, m.NB), 1024);
+            return c;
+        };
+        L.c_lm = coded(L.lm, 1, false);
+        L.c_lm_code_off = at;
+        L.c_stamp_off = at + 1024;
+        L.c_layer0_off = at + 2048;
+        at = 0;
+        L.c_qkv = coded(L.qkv, 1, false);
+        L.c_wo = coded(L.wo, 1, false);
+        L.c_gu = coded(L.gu, 2, false);
+        L.c_wd = coded(L.wd, 1, true);
+        L.c_code_off = at;
+        at = align_up(at + (kCodeCounts + 7 * 128) * 4, 1024);
+        L.c_layer_stride = at;
+        if (c->coded) L.weight_bytes = L.coded_off + L.c_layer0_off + size_t(c->n_layers) * L.c_layer_stride;
+    }
     // the kernel addresses a matrix with 32-bit byte offsets
     constexpr size_t k4G = size_t(1) << 32;
     if (L.qkv.bytes() >= k4G || L.wo.bytes() >= k4G || L.gu.bytes() >= k4G || L.wd.bytes() >= k4G || L.lm.bytes() >= k4G)

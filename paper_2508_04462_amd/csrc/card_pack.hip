@@ -5,44 +5,116 @@
 namespace card {
 
 // ------------------------------------------------------------------------------------------
-// Weight re-layout: canonical row-major bf16 -> fragments in stream order.  One thread per 8-element chunk.
+// Weight re-layout: canonical row-major bf16 -> fragments in stream order, and the coded copy.  One wavefront per fragment: its
+// stores are whole lines (one thread per chunk of a row: 8B shape with the coded copy 42 ms longer than without, now 4).
 // ------------------------------------------------------------------------------------------
 enum RowMap { MAP_IDENT = 0, MAP_ROPE = 1, MAP_GATE = 2, MAP_UP = 3 };
 
 struct PackArgs {
     const __bf16* src;  // [src_rows][K]
     __bf16* dst;        // packed matrix base
-    int32_t src_rows, K, Ks, n_rows;  // n_rows: packed rows this call fills (incl. zero padding)
+    int32_t src_rows, K, Ks;
     int32_t Nt, NB, nwg;              // stream order: tiles of the matrix, batch width, grid size
     int32_t prow0;      // first packed row (MAP_IDENT / MAP_ROPE)
     int32_t map, head_dim;
+    int32_t t0, tiles;  // tiles of the matrix that hold rows of this tensor
+    uint32_t* stamp;    // {magic, grid size}
+    // coded copy (or null): its planes and its stamp, the bits of this tensor's fragments in stream order and in grouped order (or null)
+    char* planes;
+    uint32_t* coded_stamp;
+    unsigned long long *fl, *gfl;
+    uint32_t *base4, *counts;  // base in all four bytes; 128 counters
 };
 
+// Whoever verifies with these weights must run the grid they are laid out for.
+__global__ __launch_bounds__(128) void k_pack_begin(PackArgs a) {
+    const int i = threadIdx.x;
+    if (a.planes) a.counts[i] = 0u;
+    if (i == 0) {
+        a.stamp[0] = kStampMagic;
+        a.stamp[1] = uint32_t(a.nwg);
+        if (a.planes) {
+            a.coded_stamp[0] = kCodedMagic;
+            a.coded_stamp[1] = uint32_t(a.nwg);
+        }
+    }
+}
+// Coded copy: weights counted by bits 8-14 (of large tensors an eighth, spread over all of it: it is the usual ones that count), and
+// the window of eight values that holds most of them.
+__global__ __launch_bounds__(256) void k_pack_count(PackArgs a) {
+    __shared__ uint32_t n[128 * 32];  // 32 copies: neighbouring lanes mostly count the same value
+    for (int i = threadIdx.x; i < 128 * 32; i += 256) n[i] = 0u;
+    __syncthreads();
+    const int64_t chunks = int64_t(a.src_rows) * a.K / 8, pieces = (chunks + 255) / 256, every = pieces >= 1024 ? 8 : 1;
+    for (int64_t p = int64_t(blockIdx.x) * every; p < pieces; p += int64_t(gridDim.x) * every) {
+        const int64_t i = p * 256 + threadIdx.x;
+        if (i >= chunks) break;
+        const uint4v v = reinterpret_cast<const uint4v*>(a.src)[i];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) atomicAdd(&n[((v[e >> 1] >> ((e & 1) * 16 + 8)) & 127u) * 32 + (threadIdx.x & 31)], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 128) {
+        uint32_t sum = 0;
+        for (int c = 0; c < 32; ++c) sum += n[threadIdx.x * 32 + ((c + threadIdx.x) & 31)];
+        if (sum) atomicAdd(a.counts + threadIdx.x, sum);
+    }
+}
+__global__ __launch_bounds__(128) void k_pack_base(PackArgs a) {
+    __shared__ uint32_t n[136];
+    __shared__ unsigned long long best;
+    const int i = threadIdx.x;
+    n[i] = a.counts[i];
+    if (i == 0) best = 0ull;
+    __syncthreads();
+    if (i <= 120) {
+        uint32_t sum = 0;
+        for (int q = 0; q < 8; ++q) sum += n[i + q];
+        atomicMax(&best, (static_cast<unsigned long long>(sum) << 32) | uint32_t(i));
+    }
+    __syncthreads();
+    if (i == 0) *a.base4 = uint32_t(best & 0xffffffffull) * 0x01010101u;
+}
+
 __global__ __launch_bounds__(256) void k_pack(PackArgs a) {
-    const int64_t chunks_per_row = int64_t(a.Ks) * 4;
-    const int64_t id = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (id >= int64_t(a.n_rows) * chunks_per_row) return;
-    const int idx = int(id / chunks_per_row), ch = int(id % chunks_per_row);
-    int prow, srow;
-    if (a.map == MAP_IDENT) {
-        prow = a.prow0 + idx;
-        srow = idx;
-    } else if (a.map == MAP_ROPE) {
-        prow = a.prow0 + idx;
+    const int64_t id = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (id >= int64_t(a.tiles) * a.Ks) return;
+    const int lane = threadIdx.x & 63, t = a.t0 + int(id / a.Ks), s = int(id % a.Ks);
+    const int row = lane & 15, idx = t * 16 + row - a.prow0;
+    int srow = idx;
+    bool mine = true;
+    if (a.map == MAP_ROPE) {
         const int h = a.head_dim, i = idx % h;
         srow = (idx / h) * h + (i >> 1) + (i & 1) * (h >> 1);
-    } else {
-        prow = (idx >> 3) * 16 + (idx & 7) + (a.map == MAP_UP ? 8 : 0);
-        srow = idx;
+    } else if (a.map != MAP_IDENT) {  // eight gate rows, then the eight up rows that belong to them
+        srow = t * 8 + (row & 7);
+        mine = (row >= 8) == (a.map == MAP_UP);
     }
-    const int k0 = ch * 8;
+    const int k0 = s * 32 + (lane >> 4) * 8;
     bf16x8 v;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = static_cast<__bf16>(0.f);
-    if (srow < a.src_rows && k0 < a.K) v = *reinterpret_cast<const bf16x8*>(a.src + size_t(srow) * a.K + k0);
-    const int t = prow >> 4, s = ch >> 2;
-    const int lane = (ch & 3) * 16 + (prow & 15);
-    reinterpret_cast<bf16x8*>(a.dst)[size_t(stream_frag_index(a.Nt, a.Ks, a.NB, a.nwg, t, s)) * 64 + lane] = v;
+    if (mine && srow < a.src_rows && k0 < a.K) v = *reinterpret_cast<const bf16x8*>(a.src + size_t(srow) * a.K + k0);
+    const size_t f = size_t(stream_frag_index(a.Nt, a.Ks, a.NB, a.nwg, t, s));
+    if (mine) reinterpret_cast<bf16x8*>(a.dst)[f * 64 + lane] = v;
+    if (!a.planes) return;
+    const size_t n = size_t(a.Nt) * a.Ks;
+    const uint4v c = encode_weights(v, *a.base4 & 127u);
+    if (mine) {
+        *reinterpret_cast<unsigned long long*>(a.planes + f * 512 + lane * 8) = uint64_t(c[0]) | (uint64_t(c[1]) << 32);
+        *reinterpret_cast<uint32_t*>(a.planes + n * 512 + f * 256 + lane * 4) = c[2];
+        *reinterpret_cast<uint32_t*>(a.planes + n * 768 + f * 256 + lane * 4) = c[3];
+    }
+    // (a word is shared with other fragments and other tensors, which may be packed at the same time)
+    const bool rest = __builtin_amdgcn_ballot_w64(mine && c[3] != 0u) != 0ull;
+    auto mark = [&](unsigned long long* words, const FlagPlace& p) {
+        if (rest) atomicOr(words + p.word, 1ull << p.bit);
+        else atomicAnd(words + p.word, ~(1ull << p.bit));
+    };
+    if (lane == 0) {
+        mark(a.fl, stream_flag(a.Nt, a.Ks, a.NB, a.nwg, t, s));
+        if (a.gfl) mark(a.gfl, grouped_flag(a.Nt, a.Ks, a.nwg, t, s));
+    }
 }
 
 // A workspace is prepared by clearing all of it (control words must start at zero; the kernel

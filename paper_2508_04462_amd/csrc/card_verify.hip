@@ -9,7 +9,9 @@
 //     fragments of the whole step in consumption order, keep 8 loads of 1 KiB in flight each
 //     and push what arrives into a per-wavefront FIFO in LDS (28 KiB each).  The weights are
 //     stored in exactly that order, so each producer reads one contiguous run per matrix (four
-//     interleaved runs in the grouped down-projection of the kernels for r > 8: plan_phase_grouped);
+//     interleaved runs in the grouped down-projection of the kernels for r > 8: plan_phase_grouped).
+//     Where the blob holds a coded copy of the matrices (12 bits per weight, CodedDesc), they stream and decode that
+//     (producer_coded);
 //   * four CONSUMER wavefronts pop fragments from their FIFO into the matrix pipe, run the
 //     epilogues, the attention phase and the grid barriers.
 //
@@ -60,6 +62,10 @@ struct MegaArgs {
     int32_t grid;           // the grid size that has to be: nwg, or more where the last positions of that grid have nothing to do
     size_t embed_off, g_final_off, layer0_off, layer_stride, g_attn_off, g_ffn_off;
     MatDesc qkv, wo, gu, wd, lm;  // lm.off absolute, the others relative to the layer base
+    const char* cbase;            // the coded copy of the matrices, or null
+    const uint32_t* c_stamp;
+    size_t c_layer0_off, c_layer_stride, c_code_off, c_lm_code_off;
+    CodedDesc c_qkv, c_wo, c_gu, c_wd, c_lm;
     __bf16* kpool;
     __bf16* vpool;
     size_t pool_layer_elems;
@@ -322,6 +328,12 @@ __device__ __forceinline__ PhasePlan plan_phase_grouped(const bf16x8* w, int Nt,
     return p;
 }
 
+// weights laid out for another grid size would stream in the wrong order
+__device__ __forceinline__ bool bad_stamp(const MegaArgs& a) {
+    if (a.cbase && (a.c_stamp[0] != kCodedMagic || a.c_stamp[1] != uint32_t(a.grid))) return true;
+    return a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.grid);
+}
+
 enum StreamPhase { SP_QKV = 0, SP_WO = 1, SP_GU = 2, SP_WD = 3 };
 
 // Whether the down-projection runs in groups of four workgroups (kernels for r > 8 only): the
@@ -497,6 +509,232 @@ __device__ __forceinline__ void producer(const MegaArgs& a, MegaSmem& sm, int w,
     }
 }
 
+// ---- producer from the coded copy ----------------------------------------------------------------
+// As `producer`, but a fragment comes from three planes (CodedDesc): 768 bytes, and 256 more where its bit says so (an offset behind
+// the matrix otherwise: zeros, no memory access).  It is decoded on the way into the FIFO, so consumers see no difference.
+//
+// Bound by what a wavefront can issue as much as by HBM, which is why it is written for few instructions, 25 per
+// fragment, 12 of them the decoding.  Timed without the decoding: with `producer`'s 48 per fragment a quarter fewer bytes made an 8B step 1.5 %
+// faster, 7 instructions for whole fragments made it no faster, both together 15 % (70B widths 19 %).  The ring is walked four
+// fragments at a time ("quad"): one look at the FIFO, one set of offsets, one count for the consumer (one per fragment: 2816 us against
+// 2778 for an 8B step), one look at what is left of the run.  A run ends where the batch or the word of bits ends, at most 16 quads on;
+// nothing else is looked at in between, and nothing that a scalar load brings is touched (a wait per quad: 2778 -> 2761).
+// A batch (NB tiles) fills whole quads: the places behind its last fragment hold whatever follows in the planes and the consumer
+// skips them.  So a quad never changes the matrix, never wraps in the FIFO, and is the same straight line on every path: only then
+// does the compiler's wait in front of a slot's use leave exactly the other kRing - 1 fragments in flight.
+//
+// Steps, same states, us with `producer` / with this one: 1B decode 875 / 799, 8B r = 8 3204 / 2780, 8B decode at 2041 tokens 3227 / 2762, 7B r = 32
+// 4368 / 4004, r = 13 3482 / 2985, 70B widths 2760 / 2313, 8B widths r = 5 at 32 700 tokens 688 / 586, 32 tree rows of the 1B shape 1281 / 1193.
+//
+// GROUPED (the kernels for r > 8): a phase planned by plan_phase_grouped interleaves four runs, one
+// per tile of the batch: place u of a quad carries tile u of a k-step.
+typedef const __attribute__((address_space(4))) unsigned long long* ConstWords;  // (scalar loads: written by earlier kernels only)
+typedef const __attribute__((address_space(4))) uint32_t* ConstWord;
+constexpr uint32_t kNoRest = 0xfffffc00u;  // offset behind any matrix (scalar and lane offset are added without wrapping)
+
+template <bool GROUPED>
+__device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, int w, int lane, int wg) {
+    static_assert(kRing == 8 && kFifo % 4 == 0, "two quads in flight, whole quads in the FIFO");
+    // The pair's plan of each kind of phase, lane by lane: QKV, O, gate/up, down, of even and of odd layers (0-7), and the vocabulary
+    // head (8).  Where a phase lies in the blob is all that its layer adds; a switch of phases reads a lane.
+    // (Planned there by scalar divisions, the phases' 40 scalar values on top of the consumers' made every kernel spill into memory.)
+    uint32_t k_first, k_tiles, k_steps, k_tile, k_nb, k_skip, k_place, k_n, k_code, k_up, k_off[2], k_fl[2];
+    {
+        const int kind = min(lane, 8), k = kind >> 1;
+        auto of = [&](auto&& f) { return k == 0 ? f(a.qkv) : k == 1 ? f(a.wo) : k == 2 ? f(a.gu) : k == 3 ? f(a.wd) : f(a.lm); };
+        auto ofc = [&](auto&& f) { return k == 0 ? f(a.c_qkv) : k == 1 ? f(a.c_wo) : k == 2 ? f(a.c_gu) : k == 3 ? f(a.c_wd) : f(a.c_lm); };
+        const int Nt = of([](const MatDesc& m) { return m.Nt; }), Ks = of([](const MatDesc& m) { return m.Ks; });
+        const int turned = k == 0 || k == 1 ? kind & 1 : k == 3 ? ~kind & 1 : 0;
+        const int pos = (wg + turned * (a.nwg / 2)) % a.nwg;
+        const bool grouped = GROUPED && k == 3 && down_grouped(a);
+        const StreamRun r = stream_run(Nt, Ks, a.nwg, grouped ? pos & ~3 : pos, grouped ? pos & 3 : w);
+        const int len = r.s1 - r.s0, sub0 = grouped ? w * len / kStreamWaves : 0, sub1 = grouped ? (w + 1) * len / kStreamWaves : len;
+        k_first = uint32_t(r.first) + uint32_t(sub0);
+        k_tiles = uint32_t(grouped ? 4 * r.cnt : r.cnt);
+        k_steps = uint32_t(sub1 - sub0);
+        k_tile = uint32_t(pos);
+        k_nb = uint32_t(grouped ? 4 : k == 0 ? kNbQkv : k == 1 || k == 3 ? kNbOne : kNbWide);
+        k_skip = uint32_t(grouped ? len : 0);
+        k_place = uint32_t(grouped ? r.cnt * Ks : 1);
+        k_n = uint32_t(Nt) * uint32_t(Ks);
+        const uint64_t off = ofc([](const CodedDesc& m) { return uint64_t(m.off); });
+        const uint32_t words = uint32_t(grouped ? a.c_wd.fl2_run : ofc([](const CodedDesc& m) { return m.fl_run; }));
+        const uint64_t fl = (grouped ? uint64_t(a.c_wd.fl2) : ofc([](const CodedDesc& m) { return uint64_t(m.fl); })) +
+                            uint64_t(uint32_t(pos * kStreamWaves + w) * words) * 8u;
+        k_off[0] = uint32_t(off);
+        k_off[1] = uint32_t(off >> 32);
+        k_fl[0] = uint32_t(fl);
+        k_fl[1] = uint32_t(fl >> 32);
+        k_up = k == 2 ? uint32_t(a.c_gu.fl2 - a.c_gu.fl) : 0u;
+        k_code = k == 0 ? CT_Q : k == 1 ? CT_O : k == 2 ? CT_G : k == 3 ? CT_D : 0u;
+    }
+    const int n_ph = 4 * a.L + 1;
+    auto kind_of = [&](int ph) { return ph >= 4 * a.L ? 8 : (ph & 3) * 2 + ((ph >> 2) & 1); };
+    auto pick = [](uint32_t v, int kind) { return uint32_t(__builtin_amdgcn_readlane(int(v), kind)); };
+    auto pick64 = [&](const uint32_t (&v)[2], int kind) { return uint64_t(pick(v[0], kind)) | uint64_t(pick(v[1], kind)) << 32; };
+    auto layer_at = [&](int ph) {
+        return reinterpret_cast<uint64_t>(a.cbase) + (ph >= 4 * a.L ? 0 : a.c_layer0_off + uint64_t(uint32_t(ph) >> 2) * a.c_layer_stride);
+    };
+    // The next phase: its first words and its bases, requested while the one in front of it is streamed (scalar loads take a memory latency).
+    int nx_ph = -1;
+    unsigned long long nx_word = 0ull, nx_word2 = 0ull;
+    uint32_t nx_base0 = 0, nx_base1 = 0, nx_base2 = 0;  // of all rows; of gate and up rows; of q, k and v tiles
+    auto request_ahead = [&]() {
+        do ++nx_ph;
+        while (nx_ph < n_ph && (pick(k_tiles, kind_of(nx_ph)) == 0u || pick(k_steps, kind_of(nx_ph)) == 0u));
+        const int ph = min(nx_ph, n_ph - 1), kind = kind_of(ph);  // (behind the last phase: whatever, nobody uses it)
+        const uint64_t at = layer_at(ph), fl = at + pick64(k_fl, kind);
+        nx_word = *ConstWords(fl);
+        nx_word2 = *ConstWords(fl + pick(k_up, kind));
+        const ConstWord code = ConstWord(at + (ph >= 4 * a.L ? a.c_lm_code_off : a.c_code_off)) + pick(k_code, kind);
+        nx_base0 = code[0];
+        nx_base1 = code[1];
+        nx_base2 = code[2];
+    };
+    // the next quad: resource, offsets of its first place in the planes, from place to place (low plane; half of that in the others),
+    // its bits and those of the quads behind it; quads left in the batch from the word's first on (behind the stream an empty resource: zeros, no access)
+    __amdgpu_buffer_rsrc_t cur_rs = make_rsrc(a.wbase, 0);
+    uint32_t off_low = 0, off_high = 0, off_rest = 0, left = 0, issued = 0;
+    uint32_t run = 0;  // quads up to the end of the batch or of the word, whichever comes first (behind the stream: more than will ever be asked for)
+    uint32_t place = 512u, quad_step = 2048u;
+    unsigned long long word = 0ull, word_a = 0ull, word_b = 0ull;  // the latter two: of the next word, requested when `word` began
+    uint32_t base_even = 0, base_odd = 0;  // of places 0 and 2, 1 and 3
+    // what is left of the phase behind the batch
+    uint32_t first = 0, n = 0, steps = 0, nb = 0, skip = 0, up = 0, tiles = 0, t_next = 0, qkv_bases = 0;
+    uint64_t words_at = 0;
+    auto next_word = [&]() {
+        word = word_a | word_b;
+        words_at += 8u;
+        word_a = *ConstWords(words_at);
+        word_b = *ConstWords(words_at + up);
+        run = min(left, 16u);
+        issued += 4u * run;
+    };
+    auto next_batch = [&]() {
+        if (tiles == 0u) {
+            if (nx_ph >= n_ph) {
+                run = 0x7fffffffu;
+                cur_rs = make_rsrc(a.wbase, 0);
+                return;
+            }
+            const int kind = kind_of(nx_ph);
+            const uint64_t at = layer_at(nx_ph);
+            n = pick(k_n, kind);
+            cur_rs = make_rsrc(reinterpret_cast<const void*>(at + pick64(k_off, kind)), n << 10);
+            first = pick(k_first, kind);
+            steps = pick(k_steps, kind);
+            nb = pick(k_nb, kind);
+            tiles = pick(k_tiles, kind);
+            t_next = pick(k_tile, kind);
+            if constexpr (GROUPED) {
+                skip = pick(k_skip, kind);
+                place = pick(k_place, kind) * 512u;
+                quad_step = skip != 0u ? 512u : 2048u;
+            }
+            words_at = at + pick64(k_fl, kind);
+            up = pick(k_up, kind);
+            word_a = nx_word;
+            word_b = nx_word2;
+            base_even = base_odd = kind >> 1 == SP_GU && (lane & 8) ? +nx_base1 : +nx_base0;  // gate rows: lanes 0-7 of sixteen, up rows: 8-15
+            qkv_bases = kind >> 1 == SP_QKV ? 0x80000000u | (nx_base0 & 127u) | (nx_base1 & 127u) << 8 | (nx_base2 & 127u) << 16 : 0u;
+            if (a.ts && w == 0 && lane == 0 && (nx_ph >> 2) == a.ts_layer) a.ts[size_t(wg) * 32 + 17 + (nx_ph & 3)] = wall_clock64();
+            request_ahead();
+        }
+        const uint32_t nv = min(nb, tiles), frags = nv * steps;
+        left = (frags + 3u) / 4u;
+        off_low = first * 512u;
+        off_high = (n * 2u + first) * 256u;
+        off_rest = off_high + n * 256u;
+        if (qkv_bases != 0u) {
+            auto base_of = [&](uint32_t t) {
+                const int row = int(t) * 16, sh = row < a.qd ? 0 : row < a.qd + a.kvd ? 8 : 16;
+                return (qkv_bases >> sh & 127u) * 0x01010101u;
+            };
+            base_even = base_of(t_next);
+            base_odd = nv > 1u ? base_of(t_next + uint32_t(a.nwg)) : base_even;
+        }
+        next_word();
+        first += GROUPED && skip != 0u ? skip : frags;
+        tiles -= nv;
+        t_next += nb * uint32_t(a.nwg);
+    };
+    // what the ring's two quads were coded with
+    uint32_t even[2], odd[2];
+    uint4v rg[kRing];
+    auto load = [&](uint4v& dst, int u) {
+        int vl = lane * 8, vh = lane * 4;
+        uint32_t sl = off_low, sh = off_high, sr = off_rest;
+        if constexpr (GROUPED) {
+            sl += uint32_t(u) * place;
+            sh += uint32_t(u) * (place / 2u);
+            sr += uint32_t(u) * (place / 2u);
+        } else {
+            vl += u * 512;
+            vh += u * 256;
+        }
+        sr = (uint32_t(word) >> u) & 1u ? sr : kNoRest;
+        const uint2v low = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(cur_rs, vl, int(sl), kAuxNT));
+        const uint32_t high = __builtin_amdgcn_raw_buffer_load_b32(cur_rs, vh, int(sh), kAuxNT);
+        const uint32_t rest = __builtin_amdgcn_raw_buffer_load_b32(cur_rs, vh, int(sr), kAuxNT);
+        dst = uint4v{low[0], low[1], high, rest};
+    };
+    auto loaded = [&](int q) {  // a quad has been requested
+        even[q] = base_even;
+        odd[q] = base_odd;
+        off_low += GROUPED ? quad_step : 2048u;
+        off_high += GROUPED ? quad_step / 2u : 1024u;
+        off_rest += GROUPED ? quad_step / 2u : 1024u;
+        word >>= 4;
+        if (__builtin_expect(--run == 0, 0)) {
+            left -= min(left, 16u);
+            if (left == 0) next_batch();
+            else next_word();
+        }
+    };
+    uint32_t pushed = 0, head_seen = 0, pofs = 0;
+    int32_t most = kFifo - 4;  // fragments in the FIFO that leave room for a quad
+    auto pass_on = [&](int q) {
+        if (__builtin_expect(int32_t(pushed - head_seen) > most, 0)) {
+            uint32_t spins = 0;
+            while (true) {
+                head_seen = lds_peek(&sm.head[w]);
+                if (int32_t(pushed - head_seen) <= most) break;
+                __builtin_amdgcn_s_sleep(1);
+                if (++spins > kLdsSpinLimit || (spins & 63u) == 0 && lds_peek(reinterpret_cast<uint32_t*>(&sm.failed)) != 0) {
+                    most = 0x7fffffff;
+                    lds_post(reinterpret_cast<uint32_t*>(&sm.failed), 1u);
+                }
+            }
+        }
+        uint4v* slots = reinterpret_cast<uint4v*>(reinterpret_cast<char*>(&sm.fifo[w][0][lane]) + pofs);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            asm volatile("" ::: "memory");
+            slots[u * 64] = decode_weights(rg[q * 4 + u], (u & 1) ? odd[q] : even[q]);
+            asm volatile("" ::: "memory");
+            load(rg[q * 4 + u], u);
+        }
+        // LDS runs a wavefront's instructions in order: the count lands after the fragments
+        asm volatile("" ::: "memory");
+        pushed += 4u;
+        lds_post(&sm.tail[w], pushed);
+        pofs = pofs + 4096u == uint32_t(kFifo) * 1024u ? 0u : pofs + 4096u;
+        loaded(q);
+    };
+    request_ahead();
+    next_batch();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load(rg[q * 4 + u], u);
+        loaded(q);
+    }
+    do {  // (an odd number of quads: the last one pushed is empty, nobody pops it)
+        pass_on(0);
+        pass_on(1);
+    } while (int32_t(issued - pushed) > 0);
+}
+
 // Consumer side of a FIFO (wavefront-uniform state).
 struct FifoC {
     uint32_t head, tail_seen;  // in fragments
@@ -507,12 +745,12 @@ struct FifoC {
 
 // Wait until `need` fragments are there.
 __device__ __forceinline__ void fifo_wait(MegaSmem& sm, FifoC& f, int w, uint32_t need) {
-    if (__builtin_expect(f.tail_seen - f.head >= need, 1)) return;
+    if (__builtin_expect(int32_t(f.tail_seen - f.head) >= int32_t(need), 1)) return;
     const unsigned long long w0 = wall_clock64();
     uint32_t spins = 0;
     while (!f.dead) {
         f.tail_seen = lds_peek(&sm.tail[w]);
-        if (f.tail_seen - f.head >= need) break;
+        if (int32_t(f.tail_seen - f.head) >= int32_t(need)) break;
         __builtin_amdgcn_s_sleep(1);
         if (++spins > kLdsSpinLimit || (spins & 63u) == 0 && lds_peek(reinterpret_cast<uint32_t*>(&sm.failed)) != 0) {
             f.dead = true;
@@ -608,7 +846,7 @@ struct NoHook {
 // so the four workgroups hand their blocks over in memory and the last one to arrive adds the four
 // (always in the order of the quarters, whoever comes last) and runs the epilogue for all four
 // tiles.
-template <int H, int NB, int MT, int EPI, bool PK, bool ROPE_LDS = false, typename Hook = NoHook, bool GRP4 = false>
+template <int H, int NB, int MT, int EPI, bool PK, bool CODED, bool ROPE_LDS = false, typename Hook = NoHook, bool GRP4 = false>
 __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P, const __bf16* xf, uint32_t xf_bytes,
                                            const EpiArgs& ea, FifoC& fc, MegaSmem& sm, int wave, int lane,
                                            uint32_t& cgen, Hook after_k = Hook()) {
@@ -784,6 +1022,12 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
 #pragma unroll
                 for (int u = 0; u < SG; ++u) refill(xh[gg * SG + u], xl[gg * SG + u]);
             }
+        }
+        if constexpr (CODED) {  // the places that fill the batch's last quad (producer_coded)
+            const uint32_t fill = uint32_t(-(nvalid * n_steps)) & 3u;
+            fc.head += fill;
+            fc.pos += fill;
+            fc.pos = fc.pos >= uint32_t(kFifo) ? fc.pos - uint32_t(kFifo) : fc.pos;
         }
         if (b + 1 == n_batches) {
             if (gts) {
@@ -1609,8 +1853,9 @@ __device__ __forceinline__ void attn_phase(const MegaArgs& a, int layer, MegaSme
 // ---- the kernel ----------------------------------------------------------------------------------
 // DR: draft-side call (tree rows with a visibility mask, per-row top-k in the vocabulary phase).  PC: one of several
 // such calls for a level, perhaps at the same time (a kernel of its own: with the walk over shared pages in the other
-// draft-side kernels a 32-row call of the 1B shape takes 1302 us instead of 1274).
-template <int MT, int H, bool PK, bool DR, bool PC = false>
+// draft-side kernels a 32-row call of the 1B shape takes 1302 us instead of 1274).  CODED: weights from the coded copy (its own again: with
+// both producers in one kernel the smallest shape takes 70.3 us a step instead of 68.4).
+template <int MT, int H, bool PK, bool DR, bool PC, bool CODED>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_verify(MegaArgs a) {
     __shared__ MegaSmem sm;
     const int tid = threadIdx.x;
@@ -1641,7 +1886,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
     }
 
     if (wave >= kMegaWaves) {
-        producer<!PK>(a, sm, wave - kMegaWaves, lane, wg);
+        if constexpr (CODED) producer_coded<!PK>(a, sm, wave - kMegaWaves, lane, wg);
+        else producer<!PK>(a, sm, wave - kMegaWaves, lane, wg);
         return;
     }
 
@@ -1740,7 +1986,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         };
         CARD_TS(0)
         ea.ts0 = 21;
-        gemm_phase<H, kNbQkv, MT, PC ? ME_QKV_PIECE : ME_QKV, PK, ROPE_LDS>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
+        gemm_phase<H, kNbQkv, MT, PC ? ME_QKV_PIECE : ME_QKV, PK, CODED, ROPE_LDS>(a, p_qkv, a.xfrag + v0 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea, fc,
                                           sm, wave, lane, cgen, preload);
         CARD_TS(1)
         // As with the plans, the first task's divisions in front of the barrier (1B decode 892 -> 885 us, 7B r = 32 4330 -> 4286, 8B r = 8
@@ -1773,7 +2019,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ss_new = a.ss + v1 * ss_stride;
         ea.gain_next = reinterpret_cast<const float*>(lb + a.g_ffn_off);
         ea.ts0 = 24;
-        gemm_phase<H, kNbOne, MT, ME_RESID, PK>(a, p_wo, a.attfrag + size_t(l) * a.attfrag_stride,
+        gemm_phase<H, kNbOne, MT, ME_RESID, PK, CODED>(a, p_wo, a.attfrag + size_t(l) * a.attfrag_stride,
                                             uint32_t(a.attfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         CARD_TS(5)
         const PhasePlan p_gu = stream_phase<!PK>(a, 4 * l + SP_GU, wg, wave);
@@ -1786,7 +2032,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ss_in = a.ss + v1 * ss_stride;
         ea.actfrag = a.actfrag + size_t(l) * a.actfrag_stride;
         ea.ts0 = 0;
-        gemm_phase<H, kNbWide, MT, ME_SWIGLU, PK>(a, p_gu, a.xfrag + v1 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea,
+        gemm_phase<H, kNbWide, MT, ME_SWIGLU, PK, CODED>(a, p_gu, a.xfrag + v1 * a.xfrag_stride, uint32_t(a.xfrag_stride * 2), ea,
                                               fc, sm, wave, lane, cgen);
         CARD_TS(7)
         const PhasePlan p_wd = stream_phase<!PK>(a, 4 * l + SP_WD, wg, wave);
@@ -1805,13 +2051,13 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ts0 = 27;
         if constexpr (!PK) {
             if (down_grouped(a))
-                gemm_phase<H, 4, MT, ME_RESID, false, false, NoHook, true>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
+                gemm_phase<H, 4, MT, ME_RESID, false, CODED, false, NoHook, true>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
                                                                  uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
             else
-                gemm_phase<H, kNbOne, MT, ME_RESID, false>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
+                gemm_phase<H, kNbOne, MT, ME_RESID, false, CODED>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
                                                         uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         } else {
-            gemm_phase<H, kNbOne, MT, ME_RESID, PK>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
+            gemm_phase<H, kNbOne, MT, ME_RESID, PK, CODED>(a, p_wd, a.actfrag + size_t(l) * a.actfrag_stride,
                                                 uint32_t(a.actfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         }
         CARD_TS(9)
@@ -1828,7 +2074,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         ea.ss_in = a.ss + size_t(2 * a.L) * ss_stride;
         LmState lm = {{0ull, 0ull}, -1e30f, 0.f};
         ea.lm = &lm;
-        gemm_phase<H, kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK>(a, p_qkv, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
+        gemm_phase<H, kNbWide, MT, DR ? ME_LM_TOPK : ME_LM, PK, CODED>(a, p_qkv, a.xfrag + size_t(2 * a.L) * a.xfrag_stride,
                                           uint32_t(a.xfrag_stride * 2), ea, fc, sm, wave, lane, cgen);
         if (!DR && tid < a.r && sm.wg_best[tid] != 0ull)
             __hip_atomic_fetch_max(&a.best[tid], sm.wg_best[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1861,7 +2107,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         // Rows are merged by one workgroup each: thread t holds workgroup t's sorted list of topk keys (in
         // sixteen places) for the row and its (max, sum) pair; the log-sum-exp folds the pairs, then k rounds of
         // "largest list head in the workgroup" emit the row's k best tokens with their probabilities.
-        const bool bad_layout = a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.grid);  // no token then, as behind the last one
+        const bool bad_layout = bad_stamp(a);  // no token then, as behind the last one
         for (int m = wg; m < a.r; m += nwg) {
             unsigned long long mine[16];
             float pm = -1e30f, ps = 0.f;
@@ -1928,7 +2174,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
             int j = 0;
             while (j < a.r && a.cand[j] == sm.pred[j]) ++j;
             // weights laid out for another grid size would stream in the wrong order
-            const bool bad_layout = a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.grid);
+            const bool bad_layout = bad_stamp(a);
             // a token id outside the vocabulary was clamped by the embedding gather: the step is void
             bool bad_token = false;
             for (int i = 0; i < a.r; ++i) bad_token = bad_token || a.cand[i] < 0 || a.cand[i] >= a.V;

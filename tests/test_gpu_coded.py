@@ -1,0 +1,97 @@
+"""The coded copy of the weights gives the bits of the weights themselves: same blob, called with cfg.coded 1 and 0."""
+import pytest
+import torch
+
+import card_inputs as ci
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # widths that are no multiples of the tiles, three k-steps to a wavefront pair and fewer, a last k-step that is part zeros
+    "odd": ci.ModelShape("odd", 2, 320, 5, 5, 64, 264, 1003, ctx=64, r=8),
+    # heads of 128, tile counts that are multiples of four (grouped down-projection for more than eight rows)
+    "wide": ci.ModelShape("wide", 2, 512, 4, 2, 128, 1416, 2050, ctx=64, r=8),
+}
+
+
+def _weights(kind, rows, cols, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.empty((rows, cols), device="cuda").normal_(0.0, 0.02, generator=g)
+    if kind == "scales":  # every tensor in a range of its own
+        w *= 2.0 ** ((seed * 7) % 9 - 6)
+    elif kind == "spread":  # every weight needs its rest: exponents far apart, zeros and denormals among them
+        e = torch.randint(-60, 1, w.shape, device="cuda", generator=g)
+        w = torch.ldexp(w, e)
+        w[:, ::5] = 0.0
+        w[::7, 1::5] = 1e-40
+    elif kind == "outliers":
+        w[torch.rand(w.shape, device="cuda", generator=g) < 0.002] *= 300.0
+    return w.to(torch.bfloat16)
+
+
+def _pack(tgt, shape, kind, seed):
+    d, f = shape.d_model, shape.d_ffn
+    dims = {"wq": (shape.q_dim, d), "wk": (shape.kv_dim, d), "wv": (shape.kv_dim, d), "wo": (d, shape.q_dim), "wg": (f, d), "wu": (f, d),
+            "wd": (d, f)}
+    tgt.pack("embed", 0, _weights("normal", shape.vocab, d, seed))
+    tgt.pack("lm_head", 0, _weights(kind, shape.vocab, d, seed + 1))
+    tgt.pack("g_final", 0, torch.ones(d))
+    for layer in range(shape.n_layers):
+        for i, (name, (n, k)) in enumerate(dims.items()):
+            tgt.pack(name, layer, _weights(kind, n, k, seed + 10 * layer + i + 2))
+        for name in ("g_attn", "g_ffn"):
+            tgt.pack(name, layer, torch.ones(d))
+
+
+def _run(tgt, coded, r, n_ctx):
+    """Logits of a step of r rows, candidates of a tree level of as many rows, and both page pools."""
+    import paper_2508_04462_amd as card
+
+    tgt.cfg.coded = coded
+    toks = [(37 * i + 5) % tgt.cfg.vocab for i in range(n_ctx + r)]
+    tgt.k_pages.zero_()
+    tgt.v_pages.zero_()
+    tgt.prefill(toks[:n_ctx], chunk=8)
+    res = tgt.verify(n_ctx, -1, toks[n_ctx:], want_logits=True)
+    assert res["accepted_len"] >= 0
+    base, mask_base = n_ctx + r, n_ctx // 16 * 16
+    st, rows = card.card_tree_mask_level(None, [-1] * r, base, n_ctx, mask_base, (base + r - mask_base + 31) // 32)
+    assert st == card.CARD_OK
+    lv = tgt.draft_level(n_ctx, toks[n_ctx:], [n_ctx] * r, base, rows, mask_base, 5)
+    return [torch.as_tensor(x).contiguous().view(torch.uint8).cpu() for x in
+            (res["logits"], lv["topk_tokens"], lv["topk_probs"], tgt.k_pages, tgt.v_pages)]
+
+
+@pytest.mark.parametrize("grid_wgs", [0, 24, 5])  # one tile per workgroup at most; several batches; an odd grid
+@pytest.mark.parametrize("kind", ["normal", "scales", "spread", "outliers"])
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_coded_weights_give_the_same_bits(monkeypatch, name, kind, grid_wgs):
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd import runtime
+
+    monkeypatch.setattr(runtime, "CODED_MIN_LAYER_BYTES", 0)
+    shape = SHAPES[name]
+    tgt = card.Target(shape, 160, grid_wgs=grid_wgs, pool_fill=0)
+    assert tgt.cfg.coded == 1
+    tgt.packed.fill_(0xA5)  # nothing may depend on what the memory held
+    # (weights packed over others leave nothing of them behind)
+    _pack(tgt, shape, "spread" if kind == "normal" else "normal", 900)
+    _pack(tgt, shape, kind, 50)
+    for r in (1, 8, 13, 32):
+        for got, want in zip(_run(tgt, 1, r, 41), _run(tgt, 0, r, 41)):
+            assert torch.equal(got, want), (name, kind, grid_wgs, r)
+
+
+def test_a_blob_without_the_copy_is_reported(monkeypatch):
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd import runtime
+
+    monkeypatch.setattr(runtime, "CODED_MIN_LAYER_BYTES", 0)
+    shape = SHAPES["wide"]
+    tgt = card.Target(shape, 160, pool_fill=0)
+    tgt.packed.zero_()
+    tgt.cfg.coded = 0
+    _pack(tgt, shape, "normal", 3)
+    assert tgt.verify(0, -1, [1, 2, 3])["accepted_len"] >= 0
+    tgt.cfg.coded = 1
+    assert tgt.verify(0, -1, [1, 2, 3])["accepted_len"] == -1
