@@ -36,6 +36,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "card_common.hip"
 
 namespace card {
@@ -967,61 +969,75 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
             for (int j = 0; j < MT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
         const int nvalid = min(NB, P.cnt - b * NB);
 
-        for (int xb = 0; xb < n_xb; ++xb) {
+        // W: tiles that the loop's groups are laid out for, at least the batch's (a narrow batch then takes several k-steps per group)
+        auto k_loop = [&](auto width) {
+            constexpr int W = decltype(width)::value, SGW = GRP / W < XD ? GRP / W : XD;
+            static_assert(XD % SGW == 0, "ring of whole groups");
+            for (int xb = 0; xb < n_xb; ++xb) {
 #pragma unroll
-            for (int gg = 0; gg < XD / SG; ++gg) {
-                const int st0 = xb * XD + gg * SG;  // first (virtual) k-step of the group
-                int nvs = n_steps - st0;
-                nvs = nvs > SG ? SG : nvs;
-                if (nvs > 0) {
-                    // the group: nvs k-steps x nvalid tiles, step-major, in consecutive FIFO slots
-                    const uint32_t need = uint32_t(nvs * nvalid);
-                    fifo_wait(sm, fc, wave, need);
-                    bf16x8 fr[SG][NB];
-                    const bool straight = fc.pos + uint32_t(GRP) <= uint32_t(kFifo);  // no wrap inside the group
-                    if (straight && nvs == SG && (SG == 1 || nvalid == NB)) {
-                        // Static slot offsets.  With one k-step per group the slots of tiles the batch
-                        // does not have hold stale bits: they only reach those tiles' accumulators,
-                        // which nobody reads.
-                        const uint4v* grp = &sm.fifo[wave][fc.pos][lane];
+                for (int gg = 0; gg < XD / SGW; ++gg) {
+                    const int st0 = xb * XD + gg * SGW;  // first (virtual) k-step of the group
+                    int nvs = n_steps - st0;
+                    nvs = nvs > SGW ? SGW : nvs;
+                    if (nvs > 0) {
+                        // the group: nvs k-steps x nvalid tiles, step-major, in consecutive FIFO slots
+                        const uint32_t need = uint32_t(nvs * nvalid);
+                        fifo_wait(sm, fc, wave, need);
+                        bf16x8 fr[SGW][W];
+                        const bool straight = fc.pos + uint32_t(SGW * W) <= uint32_t(kFifo);  // no wrap inside the group
+                        if (straight && nvs == SGW && (SGW == 1 || nvalid == W)) {
+                            // Static slot offsets.  With one k-step per group the slots of tiles the batch
+                            // does not have hold stale bits: they only reach those tiles' accumulators,
+                            // which nobody reads.
+                            const uint4v* grp = &sm.fifo[wave][fc.pos][lane];
 #pragma unroll
-                        for (int k = 0; k < GRP; ++k) fr[k / NB][k % NB] = __builtin_bit_cast(bf16x8, grp[k * 64]);
-                    } else {
-                        // The same, slot by slot (the group wraps, or a narrow batch).  Every slot is read, needed or not: a read
-                        // under a condition and zeros where it does not hold cost 16-19 registers, which spilled in the kernels of two
-                        // row tiles (32 tree rows of the 1B shape 1278 -> 1252 us, 8B r = 5 at 32 700 tokens 671 -> 668; others within 0.6 %).
+                            for (int k = 0; k < SGW * W; ++k) fr[k / W][k % W] = __builtin_bit_cast(bf16x8, grp[k * 64]);
+                        } else {
+                            // The same, slot by slot (the group wraps, or a narrow batch).  Every slot is read, needed or not: a read
+                            // under a condition and zeros where it does not hold cost 16-19 registers, which spilled in the kernels of two
+                            // row tiles (32 tree rows of the 1B shape 1278 -> 1252 us, 8B r = 5 at 32 700 tokens 671 -> 668; others within 0.6 %).
 #pragma unroll
-                        for (int u = 0; u < SG; ++u)
+                            for (int u = 0; u < SGW; ++u)
 #pragma unroll
-                            for (int i = 0; i < NB; ++i) {
-                                uint32_t sl = fc.pos + uint32_t(u * nvalid + i);
-                                sl = sl >= uint32_t(kFifo) ? sl - uint32_t(kFifo) : sl;
-                                fr[u][i] = __builtin_bit_cast(bf16x8, sm.fifo[wave][sl][lane]);
-                            }
+                                for (int i = 0; i < W; ++i) {
+                                    uint32_t sl = fc.pos + uint32_t(u * nvalid + i);
+                                    sl = sl >= uint32_t(kFifo) ? sl - uint32_t(kFifo) : sl;
+                                    fr[u][i] = __builtin_bit_cast(bf16x8, sm.fifo[wave][sl][lane]);
+                                }
+                        }
+                        // LDS runs a wavefront's instructions in order: the slots are read before this lands
+                        asm volatile("" ::: "memory");
+                        fc.head += need;
+                        fc.pos += need;
+                        fc.pos = fc.pos >= uint32_t(kFifo) ? fc.pos - uint32_t(kFifo) : fc.pos;
+                        lds_post(&sm.head[wave], fc.head);
+#pragma unroll
+                        for (int u = 0; u < SGW; ++u) {
+                            if (u >= nvs) break;  // (behind the wavefront's share: neither weights nor activations)
+                            const int slot = gg * SGW + u;
+#pragma unroll
+                            for (int i = 0; i < W; ++i)
+#pragma unroll
+                                for (int j = 0; j < MT; ++j) {
+                                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[u][i], xh[slot][j], acc[i][j], 0, 0, 0);
+                                    if constexpr (!PK)
+                                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[u][i], xl[slot][j], acc[i][j], 0, 0, 0);
+                                }
+                        }
                     }
-                    // LDS runs a wavefront's instructions in order: the slots are read before this lands
-                    asm volatile("" ::: "memory");
-                    fc.head += need;
-                    fc.pos += need;
-                    fc.pos = fc.pos >= uint32_t(kFifo) ? fc.pos - uint32_t(kFifo) : fc.pos;
-                    lds_post(&sm.head[wave], fc.head);
 #pragma unroll
-                    for (int u = 0; u < SG; ++u) {
-                        if (u >= nvs) break;  // (behind the wavefront's share: neither weights nor activations)
-                        const int slot = gg * SG + u;
-#pragma unroll
-                        for (int i = 0; i < NB; ++i)
-#pragma unroll
-                            for (int j = 0; j < MT; ++j) {
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[u][i], xh[slot][j], acc[i][j], 0, 0, 0);
-                                if constexpr (!PK)
-                                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[u][i], xl[slot][j], acc[i][j], 0, 0, 0);
-                            }
-                    }
+                    for (int u = 0; u < SGW; ++u) refill(xh[gg * SGW + u], xl[gg * SGW + u]);
                 }
-#pragma unroll
-                for (int u = 0; u < SG; ++u) refill(xh[gg * SG + u], xl[gg * SG + u]);
             }
+        };
+        // (Only in the kernels for 9-16 rows, and only for one or two tiles: 7B r = 9, 13, 16, where a workgroup's last batch has as many, 1500, 1521, 1551 ->
+        // 1467, 1492, 1527 us for 14 layers; with four tiles 1B r = 13 903 -> 912.  In the kernels for up to eight rows it cost registers and
+        // 0.5-4 %, with two row tiles 2-6 %.)
+        if constexpr (!PK && MT == 1 && NB == kNbWide) {
+            if (nvalid <= 2) k_loop(std::integral_constant<int, 2>{});
+            else k_loop(std::integral_constant<int, NB>{});
+        } else {
+            k_loop(std::integral_constant<int, NB>{});
         }
         if constexpr (CODED) {  // the places that fill the batch's last quad (producer_coded)
             const uint32_t fill = uint32_t(-(nvalid * n_steps)) & 3u;
