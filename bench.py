@@ -665,14 +665,16 @@ def main():
     kbytes = step_bytes(shape, ctx)
     k_ms = sum(ms_each) / max(len(ms_each), 1)
     achieved = kbytes / (k_ms * 1e-3) / 1e9 if k_ms > 0 else 0.0
-    traffic, traffic_src = None, None
+    traffic, traffic_coded, traffic_src = None, None, None
     tpath = os.path.join(ROOT, "profiles", "traffic.json")
     if os.path.exists(tpath):
         try:
-            traffic = json.load(open(tpath)).get(f"{args.shape}:ctx{ctx}:r{r}")
+            # (a step on coded weights moves fewer bytes than whole bf16 weights have: a figure of its own)
+            stored, key = json.load(open(tpath)), f"{args.shape}:ctx{ctx}:r{r}"
+            traffic, traffic_coded = (None, stored.get(key + ":coded")) if rig.tgt.cfg.coded else (stored.get(key), None)
             traffic_src = "stored: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised under profiles/, not measured in this run"
         except Exception:
-            traffic = None
+            traffic = traffic_coded = None
 
     out = {
         "metric": "verified_tokens_per_s",
@@ -697,7 +699,7 @@ def main():
                    "global_batch": 1, "seq_len": ctx, "r": r, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "kernel": "k_verify (whole step, one persistent kernel)", "achieved": achieved,
                      "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_src,
+                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_coded": traffic_coded, "traffic_source": traffic_src,
                      "bytes_per_launch": kbytes, "avg_launch_us": k_ms * 1e3, "launches_timed": len(ms_each)},
         "paper_context": PAPER_CONTEXT,
     }
