@@ -66,8 +66,11 @@ typedef struct card_model_cfg {
     int32_t coded;    /* 1: the packed weights hold a second, coded copy of the matrices behind
                          the first, 12 bits per weight and exact, which verification and draft
                          calls of up to 32 rows read instead: a quarter fewer bytes per step, twice
-                         the memory (card_packed_weight_bytes).  Pack and call with the same
-                         value, or call with 0 on weights packed with 1.  0: no such copy         */
+                         the memory (card_packed_weight_bytes), at most 1007 layers.  Pack and call
+                         with the same value, or call with 0 on weights packed with 1.  Called with 1
+                         on weights of which a matrix was last packed with 0, verification reports
+                         accepted_len = -1 and draft calls no candidates; nothing behind the whole
+                         weights is read then.  0: no such copy                                  */
 } card_model_cfg;
 
 /* Tensors of the canonical (caller-side) weight set. Matrices are bf16, row-major

@@ -246,7 +246,6 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
         a.c_layer_stride = L.c_layer_stride;
         a.c_code_off = L.c_code_off;
         a.c_lm_code_off = L.c_lm_code_off;
-        a.c_stamp = reinterpret_cast<const uint32_t*>(a.cbase + L.c_stamp_off);
         const auto desc = [&](CodedDesc c, const MatDesc& m) {
             c.fl_run = flag_run_words(m.Nt, m.Ks, m.NB, grid);
             c.fl2_run = grouped_run_words(m.Nt, m.Ks, grid);
@@ -761,10 +760,12 @@ int card_weights_pack_tensor(const card_model_cfg* cfg, int32_t tensor, int32_t 
         a.t0 = half ? 0 : prow0 / 16;
         a.tiles = half ? m.Nt : n_rows / 16;
         a.stamp = reinterpret_cast<uint32_t*>(pb + L.stamp_off);
+        const int slot = per_layer ? layer : cfg->n_layers;
+        if (slot < kCopySlots) a.copy_word = a.stamp + kCopyWord + slot / 4;
+        a.copy_bit = 1u << (slot % 4 * 8 + which);
         if (cfg->coded) {
             uint32_t* code = reinterpret_cast<uint32_t*>(clb + (per_layer ? L.c_code_off : L.c_lm_code_off));
             a.planes = clb + c.off;
-            a.coded_stamp = reinterpret_cast<uint32_t*>(cb + L.c_stamp_off);
             a.fl = reinterpret_cast<unsigned long long*>(clb + (map == MAP_UP ? c.fl2 : c.fl));
             // (only grids that can take it in groups: elsewhere a run of the grouped order has no room of its own)
             if (tensor == CARD_T_WD && (m.Nt & 3) == 0 && ((a.nwg & 7) == 0 || m.Nt <= a.nwg))

@@ -16,7 +16,6 @@ constexpr int kKvBlock = 16;
 constexpr int kNbQkv = 2, kNbOne = 1, kNbWide = 8;
 constexpr int kFlagCopies = 32;  // copies of the barrier flags (256 words each): pollers spread over them
 constexpr uint32_t kStampMagic = 0x43415244u;  // "CARD"
-constexpr uint32_t kCodedMagic = 0x43415245u;  // stamp of the coded copy
 constexpr uint32_t kWsMagic = 0x57534b31u;     // workspace control words initialised ("WSK1"), word kBarMagic
 // words of the barrier block: [1] exit counter, [2] error flag, [3] barrier epoch, [4] magic
 constexpr int kBarExit = 1, kBarError = 2, kBarEpoch = 3, kBarMagic = 4;
@@ -70,6 +69,19 @@ CARD_HD inline int64_t stream_frag_index(int32_t Nt, int32_t Ks, int32_t NB, int
 }
 
 // ---- the coded copy of the matrices (card_model_cfg.coded) -----------------------------------------------
+// Which tensors the copy holds stands in the stamp block, which every blob has: from word kCopyWord on a byte per layer, bit i for
+// tensor i of CodeTensor, and behind the last layer one for the vocabulary head (bit 0).  Packing a tensor sets its bit or, without a copy, clears
+// it, whatever the memory held before; so once everything has been packed the bits are right.  Steps on the copy need all of them.
+constexpr int kCopyWord = 4, kCopySlots = (256 - kCopyWord) * 4;  // (the block has 256 words)
+CARD_HD inline int32_t copy_words(int32_t n_layers) { return n_layers / 4 + 1; }
+CARD_HD inline uint32_t copy_bits_needed(int32_t n_layers, int32_t word) {
+    uint32_t need = 0;
+    for (int32_t b = 0; b < 4; ++b) {
+        const int32_t slot = word * 4 + b;
+        need |= (slot < n_layers ? 0x7fu : slot == n_layers ? 1u : 0u) << (8 * b);
+    }
+    return need;
+}
 // The verify kernel's steps are bound by the bytes of the weights, and of a bf16 weight's sixteen bits four are nearly always
 // known: weights, trained or normally distributed, spread over few exponents.  A coded matrix holds its fragments (in stream order, n = Nt * Ks of
 // them) in three planes:
@@ -137,9 +149,9 @@ struct Layout {
     size_t embed_off, lm_off, g_final_off, stamp_off, layer0_off, layer_stride, weight_bytes;
     MatDesc qkv, wo, gu, wd, lm;  // layer matrices relative to the layer base; lm absolute
     size_t g_attn_off, g_ffn_off; // relative to the layer base
-    // coded copy: where it begins in the blob (behind everything else), from there: the vocabulary head's planes and code block, the stamp, the layers
+    // coded copy: where it begins in the blob (behind everything else), from there: the vocabulary head's planes and code block, the layers
     CodedDesc c_qkv, c_wo, c_gu, c_wd, c_lm;
-    size_t coded_off, c_stamp_off, c_lm_code_off, c_layer0_off, c_layer_stride, c_code_off;  // c_code_off: in a layer
+    size_t coded_off, c_lm_code_off, c_layer0_off, c_layer_stride, c_code_off;  // c_code_off: in a layer
     size_t ws_bytes;
     // workspace of the persistent kernel (byte offsets) and strides in elements
     size_t m_xres_off, m_xfrag_off, m_ss_off, m_qfrag_off, m_attfrag_off, m_actfrag_off, m_apart_off, m_bar_off,
@@ -177,6 +189,7 @@ inline bool cfg_valid(const card_model_cfg* c) {
     if (!(c->rope_theta > 0.f) || !(c->rms_eps >= 0.f)) return false;
     if (c->grid_wgs < 0 || c->grid_wgs > 256) return false;
     if (c->coded != 0 && c->coded != 1) return false;
+    if (c->coded && c->n_layers >= kCopySlots) return false;
     return true;
 }
 
@@ -192,7 +205,7 @@ inline Layout make_layout(const card_model_cfg* c) {
     off = align_up(off + L.lm.bytes(), 1024);
     L.g_final_off = off;
     off = align_up(off + size_t(d) * 4, 1024);
-    L.stamp_off = off;  // {magic, grid size the stream order was laid out for}
+    L.stamp_off = off;  // {magic, grid size the stream order was laid out for}; from word kCopyWord on: what the coded copy holds
     off += 1024;
     L.layer0_off = off;
     size_t lo = 0;
@@ -226,8 +239,7 @@ inline Layout make_layout(const card_model_cfg* c) {
         };
         L.c_lm = coded(L.lm, 1, false);
         L.c_lm_code_off = at;
-        L.c_stamp_off = at + 1024;
-        L.c_layer0_off = at + 2048;
+        L.c_layer0_off = at + 1024;
         at = 0;
         L.c_qkv = coded(L.qkv, 1, false);
         L.c_wo = coded(L.wo, 1, false);

@@ -19,9 +19,9 @@ struct PackArgs {
     int32_t map, head_dim;
     int32_t t0, tiles;  // tiles of the matrix that hold rows of this tensor
     uint32_t* stamp;    // {magic, grid size}
-    // coded copy (or null): its planes and its stamp, the bits of this tensor's fragments in stream order and in grouped order (or null)
+    uint32_t *copy_word, copy_bit;  // where the stamp block says that the coded copy holds this tensor (or null)
+    // coded copy (or null): its planes, the bits of this tensor's fragments in stream order and in grouped order (or null)
     char* planes;
-    uint32_t* coded_stamp;
     unsigned long long *fl, *gfl;
     uint32_t *base4, *counts;  // base in all four bytes; 128 counters
 };
@@ -33,10 +33,9 @@ __global__ __launch_bounds__(128) void k_pack_begin(PackArgs a) {
     if (i == 0) {
         a.stamp[0] = kStampMagic;
         a.stamp[1] = uint32_t(a.nwg);
-        if (a.planes) {
-            a.coded_stamp[0] = kCodedMagic;
-            a.coded_stamp[1] = uint32_t(a.nwg);
-        }
+        // (a word is shared with other tensors, which may be packed at the same time)
+        if (a.planes) atomicOr(a.copy_word, a.copy_bit);
+        else if (a.copy_word) atomicAnd(a.copy_word, ~a.copy_bit);
     }
 }
 // Coded copy: weights counted by bits 8-14 (of large tensors an eighth, spread over all of it: it is the usual ones that count), and

@@ -65,7 +65,6 @@ struct MegaArgs {
     size_t embed_off, g_final_off, layer0_off, layer_stride, g_attn_off, g_ffn_off;
     MatDesc qkv, wo, gu, wd, lm;  // lm.off absolute, the others relative to the layer base
     const char* cbase;            // the coded copy of the matrices, or null
-    const uint32_t* c_stamp;
     size_t c_layer0_off, c_layer_stride, c_code_off, c_lm_code_off;
     CodedDesc c_qkv, c_wo, c_gu, c_wd, c_lm;
     __bf16* kpool;
@@ -135,7 +134,7 @@ struct __align__(16) MegaSmem {
     uint32_t head[kMegaWaves];   // fragments popped so far (written by the consumer)
     uint32_t cbar;               // arrivals at the consumer barrier (monotonic)
     int failed;
-    int ws_ok;
+    int usable;  // the workspace has been prepared, the weights are what the kernel reads
     uint32_t epoch;
     int pred[kMaxR + 1];
     int row_page[kMaxR];  // page that row m's key and value go to
@@ -332,8 +331,17 @@ __device__ __forceinline__ PhasePlan plan_phase_grouped(const bf16x8* w, int Nt,
 
 // weights laid out for another grid size would stream in the wrong order
 __device__ __forceinline__ bool bad_stamp(const MegaArgs& a) {
-    if (a.cbase && (a.c_stamp[0] != kCodedMagic || a.c_stamp[1] != uint32_t(a.grid))) return true;
     return a.stamp[0] != kStampMagic || a.stamp[1] != uint32_t(a.grid);
+}
+
+// Whether the blob holds all of the coded copy (a wavefront's question): one that does not may end where the copy would begin.
+__device__ __forceinline__ bool copy_complete(const MegaArgs& a, int lane) {
+    bool missing = false;
+    for (int i = lane; i < copy_words(a.L); i += 64) {
+        const uint32_t need = copy_bits_needed(a.L, i);
+        missing = missing || (a.stamp[kCopyWord + i] & need) != need;
+    }
+    return __builtin_amdgcn_ballot_w64(missing) == 0ull;
 }
 
 enum StreamPhase { SP_QKV = 0, SP_WO = 1, SP_GU = 2, SP_WD = 3 };
@@ -1881,8 +1889,10 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
         sm.failed = 0;
         sm.cbar = 0;
         sm.epoch = __hip_atomic_load(&a.bar[kBarEpoch], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sm.ws_ok = __hip_atomic_load(&a.bar[kBarMagic], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kWsMagic;
+        sm.usable = __hip_atomic_load(&a.bar[kBarMagic], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kWsMagic;
     }
+    if constexpr (CODED)  // (a wavefront's own LDS accesses stay in order)
+        if (wave == 0 && !copy_complete(a, lane)) sm.usable = 0;
     if (tid < kMegaWaves) sm.tail[tid] = sm.head[tid] = 0;
     if (tid < kMaxR) {
         sm.wg_best[tid] = 0ull;
@@ -1890,13 +1900,23 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(2
     }
     __syncthreads();  // the only hardware barrier: producers and consumers part ways here
     // A workspace whose control words were never prepared could hold flags that let barriers fall
-    // through: every workgroup reads the same word, so all of them leave, and the step fails.
-    if (!sm.ws_ok) {
+    // through: every workgroup reads the same word, so all of them leave, and the step fails.  Likewise without a coded copy (whose
+    // words no step writes): the weights may end where the producers would begin to read.
+    if (__builtin_expect(!sm.usable, 0)) {
         if (wg == 0 && tid == 0) {
             a.out->accepted_len = -1;
             a.out->correction_token = -1;
             a.out->kv_first_slot = a.ctx_len;
             a.out->kv_count = 0;
+            if constexpr (CODED) {
+                if (a.row_argmax)
+                    for (int i = 0; i < a.r; ++i) a.row_argmax[i] = -1;
+                if constexpr (DR)
+                    for (int i = 0; i < a.r * a.topk; ++i) {
+                        a.topk_tok[i] = -1;
+                        a.topk_prob[i] = 0.f;
+                    }
+            }
         }
         return;
     }

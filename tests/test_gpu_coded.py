@@ -95,3 +95,58 @@ def test_a_blob_without_the_copy_is_reported(monkeypatch):
     assert tgt.verify(0, -1, [1, 2, 3])["accepted_len"] >= 0
     tgt.cfg.coded = 1
     assert tgt.verify(0, -1, [1, 2, 3])["accepted_len"] == -1
+
+
+def _refused(tgt):
+    """A step and a draft call both end at once: no token, nothing written to the cache."""
+    tgt.k_pages.fill_(0x5A)
+    res = tgt.verify(0, -1, [1, 2, 3])
+    lv = tgt.draft_level(0, [1, 2], [0, 0], 0, [[1], [2]], 0, 3)
+    return ((res["accepted_len"], res["correction_token"], res["kv_count"]) == (-1, -1, 0) and res["row_argmax"] == [-1] * 3
+            and bool((lv["topk_tokens"] == -1).all()) and not bool(lv["topk_probs"].any()) and bool((tgt.k_pages == 0x5A).all()))
+
+
+def test_weights_that_end_where_the_copy_would_begin_are_reported(monkeypatch):
+    """Packed without the copy into a blob that has no room for one: the kernel must look before it streams."""
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd import runtime
+
+    monkeypatch.setattr(runtime, "CODED_MIN_LAYER_BYTES", 0)
+    shape = SHAPES["wide"]
+    tgt = card.Target(shape, 160, pool_fill=0)
+    tgt.packed.fill_(0xFF)  # (as memory that held a blob with a copy may)
+    whole = card.card_packed_weight_bytes(card.make_cfg(shape, 160))
+    assert whole < tgt.packed.numel()
+    tgt.packed = tgt.packed[:whole].clone()
+    tgt.cfg.coded = 0
+    _pack(tgt, shape, "normal", 3)
+    assert tgt.verify(0, -1, [1, 2, 3])["accepted_len"] >= 0
+    tgt.cfg.coded = 1
+    assert _refused(tgt)
+    tgt.cfg.coded = 0  # the same object keeps working
+    assert tgt.verify(0, -1, [1, 2, 3])["accepted_len"] >= 0
+
+
+@pytest.mark.parametrize("name,layer", [("wq", 0), ("wu", 1), ("wd", 4), ("lm_head", 0)])
+def test_a_tensor_packed_without_its_copy_ends_the_copy(monkeypatch, name, layer):
+    """... until that tensor is packed with it again, whatever else is packed in between."""
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd import runtime
+
+    monkeypatch.setattr(runtime, "CODED_MIN_LAYER_BYTES", 0)
+    shape = SHAPES["odd"].with_layers(5)
+    tgt = card.Target(shape, 160, pool_fill=0)
+    _pack(tgt, shape, "normal", 7)
+    before = _run(tgt, 1, 8, 41)
+    d, f = shape.d_model, shape.d_ffn
+    rows, cols = {"wq": (shape.q_dim, d), "wu": (f, d), "wd": (d, f), "lm_head": (shape.vocab, d)}[name]
+    new = _weights("normal", rows, cols, 999)
+    tgt.cfg.coded = 0
+    tgt.pack(name, layer, new)
+    tgt.cfg.coded = 1
+    assert _refused(tgt)
+    tgt.pack("wk", 0, _weights("normal", shape.kv_dim, d, 8))
+    assert _refused(tgt)
+    tgt.pack(name, layer, new)
+    now, whole = _run(tgt, 1, 8, 41), _run(tgt, 0, 8, 41)
+    assert all(torch.equal(a, b) for a, b in zip(now, whole)) and not torch.equal(now[0], before[0])
