@@ -27,7 +27,7 @@ PROMPT_MIN_TOKENS = 33
 LEVEL_ONE_PASS_ROWS = 32
 
 # A Target keeps a coded copy of its weights beside them (a quarter fewer bytes per step, twice the memory) where half of the GPU's
-# memory stays free then: a model that needs the memory, or shares it with large ones, keeps to the weights alone.  Steps are faster
+# memory stays free beside all that the Target takes: a model that needs the memory, or shares it with large ones, keeps to the weights alone.  Steps are faster
 # with it at every size, r = 8 us without / with: 2 layers of 1.4 MiB 75 / 73, 8 of 5.4 MiB 283 / 279, 8 of 21 MiB 317 / 309, 16 of 116 MiB 902 / 826, 32 of 416 MiB
 # 3206 / 2784.  Layers below this size gain 1-3 % and go without: a small model's Target keeps the configuration that make_cfg gives.
 CODED_MIN_LAYER_BYTES = 4 << 20
@@ -63,9 +63,11 @@ class Target:
     """The target model's device state: packed weights, workspace, paged KV cache."""
 
     def __init__(self, shape, max_ctx: int, max_r: int = 32, device: str = "cuda:0",
-                 page_order: Optional[Sequence[int]] = None, grid_wgs: int = 0, pool_fill: Optional[int] = None):
+                 page_order: Optional[Sequence[int]] = None, grid_wgs: int = 0, pool_fill: Optional[int] = None,
+                 coded: Optional[bool] = None):
         """pool_fill: byte value the KV page pools start with (tests; None = whatever torch.empty
-        hands out)."""
+        hands out).  coded: whether to keep a coded copy of the weights beside them (None: where there is room for it, see
+        CODED_MIN_LAYER_BYTES; say which where packed weights are to fit another Target of the shape)."""
         if not torch.cuda.is_available():
             raise RuntimeError("libcard needs a GPU: there is no CPU path")
         self.device = torch.device(device)
@@ -73,15 +75,12 @@ class Target:
         wbytes = B.card_packed_weight_bytes(self.cfg)
         if wbytes == 0:
             raise B.CardError(B.CARD_EINVAL, "card_packed_weight_bytes")
-        self.packed = self._take_coded(wbytes)
-        if self.packed is None:
-            self.packed = torch.empty(wbytes, dtype=torch.uint8, device=self.device)
-        self.workspace = torch.empty(B.card_workspace_bytes(self.cfg), dtype=torch.uint8, device=self.device)
-        _check(B.card_workspace_init(self.cfg, self.workspace, self._stream()), "card_workspace_init")
         self.n_pages = self.cfg.max_ctx // 16
-        pool = B.card_kv_pool_bytes(self.cfg, self.n_pages)
-        self.k_pages = torch.empty(pool, dtype=torch.uint8, device=self.device)
-        self.v_pages = torch.empty(pool, dtype=torch.uint8, device=self.device)
+        self.cfg.coded = int(self._room_for_copy(wbytes) if coded is None else coded)
+        if self.cfg.coded == 0 or not self._allocate(may_fail=coded is None):
+            self.cfg.coded = 0
+            self._allocate()
+        _check(B.card_workspace_init(self.cfg, self.workspace, self._stream()), "card_workspace_init")
         if pool_fill is not None:
             self.k_pages.fill_(pool_fill)
             self.v_pages.fill_(pool_fill)
@@ -93,21 +92,31 @@ class Target:
         self.row_argmax = torch.zeros(32, dtype=torch.int32, device=self.device)
         self.cand = torch.zeros(32, dtype=torch.int32, device=self.device)
 
-    def _take_coded(self, wbytes: int) -> Optional[torch.Tensor]:
-        """Room for the packed weights with their coded copy (cfg.coded is then set), or None."""
+    def _bytes(self) -> List[int]:
+        """Of the packed weights, the workspace and the two page pools."""
+        pool = B.card_kv_pool_bytes(self.cfg, self.n_pages)
+        return [B.card_packed_weight_bytes(self.cfg), B.card_workspace_bytes(self.cfg), pool, pool]
+
+    def _room_for_copy(self, wbytes: int) -> bool:
         if wbytes < CODED_MIN_LAYER_BYTES * self.cfg.n_layers:
-            return None
+            return False
         self.cfg.coded = 1
-        both = B.card_packed_weight_bytes(self.cfg)
+        need = self._bytes()
         free, total = torch.cuda.mem_get_info(self.device)
         free += torch.cuda.memory_reserved(self.device) - torch.cuda.memory_allocated(self.device)
-        if both > 0 and free - both >= total // 2:
-            try:
-                return torch.empty(both, dtype=torch.uint8, device=self.device)
-            except torch.cuda.OutOfMemoryError:
-                pass
-        self.cfg.coded = 0
-        return None
+        return need[0] > 0 and free - sum(need) >= total // 2
+
+    def _allocate(self, may_fail: bool = False) -> bool:
+        buf: List[Optional[torch.Tensor]] = []
+        try:
+            for n in self._bytes():
+                buf.append(torch.empty(n, dtype=torch.uint8, device=self.device))
+        except torch.cuda.OutOfMemoryError:
+            if not may_fail:
+                raise
+            return False
+        self.packed, self.workspace, self.k_pages, self.v_pages = buf
+        return True
 
     # -- weights
     def pack(self, name: str, layer: int, src: torch.Tensor) -> None:

@@ -150,3 +150,55 @@ def test_a_tensor_packed_without_its_copy_ends_the_copy(monkeypatch, name, layer
     tgt.pack(name, layer, new)
     now, whole = _run(tgt, 1, 8, 41), _run(tgt, 0, 8, 41)
     assert all(torch.equal(a, b) for a, b in zip(now, whole)) and not torch.equal(now[0], before[0])
+
+
+def _sizes(max_ctx):
+    """Bytes of a Target of the small shape with the copy: packed weights; workspace and page pools."""
+    import paper_2508_04462_amd as card
+
+    cfg = card.make_cfg(SHAPES["wide"], max_ctx)
+    cfg.coded = 1
+    return card.card_packed_weight_bytes(cfg), card.card_workspace_bytes(cfg) + 2 * card.card_kv_pool_bytes(cfg, max_ctx // 16)
+
+
+def test_the_copy_needs_room_beside_everything_that_the_target_takes(monkeypatch):
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd import runtime
+
+    monkeypatch.setattr(runtime, "CODED_MIN_LAYER_BYTES", 0)
+    monkeypatch.setattr(torch.cuda, "memory_reserved", lambda *a: 0)
+    monkeypatch.setattr(torch.cuda, "memory_allocated", lambda *a: 0)
+    both, rest = _sizes(160)
+    total = 1 << 36
+    for free, coded in ((total // 2 + both + rest, 1), (total // 2 + both + rest - 1, 0), (total // 2 + both, 0)):
+        monkeypatch.setattr(torch.cuda, "mem_get_info", lambda *a: (free, total))
+        tgt = card.Target(SHAPES["wide"], 160)
+        assert tgt.cfg.coded == coded
+        assert tgt.packed.numel() == card.card_packed_weight_bytes(tgt.cfg)
+
+
+@pytest.mark.parametrize("nth", [0, 1, 2, 3])
+def test_where_memory_runs_out_the_target_does_without_the_copy(monkeypatch, nth):
+    import paper_2508_04462_amd as card
+    from paper_2508_04462_amd import runtime
+
+    monkeypatch.setattr(runtime, "CODED_MIN_LAYER_BYTES", 0)
+    both, _ = _sizes(160)
+    empty, taken = torch.empty, []
+
+    def short(*a, **kw):
+        if len(taken) <= nth and kw.get("dtype") == torch.uint8:
+            taken.append(a[0])
+            if len(taken) > nth:
+                raise torch.cuda.OutOfMemoryError("out of memory")
+        return empty(*a, **kw)
+
+    monkeypatch.setattr(torch, "empty", short)
+    tgt = card.Target(SHAPES["wide"], 160)
+    assert taken[0] == both and len(taken) == nth + 1
+    assert tgt.cfg.coded == 0 and tgt.packed.numel() == card.card_packed_weight_bytes(tgt.cfg) < both
+    # asked for, it is taken or refused; not wanted, it is left out
+    assert card.Target(SHAPES["wide"], 160, coded=True).cfg.coded == 1 and card.Target(SHAPES["wide"], 160, coded=False).cfg.coded == 0
+    taken.clear()
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        card.Target(SHAPES["wide"], 160, coded=True)
