@@ -49,7 +49,7 @@ const char* card_strerror(int status);
  * (the LLaMA / Qwen families named in Experimental Setup, "Models and Datasets").
  * Constraints: head_dim in {64, 128}; d_model a multiple of 64; d_ffn a multiple of 8;
  * n_q_heads a multiple of n_kv_heads; kv_block == 16; max_ctx a positive multiple of 16;
- * 1 <= max_r <= 32; every packed matrix below 4 GiB; 0 <= grid_wgs <= 256.
+ * 1 <= max_r <= 32; every packed matrix below 4 GiB; 0 <= grid_wgs <= 256 (without CARD_CODED).
  * ---------------------------------------------------------------------------------------- */
 typedef struct card_model_cfg {
     int32_t n_layers, d_model, n_q_heads, n_kv_heads, head_dim, d_ffn, vocab;
@@ -62,16 +62,17 @@ typedef struct card_model_cfg {
                          caller runs beside it (the draft model of the paper runs in parallel
                          with the target: CARD Design, first paragraph).  The packed weight
                          order depends on it: pack and verify with the same value.  (Workgroups
-                         of either that a small model has no work for are not launched.)      */
-    int32_t coded;    /* 1: the packed weights hold a second, coded copy of the matrices behind
-                         the first, 12 bits per weight and exact, which verification and draft
-                         calls of up to 32 rows read instead: a quarter fewer bytes per step, twice
-                         the memory (card_packed_weight_bytes), at most 1007 layers.  Pack and call
-                         with the same value, or call with 0 on weights packed with 1.  Called with 1
-                         on weights of which a matrix was last packed with 0, verification reports
-                         accepted_len = -1 and draft calls no candidates; nothing behind the whole
-                         weights is read then.  0: no such copy                                  */
+                         of either that a small model has no work for are not launched.)
+                         With CARD_CODED added, coded weights:                                  */
 } card_model_cfg;
+
+/* Added to card_model_cfg.grid_wgs: the packed weights hold a second, coded copy of the matrices behind
+ * the first, 12 bits per weight and exact, which verification and draft calls of up to 32 rows read
+ * instead: a quarter fewer bytes per step, twice the memory (card_packed_weight_bytes), at most 1007
+ * layers.  Pack and call with it, or call without it on weights packed with it.  Called with it on
+ * weights of which a matrix was last packed without, verification reports accepted_len = -1 and draft
+ * calls no candidates; nothing behind the whole weights is read then. */
+#define CARD_CODED (1 << 30)
 
 /* Tensors of the canonical (caller-side) weight set. Matrices are bf16, row-major
  * [out_features][in_features]; gains are fp32 vectors of d_model entries. */

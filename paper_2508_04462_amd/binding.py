@@ -10,6 +10,8 @@ lib_path = os.path.join(_PKG, "libcard.so")
 
 CARD_OK, CARD_EINVAL, CARD_ERANGE, CARD_ECAPACITY, CARD_EDEVICE, CARD_ESTALE, CARD_ETOOBIG = 0, -1, -2, -3, -4, -5, -6
 
+CARD_CODED = 1 << 30  # in the header's grid_wgs
+
 TENSOR_IDS = {
     "embed": 0, "wq": 1, "wk": 2, "wv": 3, "wo": 4, "wg": 5, "wu": 6, "wd": 7,
     "lm_head": 8, "g_attn": 9, "g_ffn": 10, "g_final": 11,
@@ -27,9 +29,25 @@ class CardModelCfg(C.Structure):
         ("n_layers", C.c_int32), ("d_model", C.c_int32), ("n_q_heads", C.c_int32),
         ("n_kv_heads", C.c_int32), ("head_dim", C.c_int32), ("d_ffn", C.c_int32),
         ("vocab", C.c_int32), ("rope_theta", C.c_float), ("rms_eps", C.c_float),
-        ("kv_block", C.c_int32), ("max_ctx", C.c_int32), ("max_r", C.c_int32), ("grid_wgs", C.c_int32),
-        ("coded", C.c_int32),
+        ("kv_block", C.c_int32), ("max_ctx", C.c_int32), ("max_r", C.c_int32), ("grid", C.c_int32),
     ]
+
+    # the header's grid_wgs in its two parts
+    @property
+    def grid_wgs(self) -> int:
+        return self.grid if self.grid < 0 else self.grid & ~CARD_CODED
+
+    @grid_wgs.setter
+    def grid_wgs(self, n: int) -> None:
+        self.grid = n | (CARD_CODED if self.coded else 0)
+
+    @property
+    def coded(self) -> int:
+        return int(self.grid >= 0 and self.grid & CARD_CODED != 0)
+
+    @coded.setter
+    def coded(self, on: int) -> None:
+        self.grid = self.grid_wgs | (CARD_CODED if on else 0)
 
 
 class CardKV(C.Structure):

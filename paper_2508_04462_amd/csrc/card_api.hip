@@ -83,9 +83,9 @@ int cu_count() {
 int grid_size(const card_model_cfg* cfg) {
     const int cus = cu_count();
     int n = cus > 256 ? 256 : cus;
-    if (cfg && cfg->grid_wgs > 0) {
-        if (cfg->grid_wgs > n) return 0;
-        n = cfg->grid_wgs;
+    if (cfg && cfg_grid(cfg) > 0) {
+        if (cfg_grid(cfg) > n) return 0;
+        n = cfg_grid(cfg);
     }
     return n;
 }
@@ -240,7 +240,7 @@ int verify_impl(const card_model_cfg* cfg, const void* packed, const card_kv* kv
     a.gu = L.gu;
     a.wd = L.wd;
     a.lm = L.lm;
-    if (cfg->coded) {
+    if (cfg_coded(cfg)) {
         a.cbase = a.wbase + L.coded_off;
         a.c_layer0_off = L.c_layer0_off;
         a.c_layer_stride = L.c_layer_stride;
@@ -763,7 +763,7 @@ int card_weights_pack_tensor(const card_model_cfg* cfg, int32_t tensor, int32_t 
         const int slot = per_layer ? layer : cfg->n_layers;
         if (slot < kCopySlots) a.copy_word = a.stamp + kCopyWord + slot / 4;
         a.copy_bit = 1u << (slot % 4 * 8 + which);
-        if (cfg->coded) {
+        if (cfg_coded(cfg)) {
             uint32_t* code = reinterpret_cast<uint32_t*>(clb + (per_layer ? L.c_code_off : L.c_lm_code_off));
             a.planes = clb + c.off;
             a.fl = reinterpret_cast<unsigned long long*>(clb + (map == MAP_UP ? c.fl2 : c.fl));
@@ -774,7 +774,7 @@ int card_weights_pack_tensor(const card_model_cfg* cfg, int32_t tensor, int32_t 
             a.counts = code + kCodeCounts + 128 * which;
         }
         hipLaunchKernelGGL(k_pack_begin, dim3(1), dim3(128), 0, st, a);
-        if (cfg->coded) {
+        if (cfg_coded(cfg)) {
             const int64_t pieces = (int64_t(src_rows) * m.K / 8 + 255) / 256;
             hipLaunchKernelGGL(k_pack_count, dim3(uint32_t(std::min<int64_t>(pieces, 1024))), dim3(256), 0, st, a);
             hipLaunchKernelGGL(k_pack_base, dim3(1), dim3(128), 0, st, a);

@@ -68,7 +68,7 @@ CARD_HD inline int64_t stream_frag_index(int32_t Nt, int32_t Ks, int32_t NB, int
     return r.first + int64_t(b) * NB * (r.s1 - r.s0) + int64_t(s - r.s0) * nv + i;
 }
 
-// ---- the coded copy of the matrices (card_model_cfg.coded) -----------------------------------------------
+// ---- the coded copy of the matrices (CARD_CODED) -----------------------------------------------
 // Which tensors the copy holds stands in the stamp block, which every blob has: from word kCopyWord on a byte per layer, bit i for
 // tensor i of CodeTensor, and behind the last layer one for the vocabulary head (bit 0).  Packing a tensor sets its bit or, without a copy, clears
 // it, whatever the memory held before; so once everything has been packed the bits are right.  Steps on the copy need all of them.
@@ -175,6 +175,9 @@ inline MatDesc make_mat(size_t off, int32_t N, int32_t K, int32_t NB) {
     return m;
 }
 
+inline int32_t cfg_grid(const card_model_cfg* c) { return c->grid_wgs & ~CARD_CODED; }
+inline bool cfg_coded(const card_model_cfg* c) { return (c->grid_wgs & CARD_CODED) != 0; }
+
 inline bool cfg_valid(const card_model_cfg* c) {
     if (!c) return false;
     if (c->n_layers <= 0 || c->d_model <= 0 || c->n_q_heads <= 0 || c->n_kv_heads <= 0 || c->d_ffn <= 0 ||
@@ -187,9 +190,8 @@ inline bool cfg_valid(const card_model_cfg* c) {
     if (c->max_ctx <= 0 || c->max_ctx % kKvBlock) return false;
     if (c->max_r < 1 || c->max_r > kMaxR) return false;
     if (!(c->rope_theta > 0.f) || !(c->rms_eps >= 0.f)) return false;
-    if (c->grid_wgs < 0 || c->grid_wgs > 256) return false;
-    if (c->coded != 0 && c->coded != 1) return false;
-    if (c->coded && c->n_layers >= kCopySlots) return false;
+    if (cfg_grid(c) < 0 || cfg_grid(c) > 256) return false;
+    if (cfg_coded(c) && c->n_layers >= kCopySlots) return false;
     return true;
 }
 
@@ -248,7 +250,7 @@ inline Layout make_layout(const card_model_cfg* c) {
         L.c_code_off = at;
         at = align_up(at + (kCodeCounts + 7 * 128) * 4, 1024);
         L.c_layer_stride = at;
-        if (c->coded) L.weight_bytes = L.coded_off + L.c_layer0_off + size_t(c->n_layers) * L.c_layer_stride;
+        if (cfg_coded(c)) L.weight_bytes = L.coded_off + L.c_layer0_off + size_t(c->n_layers) * L.c_layer_stride;
     }
     // the kernel addresses a matrix with 32-bit byte offsets
     constexpr size_t k4G = size_t(1) << 32;

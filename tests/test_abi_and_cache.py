@@ -402,3 +402,26 @@ def test_planted_agreement_is_per_text_index_and_follows_every_on_path_parent():
     first = [half(i, 1, [1, 2], [0, 0], 0, [truth[i - 1]])[0] for i in range(1, 30)]
     again = [half(i, 1, [1, 2], [0, 0], 0, [truth[i - 1]])[0] for i in range(1, 30)]
     assert first == again and 5 < sum(t[0] == truth[i] for i, t in zip(range(1, 30), first)) < 25
+
+
+def test_the_model_description_of_older_programs_is_read_as_it_was():
+    """Thirteen 32-bit fields, whatever lies behind them; the coded copy is asked for by a flag in the last one."""
+    shape = ci.SHAPES["tiny"]
+    want = card.make_cfg(shape, 160, grid_wgs=64)
+    assert ctypes.sizeof(card.CardModelCfg) == 13 * 4
+    size = card.lib.card_packed_weight_bytes
+    for garbage in (0, 1, 2, -1, 0x40000000):
+        mem = (ctypes.c_int32 * 20)(*([garbage] * 20))
+        ctypes.memmove(mem, ctypes.byref(want), 13 * 4)
+        assert size(ctypes.cast(mem, size.argtypes[0])) == card.card_packed_weight_bytes(want) > 0
+    both = card.make_cfg(shape, 160, grid_wgs=64)
+    both.coded = 1
+    assert (both.grid_wgs, both.coded, want.coded) == (64, 1, 0)
+    assert card.card_packed_weight_bytes(both) > 1.9 * card.card_packed_weight_bytes(want) - 2 * shape.vocab * shape.d_model
+    both.grid_wgs = 257
+    assert (both.grid_wgs, both.coded, card.card_packed_weight_bytes(both)) == (257, 1, 0)
+    both.grid_wgs = 8
+    both.coded = 0
+    assert (both.grid_wgs, both.coded) == (8, 0)
+    for bad in (-1, 257, 1 << 29, -(1 << 31), (1 << 30) + 257):
+        assert card.card_packed_weight_bytes(card.make_cfg(shape, 160, grid_wgs=bad)) == 0, bad
