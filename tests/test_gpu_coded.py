@@ -11,6 +11,9 @@ SHAPES = {
     "odd": ci.ModelShape("odd", 2, 320, 5, 5, 64, 264, 1003, ctx=64, r=8),
     # heads of 128, tile counts that are multiples of four (grouped down-projection for more than eight rows)
     "wide": ci.ModelShape("wide", 2, 512, 4, 2, 128, 1416, 2050, ctx=64, r=8),
+    # batches of more fragments than a word has bits, ending off a word's border: gate/up and the vocabulary head (8 tiles x 9 or 10 k-steps), the
+    # down-projection (64 or 65) and the grouped one (4 tiles x 16 or 17)
+    "long": ci.ModelShape("long", 2, 1216, 4, 2, 128, 8264, 2050, ctx=64, r=8),
 }
 
 
@@ -202,3 +205,52 @@ def test_where_memory_runs_out_the_target_does_without_the_copy(monkeypatch, nth
     taken.clear()
     with pytest.raises(torch.cuda.OutOfMemoryError):
         card.Target(SHAPES["wide"], 160, coded=True)
+
+
+@pytest.mark.parametrize("background", ["zeros", "normal"])
+def test_every_bit_pattern_keeps_its_value(background):
+    """A vocabulary head with one row per pattern of sixteen bits, among zeros (its bits are then all that a logit has) or ordinary weights."""
+    import paper_2508_04462_amd as card
+
+    shape = ci.ModelShape("patterns", 1, 256, 4, 4, 64, 256, 65536, ctx=64, r=8)
+    tgt = card.Target(shape, 64, pool_fill=0, coded=True)
+    _pack(tgt, shape, "normal", 11)
+    head = _weights("normal", shape.vocab, shape.d_model, 12) if background == "normal" else torch.zeros(shape.vocab, shape.d_model,
+                                                                                                         dtype=torch.bfloat16, device="cuda")
+    rows = torch.arange(65536, device="cuda")
+    head.view(torch.int16)[rows, rows * 37 % shape.d_model] = torch.where(rows < 32768, rows, rows - 65536).to(torch.int16)
+    tgt.pack("lm_head", 0, head)
+    for r in (1, 8, 13, 32):
+        got = []
+        for coded in (1, 0):
+            tgt.cfg.coded = coded
+            got.append(tgt.verify(0, -1, list(range(1, r + 1)), want_logits=True)["logits"].view(torch.int32))
+        assert torch.equal(got[0], got[1]), (background, r)
+        values = got[0].view(torch.float32)
+        # (NaN where the pattern is one, at the least; almost all others are finite)
+        assert bool(values[:, 0x7F81:0x7FFF].isnan().all()) and float(values.isfinite().float().mean()) > 0.9
+
+
+@pytest.mark.parametrize("name", ["odd", "wide"])
+@pytest.mark.parametrize("n", [12, 20, 60])  # pieces of 8 rows, of up to 16, of up to 32
+def test_pieces_of_a_level_give_the_same_bits(name, n):
+    """Calls of a level side by side, on whole weights and on the coded copy (kernels of their own for each)."""
+    import paper_2508_04462_amd as card
+
+    shape = SHAPES[name]
+    tgt = card.Target(shape, 192, grid_wgs=64, pool_fill=0, coded=True)
+    _pack(tgt, shape, "outliers", 21)
+    tgt.enable_lanes(2)
+    toks = [(37 * i + 5) % shape.vocab for i in range(41 + n)]
+    st, rows = card.card_tree_mask_level(None, [-1] * n, 41, 41, 32, (41 + n - 32 + 31) // 32)
+    assert st == card.CARD_OK
+    out = []
+    for coded in (1, 0):
+        tgt.cfg.coded = coded
+        tgt.k_pages.zero_()
+        tgt.v_pages.zero_()
+        tgt.prefill(toks[:41], chunk=8)
+        lv = tgt.draft_level_wide(41, toks[41:], [41] * n, 41, rows, 32, 5)
+        out.append([x.contiguous().view(torch.uint8).cpu() for x in (lv["topk_tokens"], lv["topk_probs"], tgt.k_pages, tgt.v_pages)])
+        assert bool((lv["topk_tokens"] >= 0).all())
+    assert all(torch.equal(a, b) for a, b in zip(*out))
