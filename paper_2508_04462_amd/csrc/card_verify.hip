@@ -540,7 +540,6 @@ __device__ __forceinline__ void producer(const MegaArgs& a, MegaSmem& sm, int w,
 // per tile of the batch: place u of a quad carries tile u of a k-step.
 typedef const __attribute__((address_space(4))) unsigned long long* ConstWords;  // (scalar loads: written by earlier kernels only)
 typedef const __attribute__((address_space(4))) uint32_t* ConstWord;
-constexpr uint32_t kNoRest = 0xfffffc00u;  // offset behind any matrix (scalar and lane offset are added without wrapping)
 
 template <bool GROUPED>
 __device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, int w, int lane, int wg) {
@@ -625,6 +624,7 @@ __device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, 
             if (nx_ph >= n_ph) {
                 run = 0x7fffffffu;
                 cur_rs = make_rsrc(a.wbase, 0);
+                off_low = off_high = off_rest = n = 0;
                 return;
             }
             const int kind = kind_of(nx_ph);
@@ -682,7 +682,7 @@ __device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, 
             vl += u * 512;
             vh += u * 256;
         }
-        sr = (uint32_t(word) >> u) & 1u ? sr : kNoRest;
+        sr = (uint32_t(word) >> u) & 1u ? sr : n << 10;  // (what the resource's size less the scalar offset leaves room for: nothing)
         const uint2v low = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(cur_rs, vl, int(sl), kAuxNT));
         const uint32_t high = __builtin_amdgcn_raw_buffer_load_b32(cur_rs, vh, int(sh), kAuxNT);
         const uint32_t rest = __builtin_amdgcn_raw_buffer_load_b32(cur_rs, vh, int(sr), kAuxNT);
