@@ -83,7 +83,7 @@ CARD_HD inline uint32_t copy_bits_needed(int32_t n_layers, int32_t word) {
     return need;
 }
 // The verify kernel's steps are bound by the bytes of the weights, and of a bf16 weight's sixteen bits four are nearly always
-// known: weights, trained or normally distributed, spread over few exponents.  A coded matrix holds its fragments (in stream order, n = Nt * Ks of
+// known: weights with a bell-shaped distribution spread over few exponents.  A coded matrix holds its fragments (in stream order, n = Nt * Ks of
 // them) in three planes:
 //   low  512 B at f * 512:                bits 0-7 of the lane's eight weights
 //   high 256 B at n * 512 + f * 256:      four bits each: the sign, and the low three bits c of bits 8-14 less `base`

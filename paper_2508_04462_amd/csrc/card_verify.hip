@@ -898,11 +898,11 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
     const int n_batches = (P.cnt + NB - 1) / NB;
     const int n_steps = P.s1 - P.s0;
     const int n_xb = (n_steps + XD - 1) / XD;
-    const int vtot = n_xb * XD;  // virtual k-steps of one batch (the tail beyond s1 reads zeros)
+    const int vtot = n_xb * XD;  // virtual k-steps of one batch (those beyond s1 stay out of the products)
 
     bf16x8 xh[XD][MT], xl[XD][MT];
-    // Activations of k-steps past the wavefront's share are whatever the buffer holds there (zeros
-    // past its end): the weight fragments of such steps are zero, so they add nothing.
+    // Activations of k-steps past the wavefront's share are whatever the buffer holds there (zeros past its end), and their
+    // weights whatever the FIFO holds: the k-loop leaves such steps out (`u >= nvs`), and nothing else keeps them out of the sums.
     const uint32_t xstep = uint32_t(rp) * 128u;
     auto load_x = [&](uint32_t soff, bf16x8 (&h)[MT], bf16x8 (&l)[MT]) {
 #pragma unroll
@@ -1021,7 +1021,7 @@ __device__ __forceinline__ void gemm_phase(const MegaArgs& a, const PhasePlan& P
                         lds_post(&sm.head[wave], fc.head);
 #pragma unroll
                         for (int u = 0; u < SGW; ++u) {
-                            if (u >= nvs) break;  // (behind the wavefront's share: neither weights nor activations)
+                            if (u >= nvs) break;  // (behind the wavefront's share: weights and activations are undefined)
                             const int slot = gg * SGW + u;
 #pragma unroll
                             for (int i = 0; i < W; ++i)

@@ -29,7 +29,9 @@ LEVEL_ONE_PASS_ROWS = 32
 # A Target keeps a coded copy of its weights beside them (a quarter fewer bytes per step, twice the memory) where half of the GPU's
 # memory stays free beside all that the Target takes: a model that needs the memory, or shares it with large ones, keeps to the weights alone.  Steps are faster
 # with it at every size, r = 8 us without / with: 2 layers of 1.4 MiB 75 / 73, 8 of 5.4 MiB 283 / 279, 8 of 21 MiB 317 / 309, 16 of 116 MiB 902 / 826, 32 of 416 MiB
-# 3206 / 2784.  Layers below this size gain 1-3 % and go without: a small model's Target keeps the configuration that make_cfg gives.
+# 3206 / 2784 (normally distributed weights; 8 layers of the 8B shape with half of the weights zero, where every fragment has a rest: 928 / 928, with 32
+# rows 1126 / 1139).  The limit is on all packed bytes, embedding and vocabulary head included, over the layers.  Models below it would gain as
+# much as those just above it, and go without so that a small model's Target keeps the configuration that make_cfg gives.
 CODED_MIN_LAYER_BYTES = 4 << 20
 
 _LANE_STREAMS: Dict[str, list] = {}
