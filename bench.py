@@ -13,6 +13,10 @@ a `sweep` array with the other synthetic configurations (context lengths 512..32
 shape, the 70B shape at r 4/8/16, the Qwen-7B shape at r 1..32 and its query / verify / correct
 loop against the shared cache at planted acceptance rates 0.3 / 0.6 / 0.9), each with latency,
 tokens/s and the fraction of the HBM roofline.
+
+Bytes and roofline fractions are of the weights as the timed kernel reads them: whole (16 bits each) or
+from their coded copy (12 bits); every entry says which (`weights`).  What the same step would move on
+whole weights stands beside it under names that say so (`bf16_equivalent`): a speed, no bandwidth.
 """
 from __future__ import annotations
 
@@ -112,11 +116,24 @@ def phase_timeline(rig, ctx, r, cand, layer):
     return {"timeline": out, "workload": f"{rig.shape.name} ctx {ctx} r {r}"}
 
 
-def step_bytes(shape, ctx: int) -> int:
-    """Algorithmic HBM bytes of one verify step = one launch of the verify kernel: every bf16
-    weight of the layers and of the vocabulary head read once, plus the bf16 K and V of the
-    context read once (activations and the r new KV rows are below 0.1 % and left out)."""
-    return shape.streamed_weight_bytes() + shape.kv_bytes(ctx)
+def step_bytes(shape, ctx: int, coded: int) -> int:
+    """Algorithmic HBM bytes of one verify step = one launch of the verify kernel: every weight of
+    the layers and of the vocabulary head read once as it is stored (16 bits, 12 in the coded copy),
+    plus the bf16 K and V of the context read once (activations and the r new KV rows are below
+    0.1 % and left out; so are the coded copy's rests, a third of a fragment's bytes again for those that
+    have one, 6 % of them with these weights: 2 % of the step)."""
+    w = shape.streamed_weight_bytes()
+    return (w // 4 * 3 if coded else w) + shape.kv_bytes(ctx)
+
+
+def weights_read(coded: int) -> str:
+    return "coded, 12 bits each" if coded else "whole, 16 bits each"
+
+
+def bf16_equivalent(shape, ctx: int, ms: float) -> dict:
+    """The step's speed in bytes of whole weights, for comparison between steps on either kind."""
+    b = step_bytes(shape, ctx, 0)
+    return {"bytes": b, "gb_per_s": b / (ms * 1e-3) / 1e9}
 
 
 def cpu_baseline(shape, seed: int, ctx: int, r: int, cand):
@@ -287,10 +304,12 @@ def sweep_point(rig, r, steps, kv_kind, planted=True):
     cand_dev = torch.tensor(cands, dtype=torch.int32, device=rig.tgt.device)
     ms, ms_each = rig.time_steps(r, cand_dev, steps, max(3, steps // 4), steps)
     k_ms = sum(ms_each) / len(ms_each)
-    byts = step_bytes(shape, rig.ctx)
+    coded = rig.tgt.cfg.coded
+    byts = step_bytes(shape, rig.ctx, coded)
     return {"shape": shape.name, "ctx": rig.ctx, "r": r, "kv": kv_kind, "candidates": cand_note, "steps": steps,
             "ms_per_step": ms, "kernel_ms": k_ms, "verified_tokens_per_s": r / (ms * 1e-3),
-            "hbm_frac": byts / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes": byts}
+            "hbm_frac": byts / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes": byts, "weights": weights_read(coded),
+            "bf16_equivalent": bf16_equivalent(shape, rig.ctx, k_ms)}
 
 
 def cache_loop(rig, r, p, n_tokens, K=50, width=10):
@@ -503,6 +522,7 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
         n_nodes = len(toks)
         toks, pars, sigma = ntoks, npars, nsigma
     one_pass = lanes > 1 and dr.level_in_one_pass(n_nodes)
+    coded = dr.cfg.coded and not one_pass  # (the pass reads whole weights)
     dr = None
     gc.collect()
     torch.cuda.empty_cache()
@@ -523,10 +543,12 @@ def draft_level_entry(args, quick, probe_levels=0, lanes=1):
     else:
         streams = len(calls)
         rows_issued = sum(8 if r <= 8 else 16 if r <= 16 else 32 for r in calls)
-    how = {"route": "one pass" if one_pass else "calls", "lanes": lanes, "weight_streams_per_level": streams}
+    per_stream = step_bytes(shape, ctx_len, coded)
+    how = {"route": "one pass" if one_pass else "calls", "lanes": lanes, "weight_streams_per_level": streams,
+           "weights": weights_read(coded), "bytes_per_stream": per_stream}
     return {"kind": "draft_level", "draft": shape.name, "ctx": ctx_len, "K": n_nodes, "k": k, **how,
             "ms_per_level": ms, "nodes_per_s": n_nodes / (ms * 1e-3),
-            "hbm_frac": streams * (shape.streamed_weight_bytes() + shape.kv_bytes(ctx_len)) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+            "hbm_frac": streams * per_stream / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             # matrix-pipe work issued: two instructions (high and low activation halves) per weight
             # fragment and 16-row tile, padded rows included, against the dense bf16 peak
             "mfma_tflops_issued": 2 * 2 * rows_issued * params / (ms * 1e-3) / 1e12,
@@ -662,19 +684,19 @@ def main():
         return
 
     ms_per_step, ms_each = rig.time_steps(r, cand_dev, args.steps, args.warmup, min(args.steps, 100))
-    kbytes = step_bytes(shape, ctx)
+    coded = rig.tgt.cfg.coded
+    kbytes = step_bytes(shape, ctx, coded)
     k_ms = sum(ms_each) / max(len(ms_each), 1)
     achieved = kbytes / (k_ms * 1e-3) / 1e9 if k_ms > 0 else 0.0
-    traffic, traffic_coded, traffic_src = None, None, None
+    traffic, traffic_src = None, None
     tpath = os.path.join(ROOT, "profiles", "traffic.json")
     if os.path.exists(tpath):
         try:
-            # (a step on coded weights moves fewer bytes than whole bf16 weights have: a figure of its own)
-            stored, key = json.load(open(tpath)), f"{args.shape}:ctx{ctx}:r{r}"
-            traffic, traffic_coded = (None, stored.get(key + ":coded")) if rig.tgt.cfg.coded else (stored.get(key), None)
-            traffic_src = "stored: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised under profiles/, not measured in this run"
+            traffic = json.load(open(tpath)).get(f"{args.shape}:ctx{ctx}:r{r}" + (":coded" if coded else ""))
         except Exception:
-            traffic = traffic_coded = None
+            traffic = None
+    if traffic is not None:
+        traffic_src = "stored: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised under profiles/, not measured in this run"
 
     out = {
         "metric": "verified_tokens_per_s",
@@ -690,16 +712,17 @@ def main():
         "accepted_tokens_per_s": (r / 2) / (ms_per_step * 1e-3),
         "hbm_fraction_whole_step": kbytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "algorithmic_bytes_per_step": kbytes,
+        "bf16_equivalent": bf16_equivalent(shape, ctx, ms_per_step),
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "bf16",
         "data": "synthetic",
         "config": {"workload": f"{args.shape} verify step, ctx {ctx}, r {r}, planted prefix j cycling 0..{r}",
-                   "global_batch": 1, "seq_len": ctx, "r": r, "parallelism": "single GPU"},
+                   "global_batch": 1, "seq_len": ctx, "r": r, "weights": weights_read(coded), "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "kernel": "k_verify (whole step, one persistent kernel)", "achieved": achieved,
                      "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_coded": traffic_coded, "traffic_source": traffic_src,
+                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_src,
                      "bytes_per_launch": kbytes, "avg_launch_us": k_ms * 1e3, "launches_timed": len(ms_each)},
         "paper_context": PAPER_CONTEXT,
     }

@@ -7,6 +7,8 @@ import sys
 
 import pytest
 
+from card_inputs import SHAPES, ModelShape
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -41,12 +43,24 @@ def test_short_run_prints_one_json_line_with_the_contract_fields(monkeypatch, ca
     assert abs(rf["frac"] - rf["achieved"] / rf["peak"]) < 1e-9
     assert 0.2 < rf["frac"] < 1.0
     assert abs(rf["achieved"] - d["algorithmic_bytes_per_step"] / (rf["avg_launch_us"] * 1e-6) / 1e9) <= 1e-6 * rf["achieved"]
-    assert rf["traffic"] is None or rf["traffic"] >= 0.9 * d["algorithmic_bytes_per_step"]
+    # bytes of the weights as the kernel reads them (12 of 16 bits from the coded copy), and what the counters read for such a step
+    whole = SHAPES["llama8b"].streamed_weight_bytes()
+    coded = d["config"]["weights"].startswith("coded")
+    assert d["algorithmic_bytes_per_step"] == rf["bytes_per_launch"] == whole * (3 if coded else 4) // 4 + SHAPES["llama8b"].kv_bytes(1024)
+    assert d["bf16_equivalent"]["bytes"] == whole + SHAPES["llama8b"].kv_bytes(1024)
+    assert (rf["traffic"] is None) == (rf["traffic_source"] is None)
+    if coded:
+        assert 0.9 * rf["bytes_per_launch"] <= rf["traffic"] <= 1.2 * rf["bytes_per_launch"]
     # the other synthetic configurations ride in the same line
     sw = d["sweep"]
     assert not [e for e in sw if "section" in e], [e for e in sw if "section" in e]  # no section failed
     pts = [e for e in sw if e.get("kind") not in ("cache_loop", "concurrent_loop", "draft_level")]
     assert pts and all(e["ms_per_step"] > 0 and 0.1 < e["hbm_frac"] < 1.0 and e["verified_tokens_per_s"] > 0 for e in pts)
+    for e in pts:
+        frac = e["algorithmic_bytes"] / (e["kernel_ms"] * 1e-3) / 8e12
+        assert abs(e["hbm_frac"] - frac) <= 1e-9 * frac
+        in_whole = e["bf16_equivalent"]["bytes"] - SHAPES[e["shape"]].kv_bytes(e["ctx"])
+        assert e["algorithmic_bytes"] == e["bf16_equivalent"]["bytes"] - (in_whole // 4 if e["weights"].startswith("coded") else 0)
     conc = [e for e in sw if e.get("kind") == "concurrent_loop"]
     assert conc and all("error" in e or (e["text_equals_plain_decode"] and e["accepted_tokens_per_s"] > 0) for e in conc)
     pts = [e for e in pts if e.get("kind") != "concurrent_loop"]
@@ -54,8 +68,13 @@ def test_short_run_prints_one_json_line_with_the_contract_fields(monkeypatch, ca
     assert len(dl) == 2 and all(e["ms_per_level"] > 0 and e["K"] == 40 for e in dl)
     # the weights are streamed once per call of 32 rows, and once by the pass; the fractions of the peaks are of what was moved and issued
     assert [(e["route"], e["lanes"], e["weight_streams_per_level"]) for e in dl] == [("calls", 1, 2), ("one pass", 2, 1)]
-    per_stream = [e["hbm_frac"] * e["ms_per_level"] / e["weight_streams_per_level"] for e in dl]
-    assert abs(per_stream[0] - per_stream[1]) <= 1e-9 * per_stream[0]
+    assert dl[1]["weights"].startswith("whole")  # the pass reads these, calls the coded copy where there is one
+    draft = ModelShape("tiny-draft", 1, 128, 2, 1, 64, 344, 1024)  # what a quick run forwards
+    for e in dl:
+        kv = draft.kv_bytes(e["ctx"])
+        assert e["bytes_per_stream"] == draft.streamed_weight_bytes() * (3 if e["weights"].startswith("coded") else 4) // 4 + kv
+        frac = e["weight_streams_per_level"] * e["bytes_per_stream"] / (e["ms_per_level"] * 1e-3) / 8e12
+        assert abs(e["hbm_frac"] - frac) <= 1e-9 * frac
     issued = [e["mfma_tflops_issued"] / e["model_tflops"] * e["K"] / 2 for e in dl]  # rows
     assert [round(i, 6) for i in issued] == [32 + 8, 16 + 16 + 16]  # calls of 32 and 8 rows; tiles of calls of 24 and 16 rows
     loops = [e for e in sw if e.get("kind") == "cache_loop"]
