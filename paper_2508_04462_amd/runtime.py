@@ -94,6 +94,18 @@ class Target:
         self.row_argmax = torch.zeros(32, dtype=torch.int32, device=self.device)
         self.cand = torch.zeros(32, dtype=torch.int32, device=self.device)
 
+    @property
+    def packed(self) -> torch.Tensor:
+        """The packed weights.  Another Target's of the shape may take their place: without room for the coded
+        copy, this Target's steps read the whole weights from then on."""
+        return self._packed
+
+    @packed.setter
+    def packed(self, blob: torch.Tensor) -> None:
+        if self.cfg.coded and blob.numel() * blob.element_size() < B.card_packed_weight_bytes(self.cfg):
+            self.cfg.coded = 0
+        self._packed = blob
+
     def _bytes(self) -> List[int]:
         """Of the packed weights, the workspace and the two page pools."""
         pool = B.card_kv_pool_bytes(self.cfg, self.n_pages)

@@ -155,6 +155,35 @@ def test_a_tensor_packed_without_its_copy_ends_the_copy(monkeypatch, name, layer
     assert all(torch.equal(a, b) for a, b in zip(now, whole)) and not torch.equal(now[0], before[0])
 
 
+def test_a_target_takes_the_packed_weights_of_another():
+    """... whichever of the two keeps the copy."""
+    import paper_2508_04462_amd as card
+
+    shape = SHAPES["odd"]
+    tgts = {coded: card.Target(shape, 160, pool_fill=0, coded=coded) for coded in (False, True)}
+    for tgt in tgts.values():
+        _pack(tgt, shape, "outliers", 31)
+    want = _run(tgts[False], 0, 8, 41)
+    for coded in (False, True):
+        tgt = card.Target(shape, 160, pool_fill=0, coded=coded)
+        for blob in (tgts[True].packed, tgts[False].packed, tgts[True].packed):
+            tgt.packed = blob
+            assert all(torch.equal(a, b) for a, b in zip(_run(tgt, tgt.cfg.coded, 8, 41), want)), coded
+        assert tgt.cfg.coded == 0  # once given a blob without a copy
+
+
+@pytest.mark.parametrize("name,layers", [("llama8b", 2), ("qwen7b", 2), ("llama70b", 1)])
+def test_wide_models_give_the_same_bits_on_either_kind_of_weights(name, layers):
+    import paper_2508_04462_amd as card
+
+    shape = ci.SHAPES[name].with_layers(layers)
+    tgt = card.Target(shape, 160, pool_fill=0, coded=True)
+    _pack(tgt, shape, "outliers", 41)
+    for r in (1, 8, 13, 32):
+        for got, want in zip(_run(tgt, 1, r, 41), _run(tgt, 0, r, 41)):
+            assert torch.equal(got, want), (name, r)
+
+
 def _sizes(max_ctx):
     """Bytes of a Target of the small shape with the copy: packed weights; workspace and page pools."""
     import paper_2508_04462_amd as card
