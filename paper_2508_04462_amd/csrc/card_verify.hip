@@ -540,6 +540,11 @@ __device__ __forceinline__ void producer(const MegaArgs& a, MegaSmem& sm, int w,
 // per tile of the batch: place u of a quad carries tile u of a k-step.
 typedef const __attribute__((address_space(4))) unsigned long long* ConstWords;  // (scalar loads: written by earlier kernels only)
 typedef const __attribute__((address_space(4))) uint32_t* ConstWord;
+// Scalar offset of a load without a rest, and size of a matrix's resource: nothing is left of the resource there, whichever way that is worked
+// out.  No matrix is larger (below 4 GiB, whole KiB).  Places behind a matrix's last fragment may read on, into its bits at most.  With the
+// matrix's own size for both, which no instruction holds as a constant, a quad has 5 scalar instructions more: 8B r = 8 2743 -> 2753 us, 7B r = 13 / 32
+// 2881 / 3955 -> 2894 / 3962, 70B widths 2237 -> 2242 (same states, one process).
+constexpr uint32_t kNoRest = 0xfffffc00u;
 
 template <bool GROUPED>
 __device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, int w, int lane, int wg) {
@@ -624,13 +629,14 @@ __device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, 
             if (nx_ph >= n_ph) {
                 run = 0x7fffffffu;
                 cur_rs = make_rsrc(a.wbase, 0);
-                off_low = off_high = off_rest = n = 0;
+                off_low = off_high = off_rest = 0;
+                word = ~0ull;  // (offsets from zero for all three, then, for the two quads that are still asked for)
                 return;
             }
             const int kind = kind_of(nx_ph);
             const uint64_t at = layer_at(nx_ph);
             n = pick(k_n, kind);
-            cur_rs = make_rsrc(reinterpret_cast<const void*>(at + pick64(k_off, kind)), n << 10);
+            cur_rs = make_rsrc(reinterpret_cast<const void*>(at + pick64(k_off, kind)), kNoRest);
             first = pick(k_first, kind);
             steps = pick(k_steps, kind);
             nb = pick(k_nb, kind);
@@ -682,7 +688,7 @@ __device__ __forceinline__ void producer_coded(const MegaArgs& a, MegaSmem& sm, 
             vl += u * 512;
             vh += u * 256;
         }
-        sr = (uint32_t(word) >> u) & 1u ? sr : n << 10;  // (what the resource's size less the scalar offset leaves room for: nothing)
+        sr = (uint32_t(word) >> u) & 1u ? sr : kNoRest;
         const uint2v low = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(cur_rs, vl, int(sl), kAuxNT));
         const uint32_t high = __builtin_amdgcn_raw_buffer_load_b32(cur_rs, vh, int(sh), kAuxNT);
         const uint32_t rest = __builtin_amdgcn_raw_buffer_load_b32(cur_rs, vh, int(sr), kAuxNT);
