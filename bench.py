@@ -364,8 +364,9 @@ def cache_loop(rig, r, p, n_tokens, K=50, width=10):
     dt = time.perf_counter() - t0
     if steps == 0:
         return {"shape": shape.name, "ctx": rig.ctx, "r": r, "kind": "cache_loop", "planted_acceptance": p,
-                "error": "the first step already left the greedy text (near-tie)"}
+                "weights": weights_read(rig.tgt.cfg.coded), "error": "the first step already left the greedy text (near-tie)"}
     return {"shape": shape.name, "ctx": rig.ctx, "r": r, "kind": "cache_loop", "planted_acceptance": p, "K": K,
+            "weights": weights_read(rig.tgt.cfg.coded),
             "left_greedy_text_at": left_at, "steps": steps, "hit_rate": hits / steps, "mean_accepted_len": emitted / steps,
             "ms_per_step": dt * 1e3 / steps, "accepted_tokens_per_s": emitted / dt,
             "plain_decode_tokens_per_s": None}
@@ -429,6 +430,7 @@ def concurrent_loop_entries(args, decode_tps, quick, grids=(192, 64)):
         loop.d_absorbed = 0
         e = {"kind": "concurrent_loop", "target": t_shape.name, "draft": d_shape.name, "ctx": ctx_len + n_done,
              "target_workgroups": grids[0], "draft_workgroups": grids[1], "planted_acceptance": p, "planted_sibling_catch": q,
+             "target_weights": weights_read(tgt.cfg.coded), "draft_weights": weights_read(dr.cfg.coded),
              "K": K, "k": 8, "depth": depth, "r_max": r_max, "plain_decode_tokens_per_s_whole_gpu": decode_tps,
              "smallest_top2_gap_of_the_stretch": min(gaps[n_done: n_done + n_tok + r_max + 2])}
         try:

@@ -77,6 +77,8 @@ def test_short_run_prints_one_json_line_with_the_contract_fields(monkeypatch, ca
         assert abs(e["hbm_frac"] - frac) <= 1e-9 * frac
     issued = [e["mfma_tflops_issued"] / e["model_tflops"] * e["K"] / 2 for e in dl]  # rows
     assert [round(i, 6) for i in issued] == [32 + 8, 16 + 16 + 16]  # calls of 32 and 8 rows; tiles of calls of 24 and 16 rows
+    kinds = ("whole, 16 bits each", "coded, 12 bits each")
+    assert all(e[key] in kinds for e in sw for key in (("target_weights", "draft_weights") if e.get("kind") == "concurrent_loop" else ("weights",)))
     loops = [e for e in sw if e.get("kind") == "cache_loop"]
     assert loops and all("error" in e or (e["accepted_tokens_per_s"] > 0 and 1.0 <= e["mean_accepted_len"] <= e["r"])
                          for e in loops)
